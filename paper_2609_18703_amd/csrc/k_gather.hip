@@ -171,7 +171,7 @@ __global__ __launch_bounds__(kBlock) void k_gather_scatter(
 #define RO_SCAN_WG 3                        // workgroups per CU
 #endif
 // One tile = 4096 canonical children, 16 consecutive per thread; every 16
-// threads cover one copy sub-tile of 256 children and record its first output
+// four threads cover one group of 64 children and record its first output
 // byte.  A workgroup holds one tile at a time, but as soon as the tile's
 // look-back is done it draws the next ticket, finds the next tile's parents
 // and issues the loads of its slots, which are then in flight while the
@@ -318,9 +318,9 @@ __global__ __launch_bounds__(kBlock) void k_gather_scan(
         const int64_t ex = block_excl_scan(sum, s_wave, tot);
         const uint64_t pre = tile_prefix_inl(desc, t, sepoch, (uint64_t)tot, &s_b, ctl);
         const int64_t base = (int64_t)pre + ex;
-        if ((threadIdx.x % (kSub / kItems)) == 0) {
-            const int64_t sb = t * (kTile / kSub) + threadIdx.x / (kSub / kItems);
-            sub_base[sb] = base;                    // first byte of each copy sub-tile
+        if ((threadIdx.x % (kGrp / kItems)) == 0) {
+            const int64_t sb = t * (kTile / kGrp) + threadIdx.x / (kGrp / kItems);
+            sub_base[sb] = base;                    // first byte of each group of 64
         }
         if (t == ntiles - 1 && threadIdx.x == 0) {
             ctl->total = (int64_t)pre + tot;
@@ -475,25 +475,22 @@ __global__ __launch_bounds__(kBlock) void k_gather_finalize(
 // the runtime passes workspace arrays in that case.
 
 // ---------------------------------------------------------------- copy
-// First sub-tile whose output holds byte `lo`: the largest s in [0, nsub)
-// with sub_base[s] <= lo (sub_base[0] = 0).
-__device__ __forceinline__ int64_t find_sub_tile(const int64_t *__restrict__ sub_base, int64_t nsub, int64_t lo)
-{
-    return wave_last_le(sub_base, 0, nsub, lo);
-}
-
 // Each wave works alone on its units of output bytes, with no workgroup
-// barrier.  For each sub-tile of kSub canonical children that a unit touches,
-// it rebuilds the destination offsets with a wave scan, clips every record to
-// the unit's byte range (shifting the source start of a record that begins
-// before it), and writes that range with aligned 16-byte stores.  Byte-sized
-// units keep the chip busy whether the records are a few bytes or megabytes
-// long, and few parents or many.
+// barrier.  A unit starts at the group of 64 canonical children that holds
+// its first byte (a wave search over the groups' first bytes) and takes four
+// groups at a time: the groups' starts are known from the scan, so each group
+// needs only the exclusive sum of its own lengths, and a group past the
+// unit's end is not read.  Every record is clipped to the unit's byte range
+// (shifting the source start of a record that begins before it), and that
+// range is written with aligned 16-byte stores.  Byte-sized units keep the
+// chip busy whether the records are a few bytes or megabytes long, and few
+// parents or many.
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RO_COPY_WAVES))) void k_gather_copy(
     const int64_t *__restrict__ offsets, int64_t P, const Canon *__restrict__ canon, int64_t canon_cap,
-    const int64_t *__restrict__ sub_base, uint8_t *__restrict__ out, uint32_t epoch, Ctl *ctl)
+    const int64_t *__restrict__ sub_base, uint8_t *__restrict__ out, int64_t slots, uint32_t epoch, Ctl *ctl)
 {
     constexpr int kWaves = kBlock / 64;
+    constexpr int kGroups = kSub / kGrp;
     __shared__ int32_t s_dst_all[kWaves][kSub + 1];     // clipped destination offset of each record
     __shared__ uint64_t s_src_all[kWaves][kSub];        // source address of its first clipped byte
     __shared__ int32_t s_edge_all[kWaves][kEdgeCap];    // edge chunks of the window
@@ -503,12 +500,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RO_COPY_
     const int64_t N = N0 <= canon_cap ? N0 : 0;
     const int64_t T = N > 0 ? ctl->total : 0;           // output bytes, from the scan
     if (T <= 0) return;
-    const int64_t nsub = (N + kSub - 1) / kSub;
+    const int64_t ngrp = (N + kGrp - 1) / kGrp;
     const uint64_t outa = reinterpret_cast<uint64_t>(out);
     const int64_t mis = (int64_t)(outa & 15);
     const int64_t nwaves = (int64_t)gridDim.x * kWaves;
     int64_t G, nunits;
-    copy_units(T, nwaves, mis, G, nunits);
+    copy_units(T, slots, mis, G, nunits);
     const int wave = uni32((int)(threadIdx.x >> 6)), lane = lane_id();
     int32_t *s_dst = s_dst_all[wave];
     uint64_t *s_src = s_src_all[wave];
@@ -517,50 +514,48 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RO_COPY_
     for (int64_t u = (int64_t)blockIdx.x * kWaves + wave; u < nunits; u += nwaves) {
         const int64_t lo = max64(u * G - mis, 0);
         const int64_t hi = min64((u + 1) * G - mis, T);
-        for (int64_t sb = uni64(find_sub_tile(sub_base, nsub, lo)); sb < nsub; ++sb) {
-            const int64_t D0 = sub_base[sb];
-            if (D0 >= hi) break;
-            const int64_t c0 = sb * kSub;
-            const int64_t cnt = min64(kSub, N - c0);
-            // surviving lengths -> destination offsets relative to the sub-tile
-            int64_t lsum = 0;
-            uint32_t l[kCopyPer];
-            uint64_t s[kCopyPer];
-            // whole 16-byte slots, all four loads in flight together (a
-            // slot past the expansion re-reads the last one and is ignored)
-            uint4 ev[kCopyPer];
+        for (int64_t g = uni64(wave_last_le(sub_base, 0, ngrp, lo)); g < ngrp; g += kGroups) {
+            // first bytes of the window's groups and of the one after it
+            const int64_t gl = g + (lane < kGroups ? lane : kGroups);
+            const int64_t dl = gl < ngrp ? sub_base[gl] : T;
+            int64_t D[kGroups + 1];
 #pragma unroll
-            for (int k = 0; k < kCopyPer; ++k) {
-                const int64_t r = (int64_t)lane * kCopyPer + k;
-                ev[k] = ld16(reinterpret_cast<uint64_t>(&canon[c0 + (r < cnt ? r : cnt - 1)]));
-            }
-#pragma unroll
-            for (int k = 0; k < kCopyPer; ++k) {
-                const int64_t r = (int64_t)lane * kCopyPer + k;
-                const bool ok = r < cnt && ev[k].w == ((epoch << 2) | RO_SUCCESS);
-                l[k] = ok ? ev[k].z : 0u;
-                s[k] = ok ? ((uint64_t)ev[k].y << 32 | ev[k].x) : 0ull;
-                lsum += l[k];
-            }
-            const int64_t inc = wave_incl_sum(lsum);
-            const int64_t tot = uni64(__shfl(inc, 63, 64));
-            // this unit's part of the sub-tile: [ws, we), relative to D0
-            const int64_t ws = max64(lo - D0, 0), we = min64(hi - D0, tot);
+            for (int k = 0; k <= kGroups; ++k) D[k] = uni64(__shfl(dl, k, 64));
+            if (D[0] >= hi) break;
+            // this unit's part of the window
+            const int64_t ws = max64(lo, D[0]), we = min64(hi, D[kGroups]);
             if (we > ws) {
-                int64_t run = inc - lsum;
+                // whole 16-byte slots, the loads of all groups in flight
+                // together (a slot past the expansion re-reads the last one
+                // and is ignored; a group past the unit holds nothing of it)
+                uint4 ev[kGroups];
 #pragma unroll
-                for (int k = 0; k < kCopyPer; ++k) {
-                    const int r = lane * kCopyPer + k;
-                    const int64_t cs = min64(max64(run, ws), we);
-                    s_dst[r] = (int32_t)(cs - ws);
-                    s_src[r] = s[k] + (uint64_t)(cs - run);
-                    run += l[k];
+                for (int k = 0; k < kGroups; ++k) {
+                    const int64_t c = (g + k) * kGrp + lane;
+                    ev[k] = make_uint4(0, 0, 0, 0);
+                    if (D[k] < we) ev[k] = ld16(reinterpret_cast<uint64_t>(&canon[c < N ? c : N - 1]));
+                }
+#pragma unroll
+                for (int k = 0; k < kGroups; ++k) {
+                    const int r = k * kGrp + lane;
+                    if (D[k] < we) {
+                        const bool ok = g * kGrp + r < N && ev[k].w == ((epoch << 2) | RO_SUCCESS);
+                        const uint32_t l = ok ? ev[k].z : 0u;
+                        const int64_t run = D[k] + (int64_t)wave_incl_sum_dpp(l) - l;
+                        const int64_t cs = min64(max64(run, ws), we);
+                        s_dst[r] = (int32_t)(cs - ws);
+                        s_src[r] = (ok ? ((uint64_t)ev[k].y << 32 | ev[k].x) : 0ull) + (uint64_t)(cs - run);
+                    } else {
+                        s_dst[r] = (int32_t)(we - ws);
+                        s_src[r] = 0;
+                    }
                 }
                 if (lane == 0) s_dst[kSub] = (int32_t)(we - ws);
                 __builtin_amdgcn_wave_barrier();
-                copy_window_nb<RO_COPY_STEPS>(s_dst, s_src, s_edge, s_edger, (int)(we - ws), outa, D0 + ws, lane);
+                copy_window_nb<RO_COPY_STEPS>(s_dst, s_src, s_edge, s_edger, (int)(we - ws), outa, ws, lane);
                 __builtin_amdgcn_wave_barrier();
             }
+            if (D[kGroups] >= hi) break;
         }
     }
 }
@@ -596,11 +591,16 @@ hipError_t launch_gather(const Launch &L, const GatherArgs &a, const GatherWs &w
                        a.P, w.canon_cap, a.out_off, a.out_cap, a.out_data != nullptr ? 1 : 0, a.ns, a.nf,
                        a.nk, a.complete, a.pstate, a.cdst, a.barrier, w.gkey, a.n_rejected, epoch, L.ctl);
     if (a.out_data != nullptr && !in_place) {
-        // many small workgroups: a unit's cost varies with the records it
-        // meets, and a deep queue of workgroups evens out the tail
-        const int64_t grid_c = (int64_t)L.num_cus * RO_COPY_GRID;
+        // One unit per wave, handed out in output order as workgroups end, as
+        // far as out_cap (the most the total can be) asks for them: a
+        // persistent grid striding over the units was slower.
+        const int64_t slots = (int64_t)L.num_cus * 4 * RO_COPY_WAVES;
+        const int64_t max_c = (int64_t)L.num_cus * RO_COPY_GRID, max_s = (int64_t)L.num_cus * 32;
+        const int64_t big_c = a.out_cap / (kCopyUnit * 4) + 1, small_c = a.out_cap / (kCopyMinUnit * 4) + 1;
+        int64_t grid_c = small_c < max_s ? small_c : max_s;
+        grid_c = big_c > grid_c ? (big_c < max_c ? big_c : max_c) : grid_c;
         RO_LAUNCH(L, RO_K_GATHER_COPY, k_gather_copy, dim3((unsigned)grid_c), dim3(kBlock), 0, L.stream, a.offsets,
-                  a.P, w.canon, w.canon_cap, w.sub_base, a.out_data, epoch, L.ctl);
+                  a.P, w.canon, w.canon_cap, w.sub_base, a.out_data, slots, epoch, L.ctl);
     }
     return hipGetLastError();
 }

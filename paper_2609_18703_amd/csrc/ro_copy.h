@@ -21,8 +21,6 @@ __device__ __forceinline__ uint4 ld16(uint64_t a)
 }
 __device__ __forceinline__ void st8(uint64_t a, uint8_t v) { *(RO_GLOBAL uint8_t *)a = v; }
 
-constexpr int kCopyPer = kSub / 64;       // records per lane in a wave's copy prologue
-
 // Largest r in [r, kSub] with s_dst[r] <= pos, given s_dst[r] <= pos: a few
 // linear steps (the usual distance between neighbouring chunks), then a
 // binary search.  Zero-length records are stepped over.
@@ -203,36 +201,44 @@ __device__ __forceinline__ void copy_window_nb(const int32_t *s_dst, const uint6
 
 // Output bytes are split into units of G bytes (the last one shorter), cut
 // where the destination address is 16-byte aligned, so that unit edges need
-// no partial stores.  G is chosen from the total so that every wave of the
-// grid gets about kCopyUnits units, but never under kCopyMinUnit bytes (a
-// unit re-reads the slot descriptors of the sub-tiles it touches) nor over
-// 1 GiB (positions inside a unit are 32-bit).
+// no partial stores.  One unit is one wave's work, and G follows the total:
+//   * small totals: a unit for every wave the chip holds at once, down to
+//     1 KiB.  A wave copies its unit step after step, so a large unit leaves
+//     the chip idle and makes the copy as long as one wave's walk through it
+//     (units of at least 128 KiB: 473 KB in 188 us and 1.6 MB in 143 us; so
+//     9.3 and 19 us);
+//   * larger totals: about kCopyUnit bytes and a whole number of units per
+//     wave slot.  Units of 48 KiB handed out in output order keep the bytes in
+//     flight on the whole chip within about 200 MB of the output: 25 GB in
+//     random record order take 10.0 ms against 10.8 ms with units of 384 KiB,
+//     8 million records in order 2.05 against 2.27 ms.  Units under 32 KiB pay
+//     more for finding their records than they gain.
 // Copy kernels trade per-wave registers for occupancy: the compiler keeps
 // register use low enough for at least this many waves per SIMD.
 #ifndef RO_COPY_WAVES
 #define RO_COPY_WAVES 4
 #endif
 #ifndef RO_COPY_STEPS
-#define RO_COPY_STEPS 6
+#define RO_COPY_STEPS 5                     // 64-chunk steps in flight per wave
 #endif
 #ifndef RO_COPY_GRID
-#define RO_COPY_GRID 32                     // gather copy workgroups per CU
+#define RO_COPY_GRID 128                    // gather copy workgroups per CU, at most
 #endif
-#ifndef RO_COPY_UNITS
-#define RO_COPY_UNITS 2
+#ifndef RO_COPY_UNIT
+#define RO_COPY_UNIT (48 << 10)
 #endif
-#ifndef RO_COPY_MIN_UNIT
-#define RO_COPY_MIN_UNIT (128 << 10)
-#endif
-constexpr int64_t kCopyUnits = RO_COPY_UNITS;
-constexpr int64_t kCopyMinUnit = RO_COPY_MIN_UNIT;
+constexpr int64_t kCopyUnit = RO_COPY_UNIT;
+constexpr int64_t kCopyMinUnit = 1 << 10;
 
-// Unit size G and unit count for T output bytes copied by nwaves waves into
-// a buffer whose address is `mis` bytes past a 16-byte boundary.
-__device__ __forceinline__ void copy_units(int64_t T, int64_t nwaves, int64_t mis, int64_t &G, int64_t &nunits)
+// Unit size G and unit count for T output bytes copied into a buffer whose
+// address is `mis` bytes past a 16-byte boundary by a chip that holds `slots`
+// waves of the copy at once: a whole number of units per slot.
+__device__ __forceinline__ void copy_units(int64_t T, int64_t slots, int64_t mis, int64_t &G, int64_t &nunits)
 {
-    G = (T + nwaves * kCopyUnits - 1) / (nwaves * kCopyUnits);
-    G = (G + 1023) & ~(int64_t)1023;
+    int64_t rounds = (T + slots * kCopyUnit / 2) / (slots * kCopyUnit);
+    rounds = rounds < 1 ? 1 : rounds;
+    G = (T + mis + slots * rounds - 1) / (slots * rounds);
+    G = (G + 255) & ~(int64_t)255;
     G = G < kCopyMinUnit ? kCopyMinUnit : (G > ((int64_t)1 << 30) ? ((int64_t)1 << 30) : G);
     nunits = (T + mis + G - 1) / G;
 }

@@ -29,6 +29,27 @@ __device__ __forceinline__ int64_t uni64(int64_t v)
 }
 
 // ---- wave64 reductions / scans -------------------------------------------
+// Inclusive sum over the lanes of a wave on the DPP network: four row shifts
+// (rows of 16 lanes) and two row broadcasts, no LDS traffic.  Lanes a step
+// does not reach add `old` = 0.
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint64_t dpp_add64(uint64_t v)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, kCtrl, kRows, 0xf, false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), kCtrl, kRows, 0xf, false);
+    return v + ((uint64_t)hi << 32 | lo);
+}
+__device__ __forceinline__ uint64_t wave_incl_sum_dpp(uint64_t v)
+{
+    v = dpp_add64<0x111, 0xf>(v);           // row_shr:1
+    v = dpp_add64<0x112, 0xf>(v);           // row_shr:2
+    v = dpp_add64<0x114, 0xf>(v);           // row_shr:4
+    v = dpp_add64<0x118, 0xf>(v);           // row_shr:8
+    v = dpp_add64<0x142, 0xa>(v);           // row_bcast:15 into rows 1 and 3
+    v = dpp_add64<0x143, 0xc>(v);           // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_incl_sum(T v)
 {
@@ -295,13 +316,14 @@ __device__ __forceinline__ int64_t advance_parent(const int64_t *offsets, int64_
 // Called by all 64 lanes of a wave, which get the same result.  Each round
 // the lanes probe 64 evenly spaced entries of the remaining range and a
 // ballot keeps the gap holding the answer, so n entries take about
-// log_65(n) rounds of one load each.
+// log_64(n) rounds of one load each.  (Probes sit at the odd 128ths of the
+// range: a shift where 65ths would take a 64-bit division.)
 __device__ __forceinline__ int64_t wave_last_le(const int64_t *a, int64_t lo, int64_t hi, int64_t x)
 {
     const int lane = lane_id();
     int64_t l = lo, h = hi;
     while (h - l > 1) {
-        const int64_t idx = l + ((h - l) * (int64_t)(lane + 1)) / 65;
+        const int64_t idx = l + (((h - l) * (int64_t)(2 * lane + 1)) >> 7);    // in [l, h)
         const uint64_t m = __ballot(a[idx] <= x);
         const int k = __popcll(m);                 // the true probes form a prefix
         const int64_t nl = k > 0 ? __shfl(idx, k - 1, 64) : l;

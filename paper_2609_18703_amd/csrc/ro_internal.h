@@ -11,7 +11,8 @@ namespace ro {
 constexpr int kBlock = 256;                 // threads per workgroup (4 waves of 64)
 constexpr int kItems = 16;                  // items per thread in scan tiles
 constexpr int kTile = kBlock * kItems;      // 4096 entries per scan tile
-constexpr int kSub = 256;                   // children per copy sub-tile (the scan records where each starts)
+constexpr int kSub = 256;                   // children per copy window
+constexpr int kGrp = 64;                    // children per group: the scan records where each group's bytes start
 constexpr int kCntLds = 512;                // parents whose counts a tile aggregates in LDS
 
 // Canonical per-child record written by the report scatter.  `tag` holds the
@@ -130,7 +131,7 @@ struct GatherArgs {
 struct GatherWs {
     Canon *canon;
     int64_t canon_cap;
-    int64_t *sub_base;       // per copy sub-tile: first output byte
+    int64_t *sub_base;       // per group of kGrp children: first output byte
     int64_t sub_cap;
     uint64_t *gkey;          // [P] first group failure per parent (epoch << 32 | ~report index)
 };

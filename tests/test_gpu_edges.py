@@ -1,0 +1,92 @@
+"""GPU parity at the sizes where a kernel changes tile, group, unit or path,
+bit-exact against the CPU oracle."""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+import oracle as O  # noqa: E402
+from workloads import device as D  # noqa: E402
+
+
+def _say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2609_18703_amd as R
+    c = R.Context()
+    c.reserve(1 << 21, 1 << 18, 1 << 21)
+    yield c
+    c.close()
+
+
+def _i32(a):
+    return D.to_dev(np.ascontiguousarray(a).view(np.int32))
+
+
+def _zeros(n, dtype):
+    return torch.zeros(max(int(n), 1), dtype=dtype, device="cuda")
+
+
+def _reports(counts, lengths, states, order, lead=0, seed=0):
+    """Host report columns for children in `order` (bytes only where SUCCESS)."""
+    counts = np.asarray(counts, np.int64)
+    parent = np.repeat(np.arange(len(counts)), counts)
+    ordinal = np.arange(len(parent)) - np.repeat(np.cumsum(counts) - counts, counts)
+    ln = np.where(states[order] == O.SUCCESS, lengths[order], 0).astype(np.int64)
+    off = np.concatenate([[lead], lead + np.cumsum(ln)]).astype(np.int64)
+    data = np.random.default_rng(seed + 99).integers(0, 256, int(off[-1]) + 1).astype(np.uint8)
+    return parent[order].astype(np.uint32), ordinal[order].astype(np.uint32), states[order].astype(np.uint8), off, data
+
+
+def _gather_case(ctx, counts, lengths, states, order, mis=0, lead=0):
+    rp, ro, rs, off, data = _reports(counts, lengths, states, order, lead)
+    offs = O.expand(np.asarray(counts, np.int32), tags=False)
+    want = O.gather(rp, ro, rs, off, data, offs)
+    P, N, total = len(counts), int(offs[-1]), int(want["out_off"][-1])
+    out = torch.full((mis + max(total, 1) + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    oo, cdst = _zeros(P + 1, torch.int64), _zeros(N + 1, torch.int64)
+    ns, nf, nk = (_zeros(P, torch.int32) for _ in range(3))
+    comp, pst = _zeros(P, torch.uint8), _zeros(P, torch.uint8)
+    ctx.gather(_i32(rp), _i32(ro), D.to_dev(rs), D.to_dev(off), D.to_dev(data), D.to_dev(offs), oo, out[mis:],
+               ns, nf, nk, comp, pst, n=len(rp), out_cap=total, child_dst_off=cdst)
+    ctx.check("gather")
+    assert np.array_equal(oo.cpu().numpy(), want["out_off"])
+    for t, k in ((ns, "n_success"), (nf, "n_failed"), (nk, "n_skipped"), (comp, "complete"), (pst, "parent_state")):
+        assert np.array_equal(t.cpu().numpy()[:P], want[k]), k
+    host = out.cpu().numpy()
+    assert np.array_equal(host[mis:mis + total], want["out_data"])
+    assert (host[:mis] == 0xA5).all() and (host[mis + total:] == 0xA5).all()
+    ln = np.zeros(N, np.int64)
+    ln[order] = np.diff(off)
+    assert np.array_equal(cdst.cpu().numpy(), np.concatenate([[0], np.cumsum(ln)]))
+
+
+# children around a group of 64, a window of 256, a scan tile and several tiles
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 256, 257, 1023, 1024, 1025, 4095, 4096, 4097, 20_011])
+@pytest.mark.parametrize("record", ["tiny", "mixed", "large"])
+def test_gather_groups_and_units(ctx, n, record):
+    """Copy units from 1 KiB up to many per wave, cut anywhere in a record."""
+    rng = np.random.default_rng(n)
+    counts = []
+    left = n
+    while left > 0:
+        k = int(min(left, rng.choice([0, 0, 1, 2, 3, 7, 40, 700])))
+        counts.append(k)
+        left -= k
+    counts += [0, 0]
+    hi = {"tiny": 5, "mixed": 900, "large": min(9000, 40_000_000 // n)}[record]
+    lengths = rng.integers(0, hi + 1, n)
+    states = rng.choice([O.SUCCESS] * 8 + [O.FAILED, O.SKIPPED], n).astype(np.uint8)
+    for mis, order in ((0, rng.permutation(n)), (5, np.arange(n)), (15, rng.permutation(n))):
+        _say("gather", n, record, mis)
+        _gather_case(ctx, counts, lengths, states, order, mis=mis, lead=mis % 7)
