@@ -7,19 +7,19 @@
 // ordinal order, and zero survivors give an empty list.  The publication
 // rules of the same section reject a second, conflicting report.
 //
-// Four kernels:
+// Three kernels:
 //   scatter  : report i -> canonical slot c = offsets[p] + o (validation, one
 //              16-byte store per report; the only random-access pass).
 //   scan     : canonical order, decoupled look-back over the surviving byte
-//              lengths -> every parent's slot offset, per-parent counts (LDS
-//              aggregated), per-sub-tile output bases.
-//   finalize : per parent: complete / state, trailing slot offsets, duplicate
-//              and capacity checks.
-//   copy     : the output is cut into byte ranges of equal size; per range,
-//              a wave rebuilds the destination offsets of the canonical
-//              sub-tiles it overlaps and writes the range as aligned 16-byte
-//              stores; sources are byte-aligned records read as aligned
-//              16-byte pairs and realigned in registers.
+//              lengths -> every parent's slot offset and counts, the first
+//              byte of every group of 64 children; duplicate and capacity
+//              checks.
+//   copy     : per parent complete / state and trailing slot offsets; then
+//              the output is cut into byte ranges of equal size; per range, a
+//              wave rebuilds the destination offsets of the groups it
+//              overlaps and writes the range as aligned 16-byte stores;
+//              sources are byte-aligned records.
+// Without bytes to copy the per-parent part is a kernel of its own.
 #include "ro_copy.h"
 
 namespace ro {
@@ -167,312 +167,338 @@ __global__ __launch_bounds__(kBlock) void k_gather_scatter(
 }
 
 // ---------------------------------------------------------------- scan
-#ifndef RO_SCAN_WG
-#define RO_SCAN_WG 3                        // workgroups per CU
-#endif
-// One tile = 4096 canonical children, 16 consecutive per thread; every 16
-// four threads cover one group of 64 children and record its first output
-// byte.  A workgroup holds one tile at a time, but as soon as the tile's
-// look-back is done it draws the next ticket, finds the next tile's parents
-// and issues the loads of its slots, which are then in flight while the
-// current tile's pass 2 runs.  The current tile has posted its prefix before
-// the workgroup waits on anything for the next one, so the smallest tile not
-// yet posted always belongs to a workgroup that can post it.
+// One tile = kIt * kTh canonical children in groups of 64, a group per load of
+// a wave, so that loads, per-child outputs and LDS accesses are all
+// lane-contiguous.  Per group the wave keeps, in LDS, the exclusive byte sums
+// of its children (DPP scan) and one ballot mask per state; the sums and
+// popcounts over the groups then answer any range of the tile.  After the
+// look-back over the tiles the work goes by parent, one per thread: a parent
+// whose first child is in the tile reads its slot offset at that child and
+// its counts as the difference of two positions.  A parent that lies whole in
+// the tile has its counts stored; only the one crossing into the tile and the
+// one leaving it add to theirs.
+//
+// A workgroup finishes one tile before it posts anything of the next, but it
+// draws tickets two tiles ahead: as soon as a tile's slots are taken from
+// their registers, the next tile's parents are searched and its slot loads
+// issued, which are then in flight during the look-back and while the parents
+// are written.  It takes its tiles in ascending order, so the owner of the
+// smallest tile not yet posted never waits on a later one and can always
+// post it.
+//
+// Only as many workgroups as there are tiles take part (the others return at
+// once): draws from one ticket take about 12 ns each, one after another, and
+// 768 workgroups drawing for two tiles took 40 us (now 11).  Where every tile
+// has a workgroup of its own, each draws once.  A single tile
+// needs no ticket and no look-back.  What the tiles decide together (every
+// report in a slot of its own, bytes within the capacity) is settled by the
+// last workgroup to finish, which also clears the call's counters.
 //
 // In place (the output is the report bytes themselves, as for an upper level
 // whose slots are the level below's output): nothing is copied, and the scan
 // checks that every surviving record already sits at its output position;
 // any other would overwrite bytes still to be read (RO_EINVAL).
-template <bool kInPlace>
-__global__ __launch_bounds__(kBlock) void k_gather_scan(
+// Two tile sizes.  Up to kScanSmall reports a tile is 1,024 children by 256
+// threads (100,000 children: 98 workgroups, 13 us); beyond, 8,192 children by
+// one workgroup of 1,024 threads per CU, since a look-back reads as many
+// descriptors as there are tiles in flight and every tile draws a ticket
+// (41M children: 255 us; tiles of 4,096 with two workgroups of 512 threads
+// 285 us, of 4,096 by 256 threads 444 us, of 16,384, whose registers spill,
+// 263 us; before, tiles of 4,096 walked child by child, 305 us.  1M children:
+// 18 us, 36 us with the small tile, 39 us before; 300,000: 26, 30 and 44 us).
+// The report count stands for the child count, which only the device knows.
+constexpr int64_t kScanSmall = 131072;
+constexpr int kScanTh = 1024, kScanIt = 8;
+constexpr int kScanSmallTh = 256, kScanSmallIt = 4;
+
+template <int kTh, int kIt, bool kInPlace>
+__global__ __launch_bounds__(kTh) void k_gather_scan(
     const int64_t *__restrict__ offsets, int64_t P, const Canon *__restrict__ canon, int64_t canon_cap,
-    int64_t *__restrict__ out_off, int32_t *__restrict__ ns, int32_t *__restrict__ nf,
+    int64_t *__restrict__ out_off, int64_t out_cap, int has_data, int32_t *__restrict__ ns, int32_t *__restrict__ nf,
     int32_t *__restrict__ nk, int64_t *__restrict__ cdst, int64_t *__restrict__ sub_base, const uint8_t *out,
-    uint32_t epoch, Ctl *ctl, uint64_t *desc, int64_t desc_cap)
+    int64_t *n_rejected, uint32_t epoch, Ctl *ctl, uint64_t *desc, int64_t desc_cap)
 {
-    const uint32_t sepoch = scan_epoch(ctl);
-    __shared__ int64_t s_wave[kBlock / 64];
+    constexpr int kT = kTh * kIt;               // children per tile
+    constexpr int kG = kT / kGrp;               // groups per tile
+    constexpr int kCF = 21, kCK = 42;           // a packed count: SUCCESS, FAILED << 21, SKIPPED << 42
+    constexpr uint64_t kCM = (1u << kCF) - 1;
+    constexpr int kGL = kG <= 64 ? 1 : kG / 64; // groups per lane of the wave that scans them
+    static_assert(kGrp == 64 && (kG <= 64 || kG % 64 == 0), "one wave load per group");
+    __shared__ uint64_t s_pre[kT];              // exclusive byte sum inside the child's group
+    __shared__ uint64_t s_gt[kG];               // byte total of each group
+    __shared__ uint64_t s_gbase[kG];            // exclusive byte sum of the groups
+    __shared__ uint64_t s_m[3][kG + 1];         // per state: mask of the group's children
+    __shared__ uint64_t s_cp[kG + 1];           // exclusive packed counts of the groups
     __shared__ uint64_t s_b;
     __shared__ int64_t s_t;
-    __shared__ int32_t s_last;
-    __shared__ int64_t s_p[2][3];
-    __shared__ int32_t s_cnt[3][kCntLds];
-    __shared__ int16_t s_off[2][kTile + 2];     // offsets[pf..pl+1] - ct0, clamped to [-1, kTile + 1]
-    __shared__ uint32_t s_len[kTile + kTile / 16];
-    __shared__ alignas(16) uint8_t s_st[kTile];
+    __shared__ int64_t s_p[2][2];
+    __shared__ int32_t s_flag;
     const int64_t N0 = offsets[P];
-    // over capacity, or an invalid Expansion found by the scatter: no tiles
-    const int64_t N = (N0 <= canon_cap && read_err(ctl) == 0) ? N0 : 0;
-    const int64_t ntiles = (N + kTile - 1) / kTile;
-    int32_t *cnt_out[3] = {ns, nf, nk};
-    int64_t filled_total = 0;
-    const int wv = (int)(threadIdx.x >> 6), ln = lane_id();
+    const int64_t N = N0 <= canon_cap ? N0 : 0;
+    const int64_t ntiles = (N + kT - 1) / kT;
+    const uint32_t parts = ntiles > 1 ? (uint32_t)min64((int64_t)gridDim.x, ntiles) : 1u;
+    if (blockIdx.x >= parts) return;
+    const uint32_t sepoch = scan_epoch(ctl);
+    const int wv = uni32((int)(threadIdx.x >> 6)), ln = lane_id();
+    // an invalid Expansion found by the scatter: no tiles (one thread looks,
+    // since an error may also be raised while the scan runs)
+    if (threadIdx.x == 0) s_flag = read_err(ctl) == 0 ? 1 : 0;
+    __syncthreads();
+    const bool single = ntiles == 1;
+    const bool one = ntiles <= (int64_t)gridDim.x;      // one tile and one ticket per workgroup
+    int64_t t = s_flag == 0 ? ntiles : (single || ntiles == 0 ? 0 : next_ticket(ctl, &s_t));
+    int64_t filled = 0;
 
-    // Tile tt's parents, one wave-parallel search each: pf holds child a0,
-    // pl holds child a1 - 1, q0 is the first parent starting at or after a0
-    // (empty parents before pf may start exactly at a0).  With few enough
-    // parents, a tile-relative copy of their offsets goes to s_off[b] for
-    // pass 2 to search instead of global memory.
+    // Tile tt's parents, by waves 1 and 2: q0 is the first parent starting in
+    // it, q1 the first one starting after it, one wave-parallel search each.
     auto prepare = [&](int64_t tt, int b) {
-        const int64_t a0 = tt * kTile;
-        const int64_t a1 = min64(a0 + kTile, N);
-        if (threadIdx.x < 3 * 64) {
-            int64_t r;
-            if (wv == 0) r = wave_last_le(offsets, 0, P + 1, a0);
-            else if (wv == 1) r = wave_last_le(offsets, 0, P + 1, a1 - 1);
-            else r = a0 == 0 ? 0 : wave_last_le(offsets, 0, P + 1, a0 - 1) + 1;
-            if (ln == 0) s_p[b][wv] = r;
-        }
-        __syncthreads();
-        const int64_t pf = s_p[b][0];
-        const int64_t Rp = s_p[b][1] - pf + 1;
-        if (Rp <= kTile) {
-            for (int64_t j = threadIdx.x; j <= Rp; j += kBlock) {
-                const int64_t v = offsets[pf + j] - a0;
-                s_off[b][j] = (int16_t)(v < -1 ? -1 : (v > kTile + 1 ? kTile + 1 : v));
-            }
+        if (wv == 1 || wv == 2) {
+            const int64_t c = tt * kT + (wv == 1 ? 0 : min64(kT, N - tt * kT));
+            const int64_t r = c == 0 ? 0 : wave_last_le(offsets, 0, P + 1, c - 1) + 1;
+            if (ln == 0) s_p[b][wv - 1] = r;
         }
     };
-    // The length and tag words (8 of every 16 bytes) of tile tt's slots, each
-    // wave lane-contiguously over its 1024, into ev: the loads are only
+    // The slots of tile tt, group k of the wave into ev[k]: the loads are only
     // issued here.  A slot past the expansion re-reads the tile's first one
-    // and is ignored.
-    uint2 ev[kItems];
+    // and is ignored.  Out of place only the length and tag words are read.
+    uint2 ev[kIt];
+    uint64_t sv[kInPlace ? kIt : 1];
     auto load_slots = [&](int64_t tt) {
-        const int64_t a0 = uni64(tt * kTile);
-        const int nloc = (int)uni64(min64(a0 + kTile, N) - a0);
-        // uniform base and 32-bit unsigned lane offsets: scalar-base loads
-        const uint8_t *tb = reinterpret_cast<const uint8_t *>(canon + a0) + offsetof(Canon, len);
-        const uint32_t jb = (uint32_t)(wv * (64 * kItems) + ln);
-        if (nloc == kTile) {
+        const int64_t a0 = uni64(tt * kT);
+        const uint32_t nloc = (uint32_t)uni64(min64(kT, N - a0));
+        const uint8_t *tb = reinterpret_cast<const uint8_t *>(canon + a0);
+        const uint32_t jb = (uint32_t)(wv * (64 * kIt) + ln);
 #pragma unroll
-            for (int k = 0; k < kItems; ++k)
-                ev[k] = *reinterpret_cast<const uint2 *>(tb + (jb + 64u * k) * (uint32_t)sizeof(Canon));
-        } else {
-#pragma unroll
-            for (int k = 0; k < kItems; ++k) {
-                const uint32_t j = jb + 64u * k;
-                ev[k] = *reinterpret_cast<const uint2 *>(tb + (j < (uint32_t)nloc ? j : 0u) *
-                                                                  (uint32_t)sizeof(Canon));
-            }
+        for (int k = 0; k < kIt; ++k) {
+            const uint32_t j = jb + 64u * k, jj = j < nloc ? j : 0u;
+            ev[k] = *reinterpret_cast<const uint2 *>(tb + offsetof(Canon, len) + jj * (uint32_t)sizeof(Canon));
+            if constexpr (kInPlace) sv[k] = *reinterpret_cast<const uint64_t *>(tb + jj * (uint32_t)sizeof(Canon));
         }
     };
 
-    for (int j = threadIdx.x; j < 3 * kCntLds; j += kBlock) (&s_cnt[0][0])[j] = 0;
-    // a workgroup that sees no tiles draws no ticket, so every drawn ticket
-    // is processed even if workgroups disagree about an error raised meanwhile
-    int64_t t = ntiles > 0 ? next_ticket(ctl, &s_t) : ntiles;
     int buf = 0;
+    int64_t t_next = ntiles;
     if (t < ntiles) {
         prepare(t, 0);
         load_slots(t);
+        if (!one) t_next = next_ticket(ctl, &s_t);
     }
     while (t < ntiles) {
-        __syncthreads();                    // s_p / s_off of this tile, cleared counts
-        const int64_t ct0 = t * kTile;
-        const int64_t ct1 = min64(ct0 + kTile, N);
-        const int64_t pf = s_p[buf][0], pl = s_p[buf][1], q0t = s_p[buf][2];
-        const int64_t Rp = pl - pf + 1;
-        const int64_t R = min64(Rp, kCntLds);
-        const bool lds_ok = Rp <= kTile;
-        const int16_t *so = s_off[buf];
-
-        // pass 1: surviving lengths and filled slots into LDS; then every
-        // thread takes its 16 consecutive children from there.  s_len is
-        // padded by one word per 16 so that both access patterns are free of
-        // bank conflicts.
-        {
-            const int nloc = (int)(ct1 - ct0);
-            const int jb = wv * (64 * kItems) + ln;
-            const int lb = jb + (jb >> 4);          // s_len index of child jb + 64 k is lb + 68 k
+        __syncthreads();                    // s_p of this tile; the previous tile's LDS is done with
+        const int64_t ct0 = t * kT;
+        const int nloc = (int)min64(kT, N - ct0);
+        const int64_t q0 = s_p[buf][0], q1 = s_p[buf][1];
+        int64_t tk = ntiles;                // the ticket after the next, awaited after the look-back
+        if (threadIdx.x == 0 && !one)
+            tk = (int64_t)__hip_atomic_fetch_add(&ctl->ticket, (uint64_t)1, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+        // this thread's first parent, in flight until then
+        int64_t q = q0 + threadIdx.x;
+        int64_t a0 = 0, a1 = 0;
+        if (q < q1) {
+            a0 = offsets[q];
+            a1 = offsets[q + 1];
+        }
+        // groups: surviving lengths, state masks, exclusive byte sums
 #pragma unroll
-            for (int k = 0; k < kItems; ++k) {
-                uint32_t L = 0, S = 4;        // state, or 4 = not reported in this call
-                if (jb + k * 64 < nloc && (ev[k].y >> 2) == epoch) {
-                    S = ev[k].y & 3u;
-                    L = S == RO_SUCCESS ? ev[k].x : 0;
-                }
-                s_len[lb + 68 * k] = L;
-                s_st[jb + 64 * k] = (uint8_t)S;
+        for (int k = 0; k < kIt; ++k) {
+            const int g = wv * kIt + k, i = g * 64 + ln;
+            const bool in = i < nloc && (ev[k].y >> 2) == epoch;
+            const uint32_t S = in ? ev[k].y & 3u : 4u;
+            const uint64_t L = S == RO_SUCCESS ? ev[k].x : 0u;
+            const uint64_t m0 = __ballot(S == RO_SUCCESS), m1 = __ballot(S == RO_FAILED),
+                           m2 = __ballot(S == RO_SKIPPED);
+            const uint64_t inc = wave_incl_sum_dpp(L);
+            s_pre[i] = inc - L;
+            if (ln == 63) {
+                s_gt[g] = inc;
+                s_m[0][g] = m0;
+                s_m[1][g] = m1;
+                s_m[2][g] = m2;
             }
         }
         __syncthreads();
-        const int64_t c0 = ct0 + (int64_t)threadIdx.x * kItems;
-        const int lj = (int)threadIdx.x * kItems + (int)threadIdx.x;      // s_len index of c0
-        uint32_t sw[4];                     // the thread's 16 state bytes, four per word
-        int64_t sum = 0, filled = 0;
-        {
-            const uint4 sv = *reinterpret_cast<const uint4 *>(&s_st[threadIdx.x * kItems]);
-            sw[0] = sv.x;
-            sw[1] = sv.y;
-            sw[2] = sv.z;
-            sw[3] = sv.w;
-#pragma unroll
-            for (int k = 0; k < kItems; ++k) {
-                sum += s_len[lj + k];
-                filled += ((sw[k >> 2] >> (8 * (k & 3))) & 0xffu) < 4 ? 1 : 0;
+        // the next tile's parents, and its slot loads in flight from here on;
+        // meanwhile the first wave gets the tile's group sums and total and
+        // does the look-back (its own slot loads follow that, since its polls
+        // would wait for them)
+        if constexpr (!kInPlace) {
+            if (wv != 0 && t_next < ntiles) {
+                prepare(t_next, buf ^ 1);
+                load_slots(t_next);
             }
         }
-        filled_total += filled;
-        int64_t tot;
-        const int64_t ex = block_excl_scan(sum, s_wave, tot);
-        const uint64_t pre = tile_prefix_inl(desc, t, sepoch, (uint64_t)tot, &s_b, ctl);
-        const int64_t base = (int64_t)pre + ex;
-        if ((threadIdx.x % (kGrp / kItems)) == 0) {
-            const int64_t sb = t * (kTile / kGrp) + threadIdx.x / (kGrp / kItems);
-            sub_base[sb] = base;                    // first byte of each group of 64
-        }
-        if (t == ntiles - 1 && threadIdx.x == 0) {
-            ctl->total = (int64_t)pre + tot;
-            if (pre >= kSat) raise_err(ctl, RO_EOVERFLOW);
-        }
-
-        // the next tile: ticket, parents, and its slot loads in flight
-        const int64_t t_next = next_ticket(ctl, &s_t);
-        if (t_next < ntiles) {
-            prepare(t_next, buf ^ 1);
-            load_slots(t_next);
-        }
-
-        // pass 2: parents -- slot offsets and run-length counts
-        if (c0 < ct1) {
-            uint64_t srcv[kInPlace ? kItems : 1];
-            bool moved = false;
-            if constexpr (kInPlace) {
+        if (wv == 0) {
+            uint64_t gt[kGL], gc[kGL], lt = 0, lc = 0;
 #pragma unroll
-                for (int k = 0; k < kItems; ++k) srcv[k] = canon[min64(c0 + k, ct1 - 1)].src;
+            for (int j = 0; j < kGL; ++j) {
+                const int g = ln * kGL + j;
+                gt[j] = gc[j] = 0;
+                if (g < kG) {
+                    gt[j] = s_gt[g];
+                    gc[j] = (uint64_t)__popcll(s_m[0][g]) | (uint64_t)__popcll(s_m[1][g]) << kCF |
+                            (uint64_t)__popcll(s_m[2][g]) << kCK;
+                }
+                lt += gt[j];
+                lc += gc[j];
             }
+            uint64_t gi = wave_incl_sum_dpp(lt), ci = wave_incl_sum_dpp(lc);
+            const uint64_t tot = (uint64_t)uni64(__shfl((long long)gi, 63, 64));
+            const uint64_t ctot = (uint64_t)uni64(__shfl((long long)ci, 63, 64));
+            gi -= lt;
+            ci -= lc;
+            filled += (int64_t)((ctot & kCM) + ((ctot >> kCF) & kCM) + (ctot >> kCK));
+            const uint64_t pr = single ? 0 : lookback_wave(desc, t, sepoch, tot, ctl);
+#pragma unroll
+            for (int j = 0; j < kGL; ++j) {
+                const int g = ln * kGL + j;
+                if (g < kG) {
+                    s_gbase[g] = gi;
+                    s_cp[g] = ci;
+                    sub_base[t * kG + g] = (int64_t)(pr + gi);      // first byte of each group
+                }
+                gi += gt[j];
+                ci += gc[j];
+            }
+            if (ln == 0) {
+                s_cp[kG] = ctot;
+                s_b = pr;
+                s_t = tk;
+                if (t == ntiles - 1) {
+                    __hip_atomic_store(&ctl->total, (int64_t)(pr + tot), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (pr >= kSat) raise_err(ctl, RO_EOVERFLOW);
+                }
+            }
+        }
+        __syncthreads();
+        const int64_t pre = (int64_t)s_b;
+        const int64_t t_after = s_t;
+        if constexpr (kInPlace) {
             const uint64_t outa = reinterpret_cast<uint64_t>(out);
-            int32_t run[3] = {0, 0, 0};
-            auto flush = [&](int64_t p) {
+            bool moved = false;
 #pragma unroll
-                for (int s = 0; s < 3; ++s) {
-                    if (run[s]) {
-                        if (p - pf < R) atomicAdd(&s_cnt[s][p - pf], run[s]);
-                        else if (cnt_out[s]) atomicAdd(&cnt_out[s][p], run[s]);
-                        run[s] = 0;
-                    }
-                }
-            };
-            int64_t pos = base;
-            if (lds_ok) {
-                const int r0 = (int)(c0 - ct0), rend = (int)(ct1 - ct0);
-                int j = lds_last_le(so, 0, (int)Rp, r0);
-                if (so[j] == r0 && out_off) {
-                    // every parent whose first child is c0 (empty ones included)
-                    const int64_t qa = r0 == 0 ? q0t : pf + lds_first_ge(so, 1, j + 1, r0);
-                    for (int64_t q = qa; q <= pf + j; ++q) out_off[q] = pos;
-                }
-                int next = so[j + 1];
-                for (int k = 0; k < kItems; ++k) {
-                    const int rc = r0 + k;
-                    if (rc >= rend) break;
-                    if (rc >= next) {
-                        flush(pf + j);
-                        const int jn = lds_last_le(so, j + 1, (int)Rp, rc);
-                        if (out_off)
-                            for (int64_t q = pf + j + 1; q <= pf + jn; ++q) out_off[q] = pos;
-                        j = jn;
-                        next = so[j + 1];
-                    }
-                    const uint32_t sk = (sw[k >> 2] >> (8 * (k & 3))) & 0xffu;
-                    if (sk < 3) run[sk] += 1;
-                    if (cdst) cdst[c0 + k] = pos;
-                    if constexpr (kInPlace) moved |= s_len[lj + k] != 0 && srcv[k] != outa + (uint64_t)pos;
-                    pos += s_len[lj + k];
-                }
-                flush(pf + j);
-            } else {
-                int64_t p = upper_bound_g(offsets, pf, pl + 1, c0) - 1;
-                if (offsets[p] == c0) {
-                    const int64_t q0 = c0 == ct0 ? q0t : lower_bound_g(offsets, pf, p + 1, c0);
-                    if (out_off)
-                        for (int64_t q = q0; q <= p; ++q) out_off[q] = pos;
-                }
-                int64_t next = offsets[p + 1];
-                for (int k = 0; k < kItems; ++k) {
-                    const int64_t c = c0 + k;
-                    if (c >= ct1) break;
-                    if (c >= next) {
-                        flush(p);
-                        const int64_t pn = advance_parent(offsets, P, p, c);
-                        if (out_off)
-                            for (int64_t q = p + 1; q <= pn; ++q) out_off[q] = pos;
-                        p = pn;
-                        next = offsets[p + 1];
-                    }
-                    const uint32_t sk = (sw[k >> 2] >> (8 * (k & 3))) & 0xffu;
-                    if (sk < 3) run[sk] += 1;
-                    if (cdst) cdst[c] = pos;
-                    if constexpr (kInPlace) moved |= s_len[lj + k] != 0 && srcv[k] != outa + (uint64_t)pos;
-                    pos += s_len[lj + k];
-                }
-                flush(p);
+            for (int k = 0; k < kIt; ++k) {
+                const int g = wv * kIt + k, i = g * 64 + ln;
+                const uint64_t pos = (uint64_t)pre + s_gbase[g] + s_pre[i];
+                moved |= i < nloc && ev[k].y == ((epoch << 2) | RO_SUCCESS) && ev[k].x != 0 && sv[k] != outa + pos;
             }
             if (moved) raise_err(ctl, RO_EINVAL);
         }
-        __syncthreads();
-        for (int64_t j = threadIdx.x; j < R; j += kBlock) {
-#pragma unroll
-            for (int s = 0; s < 3; ++s) {
-                const int32_t v = s_cnt[s][j];
-                if (v && cnt_out[s]) atomicAdd(&cnt_out[s][pf + j], v);
+        if (t_next < ntiles && (kInPlace || wv == 0)) {
+            if constexpr (kInPlace) prepare(t_next, buf ^ 1);   // the check was the slots' last use
+            load_slots(t_next);
+        }
+        // parents starting in this tile: slot offsets and counts
+        auto counts_to = [&](int x) -> uint64_t {
+            const int g = x >> 6;
+            const uint64_t low = (1ull << (x & 63)) - 1;
+            return s_cp[g] + ((uint64_t)__popcll(s_m[0][g] & low) | (uint64_t)__popcll(s_m[1][g] & low) << kCF |
+                              (uint64_t)__popcll(s_m[2][g] & low) << kCK);
+        };
+        while (q < q1) {
+            const int st = (int)(a0 - ct0);
+            const bool whole = a1 <= ct0 + nloc;
+            const uint64_t c = counts_to(whole ? (int)(a1 - ct0) : nloc) - counts_to(st);
+            if (out_off) out_off[q] = pre + (int64_t)(s_gbase[st >> 6] + s_pre[st]);
+            const int32_t c0 = (int32_t)(c & kCM), c1 = (int32_t)((c >> kCF) & kCM), c2 = (int32_t)(c >> kCK);
+            if (whole) {
+                ns[q] = c0;
+                nf[q] = c1;
+                nk[q] = c2;
+            } else {
+                if (c0) atomicAdd(&ns[q], c0);
+                if (c1) atomicAdd(&nf[q], c1);
+                if (c2) atomicAdd(&nk[q], c2);
+            }
+            q += kTh;
+            if (q < q1) {
+                a0 = offsets[q];
+                a1 = offsets[q + 1];
             }
         }
-        __syncthreads();
-        for (int j = threadIdx.x; j < 3 * kCntLds; j += kBlock) (&s_cnt[0][0])[j] = 0;
+        // the parent reaching into this tile from the one before
+        if (threadIdx.x == kTh - 1 && ct0 > 0) {
+            const int64_t e = min64(offsets[q0] - ct0, nloc);
+            if (e > 0) {
+                const uint64_t c = counts_to((int)e);
+                const int32_t c0 = (int32_t)(c & kCM), c1 = (int32_t)((c >> kCF) & kCM), c2 = (int32_t)(c >> kCK);
+                if (c0) atomicAdd(&ns[q0 - 1], c0);
+                if (c1) atomicAdd(&nf[q0 - 1], c1);
+                if (c2) atomicAdd(&nk[q0 - 1], c2);
+            }
+        }
+        if (cdst) {
+#pragma unroll
+            for (int k = 0; k < kIt; ++k) {
+                const int g = wv * kIt + k, i = g * 64 + ln;
+                if (i < nloc) cdst[ct0 + i] = pre + (int64_t)(s_gbase[g] + s_pre[i]);
+            }
+        }
         t = t_next;
+        t_next = t_after;
         buf ^= 1;
     }
-    const int64_t f = block_sum(filled_total, s_wave);
-    if (threadIdx.x == 0 && f)
-        __hip_atomic_fetch_add(&ctl->n_filled, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    ticket_done(ctl, sepoch, desc, desc_cap, &s_last);
+    // the last workgroup to finish: every other one's tiles are posted (its
+    // stores were waited for before it counted itself done)
+    if (threadIdx.x == 0) {
+        int32_t last = 1;
+        if (parts > 1) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const uint64_t o = __hip_atomic_fetch_add(&ctl->gdone, (uint64_t)1 | (uint64_t)filled << 20, __ATOMIC_RELAXED,
+                                                      __HIP_MEMORY_SCOPE_AGENT);
+            last = (o & 0xfffffu) == parts - 1;
+            filled += (int64_t)(o >> 20);
+        }
+        if (last) {
+            const int64_t total = N > 0 ? __hip_atomic_load(&ctl->total, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+            if (out_off) out_off[P] = total;
+            if (cdst && N0 <= canon_cap) cdst[N0] = total;
+            if (n_rejected) *n_rejected = ctl->n_rejected;
+            if (filled != ctl->n_valid) raise_err(ctl, RO_EDUP);
+            if (has_data && total > out_cap) raise_err(ctl, RO_ECAP);
+            // cleared for the next gather (the total is rewritten by every
+            // scan with children)
+            ctl->n_valid = 0;
+            ctl->n_rejected = 0;
+            __hip_atomic_store(&ctl->gdone, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        s_flag = last;
+    }
+    __syncthreads();
+    if (parts > 1 && s_flag) ticket_reset(ctl, sepoch, desc, desc_cap);
 }
 
 // ---------------------------------------------------------------- finalize
-__global__ __launch_bounds__(kBlock) void k_gather_finalize(
-    const int64_t *__restrict__ offsets, int64_t P, int64_t canon_cap, int64_t *__restrict__ out_off,
-    int64_t out_cap, int has_data, const int32_t *__restrict__ ns, const int32_t *__restrict__ nf,
-    const int32_t *__restrict__ nk, uint8_t *__restrict__ complete, uint8_t *__restrict__ pstate,
-    int64_t *__restrict__ cdst, uint8_t *__restrict__ barrier, const uint64_t *__restrict__ gkey,
-    int64_t *n_rejected, uint32_t epoch, Ctl *ctl)
+// Complete / state of every parent from its counts, once the scan is done, and
+// the slot offsets of parents with no child at or after their start.  Part of
+// the copy's launch where there is one (one launch less, about 5 us of a
+// small gather), else a launch of its own.  `g0` of `gn` threads.
+__device__ __forceinline__ void finalize_parents(const GatherFin &f, int64_t g0, int64_t gn, int64_t N, int64_t total)
 {
-    const int64_t N0 = offsets[P];
-    const int64_t N = N0 <= canon_cap ? N0 : 0;
-    const int64_t total = N > 0 ? ctl->total : 0;
-    const int64_t gtid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (gtid == 0) {
-        if (out_off) out_off[P] = total;
-        if (cdst && N0 <= canon_cap) cdst[N0] = total;
-        if (n_rejected) *n_rejected = ctl->n_rejected;
-        if (ctl->n_filled != ctl->n_valid) raise_err(ctl, RO_EDUP);
-        if (has_data && total > out_cap) raise_err(ctl, RO_ECAP);
-        // the call's counters are read only here: cleared for the next
-        // gather (the byte total is rewritten by every scan with children)
-        ctl->n_valid = 0;
-        ctl->n_filled = 0;
-        ctl->n_rejected = 0;
-    }
-    for (int64_t p = gtid; p < P; p += (int64_t)gridDim.x * kBlock) {
-        const int64_t st = offsets[p];
-        const int64_t k = offsets[p + 1] - st;
-        if (st >= N && out_off) out_off[p] = total;       // no child at or after its start
-        const int64_t a = ns ? ns[p] : 0, b = nf ? nf[p] : 0, c = nk ? nk[p] : 0;
+    for (int64_t p = g0; p < f.P; p += gn) {
+        const int64_t st = f.offsets[p];
+        const int64_t k = f.offsets[p + 1] - st;
+        if (st >= N && f.out_off) f.out_off[p] = total;
+        const int64_t a = f.ns[p], b = f.nf[p], c = f.nk[p];
         // a barred parent's uncommitted children are suppressed: it is done
         bool barred = false;
-        if (barrier) {
-            barred = barrier[p] || (uint32_t)(gkey[p] >> 32) == epoch;
-            if (barred) barrier[p] = 1;
+        if (f.barrier) {
+            barred = f.barrier[p] || (uint32_t)(f.gkey[p] >> 32) == f.epoch;
+            if (barred) f.barrier[p] = 1;
         }
         const bool done = barred || (a + b + c) == k;
-        if (complete) complete[p] = done ? 1 : 0;
-        if (pstate) pstate[p] = !done ? RO_PENDING : ((barred || b > 0) ? RO_FAILED : RO_SUCCESS);
+        if (f.complete) f.complete[p] = done ? 1 : 0;
+        if (f.pstate) f.pstate[p] = !done ? RO_PENDING : ((barred || b > 0) ? RO_FAILED : RO_SUCCESS);
     }
 }
 
-// finalize needs all three counters even if the caller wants none of them;
-// the runtime passes workspace arrays in that case.
+__global__ __launch_bounds__(kBlock) void k_gather_finalize(GatherFin f, const Ctl *ctl)
+{
+    const int64_t N0 = f.offsets[f.P];
+    const int64_t N = N0 <= f.canon_cap ? N0 : 0;
+    finalize_parents(f, (int64_t)blockIdx.x * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock, N,
+                     N > 0 ? ctl->total : 0);
+}
 
 // ---------------------------------------------------------------- copy
 // Each wave works alone on its units of output bytes, with no workgroup
@@ -486,8 +512,8 @@ __global__ __launch_bounds__(kBlock) void k_gather_finalize(
 // chip busy whether the records are a few bytes or megabytes long, and few
 // parents or many.
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RO_COPY_WAVES))) void k_gather_copy(
-    const int64_t *__restrict__ offsets, int64_t P, const Canon *__restrict__ canon, int64_t canon_cap,
-    const int64_t *__restrict__ sub_base, uint8_t *__restrict__ out, int64_t slots, uint32_t epoch, Ctl *ctl)
+    GatherFin fin, const Canon *__restrict__ canon, const int64_t *__restrict__ sub_base, uint8_t *__restrict__ out,
+    int64_t slots, Ctl *ctl)
 {
     constexpr int kWaves = kBlock / 64;
     constexpr int kGroups = kSub / kGrp;
@@ -495,11 +521,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RO_COPY_
     __shared__ uint64_t s_src_all[kWaves][kSub];        // source address of its first clipped byte
     __shared__ int32_t s_edge_all[kWaves][kEdgeCap];    // edge chunks of the window
     __shared__ int16_t s_edger_all[kWaves][kEdgeCap];   // the record holding each one's first byte
-    if (read_err(ctl) != 0) return;                      // any recorded error: copy nothing
-    const int64_t N0 = offsets[P];
-    const int64_t N = N0 <= canon_cap ? N0 : 0;
+    const int64_t N0 = fin.offsets[fin.P];
+    const int64_t N = N0 <= fin.canon_cap ? N0 : 0;
     const int64_t T = N > 0 ? ctl->total : 0;           // output bytes, from the scan
-    if (T <= 0) return;
+    const uint32_t epoch = fin.epoch;
+    // parents go to the workgroups from the last one on, which have no unit
+    // in a small copy
+    finalize_parents(fin, (int64_t)(gridDim.x - 1 - blockIdx.x) * kBlock + threadIdx.x, (int64_t)gridDim.x * kBlock, N, T);
+    if (T <= 0 || read_err(ctl) != 0) return;            // any recorded error: copy nothing
     const int64_t ngrp = (N + kGrp - 1) / kGrp;
     const uint64_t outa = reinterpret_cast<uint64_t>(out);
     const int64_t mis = (int64_t)(outa & 15);
@@ -570,26 +599,34 @@ hipError_t launch_gather(const Launch &L, const GatherArgs &a, const GatherWs &w
     RO_LAUNCH(L, RO_K_GATHER_SCATTER, k_gather_scatter, dim3((unsigned)grid_r), dim3(kBlock), 0, L.stream,
               a.rp, a.ro, a.rs, a.roff, a.data, a.n, a.offsets, a.P, w.canon, w.canon_cap, a.ns, a.nf,
               a.nk, a.barrier, w.gkey, epoch, L.ctl);
-    // three workgroups per CU drew tickets faster than four (fewer waiting
-    // on the look-back at once) and two left the largest scans short of work
-    const int64_t grid_s = (int64_t)L.num_cus * RO_SCAN_WG;
     // output aliasing the report bytes: the scan checks that nothing moves,
     // and there is nothing to copy
     const bool in_place = a.out_data != nullptr && a.out_data == a.data;
-    if (in_place) {
-        RO_LAUNCH(L, RO_K_GATHER_SCAN, k_gather_scan<true>, dim3((unsigned)grid_s), dim3(kBlock), 0, L.stream,
-                  a.offsets, a.P, w.canon, w.canon_cap, a.out_off, a.ns, a.nf, a.nk, a.cdst, w.sub_base, a.out_data,
-                  epoch, L.ctl, L.desc, L.desc_cap);
-    } else {
-        RO_LAUNCH(L, RO_K_GATHER_SCAN, k_gather_scan<false>, dim3((unsigned)grid_s), dim3(kBlock), 0, L.stream,
-                  a.offsets, a.P, w.canon, w.canon_cap, a.out_off, a.ns, a.nf, a.nk, a.cdst, w.sub_base, nullptr,
-                  epoch, L.ctl, L.desc, L.desc_cap);
-    }
+    const bool small = a.n <= kScanSmall;
+    auto scan = in_place ? (small ? k_gather_scan<kScanSmallTh, kScanSmallIt, true> : k_gather_scan<kScanTh, kScanIt, true>)
+                         : (small ? k_gather_scan<kScanSmallTh, kScanSmallIt, false> : k_gather_scan<kScanTh, kScanIt, false>);
+    const int64_t grid_s = (int64_t)L.num_cus * (small ? 4 : 1);
+    RO_LAUNCH(L, RO_K_GATHER_SCAN, scan, dim3((unsigned)grid_s), dim3(small ? kScanSmallTh : kScanTh), 0, L.stream, a.offsets,
+              a.P, w.canon, w.canon_cap, a.out_off, a.out_cap, a.out_data != nullptr ? 1 : 0, a.ns, a.nf, a.nk, a.cdst,
+              w.sub_base, a.out_data, a.n_rejected, epoch, L.ctl, L.desc, L.desc_cap);
+    GatherFin fin;
+    fin.offsets = a.offsets;
+    fin.P = a.P;
+    fin.canon_cap = w.canon_cap;
+    fin.out_off = a.out_off;
+    fin.ns = a.ns;
+    fin.nf = a.nf;
+    fin.nk = a.nk;
+    fin.complete = a.complete;
+    fin.pstate = a.pstate;
+    fin.barrier = a.barrier;
+    fin.gkey = w.gkey;
+    fin.epoch = epoch;
     int64_t grid_f = (a.P + kBlock - 1) / kBlock;
     grid_f = grid_f < 1 ? 1 : (grid_f > (int64_t)L.num_cus * 8 ? (int64_t)L.num_cus * 8 : grid_f);
-    RO_LAUNCH(L, RO_K_GATHER_FINALIZE, k_gather_finalize, dim3((unsigned)grid_f), dim3(kBlock), 0, L.stream, a.offsets,
-                       a.P, w.canon_cap, a.out_off, a.out_cap, a.out_data != nullptr ? 1 : 0, a.ns, a.nf,
-                       a.nk, a.complete, a.pstate, a.cdst, a.barrier, w.gkey, a.n_rejected, epoch, L.ctl);
+    if (a.out_data == nullptr || in_place)
+        RO_LAUNCH(L, RO_K_GATHER_FINALIZE, k_gather_finalize, dim3((unsigned)grid_f), dim3(kBlock), 0, L.stream, fin,
+                  L.ctl);
     if (a.out_data != nullptr && !in_place) {
         // One unit per wave, handed out in output order as workgroups end, as
         // far as out_cap (the most the total can be) asks for them: a
@@ -599,8 +636,9 @@ hipError_t launch_gather(const Launch &L, const GatherArgs &a, const GatherWs &w
         const int64_t big_c = a.out_cap / (kCopyUnit * 4) + 1, small_c = a.out_cap / (kCopyMinUnit * 4) + 1;
         int64_t grid_c = small_c < max_s ? small_c : max_s;
         grid_c = big_c > grid_c ? (big_c < max_c ? big_c : max_c) : grid_c;
-        RO_LAUNCH(L, RO_K_GATHER_COPY, k_gather_copy, dim3((unsigned)grid_c), dim3(kBlock), 0, L.stream, a.offsets,
-                  a.P, w.canon, w.canon_cap, w.sub_base, a.out_data, slots, epoch, L.ctl);
+        grid_c = grid_c > grid_f ? grid_c : grid_f;         // and enough for the parents
+        RO_LAUNCH(L, RO_K_GATHER_COPY, k_gather_copy, dim3((unsigned)grid_c), dim3(kBlock), 0, L.stream, fin, w.canon,
+                  w.sub_base, a.out_data, slots, L.ctl);
     }
     return hipGetLastError();
 }

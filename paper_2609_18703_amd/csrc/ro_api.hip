@@ -143,6 +143,8 @@ hipError_t dev_alloc(T **p, int64_t n)
 }
 
 int64_t tiles_for(int64_t n) { return (n + kTile - 1) / kTile + 1; }
+// look-back tiles of a gather's scan (at its smaller tile)
+int64_t scan_tiles_for(int64_t n) { return (n + 4 * kBlock - 1) / (4 * kBlock) + 1; }
 
 // Make sure the look-back descriptors cover `tiles` tiles.
 int ensure_desc(ro_ctx *c, int64_t tiles)
@@ -192,7 +194,7 @@ int ensure_canon(ro_ctx *c, int64_t children)
     c->canon_cap = n;
     c->sub_cap = subs;
     c->cmap_cap = maps;
-    return ensure_desc(c, tiles_for(n));
+    return ensure_desc(c, scan_tiles_for(n));
 }
 
 int ensure_cnt(ro_ctx *c, int64_t parents)
@@ -452,7 +454,7 @@ int ro_gather(ro_ctx *c, const ro_reports *r, const int64_t *offsets, int64_t n_
     // device, so the report count is the host's best lower bound
     int rc = ensure_canon(c, c->canon_cap > r->n ? c->canon_cap : r->n);
     if (rc) return rc;
-    rc = ensure_desc(c, tiles_for(c->canon_cap));
+    rc = ensure_desc(c, scan_tiles_for(c->canon_cap));
     if (rc) return rc;
     GatherArgs a;
     a.rp = r->parent;

@@ -125,12 +125,26 @@ __device__ __forceinline__ void desc_put_raw(uint64_t *d, uint64_t w)
     __hip_atomic_store(d, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// By the last workgroup to finish, all its threads: the ticket back to 0 and
+// the epoch one further; when the 16-bit epoch would wrap every descriptor is
+// cleared first, so an old descriptor can never carry the epoch of a later
+// launch.
+__device__ __forceinline__ void ticket_reset(Ctl *ctl, uint32_t epoch, uint64_t *desc, int64_t desc_cap)
+{
+    const bool wrap = epoch + 1 > kMaxScanEpoch;
+    if (wrap)
+        for (int64_t i = threadIdx.x; i < desc_cap; i += blockDim.x) desc_put_raw(&desc[i], 0);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(&ctl->ticket, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ctl->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&ctl->scan_epoch, wrap ? 1u : epoch + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
 // Called once by every workgroup that takes part, after its last tile: the
 // first `parts` workgroups of the grid (ticket_done: all of them; the others
-// return without drawing a ticket).  The last one resets the ticket and
-// advances the epoch; when the 16-bit epoch would wrap it first clears every
-// descriptor, so an old descriptor can never carry the epoch of a later
-// launch.
+// return without drawing a ticket).  The last one resets.
 __device__ __forceinline__ void ticket_done_n(Ctl *ctl, uint32_t epoch, uint64_t *desc, int64_t desc_cap,
                                               int32_t *s_last, uint32_t parts)
 {
@@ -140,18 +154,7 @@ __device__ __forceinline__ void ticket_done_n(Ctl *ctl, uint32_t epoch, uint64_t
         *s_last = (d == parts - 1) ? 1 : 0;
     }
     __syncthreads();
-    if (*s_last) {
-        const bool wrap = epoch + 1 > kMaxScanEpoch;
-        if (wrap)
-            for (int64_t i = threadIdx.x; i < desc_cap; i += blockDim.x) desc_put_raw(&desc[i], 0);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            __hip_atomic_store(&ctl->ticket, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&ctl->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&ctl->scan_epoch, wrap ? 1u : epoch + 1, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
+    if (*s_last) ticket_reset(ctl, epoch, desc, desc_cap);
 }
 
 __device__ __forceinline__ void ticket_done(Ctl *ctl, uint32_t epoch, uint64_t *desc, int64_t desc_cap,

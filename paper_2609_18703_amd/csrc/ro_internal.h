@@ -13,7 +13,6 @@ constexpr int kItems = 16;                  // items per thread in scan tiles
 constexpr int kTile = kBlock * kItems;      // 4096 entries per scan tile
 constexpr int kSub = 256;                   // children per copy window
 constexpr int kGrp = 64;                    // children per group: the scan records where each group's bytes start
-constexpr int kCntLds = 512;                // parents whose counts a tile aggregates in LDS
 
 // Canonical per-child record written by the report scatter.  `tag` holds the
 // call epoch (bits 31..2) and the terminal state (bits 1..0): an entry is
@@ -32,7 +31,7 @@ struct Ctl {
     uint32_t done;           // workgroups finished (ticketed kernels)
     uint64_t ticket;         // next tile ticket (ticketed kernels)
     int64_t n_valid;         // gather: accepted (non-pending) reports of this call
-    int64_t n_filled;        // gather: canonical slots holding this call's epoch
+    uint64_t gdone;          // gather scan: workgroups finished, and slots holding this call's epoch << 20
     int64_t total;           // gather / emit: total bytes
     int64_t n_items;         // emit: emitted parents
     int64_t n_virtual;       // emit: children of emitted parents
@@ -126,6 +125,17 @@ struct GatherArgs {
     int64_t *cdst;           // per-child output positions (or null)
     uint8_t *barrier;        // group-failure barrier of the Call (or null)
     int64_t *n_rejected;     // device scalar (or null)
+};
+
+// what the per-parent part of a gather reads and writes
+struct GatherFin {
+    const int64_t *offsets;
+    int64_t P, canon_cap;
+    int64_t *out_off;
+    const int32_t *ns, *nf, *nk;
+    uint8_t *complete, *pstate, *barrier;
+    const uint64_t *gkey;
+    uint32_t epoch;
 };
 
 struct GatherWs {

@@ -90,3 +90,28 @@ def test_gather_groups_and_units(ctx, n, record):
     for mis, order in ((0, rng.permutation(n)), (5, np.arange(n)), (15, rng.permutation(n))):
         _say("gather", n, record, mis)
         _gather_case(ctx, counts, lengths, states, order, mis=mis, lead=mis % 7)
+
+
+# both scan tile sizes (up to 131,072 reports tiles of 1,024 children, beyond
+# tiles of 8,192), whole and ragged last tiles, parents over several tiles,
+# empty parents at tile boundaries, reports missing
+@pytest.mark.parametrize("n, missing", [(8192, 0), (8193, 9), (131_072, 0), (131_073, 0), (139_264, 0), (139_265, 50),
+                                        (150_000, 149_000), (300_001, 0)])
+def test_gather_scan_tiles(ctx, n, missing):
+    rng = np.random.default_rng(n + missing)
+    counts = [0, 0, min(n // 3, 100_000), 0]
+    left = n - sum(counts)
+    first = 8192 - sum(counts) % 8192          # the next parents end exactly on a tile boundary
+    if first < left:
+        counts += [first, 0, 0, 0]
+        left -= first
+    while left > 0:
+        k = int(min(left, rng.choice([0, 1, 1, 2, 5, 9, 64, 3000])))
+        counts.append(k)
+        left -= k
+    counts += [0] * 5
+    lengths = rng.integers(0, 20, n)
+    states = rng.choice([O.SUCCESS] * 6 + [O.FAILED, O.SKIPPED], n).astype(np.uint8)
+    order = rng.permutation(n)[:n - missing]
+    _say("gather scan", n, missing)
+    _gather_case(ctx, counts, lengths, states, order)
