@@ -57,10 +57,99 @@ __device__ __forceinline__ int map_shift(int64_t N, int64_t P)
     return s;
 }
 
+// Mask map, one 16-byte entry per block of 64 children: x = the parent p0 of
+// the block's first child, y = that child's ordinal, z and w = a mask with bit
+// j set (j > 0) when child j of the block is the first of its parent.  A
+// child's parent is p0 plus the number of mask bits up to it, its ordinal the
+// distance from the last of them (or from the block's start, plus y): one
+// load per lookup and no search.  Where an empty parent lies between two
+// children of the block the count would miss it: bit 31 of x then says that
+// children behind a mask bit search the offsets.  At N / 4 bytes it is larger
+// than the coarse map for large parents, so it is used while it stays in
+// every XCD's L2 (4 MB) beside the queue, or while parents are small enough
+// for the coarse map to be no smaller (use_mask_map).
+constexpr int kMaskShift = 6;
+
+// The host knows the queue, the parents and the children reserved (the map has
+// room for those), not the children themselves.  Measured, whole batch: 2.7M
+// children under 300,000 parents 23 us with this map, 48 with the coarse one;
+// 5M under 30,000 46 and 78; 8M under 20,000 91 and 107; 20M under 2.7M 238
+// and 955; but 41M under 100,000 540 (a 10 MB map) against 448.  A short queue
+// over a large reservation keeps the coarse map, whose build writes less.
+constexpr int64_t kMaskChildren = (int64_t)12 << 20;
+static bool use_mask_map(int64_t Q, int64_t P, int64_t reserved)
+{
+    if (reserved > kMaskChildren && reserved > 4 * Q) return false;
+    return Q <= kMaskChildren || Q < 64 * P;
+}
+
+// which structure a batch kernel finds an entry's parent in
+enum BatchMap { kMapSearch = 0, kMapCoarse = 1, kMapMask = 2, kMapChild = 3 };
+struct MapArgs {
+    const void *map;         // coarse or mask map, or the child -> parent map
+    int64_t cap;             // its entries
+};
+
 // entries of a thread whose lookups are in flight together
 #ifndef RO_BATCH_LOOKUPS
 #define RO_BATCH_LOOKUPS 4
 #endif
+
+// A wave builds 16 entries (1,024 children): the first parent starting among
+// them by a wave search, then 64 parents' starts per step, each of which sets
+// its bit in LDS; the parent of a block's first child is the one starting
+// there, or the last one starting before.
+__global__ __launch_bounds__(kBlock) void k_batch_mask_map(const int64_t *__restrict__ offsets, int64_t P,
+                                                           uint4 *__restrict__ map, int64_t map_cap)
+{
+    constexpr int kB = 16, kSpan = kB << kMaskShift;
+    __shared__ uint64_t s_mask[kBlock / 64][kB];
+    __shared__ uint32_t s_last[kBlock / 64][kB];      // last parent starting in the block, plus 1
+    __shared__ uint32_t s_at0[kBlock / 64][kB];       // parent starting at the block's first child, plus 1
+    __shared__ uint32_t s_empty[kBlock / 64][kB];
+    const int64_t N = offsets[P];
+    int64_t nmap = (N + (1 << kMaskShift) - 1) >> kMaskShift;
+    nmap = nmap < map_cap ? nmap : map_cap;
+    const int w = (int)(threadIdx.x >> 6), lane = lane_id();
+    const int64_t nwaves = (int64_t)gridDim.x * (kBlock / 64);
+    for (int64_t wt = (int64_t)blockIdx.x * (kBlock / 64) + w; wt * kB < nmap; wt += nwaves) {
+        const int64_t cb = wt * kSpan, ce = min64(cb + kSpan, N);
+        if (lane < kB) {
+            s_mask[w][lane] = 0;
+            s_last[w][lane] = s_at0[w][lane] = s_empty[w][lane] = 0;
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int64_t q0 = cb == 0 ? 0 : wave_last_le(offsets, 0, P + 1, cb - 1) + 1;
+        for (int64_t qb = q0;; qb += 64) {
+            const int64_t q = qb + lane;
+            const int64_t st = q < P ? offsets[q] : N, en = q < P ? offsets[q + 1] : N;
+            if (st >= cb && st < ce) {
+                const int b = (int)((st - cb) >> kMaskShift), j = (int)(st & ((1 << kMaskShift) - 1));
+                if (en > st) {
+                    if (j > 0) atomicOr((unsigned long long *)&s_mask[w][b], 1ull << j);
+                    else s_at0[w][b] = (uint32_t)q + 1;
+                    atomicMax(&s_last[w][b], (uint32_t)q + 1);
+                } else if (j > 0) {
+                    s_empty[w][b] = 1;
+                }
+            }
+            if (__ballot(st >= ce) != 0) break;
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int64_t b = wt * kB + lane;
+        if (lane < kB) {
+            uint32_t before = (uint32_t)q0;               // the last parent starting before the block, plus 1
+            for (int k = 0; k < lane; ++k) before = s_last[w][k] > before ? s_last[w][k] : before;
+            before = s_at0[w][lane] ? s_at0[w][lane] : before;
+            const uint32_t p0 = before ? before - 1 : 0u;
+            const uint64_t m = s_mask[w][lane];
+            if (b < nmap)
+                map[b] = make_uint4(p0 | (s_empty[w][lane] ? kMapOne : 0u),
+                                    (uint32_t)((b << kMaskShift) - offsets[p0]), (uint32_t)m, (uint32_t)(m >> 32));
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
 
 __global__ void k_batch_cmap(const int64_t *__restrict__ offsets, int64_t P, uint2 *__restrict__ map,
                              int64_t map_cap)
@@ -83,22 +172,12 @@ __global__ void k_batch_cmap(const int64_t *__restrict__ offsets, int64_t P, uin
 // child id below N; the others are left alone).  Every step's loads are in
 // flight together: the map entries of all K, then the rounds of a lockstep
 // binary search for the children of blocks that hold several parents (or
-// that lie past the map).  Needs P < 2^31 when nmap > 0.
+// that lie past the map).  Needs P < 2^31 and a map entry.
 template <int K>
 __device__ __forceinline__ void tags_of(const uint2 *__restrict__ map, int64_t nmap, int sh,
                                         const int64_t *__restrict__ offsets, int64_t P, const uint32_t (&c)[K],
                                         uint32_t live, uint32_t (&par)[K], uint32_t (&ord)[K])
 {
-    if (nmap == 0) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            if (!((live >> k) & 1u)) continue;
-            const int64_t p = upper_bound_g(offsets, 0, P + 1, (int64_t)c[k]) - 1;
-            par[k] = (uint32_t)p;
-            ord[k] = (uint32_t)((int64_t)c[k] - offsets[p]);
-        }
-        return;
-    }
     uint32_t l[K], h[K];
     int64_t vl[K];
     {
@@ -167,283 +246,43 @@ __device__ __forceinline__ void tags_of(const uint2 *__restrict__ map, int64_t n
     }
 }
 
-template <bool kByMap>
-__global__ __launch_bounds__(kBlock) void k_batch(
-    const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
-    const int64_t *__restrict__ offsets, int64_t P, const uint2 *__restrict__ cmap, int64_t cmap_cap,
-    int32_t B, uint32_t *__restrict__ out_child, uint32_t *__restrict__ out_parent,
-    uint32_t *__restrict__ out_ordinal, int64_t out_cap, int64_t *n_out, int64_t *n_batches,
-    const uint8_t *__restrict__ barrier, const uint32_t *__restrict__ cpar, int64_t cpar_n, Ctl *ctl,
-    uint64_t *desc, int64_t desc_cap, int64_t ntiles, int vec_ok)
+// The parent of child c by the offsets alone, among [lo, hi).
+__device__ __noinline__ int64_t search_parent(const int64_t *offsets, int64_t lo, int64_t hi, int64_t c)
 {
-    const uint32_t epoch = scan_epoch(ctl);
-    __shared__ uint32_t s_out[kTile];          // one output array of a tile, in slot order
-    __shared__ int64_t s_wave[kBlock / 64];
-    __shared__ uint64_t s_b;
-    __shared__ int64_t s_t;
-    __shared__ int32_t s_last;
-    const int64_t N = cpar ? min64(offsets[P], cpar_n) : offsets[P];   // ids past the map are out of range
-    const int sh = map_shift(offsets[P], P);     // the map's block size, as k_batch_cmap built it
-    int64_t nmap = (N + (1 << sh) - 1) >> sh;
-    nmap = nmap < cmap_cap ? nmap : cmap_cap;
-    const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
-    const bool nt = Q > kTagNtEntries;
-    for (;;) {
-        const int64_t t = next_ticket(ctl, &s_t);
-        if (t >= ntiles) break;
-        const int64_t i0 = t * kTile + (int64_t)threadIdx.x * kItems;
-        uint32_t q[kItems];
-        uint32_t kmask = 0;
-        if (vec_ok && i0 + kItems <= Q) {
-            const uint4 *qp = reinterpret_cast<const uint4 *>(queue + i0);
-#pragma unroll
-            for (int k = 0; k < kItems / 4; ++k) {
-                const uint4 x = qp[k];
-                q[4 * k] = x.x; q[4 * k + 1] = x.y; q[4 * k + 2] = x.z; q[4 * k + 3] = x.w;
-            }
-            if (keep) {
-                const uint4 kv = *reinterpret_cast<const uint4 *>(keep + i0);
-                const uint32_t w[4] = {kv.x, kv.y, kv.z, kv.w};
-#pragma unroll
-                for (int k = 0; k < kItems; ++k)
-                    kmask |= (((w[k >> 2] >> (8 * (k & 3))) & 0xffu) != 0 ? 1u : 0u) << k;
-            } else {
-                kmask = 0xffffu;
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < kItems; ++k) {
-                const int64_t i = i0 + k;
-                q[k] = 0;
-                if (i < Q) {
-                    q[k] = queue[i];
-                    if (keep == nullptr || keep[i] != 0) kmask |= 1u << k;
-                }
-            }
-        }
-        // lineage tags of the ready entries, RO_BATCH_LOOKUPS of a thread's
-        // entries at a time with all their lookups in flight; an entry of a
-        // barred parent is not ready
-        uint32_t par[kItems], ord[kItems];
-        bool bad_range = false;
-        uint32_t live = 0;
-#pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            par[k] = 0xffffffffu;
-            ord[k] = 0xffffffffu;
-            if (kmask & (1u << k)) {
-                if ((int64_t)q[k] >= N) bad_range = true;
-                else live |= 1u << k;
-            }
-        }
-        if (want_tags || barrier) {
-            if constexpr (kByMap) {
-#pragma unroll
-                for (int k = 0; k < kItems; ++k) {
-                    if (!((live >> k) & 1u)) continue;
-                    const int64_t p = (int64_t)cpar[q[k]];
-                    par[k] = (uint32_t)p;
-                    ord[k] = (uint32_t)((int64_t)q[k] - offsets[p]);
-                }
-            } else {
-                constexpr int H = RO_BATCH_LOOKUPS;
-#pragma unroll
-                for (int hf = 0; hf < kItems / H; ++hf) {
-                    uint32_t cc[H], pp[H], oo[H];
-#pragma unroll
-                    for (int k = 0; k < H; ++k) cc[k] = q[hf * H + k];
-                    tags_of<H>(cmap, nmap, sh, offsets, P, cc, (live >> (hf * H)) & ((1u << H) - 1u), pp, oo);
-#pragma unroll
-                    for (int k = 0; k < H; ++k) {
-                        if ((live >> (hf * H + k)) & 1u) {
-                            par[hf * H + k] = pp[k];
-                            ord[hf * H + k] = oo[k];
-                        }
-                    }
-                }
-            }
-            if (barrier) {
-#pragma unroll
-                for (int k = 0; k < kItems; ++k) {
-                    if (((live >> k) & 1u) && barrier[par[k]]) {
-                        kmask &= ~(1u << k);                             // suppressed: takes no slot
-                        par[k] = 0xffffffffu;
-                        ord[k] = 0xffffffffu;
-                    }
-                }
-            }
-        }
-        if (bad_range) raise_err(ctl, RO_ERANGE);
-        const int cnt = __popc(kmask);
-        int64_t tot;
-        const int64_t ex = block_excl_scan(cnt, s_wave, tot);
-        const uint64_t pre = tile_prefix(desc, t, epoch, (uint64_t)tot, &s_b, ctl);
-        const int64_t base = (int64_t)pre;
-        if (base + tot > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
-        const int64_t lim = out_cap - base < tot ? (out_cap - base > 0 ? out_cap - base : 0) : tot;
-        // stage each requested output array in LDS in slot order, then write
-        // the tile's contiguous slot range with coalesced stores
-#pragma unroll 1
-        for (int which = 0; which < 3; ++which) {
-            uint32_t *dst = which == 0 ? out_child : (which == 1 ? out_parent : out_ordinal);
-            if (dst == nullptr) continue;
-            int slot = (int)ex;
-#pragma unroll
-            for (int k = 0; k < kItems; ++k) {
-                if (kmask & (1u << k)) {
-                    s_out[slot] = which == 0 ? q[k] : (which == 1 ? par[k] : ord[k]);
-                    ++slot;
-                }
-            }
-            __syncthreads();
-            write_tags(dst, base, s_out, lim, nt);
-            __syncthreads();
-        }
-        if (t == ntiles - 1 && threadIdx.x == 0) {
-            const int64_t m = (int64_t)pre + tot;
-            if (n_out) *n_out = m;
-            if (n_batches) *n_batches = (m + B - 1) / B;
-        }
-    }
-    ticket_done(ctl, epoch, desc, desc_cap, &s_last);
+    return upper_bound_g(offsets, lo, hi, c) - 1;
 }
 
-// The ready queue with a dispatch mask and no barrier: an entry is ready iff
-// its mask byte is set, so a tile's count of ready entries is known from the
-// mask alone, before any lineage lookup.  A workgroup takes kBatchSuper
-// consecutive tiles per ticket (four times fewer tickets and look-back
-// steps), counts them, publishes their aggregate and finishes the look-back
-// first; only then does it look up the tags of each tile's ready entries and
-// write them, staged in LDS, to the tile's contiguous slot range.
-constexpr int kBatchSuper = 4;
-
-__global__ __launch_bounds__(kBlock) void k_batch_keep(
-    const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
-    const int64_t *__restrict__ offsets, int64_t P, const uint2 *__restrict__ cmap, int64_t cmap_cap, int32_t B,
-    uint32_t *__restrict__ out_child, uint32_t *__restrict__ out_parent, uint32_t *__restrict__ out_ordinal,
-    int64_t out_cap, int64_t *n_out, int64_t *n_batches, Ctl *ctl, uint64_t *desc, int64_t desc_cap,
-    int64_t nsuper, int vec_ok)
+// The same as tags_of with the mask map.
+template <int K>
+__device__ __forceinline__ void tags_of_mask(const uint4 *__restrict__ map, int64_t nmap,
+                                             const int64_t *__restrict__ offsets, int64_t P, const uint32_t (&c)[K],
+                                             uint32_t live, uint32_t (&par)[K], uint32_t (&ord)[K])
 {
-    const uint32_t epoch = scan_epoch(ctl);
-    __shared__ uint32_t s_out[kTile];
-    __shared__ int64_t s_wave[kBlock / 64];
-    __shared__ int64_t s_sub[kBatchSuper];
-    __shared__ uint64_t s_b;
-    __shared__ int64_t s_t;
-    __shared__ int32_t s_last;
-    const int64_t N = offsets[P];
-    const int sh = map_shift(offsets[P], P);     // the map's block size, as k_batch_cmap built it
-    int64_t nmap = (N + (1 << sh) - 1) >> sh;
-    nmap = nmap < cmap_cap ? nmap : cmap_cap;
-    const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
-    const bool nt = Q > kTagNtEntries;
-    for (;;) {
-        const int64_t t = next_ticket(ctl, &s_t);
-        if (t >= nsuper) break;
-        // ready flags of the super-tile's entries: bit k of km[s] is entry
-        // (tile s, this thread, item k)
-        uint32_t km[kBatchSuper];
+    uint4 e[K];
 #pragma unroll
-        for (int s = 0; s < kBatchSuper; ++s) {
-            const int64_t i0 = (t * kBatchSuper + s) * kTile + (int64_t)threadIdx.x * kItems;
-            km[s] = 0;
-            if (vec_ok && i0 + kItems <= Q) {
-                const uint4 kv = *reinterpret_cast<const uint4 *>(keep + i0);
-                const uint32_t w[4] = {kv.x, kv.y, kv.z, kv.w};
+    for (int k = 0; k < K; ++k) {
+        const int64_t j = (int64_t)(c[k] >> kMaskShift);
+        e[k] = map[((live >> k) & 1u) && j < nmap ? j : 0];
+    }
+    uint32_t slow = 0;
 #pragma unroll
-                for (int k = 0; k < kItems; ++k)
-                    km[s] |= (((w[k >> 2] >> (8 * (k & 3))) & 0xffu) != 0 ? 1u : 0u) << k;
-            } else {
-                for (int k = 0; k < kItems; ++k)
-                    if (i0 + k < Q && keep[i0 + k] != 0) km[s] |= 1u << k;
-            }
-        }
-        int64_t ex[kBatchSuper];
-        int64_t agg = 0;
+    for (int k = 0; k < K; ++k) {
+        const int j = (int)(c[k] & ((1u << kMaskShift) - 1));
+        const uint64_t m = ((uint64_t)e[k].w << 32 | e[k].z) & ((2ull << j) - 1);
+        const uint32_t n = (uint32_t)__popcll(m);
+        par[k] = (e[k].x & ~kMapOne) + n;
+        ord[k] = n ? (uint32_t)(j - (63 - __clzll((long long)m))) : e[k].y + (uint32_t)j;
+        if (((live >> k) & 1u) && ((n && (e[k].x & kMapOne)) || (int64_t)(c[k] >> kMaskShift) >= nmap)) slow |= 1u << k;
+    }
+    if (slow) {
 #pragma unroll
-        for (int s = 0; s < kBatchSuper; ++s) {
-            int64_t tot;
-            ex[s] = block_excl_scan(__popc(km[s]), s_wave, tot);
-            if (threadIdx.x == 0) s_sub[s] = agg;
-            agg += tot;
-        }
-        const int64_t pre = (int64_t)tile_prefix(desc, t, epoch, (uint64_t)agg, &s_b, ctl);
-        if (pre + agg > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
-        bool bad_range = false;
-#pragma unroll 1
-        for (int s = 0; s < kBatchSuper; ++s) {
-            const int64_t i0 = (t * kBatchSuper + s) * kTile + (int64_t)threadIdx.x * kItems;
-            uint32_t q[kItems];
-            if (vec_ok && i0 + kItems <= Q) {
-                const uint4 *qp = reinterpret_cast<const uint4 *>(queue + i0);
-#pragma unroll
-                for (int k = 0; k < kItems / 4; ++k) {
-                    const uint4 x = qp[k];
-                    q[4 * k] = x.x; q[4 * k + 1] = x.y; q[4 * k + 2] = x.z; q[4 * k + 3] = x.w;
-                }
-            } else {
-#pragma unroll
-                for (int k = 0; k < kItems; ++k) q[k] = i0 + k < Q ? queue[i0 + k] : 0u;
-            }
-            uint32_t live = 0;
-#pragma unroll
-            for (int k = 0; k < kItems; ++k) {
-                if (km[s] & (1u << k)) {
-                    if ((int64_t)q[k] >= N) bad_range = true;
-                    else live |= 1u << k;
-                }
-            }
-            uint32_t par[kItems], ord[kItems];
-#pragma unroll
-            for (int k = 0; k < kItems; ++k) {
-                par[k] = 0xffffffffu;
-                ord[k] = 0xffffffffu;
-            }
-            if (want_tags) {
-                constexpr int H = RO_BATCH_LOOKUPS;
-#pragma unroll
-                for (int hf = 0; hf < kItems / H; ++hf) {
-                    uint32_t cc[H], pp[H], oo[H];
-#pragma unroll
-                    for (int k = 0; k < H; ++k) cc[k] = q[hf * H + k];
-                    tags_of<H>(cmap, nmap, sh, offsets, P, cc, (live >> (hf * H)) & ((1u << H) - 1u), pp, oo);
-#pragma unroll
-                    for (int k = 0; k < H; ++k) {
-                        if ((live >> (hf * H + k)) & 1u) {
-                            par[hf * H + k] = pp[k];
-                            ord[hf * H + k] = oo[k];
-                        }
-                    }
-                }
-            }
-            const int64_t base = pre + s_sub[s];
-            const int64_t cnt_s = (s + 1 < kBatchSuper ? s_sub[s + 1] : agg) - s_sub[s];
-            const int64_t lim = out_cap - base < cnt_s ? (out_cap - base > 0 ? out_cap - base : 0) : cnt_s;
-#pragma unroll 1
-            for (int which = 0; which < 3; ++which) {
-                uint32_t *dst = which == 0 ? out_child : (which == 1 ? out_parent : out_ordinal);
-                if (dst == nullptr) continue;
-                int slot = (int)ex[s];
-#pragma unroll
-                for (int k = 0; k < kItems; ++k) {
-                    if (km[s] & (1u << k)) {
-                        s_out[slot] = which == 0 ? q[k] : (which == 1 ? par[k] : ord[k]);
-                        ++slot;
-                    }
-                }
-                __syncthreads();
-                write_tags(dst, base, s_out, lim, nt);
-                __syncthreads();
-            }
-        }
-        if (bad_range) raise_err(ctl, RO_ERANGE);
-        if (t == nsuper - 1 && threadIdx.x == 0) {
-            const int64_t m = pre + agg;
-            if (n_out) *n_out = m;
-            if (n_batches) *n_batches = (m + B - 1) / B;
+        for (int k = 0; k < K; ++k) {
+            if (!((slow >> k) & 1u)) continue;
+            const int64_t p = search_parent(offsets, 0, P + 1, (int64_t)c[k]);
+            par[k] = (uint32_t)p;
+            ord[k] = (uint32_t)((int64_t)c[k] - offsets[p]);
         }
     }
-    ticket_done(ctl, epoch, desc, desc_cap, &s_last);
 }
 
 // First index i in [0, n) with a[i] > x (n if none), for K keys at once
@@ -470,23 +309,315 @@ __device__ __forceinline__ void upper_bound_k(const int64_t *a, int64_t n, const
     for (int k = 0; k < K; ++k) r[k] = base[k] + (a[base[k]] <= x[k] ? 1 : 0);
 }
 
+// Tags of K entries by whichever structure the launch chose.
+template <int kMap, int K>
+__device__ __forceinline__ void entry_tags(const MapArgs &m, int64_t nmap, int sh, const int64_t *__restrict__ offsets,
+                                           int64_t P, const uint32_t (&c)[K], uint32_t live, uint32_t (&par)[K],
+                                           uint32_t (&ord)[K])
+{
+    if constexpr (kMap == kMapMask) {
+        tags_of_mask<K>(static_cast<const uint4 *>(m.map), nmap, offsets, P, c, live, par, ord);
+    } else if constexpr (kMap == kMapChild) {
+        const uint32_t *cpar = static_cast<const uint32_t *>(m.map);
+        uint32_t p[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) p[k] = ((live >> k) & 1u) ? cpar[c[k]] : 0u;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (!((live >> k) & 1u)) continue;
+            par[k] = p[k];
+            ord[k] = (uint32_t)((int64_t)c[k] - offsets[p[k]]);
+        }
+    } else if constexpr (kMap == kMapCoarse) {
+        tags_of<K>(static_cast<const uint2 *>(m.map), nmap, sh, offsets, P, c, live, par, ord);
+    } else {
+        int64_t key[K], pp[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) key[k] = ((live >> k) & 1u) ? (int64_t)c[k] : 0;
+        if (live == 0) return;
+        upper_bound_k<K>(offsets, P + 1, key, pp);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (!((live >> k) & 1u)) continue;
+            par[k] = (uint32_t)(pp[k] - 1);
+            ord[k] = (uint32_t)((int64_t)c[k] - offsets[pp[k] - 1]);
+        }
+    }
+}
+
+// Entries of the map in use: the whole expansion's or as many as it has room for.
+template <int kMap>
+__device__ __forceinline__ int64_t map_entries(const MapArgs &m, int64_t N, int sh)
+{
+    if constexpr (kMap == kMapSearch || kMap == kMapChild) return 0;
+    const int s = kMap == kMapMask ? kMaskShift : sh;
+    const int64_t n = (N + ((int64_t)1 << s) - 1) >> s;
+    return n < m.cap ? n : m.cap;
+}
+
+// A thread's kIt consecutive entries of the queue from i0 on, and the ready
+// flags of its mask.
+template <int kIt>
+__device__ __forceinline__ void load_queue(const uint32_t *__restrict__ queue, int64_t i0, int64_t Q, int vec_ok,
+                                           uint32_t (&q)[kIt])
+{
+    if (vec_ok && i0 + kIt <= Q) {
+        const uint4 *qp = reinterpret_cast<const uint4 *>(queue + i0);
+#pragma unroll
+        for (int k = 0; k < kIt / 4; ++k) {
+            const uint4 x = qp[k];
+            q[4 * k] = x.x; q[4 * k + 1] = x.y; q[4 * k + 2] = x.z; q[4 * k + 3] = x.w;
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) q[k] = i0 + k < Q ? queue[i0 + k] : 0u;
+    }
+}
+
+template <int kIt>
+__device__ __forceinline__ uint32_t load_mask(const uint8_t *__restrict__ keep, int64_t i0, int64_t Q, int vec_ok)
+{
+    uint32_t m = 0;
+    if (vec_ok && i0 + kIt <= Q) {
+        uint32_t w[kIt / 4];
+#pragma unroll
+        for (int k = 0; k < kIt / 4; ++k) w[k] = reinterpret_cast<const uint32_t *>(keep + i0)[k];
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) m |= (((w[k >> 2] >> (8 * (k & 3))) & 0xffu) != 0 ? 1u : 0u) << k;
+    } else {
+#pragma unroll
+        for (int k = 0; k < kIt; ++k)
+            if (i0 + k < Q && keep[i0 + k] != 0) m |= 1u << k;
+    }
+    return m;
+}
+
+// Tags of a thread's kIt entries, RO_BATCH_LOOKUPS at a time with all their
+// lookups in flight; entries that are not live keep 0xffffffff.
+template <int kMap, int kIt>
+__device__ __forceinline__ void thread_tags(const MapArgs &map, int64_t nmap, int sh, const int64_t *__restrict__ offsets,
+                                            int64_t P, const uint32_t (&q)[kIt], uint32_t live, uint32_t (&par)[kIt],
+                                            uint32_t (&ord)[kIt])
+{
+    constexpr int H = RO_BATCH_LOOKUPS;
+#pragma unroll
+    for (int hf = 0; hf < kIt / H; ++hf) {
+        uint32_t cc[H], pp[H], oo[H];
+#pragma unroll
+        for (int k = 0; k < H; ++k) cc[k] = q[hf * H + k];
+        entry_tags<kMap, H>(map, nmap, sh, offsets, P, cc, (live >> (hf * H)) & ((1u << H) - 1u), pp, oo);
+#pragma unroll
+        for (int k = 0; k < H; ++k) {
+            if ((live >> (hf * H + k)) & 1u) {
+                par[hf * H + k] = pp[k];
+                ord[hf * H + k] = oo[k];
+            }
+        }
+    }
+}
+
+// A tile's ready entries to its slot range: each requested array staged in
+// LDS in slot order, then written with coalesced stores.
+template <int kIt>
+__device__ __forceinline__ void write_slots(uint32_t *out_child, uint32_t *out_parent, uint32_t *out_ordinal,
+                                            const uint32_t (&q)[kIt], const uint32_t (&par)[kIt],
+                                            const uint32_t (&ord)[kIt], uint32_t kmask, int ex, int64_t base,
+                                            int64_t lim, uint32_t *s_out, bool nt)
+{
+#pragma unroll 1
+    for (int which = 0; which < 3; ++which) {
+        uint32_t *dst = which == 0 ? out_child : (which == 1 ? out_parent : out_ordinal);
+        if (dst == nullptr) continue;
+        int slot = ex;
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) {
+            if (kmask & (1u << k)) {
+                s_out[slot] = which == 0 ? q[k] : (which == 1 ? par[k] : ord[k]);
+                ++slot;
+            }
+        }
+        __syncthreads();
+        write_tags(dst, base, s_out, lim, nt);
+        __syncthreads();
+    }
+}
+
+__device__ __forceinline__ int64_t slot_room(int64_t out_cap, int64_t base, int64_t cnt)
+{
+    return out_cap - base < cnt ? (out_cap - base > 0 ? out_cap - base : 0) : cnt;
+}
+
+// The ready queue with a barrier (and perhaps a mask): kIt entries per thread
+// and tile; a barred parent's entry is not ready, so the tags come before the
+// look-back.  A queue of one tile needs neither ticket nor look-back.
+template <int kMap, int kIt>
+__global__ __launch_bounds__(kBlock) void k_batch(
+    const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
+    const int64_t *__restrict__ offsets, int64_t P, MapArgs map, int64_t max_id, int32_t B,
+    uint32_t *__restrict__ out_child, uint32_t *__restrict__ out_parent, uint32_t *__restrict__ out_ordinal,
+    int64_t out_cap, int64_t *n_out, int64_t *n_batches, const uint8_t *__restrict__ barrier, Ctl *ctl,
+    uint64_t *desc, int64_t desc_cap, int64_t ntiles, int vec_ok)
+{
+    constexpr int kT = kBlock * kIt;
+    const uint32_t epoch = scan_epoch(ctl);
+    __shared__ uint32_t s_out[kT];             // one output array of a tile, in slot order
+    __shared__ int64_t s_wave[kBlock / 64];
+    __shared__ uint64_t s_b;
+    __shared__ int64_t s_t;
+    __shared__ int32_t s_last;
+    const int64_t NP = offsets[P];
+    const int64_t N = min64(NP, max_id);       // ids past a child map are out of range
+    const int sh = map_shift(NP, P);
+    const int64_t nmap = map_entries<kMap>(map, NP, sh);
+    const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
+    const bool nt = Q > kTagNtEntries;
+    const bool single = ntiles == 1;
+    for (;;) {
+        const int64_t t = single ? 0 : next_ticket(ctl, &s_t);
+        if (t >= ntiles) break;
+        const int64_t i0 = t * kT + (int64_t)threadIdx.x * kIt;
+        uint32_t q[kIt], par[kIt], ord[kIt];
+        load_queue<kIt>(queue, i0, Q, vec_ok, q);
+        uint32_t kmask;
+        if (keep) kmask = load_mask<kIt>(keep, i0, Q, vec_ok);
+        else kmask = i0 + kIt <= Q ? (uint32_t)((1ull << kIt) - 1) : (i0 < Q ? (1u << (Q - i0)) - 1u : 0u);
+        bool bad_range = false;
+        uint32_t live = 0;
+#pragma unroll
+        for (int k = 0; k < kIt; ++k) {
+            par[k] = 0xffffffffu;
+            ord[k] = 0xffffffffu;
+            if (kmask & (1u << k)) {
+                if ((int64_t)q[k] >= N) bad_range = true;
+                else live |= 1u << k;
+            }
+        }
+        // the tags are set before the barrier test, never inside it
+        if (want_tags || barrier) thread_tags<kMap, kIt>(map, nmap, sh, offsets, P, q, live, par, ord);
+        if (barrier) {
+#pragma unroll
+            for (int k = 0; k < kIt; ++k) {
+                if (((live >> k) & 1u) && barrier[par[k]]) {
+                    kmask &= ~(1u << k);                             // suppressed: takes no slot
+                    par[k] = 0xffffffffu;
+                    ord[k] = 0xffffffffu;
+                }
+            }
+        }
+        if (bad_range) raise_err(ctl, RO_ERANGE);
+        int64_t tot;
+        const int64_t ex = block_excl_scan(__popc(kmask), s_wave, tot);
+        const int64_t base = single ? 0 : (int64_t)tile_prefix(desc, t, epoch, (uint64_t)tot, &s_b, ctl);
+        if (base + tot > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
+        write_slots<kIt>(out_child, out_parent, out_ordinal, q, par, ord, kmask, (int)ex, base,
+                         slot_room(out_cap, base, tot), s_out, nt);
+        if (t == ntiles - 1 && threadIdx.x == 0) {
+            const int64_t m = base + tot;
+            if (n_out) *n_out = m;
+            if (n_batches) *n_batches = (m + B - 1) / B;
+        }
+        if (single) return;
+    }
+    ticket_done(ctl, epoch, desc, desc_cap, &s_last);
+}
+
+// The ready queue with a dispatch mask and no barrier: an entry is ready iff
+// its mask byte is set, so a tile's count of ready entries is known from the
+// mask alone, before any lineage lookup.  A workgroup takes kSup consecutive
+// tiles per ticket, counts them, publishes their aggregate and finishes the
+// look-back first; only then does it look up the tags of each tile's ready
+// entries and write them, staged in LDS, to the tile's contiguous slot range.
+template <int kMap, int kIt, int kSup>
+__global__ __launch_bounds__(kBlock) void k_batch_keep(
+    const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
+    const int64_t *__restrict__ offsets, int64_t P, MapArgs map, int32_t B,
+    uint32_t *__restrict__ out_child, uint32_t *__restrict__ out_parent, uint32_t *__restrict__ out_ordinal,
+    int64_t out_cap, int64_t *n_out, int64_t *n_batches, Ctl *ctl, uint64_t *desc, int64_t desc_cap,
+    int64_t nsuper, int vec_ok)
+{
+    constexpr int kT = kBlock * kIt;
+    const uint32_t epoch = scan_epoch(ctl);
+    __shared__ uint32_t s_out[kT];
+    __shared__ int64_t s_wave[kBlock / 64];
+    __shared__ int64_t s_sub[kSup];
+    __shared__ uint64_t s_b;
+    __shared__ int64_t s_t;
+    __shared__ int32_t s_last;
+    const int64_t N = offsets[P];
+    const int sh = map_shift(N, P);
+    const int64_t nmap = map_entries<kMap>(map, N, sh);
+    const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
+    const bool nt = Q > kTagNtEntries;
+    const bool single = nsuper == 1;
+    for (;;) {
+        const int64_t t = single ? 0 : next_ticket(ctl, &s_t);
+        if (t >= nsuper) break;
+        // ready flags of the super-tile's entries: bit k of km[s] is entry
+        // (tile s, this thread, item k)
+        uint32_t km[kSup];
+#pragma unroll
+        for (int s = 0; s < kSup; ++s)
+            km[s] = load_mask<kIt>(keep, (t * kSup + s) * kT + (int64_t)threadIdx.x * kIt, Q, vec_ok);
+        int64_t ex[kSup];
+        int64_t agg = 0;
+#pragma unroll
+        for (int s = 0; s < kSup; ++s) {
+            int64_t tot;
+            ex[s] = block_excl_scan(__popc(km[s]), s_wave, tot);
+            if (threadIdx.x == 0) s_sub[s] = agg;
+            agg += tot;
+        }
+        const int64_t pre = single ? 0 : (int64_t)tile_prefix(desc, t, epoch, (uint64_t)agg, &s_b, ctl);
+        if (single) __syncthreads();           // s_sub
+        if (pre + agg > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
+        bool bad_range = false;
+#pragma unroll 1
+        for (int s = 0; s < kSup; ++s) {
+            uint32_t q[kIt], par[kIt], ord[kIt];
+            load_queue<kIt>(queue, (t * kSup + s) * kT + (int64_t)threadIdx.x * kIt, Q, vec_ok, q);
+            uint32_t live = 0;
+#pragma unroll
+            for (int k = 0; k < kIt; ++k) {
+                par[k] = 0xffffffffu;
+                ord[k] = 0xffffffffu;
+                if (km[s] & (1u << k)) {
+                    if ((int64_t)q[k] >= N) bad_range = true;
+                    else live |= 1u << k;
+                }
+            }
+            if (want_tags) thread_tags<kMap, kIt>(map, nmap, sh, offsets, P, q, live, par, ord);
+            const int64_t base = pre + s_sub[s];
+            const int64_t cnt_s = (s + 1 < kSup ? s_sub[s + 1] : agg) - s_sub[s];
+            write_slots<kIt>(out_child, out_parent, out_ordinal, q, par, ord, km[s], (int)ex[s], base,
+                             slot_room(out_cap, base, cnt_s), s_out, nt);
+        }
+        if (bad_range) raise_err(ctl, RO_ERANGE);
+        if (t == nsuper - 1 && threadIdx.x == 0) {
+            const int64_t m = pre + agg;
+            if (n_out) *n_out = m;
+            if (n_batches) *n_batches = (m + B - 1) / B;
+        }
+        if (single) return;
+    }
+    ticket_done(ctl, epoch, desc, desc_cap, &s_last);
+}
+
 // Every queue entry is ready (no mask): the FIFO compaction is the identity,
 // slot i holds queue[i], so no scan is needed and each entry is independent.
 // A block takes 1024 consecutive entries, lane-contiguous, so every load and
 // store instruction of a wave covers 256 contiguous bytes.
 constexpr int kAllPer = 4;
 
-template <bool kByMap>
+template <int kMap>
 __global__ __launch_bounds__(kBlock) void k_batch_all(
-    const uint32_t *__restrict__ queue, int64_t Q, const int64_t *__restrict__ offsets, int64_t P,
-    const uint2 *__restrict__ cmap, int64_t cmap_cap, int32_t B, uint32_t *__restrict__ out_child,
-    uint32_t *__restrict__ out_parent, uint32_t *__restrict__ out_ordinal, int64_t out_cap, int64_t *n_out,
-    int64_t *n_batches, const uint32_t *__restrict__ cpar, int64_t cpar_n, Ctl *ctl)
+    const uint32_t *__restrict__ queue, int64_t Q, const int64_t *__restrict__ offsets, int64_t P, MapArgs map,
+    int64_t max_id, int32_t B, uint32_t *__restrict__ out_child, uint32_t *__restrict__ out_parent,
+    uint32_t *__restrict__ out_ordinal, int64_t out_cap, int64_t *n_out, int64_t *n_batches, Ctl *ctl)
 {
-    const int64_t N = cpar ? min64(offsets[P], cpar_n) : offsets[P];   // ids past the map are out of range
-    const int sh = map_shift(offsets[P], P);     // the map's block size, as k_batch_cmap built it
-    int64_t nmap = (N + (1 << sh) - 1) >> sh;
-    nmap = nmap < cmap_cap ? nmap : cmap_cap;
+    const int64_t NP = offsets[P];
+    const int64_t N = min64(NP, max_id);       // ids past a child map are out of range
+    const int sh = map_shift(NP, P);
+    const int64_t nmap = map_entries<kMap>(map, NP, sh);
     const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         if (Q > out_cap) raise_err(ctl, RO_ECAP);
@@ -498,60 +629,80 @@ __global__ __launch_bounds__(kBlock) void k_batch_all(
     for (int64_t i0 = (int64_t)blockIdx.x * (kBlock * kAllPer); i0 < Q;
          i0 += (int64_t)gridDim.x * (kBlock * kAllPer)) {
         uint32_t q[kAllPer];
+        uint32_t live = 0;
 #pragma unroll
         for (int k = 0; k < kAllPer; ++k) {
             const int64_t i = i0 + k * kBlock + threadIdx.x;
             q[k] = i < Q ? queue[i] : 0u;
-        }
-        // the entries' parents: from the stream's own map, from the coarse
-        // map (all lookups in flight together), or without it from one
-        // lockstep search of the offsets (ids out of range search for N - 1
-        // and are reported below)
-        uint32_t par[kAllPer], ord[kAllPer];
-        if (want_tags && !kByMap) {
-            if (nmap == 0) {
-                int64_t key[kAllPer], pp[kAllPer];
-#pragma unroll
-                for (int k = 0; k < kAllPer; ++k) key[k] = (int64_t)q[k] < N ? (int64_t)q[k] : N - 1;
-                if (N > 0) {
-                    upper_bound_k<kAllPer>(offsets, P + 1, key, pp);
-#pragma unroll
-                    for (int k = 0; k < kAllPer; ++k) {
-                        par[k] = (uint32_t)(pp[k] - 1);
-                        ord[k] = (uint32_t)(key[k] - offsets[pp[k] - 1]);
-                    }
-                }
-            } else {
-                uint32_t live = 0;
-#pragma unroll
-                for (int k = 0; k < kAllPer; ++k)
-                    if (i0 + k * kBlock + threadIdx.x < Q && (int64_t)q[k] < N) live |= 1u << k;
-                tags_of<kAllPer>(cmap, nmap, sh, offsets, P, q, live, par, ord);
+            if (i < Q) {
+                if ((int64_t)q[k] < N) live |= 1u << k;
+                else bad_range = true;
             }
+        }
+        uint32_t par[kAllPer], ord[kAllPer];
+        if (want_tags) {
+            entry_tags<kMap, kAllPer>(map, nmap, sh, offsets, P, q, live, par, ord);
         }
 #pragma unroll
         for (int k = 0; k < kAllPer; ++k) {
             const int64_t i = i0 + k * kBlock + threadIdx.x;
-            if (i >= Q) continue;
-            const int64_t c = q[k];
-            if (c >= N) {
-                bad_range = true;
-                continue;
-            }
-            if (i >= lim) continue;
+            if (i >= lim || !((live >> k) & 1u)) continue;
             if (out_child) out_child[i] = q[k];
-            if (want_tags) {
-                if constexpr (kByMap) {
-                    const int64_t p = (int64_t)cpar[c];
-                    par[k] = (uint32_t)p;
-                    ord[k] = (uint32_t)(c - offsets[p]);
-                }
-                if (out_parent) out_parent[i] = par[k];
-                if (out_ordinal) out_ordinal[i] = ord[k];
-            }
+            if (out_parent) out_parent[i] = par[k];
+            if (out_ordinal) out_ordinal[i] = ord[k];
         }
     }
     if (bad_range) raise_err(ctl, RO_ERANGE);
+}
+
+// Sizes at which a queue changes path (entries):
+//   up to kDirectQueue the offsets are searched and no map is built: the map
+//   is a launch of about 5 us (100,000 entries under 243 parents: 88.7 us for
+//   the whole chain searched, 92 with the map);
+//   up to kSmallQueue a masked queue is cut into tiles of 1,024 entries
+//   (7,389 entries: 10 us, 39 us as one tile of 16,384; 98,000 entries: 18 us,
+//   57 as 6 of those);
+//   up to kMidQueue into tiles of 4,096 (1M entries: 29 us; 57 in 980 tiles of
+//   1,024, whose tickets and look-backs queue up; 66 in 61 of 16,384, too few
+//   for 256 CUs);
+//   beyond, four tiles of 4,096 per ticket (8M entries: 91 us, 107 one by one).
+constexpr int64_t kDirectQueue = 65536, kSmallQueue = 262144, kMidQueue = 1 << 20;
+
+template <int kMap>
+hipError_t launch_batch_with(const Launch &L, const uint32_t *queue, const uint8_t *keep, int64_t Q,
+                             const int64_t *offsets, int64_t P, MapArgs map, int64_t max_id, int32_t B,
+                             uint32_t *out_child, uint32_t *out_parent, uint32_t *out_ordinal, int64_t out_cap,
+                             int64_t *n_out, int64_t *n_batches, const uint8_t *barrier)
+{
+    const int64_t cap_grid = (int64_t)L.num_cus * 4;
+    if (keep == nullptr && barrier == nullptr) {
+        int64_t grid = (Q + kBlock * kAllPer - 1) / (kBlock * kAllPer);
+        grid = grid < 1 ? 1 : (grid > (int64_t)L.num_cus * 8 ? (int64_t)L.num_cus * 8 : grid);
+        RO_LAUNCH(L, RO_K_BATCH, k_batch_all<kMap>, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, Q, offsets, P,
+                  map, max_id, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.ctl);
+        return hipGetLastError();
+    }
+    const bool aligned = ((reinterpret_cast<uintptr_t>(queue) | reinterpret_cast<uintptr_t>(keep)) & 15u) == 0;
+    auto tiles = [&](int64_t per) { return Q > 0 ? (Q + per - 1) / per : 1; };
+    if (barrier == nullptr && kMap != kMapChild) {
+        if constexpr (kMap != kMapChild) {
+            const int64_t per = Q <= kSmallQueue ? kBlock * 4 : (Q <= kMidQueue ? kBlock * 16 : kBlock * 64);
+            auto kern = Q <= kSmallQueue ? k_batch_keep<kMap, 4, 1>
+                                        : (Q <= kMidQueue ? k_batch_keep<kMap, 16, 1> : k_batch_keep<kMap, 16, 4>);
+            const int64_t nsuper = tiles(per), grid = nsuper < cap_grid ? nsuper : cap_grid;
+            RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P,
+                      map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.ctl, L.desc, L.desc_cap,
+                      nsuper, aligned ? 1 : 0);
+        }
+        return hipGetLastError();
+    }
+    const bool small = Q <= kSmallQueue;
+    auto kern = small ? k_batch<kMap, 4> : k_batch<kMap, 16>;
+    const int64_t ntiles = tiles(small ? kBlock * 4 : kBlock * 16), grid = ntiles < cap_grid ? ntiles : cap_grid;
+    RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P, map,
+              max_id, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, barrier, L.ctl, L.desc,
+              L.desc_cap, ntiles, aligned ? 1 : 0);
+    return hipGetLastError();
 }
 
 hipError_t launch_batch(const Launch &L, const uint32_t *queue, const uint8_t *keep,
@@ -560,56 +711,33 @@ hipError_t launch_batch(const Launch &L, const uint32_t *queue, const uint8_t *k
                         int64_t out_cap, int64_t *n_out, int64_t *n_batches, uint32_t *cmap_words,
                         int64_t cmap_words_cap, const uint8_t *barrier, const uint32_t *cpar, int64_t cpar_n)
 {
-    // the coarse map takes two words a block; its parent field keeps a flag bit
-    uint2 *cmap = reinterpret_cast<uint2 *>(cmap_words);
-    int64_t cmap_cap = P < ((int64_t)1 << 31) ? cmap_words_cap / 2 : 0;
-    // The coarse map costs a search per 128 children; a short unmasked queue
-    // (fewer entries than parents, such as one wave of a stream) searches
-    // the offsets directly instead and skips the extra launch.
-    const bool tags = out_parent != nullptr || out_ordinal != nullptr;
-    const bool use_map = cpar == nullptr && (tags || barrier != nullptr) && cmap_cap > 0 &&
-                         !(keep == nullptr && barrier == nullptr && Q < P);
-    if (use_map) {
-        const int64_t grid_m = (int64_t)L.num_cus * 4;
-        RO_LAUNCH(L, RO_K_BATCH_SAMPLES, k_batch_cmap, dim3((unsigned)grid_m), dim3(256), 0, L.stream,
-                  offsets, P, cmap, cmap_cap);
-    } else {
-        cmap_cap = 0;
-    }
-    if (keep == nullptr && barrier == nullptr) {
-        int64_t grid_a = (Q + kBlock * kAllPer - 1) / (kBlock * kAllPer);
-        grid_a = grid_a < 1 ? 1 : (grid_a > (int64_t)L.num_cus * 8 ? (int64_t)L.num_cus * 8 : grid_a);
-        if (cpar)
-            RO_LAUNCH(L, RO_K_BATCH, k_batch_all<true>, dim3((unsigned)grid_a), dim3(kBlock), 0, L.stream, queue,
-                      Q, offsets, P, cmap, cmap_cap, B, out_child, out_parent, out_ordinal, out_cap, n_out,
-                      n_batches, cpar, cpar_n, L.ctl);
-        else
-            RO_LAUNCH(L, RO_K_BATCH, k_batch_all<false>, dim3((unsigned)grid_a), dim3(kBlock), 0, L.stream, queue,
-                      Q, offsets, P, cmap, cmap_cap, B, out_child, out_parent, out_ordinal, out_cap, n_out,
-                      n_batches, cpar, cpar_n, L.ctl);
-        return hipGetLastError();
-    }
-    const int64_t ntiles = Q > 0 ? (Q + kTile - 1) / kTile : 1;
-    const int64_t cap_grid = (int64_t)L.num_cus * 4;
-    const int64_t grid = ntiles < cap_grid ? ntiles : cap_grid;
-    const bool aligned = ((reinterpret_cast<uintptr_t>(queue) | reinterpret_cast<uintptr_t>(keep)) & 15u) == 0;
-    if (barrier == nullptr && cpar == nullptr) {
-        const int64_t nsuper = (ntiles + kBatchSuper - 1) / kBatchSuper;
-        const int64_t grid_k = nsuper < cap_grid ? nsuper : cap_grid;
-        RO_LAUNCH(L, RO_K_BATCH, k_batch_keep, dim3((unsigned)grid_k), dim3(kBlock), 0, L.stream, queue, keep, Q,
-                  offsets, P, cmap, cmap_cap, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches,
-                  L.ctl, L.desc, L.desc_cap, nsuper, aligned ? 1 : 0);
-        return hipGetLastError();
-    }
+    constexpr int64_t kAnyId = (int64_t)1 << 40;
     if (cpar)
-        RO_LAUNCH(L, RO_K_BATCH, k_batch<true>, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q,
-                  offsets, P, cmap, cmap_cap, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches,
-                  barrier, cpar, cpar_n, L.ctl, L.desc, L.desc_cap, ntiles, aligned ? 1 : 0);
-    else
-        RO_LAUNCH(L, RO_K_BATCH, k_batch<false>, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q,
-                  offsets, P, cmap, cmap_cap, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches,
-                  barrier, cpar, cpar_n, L.ctl, L.desc, L.desc_cap, ntiles, aligned ? 1 : 0);
-    return hipGetLastError();
+        return launch_batch_with<kMapChild>(L, queue, keep, Q, offsets, P, MapArgs{cpar, cpar_n}, cpar_n, B, out_child,
+                                            out_parent, out_ordinal, out_cap, n_out, n_batches, barrier);
+    // A map costs a launch and a search per block; a short unmasked queue
+    // (fewer entries than parents, such as one wave of a stream) searches
+    // the offsets directly instead.  The maps' parent fields keep a flag bit.
+    const bool tags = out_parent != nullptr || out_ordinal != nullptr;
+    const bool use_map = (tags || barrier != nullptr) && cmap_words_cap >= 4 && P < ((int64_t)1 << 31) &&
+                         !(keep == nullptr && barrier == nullptr && Q < P) && Q > kDirectQueue;
+    if (!use_map)
+        return launch_batch_with<kMapSearch>(L, queue, keep, Q, offsets, P, MapArgs{nullptr, 0}, kAnyId, B, out_child,
+                                             out_parent, out_ordinal, out_cap, n_out, n_batches, barrier);
+    const int64_t grid_m = (int64_t)L.num_cus * 4;
+    if (use_mask_map(Q, P, cmap_words_cap * 8)) {
+        uint4 *map = reinterpret_cast<uint4 *>(cmap_words);
+        const int64_t cap = cmap_words_cap / 4;
+        RO_LAUNCH(L, RO_K_BATCH_SAMPLES, k_batch_mask_map, dim3((unsigned)grid_m), dim3(kBlock), 0, L.stream, offsets, P,
+                  map, cap);
+        return launch_batch_with<kMapMask>(L, queue, keep, Q, offsets, P, MapArgs{map, cap}, kAnyId, B, out_child,
+                                           out_parent, out_ordinal, out_cap, n_out, n_batches, barrier);
+    }
+    uint2 *map = reinterpret_cast<uint2 *>(cmap_words);
+    const int64_t cap = cmap_words_cap / 2;
+    RO_LAUNCH(L, RO_K_BATCH_SAMPLES, k_batch_cmap, dim3((unsigned)grid_m), dim3(256), 0, L.stream, offsets, P, map, cap);
+    return launch_batch_with<kMapCoarse>(L, queue, keep, Q, offsets, P, MapArgs{map, cap}, kAnyId, B, out_child,
+                                         out_parent, out_ordinal, out_cap, n_out, n_batches, barrier);
 }
 
 }  // namespace ro

@@ -329,7 +329,7 @@ int ro_ctx_reserve(ro_ctx *c, int64_t max_children, int64_t max_parents, int64_t
     if (rc) return rc;
     int64_t m = max_children > max_parents ? max_children : max_parents;
     m = m > max_queue ? m : max_queue;
-    return ensure_desc(c, tiles_for(m));
+    return ensure_desc(c, scan_tiles_for(m));
 }
 
 int ro_ctx_status(ro_ctx *c)
@@ -410,7 +410,7 @@ int ro_batch(ro_ctx *c, const uint32_t *queue, const uint8_t *keep, int64_t q_le
     uint32_t *const outs[3] = {out_child, out_parent, out_ordinal};
     if (batch_outputs_alias(queue, keep, q_len, offsets, n_parents, barrier, outs, out_cap, nullptr, 0))
         return RO_EINVAL;
-    int rc = ensure_desc(c, tiles_for(q_len));
+    int rc = ensure_desc(c, scan_tiles_for(q_len));
     if (rc) return rc;
     return hip_fail(launch_batch(launch_of(c), queue, keep, q_len, offsets, n_parents, batch_size,
                                  out_child, out_parent, out_ordinal, out_cap, n_out_dev, n_batches_dev,
@@ -435,7 +435,7 @@ int ro_batch_parent(ro_ctx *c, const uint32_t *queue, const uint8_t *keep, int64
         return RO_EINVAL;
     int rc = ensure_pb(c, q_len, n_parents);
     if (rc) return rc;
-    rc = ensure_desc(c, tiles_for(q_len));
+    rc = ensure_desc(c, scan_tiles_for(q_len));
     if (rc) return rc;
     return hip_fail(launch_batch_parent(launch_of(c), queue, keep, q_len, offsets, n_parents, batch_size,
                                         out_child, out_parent, out_ordinal, out_cap, batch_off, batch_cap,
@@ -693,7 +693,7 @@ int ro_stream_batch(ro_ctx *c, ro_stream *s, const uint32_t *queue, const uint8_
     uint32_t *const outs[3] = {out_child, out_parent, out_ordinal};
     if (batch_outputs_alias(queue, keep, q_len, st.offsets, st.P, st.barrier, outs, out_cap, nullptr, 0))
         return RO_EINVAL;
-    int rc = ensure_desc(c, tiles_for(q_len));
+    int rc = ensure_desc(c, scan_tiles_for(q_len));
     if (rc) return rc;
     return hip_fail(launch_batch(launch_of(c), queue, keep, q_len, st.offsets, st.P, batch_size, out_child,
                                  out_parent, out_ordinal, out_cap, n_out_dev, n_batches_dev, nullptr, 0, st.barrier,

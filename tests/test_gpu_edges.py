@@ -115,3 +115,44 @@ def test_gather_scan_tiles(ctx, n, missing):
     order = rng.permutation(n)[:n - missing]
     _say("gather scan", n, missing)
     _gather_case(ctx, counts, lengths, states, order)
+
+
+def _batch_case(ctx, counts, queue, keep, barrier, B):
+    offs = O.expand(np.asarray(counts, np.int32), tags=False)
+    P, Q = len(counts), len(queue)
+    want = O.batch(queue, keep, offs, B, barrier=barrier)
+    m = len(want[0])
+    outs = [torch.full((Q + 3,), -1, dtype=torch.int32, device="cuda") for _ in range(3)]
+    sc = _zeros(2, torch.int64)
+    ctx.batch(_i32(queue), None if keep is None else D.to_dev(keep), D.to_dev(offs), B, *outs, sc[0:1], sc[1:2], q_len=Q,
+              out_cap=Q, barrier=None if barrier is None else D.to_dev(barrier))
+    ctx.check("batch")
+    assert sc.tolist() == [m, len(want[3])]
+    for t, w in zip(outs, want[:3]):
+        h = t.cpu().numpy().view(np.uint32)
+        assert np.array_equal(h[:m], w) and (h[m:] == 0xffffffff).all()
+
+
+# queue sizes on both sides of every path (offsets searched, tiles of 1,024,
+# tiles of 4,096, four tiles per ticket); the reservation decides between the
+# map of 64-child masks and the coarse one, or leaves children past the map
+@pytest.mark.parametrize("q_len", [1023, 65_536, 65_537, 262_144, 262_145, 1_048_576, 1_048_577])
+@pytest.mark.parametrize("reserve", [1000, 1 << 21, 13 << 20])
+def test_batch_paths(q_len, reserve):
+    import paper_2609_18703_amd as R
+    rng = np.random.default_rng(q_len + reserve)
+    n = q_len + 777
+    pool = np.concatenate([rng.integers(0, 4, n // 3), rng.choice([0, 0, 0, 1, 64, 65, 200], n // 100),
+                           [0, 5000, 0, 0, 1, 0]])
+    rng.shuffle(pool)
+    counts = pool[:np.searchsorted(np.cumsum(pool), n)].astype(np.int64)
+    counts = np.concatenate([counts, [n - counts.sum()], [0, 0]])
+    queue = rng.permutation(n)[:q_len].astype(np.uint32)
+    keep = (rng.random(q_len) < 0.8).astype(np.uint8)
+    barrier = (rng.random(len(counts)) < 0.1).astype(np.uint8)
+    c = R.Context()
+    c.reserve(reserve, len(counts), q_len)
+    for k, bar in ((None, None), (keep, None), (None, barrier), (keep, barrier)):
+        _say("batch paths", q_len, reserve, k is not None, bar is not None)
+        _batch_case(c, counts, queue, k, bar, 256)
+    c.close()
