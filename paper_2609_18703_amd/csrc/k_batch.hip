@@ -321,12 +321,14 @@ __device__ __forceinline__ void entry_tags(const MapArgs &m, int64_t nmap, int s
         const uint32_t *cpar = static_cast<const uint32_t *>(m.map);
         uint32_t p[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) p[k] = ((live >> k) & 1u) ? cpar[c[k]] : 0u;
+        for (int k = 0; k < K; ++k) p[k] = cpar[((live >> k) & 1u) ? c[k] : 0u];
+        int64_t st[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) st[k] = offsets[p[k]];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            if (!((live >> k) & 1u)) continue;
             par[k] = p[k];
-            ord[k] = (uint32_t)((int64_t)c[k] - offsets[p[k]]);
+            ord[k] = (uint32_t)((int64_t)c[k] - st[k]);
         }
     } else if constexpr (kMap == kMapCoarse) {
         tags_of<K>(static_cast<const uint2 *>(m.map), nmap, sh, offsets, P, c, live, par, ord);
@@ -517,6 +519,7 @@ __global__ __launch_bounds__(kBlock) void k_batch(
             if (n_batches) *n_batches = (m + B - 1) / B;
         }
         if (single) return;
+        if (ntiles <= (int64_t)gridDim.x) break;       // a tile for every workgroup
     }
     ticket_done(ctl, epoch, desc, desc_cap, &s_last);
 }
@@ -598,6 +601,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_keep(
             if (n_batches) *n_batches = (m + B - 1) / B;
         }
         if (single) return;
+        if (nsuper <= (int64_t)gridDim.x) break;       // a tile for every workgroup
     }
     ticket_done(ctl, epoch, desc, desc_cap, &s_last);
 }

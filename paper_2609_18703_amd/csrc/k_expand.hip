@@ -53,6 +53,7 @@ __global__ __launch_bounds__(kBlock) void k_expand_scan(const int32_t *__restric
             if (pre >= kSat || n >= ((int64_t)1 << 32)) raise_err(ctl, RO_EOVERFLOW);
             else if (want_tags && n > child_cap) raise_err(ctl, RO_ECAP);
         }
+        if (ntiles <= (int64_t)gridDim.x) break;     // a tile for every workgroup
     }
     ticket_done(ctl, epoch, desc, desc_cap, &s_last);
 }

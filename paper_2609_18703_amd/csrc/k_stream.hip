@@ -23,55 +23,43 @@
 
 namespace ro {
 
-// How many children of a parent have reported, by its size k:
-//   k < kMid   the seen bits of its children (at most three words), no counter;
-//   k < kBig   one counter, indexed by its first child >> kMidShift;
-//   k >= kBig  kSpread counters on separate lines, indexed by its first
-//              child >> kBigShift: the reports of a parent with many children
-//              would otherwise all add to one address, and atomics on one
-//              address serialise.
-// A parent of at least 2^s children is the only one whose first child falls
-// in its 2^s-child block, so these indices never collide.
-constexpr int kMidShift = 6, kBigShift = 10;
-constexpr int64_t kMid = (int64_t)1 << kMidShift, kBig = (int64_t)1 << kBigShift;
-constexpr int kSpread = 16;
+// When a parent is complete is found by its reports themselves.  A report sets
+// its child's bit in the seen bitmap with a returning atomic (which also
+// detects a repeat); the one that completes the parent's share of a 32-child
+// word either completes the parent (its only word) or counts that word for
+// it, and the one that counts the last word completes it.  So a report adds
+// to a counter only once per 32 children, and the counter of a parent of W
+// words meets W additions, not one per child.  A parent of two words or more
+// is the only one that holds both sides of its first inner word boundary,
+// whose index names its counter.  Complete parents are bits of a bitmap,
+// which the next emission reads instead of looking at every open parent
+// (select 22 -> 11 us for 500,000 parents), and clears as it emits them.
+int64_t stream_word_count(int64_t N) { return (N >> 5) + 2; }
 
-int64_t stream_mid_size(int64_t N) { return (N >> kMidShift) + 1; }
-int64_t stream_big_slots(int64_t N) { return (N >> kBigShift) + 1; }
-int64_t stream_big_size(int64_t N) { return (int64_t)kSpread * stream_big_slots(N); }
-
-__device__ __forceinline__ int64_t reported(const uint32_t *__restrict__ seen, const int32_t *__restrict__ mid,
-                                            const int32_t *__restrict__ big, int64_t nslots, int64_t st,
-                                            int64_t k)
+__device__ __forceinline__ uint32_t word_share(int64_t w, int64_t st, int64_t en)
 {
-    if (k <= 0) return 0;
-    if (k < kMid) {
-        const int64_t c1 = st + k;                  // children [st, c1)
-        int64_t n = 0;
-        for (int64_t w = st >> 5; w <= (c1 - 1) >> 5; ++w) {
-            uint32_t m = seen[w];
-            const int64_t b0 = w << 5;
-            if (st > b0) m &= 0xffffffffu << (st - b0);
-            if (c1 < b0 + 32) m &= 0xffffffffu >> (b0 + 32 - c1);
-            n += __popc(m);
-        }
-        return n;
-    }
-    if (k < kBig) return mid[st >> kMidShift];
-    const int64_t j = st >> kBigShift;
-    int64_t s = 0;
-#pragma unroll
-    for (int l = 0; l < kSpread; ++l) s += big[(int64_t)l * nslots + j];
-    return s;
+    const int64_t b0 = w << 5;
+    uint32_t m = 0xffffffffu;
+    if (st > b0) m &= 0xffffffffu << (st - b0);
+    if (en < b0 + 32) m &= 0xffffffffu >> (b0 + 32 - en);
+    return m;
 }
 
 // Validates the expansion once: offsets[0] = 0, nondecreasing, offsets[P] = N.
-__global__ void k_stream_check(const int64_t *__restrict__ offsets, int64_t P, int64_t N, Ctl *ctl)
+// Marks the parents without children complete: the first emission takes them.
+__global__ void k_stream_check(const int64_t *__restrict__ offsets, int64_t P, int64_t N, uint64_t *__restrict__ ready,
+                               Ctl *ctl)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool bad = (g == 0) && (offsets[0] != 0 || offsets[P] != N);
-    for (int64_t p = g; p < P; p += (int64_t)gridDim.x * blockDim.x)
-        if (offsets[p + 1] < offsets[p]) bad = true;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    for (int64_t w = g >> 6; w * 64 < P; w += nwaves) {
+        const int64_t p = w * 64 + lane_id();
+        const int64_t k = p < P ? offsets[p + 1] - offsets[p] : 1;
+        if (k < 0) bad = true;
+        const uint64_t m = __ballot(k == 0);
+        if (lane_id() == 0) ready[w] = m;
+    }
     if (bad) raise_err(ctl, RO_EINVAL);
 }
 
@@ -82,28 +70,29 @@ __global__ void k_stream_check(const int64_t *__restrict__ offsets, int64_t P, i
 __global__ __launch_bounds__(kBlock) void k_stream_report(
     const uint32_t *__restrict__ rp, const uint32_t *__restrict__ ro_, const uint8_t *__restrict__ rs,
     const int64_t *__restrict__ roff, const uint8_t *data, int64_t n, const int64_t *__restrict__ offsets,
-    int64_t P, int64_t N, Canon *__restrict__ canon, uint32_t *__restrict__ seen, int32_t *__restrict__ mid,
-    int32_t *__restrict__ big, int64_t nslots, uint32_t run_epoch, const uint8_t *__restrict__ barrier,
+    int64_t P, int64_t N, Canon *__restrict__ canon, uint32_t *__restrict__ seen, uint32_t *__restrict__ words,
+    uint32_t *__restrict__ ready, uint32_t run_epoch, const uint8_t *__restrict__ barrier,
     const uint64_t *__restrict__ gkey, uint32_t gf_epoch, int64_t *n_rejected, Ctl *ctl)
 {
     __shared__ int64_t s_wave[kBlock / 64];
     const int64_t gtid = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     const int64_t gstride = (int64_t)gridDim.x * kBlock;
-    const int64_t spread = (int64_t)(((blockIdx.x << 2) + (threadIdx.x >> 6)) & (kSpread - 1)) * nslots;
     int err = 0;
     int64_t rej = 0;
     if (gtid == 0 && n > 0 && roff[0] < 0) err = RO_EINVAL;
     for (int64_t i = gtid; i < n; i += gstride) {
+        // all columns at once, then the parent's two offsets: every check that
+        // stood between two loads was a trip to memory
         uint32_t s = rs[i];
         const int64_t o0 = roff[i], o1 = roff[i + 1];
+        const uint32_t p = rp[i], o = ro_[i];
+        const bool known = (int64_t)p < P;
+        const int64_t st = known ? offsets[p] : 0, en = known ? offsets[p + 1] : 0;
         if (o1 < o0) { err = RO_EINVAL; continue; }
         if (s > RO_PENDING && !(s == RO_GROUP_FAILED && barrier)) { err = RO_ESTATE; continue; }
         if (s == RO_PENDING) continue;
-        const uint32_t p = rp[i];
-        if ((int64_t)p >= P) { err = RO_ERANGE; continue; }
-        const int64_t st = offsets[p];
-        const int64_t k = offsets[p + 1] - st;
-        const uint32_t o = ro_[i];
+        if (!known) { err = RO_ERANGE; continue; }
+        const int64_t k = en - st;
         if ((int64_t)o >= k) { err = RO_ERANGE; continue; }
         const int64_t c = st + (int64_t)o;
         if (st < 0 || c >= N) { err = RO_EINVAL; continue; }
@@ -120,8 +109,12 @@ __global__ __launch_bounds__(kBlock) void k_stream_report(
         e.len = (uint32_t)len;
         e.tag = (run_epoch << 2) | s;
         canon[c] = e;
-        if (k >= kBig) atomicAdd(&big[spread + (st >> kBigShift)], 1);
-        else if (k >= kMid) atomicAdd(&mid[st >> kMidShift], 1);
+        const uint32_t share = word_share(c >> 5, st, st + k);
+        if (((old | bit) & share) == share) {
+            const int64_t nw = ((st + k - 1) >> 5) - (st >> 5) + 1;
+            if (nw == 1 || (int64_t)atomicAdd(&words[(st >> 5) + 1], 1u) + 1 == nw)
+                atomicOr(&ready[p >> 5], 1u << (p & 31));
+        }
     }
     if (err) raise_err(ctl, err);
     if (barrier) {
@@ -131,68 +124,93 @@ __global__ __launch_bounds__(kBlock) void k_stream_report(
     }
 }
 
-// Newly complete parents, compacted in ascending order (one tile = 2048
-// parents, eight per thread), and the exclusive scan of their child counts:
-// two look-back chains, one over emitted parents and one over their children.
-constexpr int kSTile = 2048;
-constexpr int kSItems = kSTile / kBlock;
+// Newly complete parents, compacted in ascending order (one tile = 8192
+// parents, eight per thread: one byte of the bitmap), and the exclusive scan
+// of their child counts: two look-back chains, one over emitted parents and
+// one over their children.  With a barrier, its bytes are read too: a barred
+// parent is complete, its uncommitted children are suppressed.
+// The cost is a chain of latencies, not the parents: ticket, bitmap, offsets
+// of the complete ones, look-back.  So tiles are large (61 for 500,000
+// parents, one round of look-back), and up to 8,192 parents need no ticket.
+constexpr int kSTh = 1024;
+constexpr int kSItems = 8;
+constexpr int kSTile = kSTh * kSItems;
 
-__global__ __launch_bounds__(kBlock) void k_stream_select(
-    const int64_t *__restrict__ offsets, int64_t P, const uint32_t *__restrict__ seen,
-    const int32_t *__restrict__ mid, const int32_t *__restrict__ big, int64_t nslots,
-    const uint8_t *__restrict__ barrier, uint8_t *__restrict__ ebar, uint8_t *__restrict__ emitted,
-    int64_t *__restrict__ ebase, int64_t *__restrict__ evoff, uint32_t *__restrict__ emit_parent,
-    int32_t *__restrict__ ecnt, int64_t ecnt_stride, int64_t cap_parents, int64_t *n_emitted, Ctl *ctl,
-    uint64_t *desc, uint64_t *desc_kids, int64_t desc_cap, int64_t ntiles)
+__global__ __launch_bounds__(kSTh) void k_stream_select(
+    const int64_t *__restrict__ offsets, int64_t P, uint8_t *__restrict__ ready, const uint8_t *__restrict__ barrier,
+    uint8_t *__restrict__ ebar, uint8_t *__restrict__ emitted, int64_t *__restrict__ ebase,
+    int64_t *__restrict__ evoff, uint32_t *__restrict__ emit_parent, int32_t *__restrict__ ecnt, int64_t ecnt_stride,
+    int64_t cap_parents, int64_t *n_emitted, Ctl *ctl, uint64_t *desc, uint64_t *desc_kids, int64_t desc_cap,
+    int64_t ntiles)
 {
     const uint32_t epoch = scan_epoch(ctl);
-    __shared__ int64_t s_wave[kBlock / 64];
+    __shared__ uint64_t s_w[kSTh / 64];
     __shared__ uint64_t s_b2[2];
     __shared__ int64_t s_t;
     __shared__ int32_t s_last;
+    const bool single = ntiles == 1;
+    const int wv = (int)(threadIdx.x >> 6), ln = lane_id();
     for (;;) {
-        const int64_t t = next_ticket(ctl, &s_t);
+        const int64_t t = single ? 0 : next_ticket(ctl, &s_t);
         if (t >= ntiles) break;
         const int64_t p0 = t * kSTile + (int64_t)threadIdx.x * kSItems;
-        uint32_t fmask = 0;
-        uint32_t kk[kSItems];
-        int64_t kids = 0;
+        const uint32_t bits = p0 < P ? ready[p0 >> 3] : 0u;
+        uint32_t fmask = bits, bmask = 0;
+        if (barrier) {
 #pragma unroll
-        for (int k = 0; k < kSItems; ++k) {
-            const int64_t p = p0 + k;
-            kk[k] = 0;
-            if (p < P && !emitted[p]) {
-                const int64_t st = offsets[p];
-                const int64_t kp = offsets[p + 1] - st;
-                // a barred parent is complete: its uncommitted children are suppressed
-                if ((barrier && barrier[p]) || reported(seen, mid, big, nslots, st, kp) == kp) {
-                    fmask |= 1u << k;
-                    kk[k] = (uint32_t)kp;
-                    kids += kp;
+            for (int k = 0; k < kSItems; ++k) {
+                if (p0 + k < P && barrier[p0 + k]) {
+                    bmask |= 1u << k;
+                    if (!emitted[p0 + k]) fmask |= 1u << k;
                 }
             }
         }
-        int64_t tot, totk;
-        const int64_t ex = block_excl_scan(__popc(fmask), s_wave, tot);
-        const int64_t exk = block_excl_scan(kids, s_wave, totk);
-        uint64_t pre, prek;
-        tile_prefix2(desc, (uint64_t)tot, desc_kids, (uint64_t)totk, t, epoch, s_b2, pre, prek, ctl);
-        int64_t e = (int64_t)pre + ex;
-        int64_t run = (int64_t)prek + exk;
+        uint32_t kk[kSItems];
+        int64_t st[kSItems];
+        uint64_t kids = 0;
+#pragma unroll
+        for (int k = 0; k < kSItems; ++k) {
+            kk[k] = 0;
+            st[k] = 0;
+            if (fmask & (1u << k)) {
+                st[k] = offsets[p0 + k];
+                kk[k] = (uint32_t)(offsets[p0 + k + 1] - st[k]);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kSItems; ++k) kids += kk[k];
+        // one block scan of children << 16 | parents (a tile holds at most 8192 parents)
+        const uint64_t v = kids << 16 | (uint64_t)__popc(fmask);
+        const uint64_t inc = wave_incl_sum_dpp(v);
+        if (ln == 63) s_w[wv] = inc;
+        __syncthreads();
+        uint64_t ex = inc - v, tot = 0;
+#pragma unroll
+        for (int i = 0; i < kSTh / 64; ++i) {
+            const uint64_t x = s_w[i];
+            ex += i < wv ? x : 0;
+            tot += x;
+        }
+        uint64_t pre = 0, prek = 0;
+        if (!single) tile_prefix2(desc, tot & 0xffffu, desc_kids, tot >> 16, t, epoch, s_b2, pre, prek, ctl);
+        int64_t e = (int64_t)pre + (int64_t)(ex & 0xffffu);
+        int64_t run = (int64_t)prek + (int64_t)(ex >> 16);
+        uint32_t left = bits;                         // complete parents that stay for a later emission
         bool over = false;
 #pragma unroll
         for (int k = 0; k < kSItems; ++k) {
             if (!(fmask & (1u << k))) continue;
             const int64_t p = p0 + k;
             if (e < cap_parents) {
-                ebase[e] = offsets[p] - run;      // canonical slot of virtual child v: ebase[e] + v
+                ebase[e] = st[k] - run;           // canonical slot of virtual child v: ebase[e] + v
                 evoff[e] = run;
-                ebar[e] = (barrier && barrier[p]) ? 1 : 0;
+                ebar[e] = (bmask >> k) & 1u;
                 if (emit_parent) emit_parent[e] = (uint32_t)p;
                 ecnt[e] = 0;
                 ecnt[ecnt_stride + e] = 0;
                 ecnt[2 * ecnt_stride + e] = 0;
                 emitted[p] = 1;
+                left &= ~(1u << k);
             } else {
                 if (e == cap_parents) {
                     // the emission stops here: its virtual children end at run
@@ -204,169 +222,173 @@ __global__ __launch_bounds__(kBlock) void k_stream_select(
             ++e;
             run += kk[k];
         }
+        if (left != bits) ready[p0 >> 3] = (uint8_t)left;
         if (over) raise_err(ctl, RO_ECAP);
         if (t == ntiles - 1 && threadIdx.x == 0) {
-            const int64_t E = (int64_t)pre + tot;
+            const int64_t E = (int64_t)pre + (int64_t)(tot & 0xffffu), V = (int64_t)prek + (int64_t)(tot >> 16);
             if (n_emitted) *n_emitted = E;
             ctl->n_items = E < cap_parents ? E : cap_parents;
             if (E <= cap_parents) {
-                evoff[E] = (int64_t)prek + totk;
-                ctl->n_virtual = (int64_t)prek + totk;
+                evoff[E] = V;
+                ctl->n_virtual = V;
             }
         }
+        if (single) return;
+        if (ntiles <= (int64_t)gridDim.x) break;  // a tile for every workgroup
+        __syncthreads();                          // s_w is written again
     }
     ticket_done(ctl, epoch, desc, desc_cap, &s_last);
 }
 
-// Byte scan over the virtual children of this emission, 1024 per tile (four
-// consecutive per thread; small tiles spread the random slot reads over many
-// compute units).  Virtual child v of emitted parent e lives in canonical
-// slot ebase[e] + v.  Writes each child's output position edst[v] and source
-// address esrc[v] for the copy, the emitted slot offsets, and per-state
-// counts (run lengths, aggregated in LDS).  Only the first min(grid, tiles)
-// workgroups take part.
-constexpr int kETile = 1024;
-constexpr int kEItems = kETile / kBlock;
-constexpr int kECntLds = 256;
+// Byte scan over the virtual children of this emission, 4096 per tile in
+// groups of 64, a group per load of a wave.  Virtual child v of emitted parent
+// e lives in canonical slot ebase[e] + v; the tile's parents are in LDS, and
+// every child finds its own there.  As in the gather's scan, exclusive byte
+// sums and state masks per group answer any range, so after the look-back the
+// work goes by parent: slot offset and counts.  Writes each child's output
+// position edst[v] and source address esrc[v] for the copy.  Only as many
+// workgroups as there are tiles take part; a single tile (most waves of a
+// long stream) needs no ticket and no look-back.
+constexpr int kETh = 1024;
+constexpr int kEItems = 4;
+constexpr int kETile = kETh * kEItems;
 
-__global__ __launch_bounds__(kBlock) void k_emit_scan(
+__global__ __launch_bounds__(kETh) void k_emit_scan(
     const int64_t *__restrict__ evoff, const int64_t *__restrict__ ebase, const Canon *__restrict__ canon,
     int64_t *__restrict__ edst, uint64_t *__restrict__ esrc, int64_t *__restrict__ emit_off,
     int32_t *__restrict__ ecnt, int64_t ecnt_stride, uint32_t run_epoch, Ctl *ctl, uint64_t *desc,
     int64_t desc_cap)
 {
+    constexpr int kG = kETile / 64;
+    constexpr int kCF = 21, kCK = 42;             // a packed count: SUCCESS, FAILED << 21, SKIPPED << 42
+    constexpr uint64_t kCM = (1u << kCF) - 1;
+    static_assert(kG == 64, "one lane per group");
     const int64_t E = ctl->n_items;
     const int64_t V = ctl->n_virtual;
     const int64_t ntiles = (V + kETile - 1) / kETile;
     if ((int64_t)blockIdx.x >= ntiles) return;
     const uint32_t parts = (uint32_t)min64((int64_t)gridDim.x, ntiles);
     const uint32_t sepoch = scan_epoch(ctl);
-    __shared__ int64_t s_wave[kBlock / 64];
+    const bool single = ntiles == 1;
+    __shared__ uint64_t s_pre[kETile];            // exclusive byte sum inside the child's group
+    __shared__ int64_t s_base[kETile + 2];        // ebase of the tile's parents
+    __shared__ int16_t s_off[kETile + 4];         // evoff of the tile's parents - vt0, clamped to [-1, kETile + 1]
+    __shared__ uint64_t s_gt[kG], s_gbase[kG];
+    __shared__ uint64_t s_m[3][kG + 1], s_cp[kG + 1];
     __shared__ uint64_t s_b;
     __shared__ int64_t s_t;
+    __shared__ int64_t s_p[2];
     __shared__ int32_t s_last;
-    __shared__ int64_t s_p[3];
-    __shared__ int16_t s_off[kETile + 2];         // evoff[pf..pl+1] - vt0, clamped to [-1, kETile + 1]
-    __shared__ int64_t s_base[kETile + 1];        // ebase[pf..pl]
-    __shared__ int32_t s_cnt[3][kECntLds];
+    const int wv = uni32((int)(threadIdx.x >> 6)), ln = lane_id();
     for (;;) {
-        const int64_t t = next_ticket(ctl, &s_t);
+        const int64_t t = single ? 0 : next_ticket(ctl, &s_t);
         if (t >= ntiles) break;
         const int64_t vt0 = t * kETile;
-        const int64_t vt1 = min64(vt0 + kETile, V);
-        // emitted parents of the tile: pf holds child vt0, pl holds vt1 - 1,
-        // q0 is the first one starting at or after vt0
-        if (threadIdx.x < 3 * 64) {
-            const int w = (int)(threadIdx.x >> 6);
-            int64_t r;
-            if (w == 0) r = wave_last_le(evoff, 0, E + 1, vt0);
-            else if (w == 1) r = wave_last_le(evoff, 0, E + 1, vt1 - 1);
-            else r = vt0 == 0 ? 0 : wave_last_le(evoff, 0, E + 1, vt0 - 1) + 1;
-            if (lane_id() == 0) s_p[w] = r;
+        const int nloc = (int)min64(kETile, V - vt0);
+        // q0: first emitted parent starting in the tile; q1: first one after it
+        if (wv < 2) {
+            const int64_t x = vt0 + (wv == 0 ? 0 : nloc);
+            const int64_t r = x == 0 ? 0 : wave_last_le(evoff, 0, E + 1, x - 1) + 1;
+            if (ln == 0) s_p[wv] = r;
         }
         __syncthreads();
-        const int64_t pf = s_p[0], pl = s_p[1], q0t = s_p[2];
-        const int64_t Rp = pl - pf + 1;
-        const int64_t R = min64(Rp, kECntLds);
+        const int64_t q0 = s_p[0], q1 = s_p[1];
+        const int64_t pf = q0 > 0 ? q0 - 1 : 0;         // holds child vt0 if none starts there
+        const int64_t Rp = q1 - pf;
         const bool lds_ok = Rp <= kETile;
         if (lds_ok) {
-            for (int64_t j = threadIdx.x; j <= Rp; j += kBlock) {
+            for (int64_t j = threadIdx.x; j <= Rp; j += kETh) {
                 const int64_t x = evoff[pf + j] - vt0;
                 s_off[j] = (int16_t)(x < -1 ? -1 : (x > kETile + 1 ? kETile + 1 : x));
                 if (j < Rp) s_base[j] = ebase[pf + j];
             }
         }
-        for (int j = threadIdx.x; j < 3 * kECntLds; j += kBlock) (&s_cnt[0][0])[j] = 0;
         __syncthreads();
-        // this thread's four virtual children: slot, length, state, source
-        const int64_t v0 = vt0 + (int64_t)threadIdx.x * kEItems;
-        int64_t e0 = 0;
-        uint32_t len[kEItems], stv[kEItems];
-        uint64_t src[kEItems];
-        int64_t sum = 0;
+        // every child's slot, then the slots, all in flight
+        int64_t slot[kEItems];
 #pragma unroll
         for (int k = 0; k < kEItems; ++k) {
-            len[k] = 0;
-            stv[k] = 4;
-            src[k] = 0;
+            const int i = (wv * kEItems + k) * 64 + ln;
+            const int rv = i < nloc ? i : nloc - 1;
+            if (lds_ok) slot[k] = s_base[lds_last_le(s_off, 0, (int)Rp, rv)];
+            else slot[k] = ebase[upper_bound_g(evoff, pf, q1, vt0 + rv) - 1];
+            slot[k] += vt0 + rv;
         }
-        if (v0 < vt1) {
-            int64_t e = lds_ok ? pf + lds_last_le(s_off, 0, (int)Rp, (int)(v0 - vt0))
-                               : upper_bound_g(evoff, pf, pl + 1, v0) - 1;
-            e0 = e;
+        Canon x[kEItems];
 #pragma unroll
-            for (int k = 0; k < kEItems; ++k) {
-                const int64_t v = v0 + k;
-                if (v >= vt1) break;
-                if (lds_ok) {
-                    const int rv = (int)(v - vt0);
-                    if (rv >= s_off[e - pf + 1]) e = pf + lds_last_le(s_off, (int)(e - pf) + 1, (int)Rp, rv);
-                } else if (v >= evoff[e + 1]) {
-                    e = advance_parent(evoff, E, e, v);
-                }
-                const int64_t c = (lds_ok ? s_base[e - pf] : ebase[e]) + v;
-                const Canon x = canon[c];
-                if ((x.tag >> 2) == run_epoch) {
-                    stv[k] = x.tag & 3u;
-                    len[k] = stv[k] == RO_SUCCESS ? x.len : 0;
-                    src[k] = x.src;
-                }
-                sum += len[k];
-            }
-        }
-        int64_t tot;
-        const int64_t ex = block_excl_scan(sum, s_wave, tot);
-        const uint64_t pre = tile_prefix(desc, t, sepoch, (uint64_t)tot, &s_b, ctl);
-        if (v0 < vt1) {
-            int64_t pos = (int64_t)pre + ex;
-            int64_t e = e0;
-            int32_t run[3] = {0, 0, 0};
-            auto flush = [&](int64_t q) {
+        for (int k = 0; k < kEItems; ++k) x[k] = canon[slot[k]];
 #pragma unroll
-                for (int s = 0; s < 3; ++s) {
-                    if (run[s]) {
-                        if (q - pf < R) atomicAdd(&s_cnt[s][q - pf], run[s]);
-                        else atomicAdd(&ecnt[s * ecnt_stride + q], run[s]);
-                        run[s] = 0;
-                    }
-                }
-            };
-            // emitted parents whose first child is v0 (empty ones included)
-            if (evoff[e] == v0) {
-                const int64_t qa = v0 == vt0 ? q0t : lower_bound_g(evoff, pf, e + 1, v0);
-                for (int64_t q = qa; q <= e; ++q) emit_off[q] = pos;
+        for (int k = 0; k < kEItems; ++k) {
+            const int g = wv * kEItems + k, i = g * 64 + ln;
+            const uint32_t S = (i < nloc && (x[k].tag >> 2) == run_epoch) ? x[k].tag & 3u : 4u;
+            const uint64_t L = S == RO_SUCCESS ? x[k].len : 0u;
+            const uint64_t m0 = __ballot(S == RO_SUCCESS), m1 = __ballot(S == RO_FAILED),
+                           m2 = __ballot(S == RO_SKIPPED);
+            const uint64_t inc = wave_incl_sum_dpp(L);
+            s_pre[i] = inc - L;
+            if (ln == 63) {
+                s_gt[g] = inc;
+                s_m[0][g] = m0;
+                s_m[1][g] = m1;
+                s_m[2][g] = m2;
             }
-#pragma unroll
-            for (int k = 0; k < kEItems; ++k) {
-                const int64_t v = v0 + k;
-                if (v >= vt1) break;
-                if (v >= evoff[e + 1]) {
-                    flush(e);
-                    const int64_t en = advance_parent(evoff, E, e, v);
-                    for (int64_t q = e + 1; q <= en; ++q) emit_off[q] = pos;
-                    e = en;
-                }
-                if (stv[k] < 3) run[stv[k]] += 1;
-                edst[v] = pos;
-                esrc[v] = src[k];
-                pos += len[k];
-            }
-            flush(e);
         }
         __syncthreads();
-        for (int64_t j = threadIdx.x; j < R; j += kBlock) {
-#pragma unroll
-            for (int s = 0; s < 3; ++s) {
-                const int32_t x = s_cnt[s][j];
-                if (x) atomicAdd(&ecnt[s * ecnt_stride + pf + j], x);
+        if (wv == 0) {
+            const uint64_t gt = s_gt[ln];
+            const uint64_t gc = (uint64_t)__popcll(s_m[0][ln]) | (uint64_t)__popcll(s_m[1][ln]) << kCF |
+                                (uint64_t)__popcll(s_m[2][ln]) << kCK;
+            const uint64_t gi = wave_incl_sum_dpp(gt), ci = wave_incl_sum_dpp(gc);
+            const uint64_t tot = (uint64_t)uni64(__shfl((long long)gi, 63, 64));
+            s_gbase[ln] = gi - gt;
+            s_cp[ln] = ci - gc;
+            if (ln == 63) s_cp[kG] = ci;
+            const uint64_t pr = single ? 0 : lookback_wave(desc, t, sepoch, tot, ctl);
+            if (ln == 0) {
+                s_b = pr;
+                if (t == ntiles - 1) {
+                    ctl->total = (int64_t)(pr + tot);
+                    edst[V] = (int64_t)(pr + tot);
+                    if (pr >= kSat) raise_err(ctl, RO_EOVERFLOW);
+                }
             }
         }
-        if (t == ntiles - 1 && threadIdx.x == 0) {
-            const int64_t total = (int64_t)pre + tot;
-            ctl->total = total;
-            edst[V] = total;
-            if (pre >= kSat) raise_err(ctl, RO_EOVERFLOW);
+        __syncthreads();
+        const int64_t pre = (int64_t)s_b;
+#pragma unroll
+        for (int k = 0; k < kEItems; ++k) {
+            const int g = wv * kEItems + k, i = g * 64 + ln;
+            if (i < nloc) {
+                edst[vt0 + i] = pre + (int64_t)(s_gbase[g] + s_pre[i]);
+                esrc[vt0 + i] = (x[k].tag >> 2) == run_epoch ? x[k].src : 0;
+            }
         }
+        auto counts_to = [&](int y) -> uint64_t {
+            const int g = y >> 6;
+            const uint64_t low = (1ull << (y & 63)) - 1;
+            return s_cp[g] + ((uint64_t)__popcll(s_m[0][g] & low) | (uint64_t)__popcll(s_m[1][g] & low) << kCF |
+                              (uint64_t)__popcll(s_m[2][g] & low) << kCK);
+        };
+        auto add_counts = [&](int64_t e, uint64_t c, bool whole) {
+            const int32_t cc[3] = {(int32_t)(c & kCM), (int32_t)((c >> kCF) & kCM), (int32_t)(c >> kCK)};
+#pragma unroll
+            for (int s = 0; s < 3; ++s) {
+                if (whole) ecnt[s * ecnt_stride + e] = cc[s];
+                else if (cc[s]) atomicAdd(&ecnt[s * ecnt_stride + e], cc[s]);
+            }
+        };
+        for (int64_t q = q0 + threadIdx.x; q < q1; q += kETh) {
+            const int st = (int)(evoff[q] - vt0);
+            const int64_t en = evoff[q + 1] - vt0;
+            emit_off[q] = pre + (int64_t)(s_gbase[st >> 6] + s_pre[st]);
+            add_counts(q, counts_to((int)min64(en, nloc)) - counts_to(st), en <= nloc);
+        }
+        if (threadIdx.x == kETh - 1 && vt0 > 0) {       // the parent reaching in from the tile before
+            const int64_t en = min64(evoff[q0] - vt0, nloc);
+            if (en > 0) add_counts(q0 - 1, counts_to((int)en), false);
+        }
+        if (single) return;
+        if (ntiles <= (int64_t)gridDim.x) break;        // a tile for every workgroup
         __syncthreads();
     }
     ticket_done_n(ctl, sepoch, desc, desc_cap, &s_last, parts);
@@ -386,10 +408,10 @@ constexpr int64_t kEmitMinUnit = RO_EMIT_MIN_UNIT;
 #ifndef RO_EMIT_GRID
 #define RO_EMIT_GRID 4                      // emission copy workgroups per CU
 #endif
-#ifndef RO_EMIT_UNITS
-#define RO_EMIT_UNITS 1                     // byte units per wave of the grid
+#ifndef RO_EMIT_UNIT
+#define RO_EMIT_UNIT (64 << 10)
 #endif
-constexpr int64_t kEmitUnits = RO_EMIT_UNITS;
+constexpr int64_t kEmitUnit = RO_EMIT_UNIT;
 #ifndef RO_EMIT_STEPS
 #define RO_EMIT_STEPS 4
 #endif
@@ -408,7 +430,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const int64_t E = ctl->n_items;
     const int64_t V = ctl->n_virtual;
     const int64_t T = V > 0 ? ctl->total : 0;
-    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    // parents go to the workgroups from the last one on, which have no bytes
+    // to copy in a small emission
+    const int64_t g = (int64_t)(gridDim.x - 1 - blockIdx.x) * blockDim.x + threadIdx.x;
     if (g == 0) {
         emit_off[E] = T;
         if (n_bytes) *n_bytes = T;
@@ -426,7 +450,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const uint64_t outa = reinterpret_cast<uint64_t>(out);
     const int64_t mis = (int64_t)(outa & 15);
     const int64_t nwaves = (int64_t)gridDim.x * kWaves;
-    int64_t G = (T + nwaves * kEmitUnits - 1) / (nwaves * kEmitUnits);
+    int64_t rounds = (T + nwaves * kEmitUnit / 2) / (nwaves * kEmitUnit);
+    rounds = rounds < 1 ? 1 : rounds;
+    int64_t G = (T + mis + nwaves * rounds - 1) / (nwaves * rounds);
     G = (G + 15) & ~(int64_t)15;
     G = G < kEmitMinUnit ? kEmitMinUnit : (G > ((int64_t)1 << 30) ? ((int64_t)1 << 30) : G);
     const int64_t nunits = (T + mis + G - 1) / G;
@@ -478,15 +504,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // Forgets every report and emission: seen bits, counters and emitted flags
 // back to zero.  Canonical slots need no clearing, since a slot is read only
 // for children of emitted parents, and those were all reported.
-__global__ void k_stream_clear(uint32_t *__restrict__ seen, int64_t n_seen, int32_t *__restrict__ mid,
-                               int64_t n_mid, int32_t *__restrict__ big, int64_t n_big,
-                               uint8_t *__restrict__ emitted, uint8_t *__restrict__ barrier, int64_t n_emitted)
+__global__ void k_stream_clear(uint32_t *__restrict__ seen, int64_t n_seen, uint32_t *__restrict__ words,
+                               int64_t n_words, uint8_t *__restrict__ emitted, uint8_t *__restrict__ barrier,
+                               int64_t n_emitted)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = g; i < n_seen; i += stride) seen[i] = 0;
-    for (int64_t i = g; i < n_mid; i += stride) mid[i] = 0;
-    for (int64_t i = g; i < n_big; i += stride) big[i] = 0;
+    for (int64_t i = g; i < n_words; i += stride) words[i] = 0;
     for (int64_t i = g; i < n_emitted; i += stride) {
         emitted[i] = 0;
         if (barrier) barrier[i] = 0;
@@ -496,15 +521,14 @@ __global__ void k_stream_clear(uint32_t *__restrict__ seen, int64_t n_seen, int3
 hipError_t launch_stream_reset(const Launch &L, StreamState &s)
 {
     RO_LAUNCH(L, RO_K_MISC, k_stream_clear, dim3((unsigned)L.num_cus * 4), dim3(256), 0, L.stream, s.seen,
-              (s.N + 31) / 32 + 1, s.mid, stream_mid_size(s.N), s.big, stream_big_size(s.N), s.emitted,
-              s.barrier, s.P);
+              (s.N + 31) / 32 + 1, s.words, stream_word_count(s.N), s.emitted, s.barrier, s.P);
     return launch_stream_init(L, s);
 }
 
 hipError_t launch_stream_init(const Launch &L, StreamState &s)
 {
     RO_LAUNCH(L, RO_K_MISC, k_stream_check, dim3((unsigned)L.num_cus), dim3(256), 0, L.stream, s.offsets, s.P,
-              s.N, L.ctl);
+              s.N, s.ready, L.ctl);
     return hipGetLastError();
 }
 
@@ -519,8 +543,8 @@ hipError_t launch_stream_report(const Launch &L, StreamState &s, const uint32_t 
     int64_t grid = (n + kBlock - 1) / kBlock;
     grid = grid < 1 ? 1 : (grid > (int64_t)L.num_cus * 8 ? (int64_t)L.num_cus * 8 : grid);
     RO_LAUNCH(L, RO_K_STREAM_REPORT, k_stream_report, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, rp, ro,
-              rs, roff, data, n, s.offsets, s.P, s.N, s.canon, s.seen, s.mid, s.big, stream_big_slots(s.N),
-              s.run_epoch, s.barrier, s.gkey, s.gf_epoch, n_rejected, L.ctl);
+              rs, roff, data, n, s.offsets, s.P, s.N, s.canon, s.seen, s.words,
+              reinterpret_cast<uint32_t *>(s.ready), s.run_epoch, s.barrier, s.gkey, s.gf_epoch, n_rejected, L.ctl);
     if (s.barrier) return launch_gf_fold(L, rs, rp, n, s.P, s.barrier, s.gkey, s.gf_epoch);
     return hipGetLastError();
 }
@@ -538,14 +562,14 @@ hipError_t launch_stream_emit(const Launch &L, StreamState &s, uint32_t *emit_pa
 {
     const int64_t ntiles = s.P > 0 ? (s.P + kSTile - 1) / kSTile : 1;
     if (2 * ntiles > L.desc_cap || (s.N + kETile - 1) / kETile > L.desc_cap) return hipErrorInvalidValue;
-    const int64_t grid = ntiles < (int64_t)L.num_cus * 4 ? ntiles : (int64_t)L.num_cus * 4;
+    // a workgroup of select per CU at most (a tile is 8192 parents); two of the scan fit a CU's LDS
+    const int64_t grid = ntiles < (int64_t)L.num_cus ? ntiles : (int64_t)L.num_cus;
     const int64_t es = s.P + 1;
-    RO_LAUNCH(L, RO_K_STREAM_SELECT, k_stream_select, dim3((unsigned)grid), dim3(kBlock), 0, L.stream,
-              s.offsets, s.P, s.seen, s.mid, s.big, stream_big_slots(s.N), s.barrier, s.ebar, s.emitted, s.ebase,
-              s.evoff, emit_parent,
-              s.ecnt, es, cap_parents, n_emitted, L.ctl, L.desc, L.desc + ntiles, L.desc_cap, ntiles);
+    RO_LAUNCH(L, RO_K_STREAM_SELECT, k_stream_select, dim3((unsigned)grid), dim3(kSTh), 0, L.stream, s.offsets, s.P,
+              reinterpret_cast<uint8_t *>(s.ready), s.barrier, s.ebar, s.emitted, s.ebase, s.evoff, emit_parent, s.ecnt,
+              es, cap_parents, n_emitted, L.ctl, L.desc, L.desc + ntiles, L.desc_cap, ntiles);
     const int64_t grid_s = (int64_t)L.num_cus * 2;
-    RO_LAUNCH(L, RO_K_STREAM_SCAN, k_emit_scan, dim3((unsigned)grid_s), dim3(kBlock), 0, L.stream, s.evoff,
+    RO_LAUNCH(L, RO_K_STREAM_SCAN, k_emit_scan, dim3((unsigned)grid_s), dim3(kETh), 0, L.stream, s.evoff,
               s.ebase, s.canon, s.edst, s.esrc, emit_off, s.ecnt, es, s.run_epoch, L.ctl, L.desc, L.desc_cap);
     const int64_t grid_c = (int64_t)L.num_cus * RO_EMIT_GRID;
     RO_LAUNCH(L, RO_K_STREAM_COPY, k_emit_out, dim3((unsigned)grid_c), dim3(kBlock), 0, L.stream, emit_off,

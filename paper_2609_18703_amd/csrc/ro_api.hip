@@ -620,8 +620,8 @@ int ro_stream_create(ro_ctx *c, const int64_t *offsets, int64_t n_parents, int64
     const size_t sizes[] = {
         (size_t)(N > 0 ? N : 1) * sizeof(Canon),            // canon
         (size_t)((N + 31) / 32 + 1) * sizeof(uint32_t),     // seen
-        (size_t)stream_mid_size(N) * sizeof(int32_t),       // mid
-        (size_t)stream_big_size(N) * sizeof(int32_t),       // big
+        (size_t)stream_word_count(N) * sizeof(uint32_t),    // words
+        (size_t)(P / 64 + 1) * sizeof(uint64_t),            // ready
         (size_t)(P + 1),                                    // emitted
         (size_t)(P + 1) * sizeof(int64_t),                  // ebase
         (size_t)(P + 2) * sizeof(int64_t),                  // evoff
@@ -658,8 +658,8 @@ int ro_stream_create(ro_ctx *c, const int64_t *offsets, int64_t n_parents, int64
     st.N = N;
     st.canon = (Canon *)(block + offs[0]);
     st.seen = (uint32_t *)(block + offs[1]);
-    st.mid = (int32_t *)(block + offs[2]);
-    st.big = (int32_t *)(block + offs[3]);
+    st.words = (uint32_t *)(block + offs[2]);
+    st.ready = (uint64_t *)(block + offs[3]);
     st.emitted = (uint8_t *)(block + offs[4]);
     st.ebase = (int64_t *)(block + offs[5]);
     st.evoff = (int64_t *)(block + offs[6]);

@@ -187,8 +187,8 @@ struct StreamState {
     int64_t P, N;
     Canon *canon;            // [N] accepted reports (tag epoch 1 = accepted)
     uint32_t *seen;          // [N/32] duplicate detection bitmap
-    int32_t *mid;            // [stream_mid_size(N)] report counters of parents with 64..1023 children
-    int32_t *big;            // [stream_big_size(N)] spread report counters of large parents
+    uint32_t *words;         // [stream_word_count(N)] complete seen words of parents with several
+    uint64_t *ready;         // [P/64 + 1] bitmap of parents complete and not emitted
     uint8_t *emitted;        // [P]
     int64_t *ebase;          // [P] per emitted parent: canonical slot of its first child minus evoff
     int64_t *evoff;          // [P+1] child offsets of the emitted parents (virtual children)
@@ -212,8 +212,7 @@ hipError_t launch_first_gf(const Launch &L, const uint8_t *rs, const uint32_t *r
 hipError_t launch_gf_fold(const Launch &L, const uint8_t *rs, const uint32_t *rp, int64_t n, int64_t P,
                           uint8_t *barrier, const uint64_t *gkey, uint32_t epoch);
 
-int64_t stream_mid_size(int64_t N);
-int64_t stream_big_size(int64_t N);
+int64_t stream_word_count(int64_t N);
 int64_t stream_desc_tiles(int64_t P, int64_t N);
 hipError_t launch_stream_init(const Launch &L, StreamState &s);
 hipError_t launch_stream_reset(const Launch &L, StreamState &s);

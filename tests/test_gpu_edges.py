@@ -156,3 +156,46 @@ def test_batch_paths(q_len, reserve):
         _say("batch paths", q_len, reserve, k is not None, bar is not None)
         _batch_case(c, counts, queue, k, bar, 256)
     c.close()
+
+
+def test_stream_word_and_tile_edges(ctx):
+    """Completion found by seen words: parents of one to many 32-child words
+    at every alignment, empty parents among them, children in random order
+    over waves; emissions of one and several scan tiles, select tiles of 8,192
+    parents."""
+    from test_gpu_stream_nested import _stream_case
+    rng = np.random.default_rng(8)
+    sizes = np.array([0, 1, 2, 5, 31, 32, 33, 63, 64, 65, 96, 127, 1023, 1025, 5000])
+    counts = np.concatenate([rng.choice(sizes[:11], 1500), sizes, rng.integers(0, 2, 8192), [4096, 0, 0]])
+    n = int(counts.sum())
+    _say("stream edges", len(counts), n)
+    waves = []
+    for ids in np.split(rng.permutation(n), [1, n // 7, n // 2, n - 3]):
+        waves.append((ids, rng.choice([O.SUCCESS] * 6 + [O.FAILED, O.SKIPPED], len(ids)),
+                      rng.choice([0, 1, 15, 16, 17, 90], len(ids))))
+    _stream_case(ctx, counts, waves, B=77)
+    # children in order, one wave per select tile boundary
+    waves = [(ids, np.zeros(len(ids), np.uint8), np.full(len(ids), 3)) for ids in np.array_split(np.arange(n), 3)]
+    _stream_case(ctx, counts, waves, B=77, runs=2)
+
+
+def test_stream_emission_beyond_capacity_is_emitted_later(ctx):
+    """Parents an emission has no room for (RO_ECAP) stay for the next one."""
+    import paper_2609_18703_amd as R
+    counts = np.array([2, 0, 1, 3, 0, 1, 2, 1, 1, 1], np.int32)
+    offs, par, ordi = O.expand(counts)
+    n, p = len(par), len(counts)
+    st = ctx.stream(D.to_dev(offs), n)
+    off = np.arange(n + 1, dtype=np.int64) * 4
+    data = D.to_dev(np.arange(4 * n, dtype=np.uint8))
+    cols = (_i32(par), _i32(ordi), _zeros(n, torch.uint8), D.to_dev(off))
+    st.report(*cols, data)
+    ep, eo, ed, sc = _zeros(p, torch.int32), _zeros(p + 1, torch.int64), _zeros(4 * n, torch.uint8), _zeros(2, torch.int64)
+    st.emit(ep, eo, ed, n_emitted=sc[0:1], n_bytes=sc[1:2], cap_parents=4, cap_bytes=4 * n)
+    assert ctx.status() == R.ECAP
+    st.emit(ep, eo, ed, n_emitted=sc[0:1], n_bytes=sc[1:2], cap_parents=p, cap_bytes=4 * n)
+    ctx.check("second emission")
+    assert sc.tolist() == [6, 4 * int(counts[4:].sum())]
+    assert ep.tolist()[:6] == list(range(4, 10))
+    assert ed.tolist()[:sc[1].item()] == list(range(4 * int(offs[4]), 4 * n))
+    st.close()
