@@ -79,10 +79,10 @@ struct ro_ctx {
 struct ro_grains {
     ro_ctx *ctx;
     int64_t n;
-    Grain *g;                 // [max(n, 1)] phase, generation and fence key per child
-    uint32_t epoch;           // of the current commit call
-    uint32_t *tag;            // [tag_cap] per report: epoch of the call in which it met another
-    int64_t tag_cap;
+    GrainTab tab;
+    void *block;              // one device allocation for the table
+    uint32_t *scratch;        // [4 * scratch_cap] per report of a commit call: (child, report) by bin; its child; contested reports
+    int64_t scratch_cap;
 };
 
 struct ro_stream {
@@ -519,18 +519,27 @@ int ro_grains_create(ro_ctx *c, int64_t n_children, ro_grains **out)
 {
     if (out) *out = nullptr;
     if (!c || !out || n_children < 0 || n_children >= ((int64_t)1 << 32)) return RO_EINVAL;
-    const int64_t n = n_children > 0 ? n_children : 1;
+    const int64_t n = n_children > 0 ? n_children : 1, w = grain_words(n);
     ro_grains *g = (ro_grains *)calloc(1, sizeof(ro_grains));
     if (!g) return RO_EINVAL;
-    if (hipMalloc((void **)&g->g, (size_t)n * sizeof(Grain)) != hipSuccess) {
+    uint32_t *b = nullptr;
+    if (dev_alloc(&b, 6 * w + 2 * kGrainBins + 64 + 2 * n) != hipSuccess) {
         free(g);
         return RO_EHIP;
     }
     g->ctx = c;
     g->n = n_children;
-    g->epoch = 0;
-    if (launch_grains_fill(launch_of(c), g->g, n) != hipSuccess) {
-        (void)hipFree(g->g);
+    g->block = b;
+    g->tab.bits = reinterpret_cast<GrainBits *>(b);
+    g->tab.met = b + 4 * w;
+    g->tab.contested = b + 5 * w;
+    g->tab.hist = b + 6 * w;
+    g->tab.cursor = g->tab.hist + kGrainBins;
+    g->tab.n_list = g->tab.cursor + kGrainBins;
+    g->tab.gen = g->tab.n_list + 64;
+    g->tab.first = g->tab.gen + n;
+    if (launch_grains_fill(launch_of(c), g->tab, n) != hipSuccess) {
+        (void)hipFree(b);
         free(g);
         return RO_EHIP;
     }
@@ -541,16 +550,15 @@ int ro_grains_create(ro_ctx *c, int64_t n_children, ro_grains **out)
 int ro_grains_reset(ro_ctx *c, ro_grains *g)
 {
     if (!c || !g || g->ctx != c) return RO_EINVAL;
-    g->epoch = 0;
-    return hip_fail(launch_grains_fill(launch_of(c), g->g, g->n > 0 ? g->n : 1));
+    return hip_fail(launch_grains_fill(launch_of(c), g->tab, g->n > 0 ? g->n : 1));
 }
 
 int ro_grains_destroy(ro_grains *g)
 {
     if (!g) return RO_EINVAL;
     if (g->ctx) (void)hipStreamSynchronize(g->ctx->stream);
-    (void)hipFree(g->g);
-    if (g->tag) (void)hipFree(g->tag);
+    (void)hipFree(g->block);
+    if (g->scratch) (void)hipFree(g->scratch);
     free(g);
     return RO_OK;
 }
@@ -559,21 +567,21 @@ int ro_grains_read(ro_ctx *c, ro_grains *g, uint32_t *phase, uint32_t *generatio
 {
     if (!c || !g || g->ctx != c) return RO_EINVAL;
     if (g->n == 0 || (!phase && !generation)) return RO_OK;
-    return hip_fail(launch_grains_read(launch_of(c), g->g, g->n, phase, generation));
+    return hip_fail(launch_grains_read(launch_of(c), g->tab, g->n, phase, generation));
 }
 
 int ro_grains_dispatch(ro_ctx *c, ro_grains *g, const uint32_t *child, int64_t n, uint32_t *out_generation)
 {
     if (!c || !g || g->ctx != c || n < 0 || (n > 0 && !child)) return RO_EINVAL;
     if (n == 0) return RO_OK;
-    return hip_fail(launch_grains_dispatch(launch_of(c), child, n, g->n, g->g, out_generation));
+    return hip_fail(launch_grains_dispatch(launch_of(c), child, n, g->n, g->tab, out_generation));
 }
 
 int ro_grains_retry(ro_ctx *c, ro_grains *g, const uint32_t *child, int64_t n)
 {
     if (!c || !g || g->ctx != c || n < 0 || (n > 0 && !child)) return RO_EINVAL;
     if (n == 0) return RO_OK;
-    return hip_fail(launch_grains_retry(launch_of(c), child, n, g->n, g->g));
+    return hip_fail(launch_grains_retry(launch_of(c), child, n, g->n, g->tab));
 }
 
 int ro_grains_commit(ro_ctx *c, ro_grains *g, const ro_reports *r, const uint32_t *generation,
@@ -583,28 +591,22 @@ int ro_grains_commit(ro_ctx *c, ro_grains *g, const ro_reports *r, const uint32_
     if (r->n >= ((int64_t)1 << 32)) return RO_EINVAL;                // report index is 32-bit
     if (r->n > 0 && (!r->parent || !r->ordinal || !r->state || !r->off || !generation || !state_out))
         return RO_EINVAL;
-    const Launch L = launch_of(c);
     const int64_t need = r->n > 0 ? r->n : 1;
-    if (need > g->tag_cap) {                  // grows with the largest call; starts untagged
-        const int64_t cap = need > 2 * g->tag_cap ? need : 2 * g->tag_cap;
+    if (need > g->scratch_cap) {              // grows with the largest call
+        const int64_t cap = need > 2 * g->scratch_cap ? need : 2 * g->scratch_cap;
         uint32_t *t = nullptr;
-        if (hipMalloc((void **)&t, (size_t)cap * sizeof(uint32_t)) != hipSuccess) return RO_EHIP;
-        if (g->tag) {
+        if (dev_alloc(&t, 4 * cap) != hipSuccess) return RO_EHIP;
+        if (g->scratch) {
             (void)hipStreamSynchronize(c->stream);
-            (void)hipFree(g->tag);
+            (void)hipFree(g->scratch);
         }
-        g->tag = t;
-        g->tag_cap = cap;
-        if (launch_grains_zero_tags(L, g->tag, cap) != hipSuccess) return RO_EHIP;
+        g->scratch = t;
+        g->scratch_cap = cap;
     }
-    if (g->epoch == 0xffffffffu) {            // keys and tags of every earlier call must read as old
-        if (launch_grains_rekey(L, g->g, g->n > 0 ? g->n : 1) != hipSuccess) return RO_EHIP;
-        if (launch_grains_zero_tags(L, g->tag, g->tag_cap) != hipSuccess) return RO_EHIP;
-        g->epoch = 0;
-    }
-    g->epoch += 1;
-    return hip_fail(launch_grains_commit(L, r->parent, r->ordinal, r->state, r->off, r->data, generation, r->n,
-                                         offsets, n_parents, g->n, g->g, g->epoch, g->tag, state_out, counts_dev));
+    return hip_fail(launch_grains_commit(launch_of(c), r->parent, r->ordinal, r->state, r->off, r->data, generation,
+                                         r->n, offsets, n_parents, g->n, g->tab, g->scratch + 2 * g->scratch_cap,
+                                         g->scratch + 3 * g->scratch_cap, reinterpret_cast<uint2 *>(g->scratch),
+                                         state_out, counts_dev));
 }
 
 int ro_stream_create(ro_ctx *c, const int64_t *offsets, int64_t n_parents, int64_t n_children,
@@ -758,8 +760,7 @@ int ro_debug_epochs(ro_ctx *c, ro_stream *s, ro_grains *g, int64_t canon_left, i
             (uint32_t)(0xffffffffll - gf_left) > s->st.gf_epoch)
             s->st.gf_epoch = (uint32_t)(0xffffffffll - gf_left);
     }
-    if (g && fence_left >= 1 && fence_left <= 0xffffffffll && (uint32_t)(0xffffffffll - fence_left) > g->epoch)
-        g->epoch = (uint32_t)(0xffffffffll - fence_left);
+    (void)fence_left;         // Grains carry no epoch
     return RO_OK;
 }
 

@@ -281,6 +281,12 @@ __device__ __noinline__ void tile_prefix2(uint64_t *desc_a, uint64_t agg_a, uint
     __syncthreads();
 }
 
+// Two neighbouring 64-bit values by one 16-byte load (8-byte aligned): a random
+// load costs by its lanes, not by its width.
+typedef int64_t v2i64 __attribute__((ext_vector_type(2)));
+typedef int64_t v2i64_a8 __attribute__((ext_vector_type(2), aligned(8)));
+__device__ __forceinline__ v2i64 ld_pair(const int64_t *p) { return *reinterpret_cast<const v2i64_a8 *>(p); }
+
 // ---- searches ---------------------------------------------------------------
 // First index i in [lo, hi) with a[i] > x (hi if none).
 __device__ __forceinline__ int64_t upper_bound_g(const int64_t *a, int64_t lo, int64_t hi, int64_t x)

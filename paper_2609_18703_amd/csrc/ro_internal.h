@@ -151,27 +151,36 @@ struct GatherWs {
 // slots and its group-failure keys
 hipError_t launch_gather(const Launch &L, const GatherArgs &a, const GatherWs &w, uint32_t epoch);
 
-// grain phases and the generation fence.  One 16-byte record per Grain:
-// word = phase (READY or IN-FLIGHT) | generation << 32, changed by one 64-bit
-// compare-and-swap; key = the accepted report, epoch << 32 | ~index, of the
-// commit call that sealed the Grain (0 while unsealed).  A report touches one
-// record: one random access.
-struct alignas(16) Grain {
-    uint64_t word;
-    uint64_t key;
+// grain phases and the generation fence: three bits per child, in one record
+// per 32 children, and two words per child that few children use
+struct alignas(16) GrainBits {
+    uint32_t inflight;       // dispatched and not retried since (a sealed child keeps its bit)
+    uint32_t sealed;
+    uint32_t retried;        // its generation is in gen[]; 0 otherwise
+    uint32_t pad;
 };
-static_assert(sizeof(Grain) == 16, "grain record");
-hipError_t launch_grains_fill(const Launch &L, Grain *g, int64_t n);
-hipError_t launch_grains_rekey(const Launch &L, Grain *g, int64_t n);
-hipError_t launch_grains_read(const Launch &L, const Grain *g, int64_t n, uint32_t *phase, uint32_t *gen);
-hipError_t launch_grains_dispatch(const Launch &L, const uint32_t *child, int64_t n, int64_t N, Grain *g,
+struct GrainTab {
+    GrainBits *bits;         // [grain_words(n)]; met, contested, hist and cursor follow in the same block
+    uint32_t *met;           // children with a passing report in the current commit call
+    uint32_t *contested;     // ... with more than one
+    uint32_t *hist, *cursor; // [kGrainBins] entries per bin of the current call, zero between calls
+    uint32_t *n_list;        // reports of contested children in the current call
+    uint32_t *gen;           // [n] generation of the children that were retried
+    uint32_t *first;         // [n] contested children: index of the first passing report
+};
+constexpr int kGrainBins = 512;
+int64_t grain_words(int64_t n);
+hipError_t launch_grains_fill(const Launch &L, const GrainTab &g, int64_t n);
+hipError_t launch_grains_read(const Launch &L, const GrainTab &g, int64_t n, uint32_t *phase, uint32_t *gen);
+hipError_t launch_grains_dispatch(const Launch &L, const uint32_t *child, int64_t n, int64_t N, const GrainTab &g,
                                   uint32_t *out_gen);
-hipError_t launch_grains_retry(const Launch &L, const uint32_t *child, int64_t n, int64_t N, Grain *g);
+hipError_t launch_grains_retry(const Launch &L, const uint32_t *child, int64_t n, int64_t N, const GrainTab &g);
+// cidx, list, pair: [n] scratch, the child of each passing report, the reports of
+// contested children, and (child, report) by bin
 hipError_t launch_grains_commit(const Launch &L, const uint32_t *rp, const uint32_t *ro, const uint8_t *rs,
                                 const int64_t *roff, const uint8_t *data, const uint32_t *rgen, int64_t n,
-                                const int64_t *offsets, int64_t P, int64_t N, Grain *g, uint32_t epoch, uint32_t *tag,
-                                uint8_t *state_out, int64_t *counts);
-hipError_t launch_grains_zero_tags(const Launch &L, uint32_t *tag, int64_t n);
+                                const int64_t *offsets, int64_t P, int64_t N, const GrainTab &g, uint32_t *cidx,
+                                uint32_t *list, uint2 *pair, uint8_t *state_out, int64_t *counts);
 
 // filter / broadcast
 constexpr int kMaxBroadcastLevels = 8;

@@ -264,3 +264,60 @@ def test_fence_many_long_repeats(ctx):
     assert want[1] == (N, 0, N, N)
     assert np.array_equal(got[0], want[0]) and got[1] == tuple(want[1])
     g.close(); og.close()
+
+
+@pytest.mark.parametrize("order", ["random", "canonical"])
+@pytest.mark.parametrize("n_children", [(3 << 17) - 1, 3 << 17, (3 << 20) + 77])
+def test_fence_around_the_size_of_a_binned_call(ctx, n_children, order):
+    """Calls of just under 3 x 2^17 children (bits set by atomics), just as many and
+    beyond (children sorted into bins), in both orders: reservation with
+    retried children among the others, a commit with stale reports, repeats of
+    random children and one child repeated 5,000 times, and a reservation that
+    names children twice, whose error leaves every named child in flight."""
+    rng = np.random.default_rng(n_children)
+    N = n_children
+    counts = np.full(N // 7 + 1, 7, np.int32)
+    counts[-1] = N - 7 * (N // 7)
+    offs = O.expand(counts, tags=False)
+    og, g = O.Grains(N), ctx.grains(N)
+    queue = np.arange(N, dtype=np.uint32) if order == "canonical" else rng.permutation(N).astype(np.uint32)
+    again = np.sort(queue[rng.random(N) < 0.01])
+    gen = torch.full((N,), -1, dtype=torch.int32, device="cuda")
+    for q in (again, queue):
+        g.dispatch(_i32(q), gen, n=len(q))
+        assert np.array_equal(gen.cpu().numpy().view(np.uint32)[:len(q)], og.dispatch(q))
+        if q is again:
+            g.retry(_i32(q))
+            og.retry(q)
+    ctx.check("dispatch")
+    gens = og.gen()
+    rep = np.concatenate([queue[rng.integers(0, N, 4000)], np.full(5000, queue[N // 3], np.uint32)])
+    child = np.concatenate([queue, rep])
+    if order == "random":
+        child = rng.permutation(child)
+    n = len(child)
+    st = rng.choice(np.array([0, 0, 0, 1, 2, 3], np.uint8), N)[child]
+    st[rng.random(n) < 0.001] = 1
+    lens = np.where(st == 0, child % 40, 0)
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    data = np.repeat((child % 251).astype(np.uint8), lens)
+    flip = rng.integers(0, max(len(data), 1), 50)
+    data[flip] ^= 1
+    gn = gens[child]
+    gn[rng.random(n) < 0.02] += 1
+    par = (child // 7).astype(np.uint32)
+    ordi = (child % 7).astype(np.uint32)
+    want = og.commit(par, ordi, st, off, data, gn, offs)
+    got = _commit(ctx, g, par, ordi, st, off, data, gn, offs)
+    assert got[1] == tuple(want[1])
+    assert np.array_equal(got[0], want[0])
+    ph, gg = _phases(g, N)
+    assert np.array_equal(ph, og.phase()) and np.array_equal(gg, og.gen())
+    # a table of its own: every child named once, and 3,000 times one of the first bin
+    g.reset()
+    twice = np.concatenate([np.full(3000, 5, np.uint32), queue])
+    g.dispatch(_i32(twice))
+    assert ctx.status() == O.ESTATE
+    ph, gg = _phases(g, N)
+    assert np.array_equal(ph, np.full(N, O.IN_FLIGHT, np.uint32)) and not gg.any()
+    g.close(); og.close()
