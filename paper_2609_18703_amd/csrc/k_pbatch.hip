@@ -22,6 +22,7 @@
 
 namespace ro {
 
+constexpr int kRTh = 512;                    // threads of the scatter
 constexpr int kRTile = (int)kPbTile;         // sort tile: 8 entries per thread
 constexpr int kRMaxBits = 9;                 // digit width; at most 512 buckets
 constexpr int kRMaxBuckets = 1 << kRMaxBits;
@@ -67,69 +68,58 @@ __global__ __launch_bounds__(kBlock) void k_rs_hist(const uint32_t *__restrict__
 
 // Stable scatter of one digit pass.  A workgroup takes a span of kRSpan
 // tiles in order, starting each digit at the span's offset from the
-// histogram scan.  Per tile: the tile's digit counts (LDS atomics) give where
-// each digit's run starts in the tile; each wave ranks its own quarter of
-// the tile (eight rounds of 64 entries, in order) among the quarter's entries
-// of the same digit, with a wave-private running count per digit plus the
-// lanes below with the same digit (one ballot per digit bit); the waves'
-// counts become per-digit bases, the tile is sorted by digit in LDS and
-// written out so that consecutive lanes store consecutive places of a
-// digit's run; the span's digit offsets then move past the tile.  Values are
-// (child << 32 | queue position); vin == nullptr: built from the compacted
-// children and the positions.
-__global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restrict__ kin,
-                                                      const uint64_t *__restrict__ vin,
-                                                      const uint32_t *__restrict__ kc, uint32_t *__restrict__ kout,
-                                                      uint64_t *__restrict__ vout, const int64_t *m_dev, int shift,
-                                                      int width, const int64_t *__restrict__ hoff, int64_t spans_cap)
+// histogram scan.  Per tile each wave ranks its own eighth (eight rounds of 64
+// entries, in order) among the eighth's entries of the same digit, with a
+// wave-private running count per digit plus the lanes below with the same
+// digit (one ballot per digit bit); the waves' counts give the tile's counts
+// and every wave's base per digit, the tile is put in order of digits in LDS
+// (values, then keys, in the same room) and written out so that consecutive
+// lanes store consecutive places of a digit's run; the span's digit offsets
+// then move past the tile.  Values are (child << 32 | queue position); vin ==
+// nullptr: built from the compacted children and the positions.
+// The runs of a digit decide the speed: 4,096 entries over 256 digits write 16
+// at a time (two passes over 10M entries, 15-bit keys: 260 us with tiles of
+// 2,048, digits of 9 and 6 bits and 610 workgroups of four waves; now 175).
+__global__ __launch_bounds__(kRTh) void k_rs_scatter(const uint32_t *__restrict__ kin,
+                                                     const uint64_t *__restrict__ vin,
+                                                     const uint32_t *__restrict__ kc, uint32_t *__restrict__ kout,
+                                                     uint64_t *__restrict__ vout, const int64_t *m_dev, int shift,
+                                                     int width, const int64_t *__restrict__ hoff, int64_t spans_cap)
 {
-    constexpr int kWaves = kBlock / 64;
-    constexpr int kQuarter = kRTile / kWaves;          // entries per wave
-    constexpr int kWRounds = kQuarter / 64;
-    static_assert(kRMaxBuckets == 2 * kBlock, "two digits per thread");
-    __shared__ int64_t s_base[kRMaxBuckets];
-    __shared__ int32_t s_tex[kRMaxBuckets];
-    __shared__ int32_t s_cnt[kWaves][kRMaxBuckets];
-    __shared__ uint32_t s_k[kRTile];
+    constexpr int kWaves = kRTh / 64;
+    constexpr int kPart = kRTile / kWaves;             // entries per wave
+    constexpr int kWRounds = kPart / 64;
+    static_assert(kRMaxBuckets == kRTh, "one digit per thread");
+    static_assert(kRTile < 65536, "places in a tile are 16-bit");
+    __shared__ int64_t s_base[kRMaxBuckets];           // place of the tile's first entry of each digit, less its place in the tile
+    __shared__ uint16_t s_cnt[kWaves][kRMaxBuckets];
     __shared__ uint64_t s_v[kRTile];
-    __shared__ int64_t s_wave[kWaves];
+    __shared__ uint32_t s_w[kWaves];
+    uint32_t *s_k = reinterpret_cast<uint32_t *>(s_v);
     const int64_t M = *m_dev;
     const int64_t nspans = (M + kRSpanLen - 1) / kRSpanLen;
     const int nb = 1 << width;
     const uint32_t mask = (uint32_t)nb - 1;
-    const int wave = (int)(threadIdx.x >> 6), lane = lane_id();
+    const int tid = (int)threadIdx.x, wave = uni32(tid >> 6), lane = lane_id();
     const uint64_t lt = (1ull << lane) - 1;
-    int32_t *cnt = s_cnt[wave];
-    const int d0 = 2 * (int)threadIdx.x, d1 = d0 + 1;
+    uint16_t *cnt = s_cnt[wave];
     for (int64_t sp = blockIdx.x; sp < nspans; sp += gridDim.x) {
-        if (d0 < nb) s_base[d0] = hoff[(int64_t)d0 * spans_cap + sp];
-        if (d1 < nb) s_base[d1] = hoff[(int64_t)d1 * spans_cap + sp];
+        int64_t next = tid < nb ? hoff[(int64_t)tid * spans_cap + sp] : 0;     // this thread's digit's next place
         for (int64_t t0 = sp * kRSpanLen; t0 < min64((sp + 1) * kRSpanLen, M); t0 += kRTile) {
-            // load the tile; count its digits
-            for (int d = threadIdx.x; d < nb; d += kBlock) s_tex[d] = 0;
-            __syncthreads();
-            const int64_t i0 = t0 + (int64_t)wave * kQuarter;
+            const int64_t i0 = t0 + (int64_t)wave * kPart;
             uint32_t key[kWRounds];
             uint64_t val[kWRounds];
-            int32_t rank[kWRounds];
+            uint32_t rank[kWRounds];
 #pragma unroll
             for (int r = 0; r < kWRounds; ++r) {
                 const int64_t i = i0 + r * 64 + lane;
                 const bool valid = i < M;
                 key[r] = valid ? kin[i] : 0;
                 val[r] = !valid ? 0 : (vin ? vin[i] : ((uint64_t)kc[i] << 32 | (uint64_t)i));
-                if (valid) atomicAdd(&s_tex[(key[r] >> shift) & mask], 1);
             }
             for (int d = lane; d < nb; d += 64) cnt[d] = 0;
-            __syncthreads();
-            // the tile's digit counts -> where each digit's run starts in the tile
-            const int32_t c0 = d0 < nb ? s_tex[d0] : 0;
-            const int32_t c1 = d1 < nb ? s_tex[d1] : 0;
-            int64_t tot;
-            const int32_t ex = (int32_t)block_excl_scan((int64_t)c0 + c1, s_wave, tot);
-            if (d0 < nb) s_tex[d0] = ex;
-            if (d1 < nb) s_tex[d1] = ex + c0;
-            // this wave's quarter: ranks among its entries of the same digit
+            __builtin_amdgcn_wave_barrier();
+            // this wave's part: ranks among its entries of the same digit
 #pragma unroll
             for (int r = 0; r < kWRounds; ++r) {
                 const bool valid = i0 + r * 64 + lane < M;
@@ -140,46 +130,69 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restric
                     const uint64_t m = __ballot(valid && bit);
                     peers &= bit ? m : ~m;
                 }
-                const int below = (int)__popcll(peers & lt);
-                rank[r] = valid ? cnt[d] + below : 0;
+                const uint32_t below = (uint32_t)__popcll(peers & lt);
+                const uint32_t had = valid ? cnt[d] : 0u;
+                rank[r] = had + below;
                 __builtin_amdgcn_wave_barrier();
-                if (valid && below == 0) cnt[d] += (int32_t)__popcll(peers);
+                if (valid && below == 0) cnt[d] = (uint16_t)(had + (uint32_t)__popcll(peers));
                 __builtin_amdgcn_wave_barrier();
             }
             __syncthreads();
-            // wave counts -> wave bases inside the tile
-            for (int d = threadIdx.x; d < nb; d += kBlock) {
-                int32_t run = s_tex[d];
+            // wave counts -> the tile's counts, where each digit starts in the
+            // tile, and the waves' bases there
+            uint32_t c[kWaves], tot = 0;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                c[w] = tid < nb ? s_cnt[w][tid] : 0u;
+                tot += c[w];
+            }
+            const uint32_t inc = (uint32_t)wave_incl_sum_dpp(tot);
+            if (lane == 63) s_w[wave] = inc;
+            __syncthreads();
+            uint32_t run = inc - tot;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) run += w < wave ? s_w[w] : 0u;
+            if (tid < nb) {
+                s_base[tid] = next - (int64_t)run;
+                next += tot;
 #pragma unroll
                 for (int w = 0; w < kWaves; ++w) {
-                    const int32_t x = s_cnt[w][d];
-                    s_cnt[w][d] = run;
-                    run += x;
+                    s_cnt[w][tid] = (uint16_t)run;
+                    run += c[w];
                 }
             }
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < kWRounds; ++r) {
                 if (i0 + r * 64 + lane >= M) continue;
-                const int32_t lp = cnt[(key[r] >> shift) & mask] + rank[r];
-                s_k[lp] = key[r];
-                s_v[lp] = val[r];
+                rank[r] += cnt[(key[r] >> shift) & mask];
+                s_k[rank[r]] = key[r];
             }
             __syncthreads();
             const int n_t = (int)min64(kRTile, M - t0);
-            for (int j = threadIdx.x; j < n_t; j += kBlock) {
-                const uint32_t k = s_k[j];
-                const uint32_t d = (k >> shift) & mask;
-                const int64_t g = s_base[d] + (j - s_tex[d]);
-                kout[g] = k;
-                vout[g] = s_v[j];
+            int64_t g[kWRounds];
+#pragma unroll
+            for (int r = 0; r < kWRounds; ++r) {
+                const int j = r * kRTh + tid;
+                g[r] = 0;
+                if (j < n_t) {
+                    const uint32_t k = s_k[j];
+                    g[r] = s_base[(k >> shift) & mask] + j;
+                    kout[g[r]] = k;
+                }
             }
             __syncthreads();
-            // the span's digit offsets move past this tile
-            if (d0 < nb) s_base[d0] += c0;
-            if (d1 < nb) s_base[d1] += c1;
+#pragma unroll
+            for (int r = 0; r < kWRounds; ++r)
+                if (i0 + r * 64 + lane < M) s_v[rank[r]] = val[r];
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < kWRounds; ++r) {
+                const int j = r * kRTh + tid;
+                if (j < n_t) vout[g[r]] = s_v[j];
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
@@ -187,55 +200,97 @@ __global__ __launch_bounds__(kBlock) void k_rs_scatter(const uint32_t *__restric
 // an error (an id out of range leaves its entry's parent unset) the parents
 // are not trusted: every kernel from here on returns at once.
 __global__ void k_pb_bounds(const uint32_t *__restrict__ key, const int64_t *m_dev, int64_t P,
-                            uint32_t *__restrict__ pstart, uint32_t *__restrict__ pend, uint32_t *__restrict__ fsize,
+                            uint32_t *__restrict__ pstart, uint32_t *__restrict__ pend, uint64_t *__restrict__ fbits,
                             Ctl *ctl)
 {
-    if (read_err(ctl) != 0) return;
     const int64_t M = *m_dev;
-    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < M; s += (int64_t)gridDim.x * blockDim.x) {
-        fsize[s] = 0;                            // group sizes are set next, at group firsts only
-        const uint32_t p = key[s];
-        if ((int64_t)p >= P) continue;
-        if (s == 0 || key[s - 1] != p) pstart[p] = (uint32_t)s;
-        if (s == M - 1 || key[s + 1] != p) pend[p] = (uint32_t)(s + 1);
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t w = tid; w <= M >> 6; w += stride) fbits[w] = 0;     // set next, at groups' firsts (none after an error)
+    if (read_err(ctl) != 0) return;
+    // four keys a thread, and the one before them
+    for (int64_t s0 = 4 * tid; s0 < M; s0 += 4 * stride) {
+        uint32_t k[4], before = s0 > 0 ? key[s0 - 1] : 0xffffffffu;
+        if (s0 + 4 <= M) {
+            const uint4 x = *reinterpret_cast<const uint4 *>(key + s0);
+            k[0] = x.x; k[1] = x.y; k[2] = x.z; k[3] = x.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) k[j] = s0 + j < M ? key[s0 + j] : 0xffffffffu;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (s0 + j < M && (s0 + j == 0 || k[j] != before)) {
+                if ((int64_t)k[j] < P) pstart[k[j]] = (uint32_t)(s0 + j);
+                if (s0 + j > 0 && (int64_t)before < P) pend[before] = (uint32_t)(s0 + j);
+            }
+            before = k[j];
+        }
+        if (s0 + 4 >= M) {
+            const uint32_t last = key[M - 1];
+            if ((int64_t)last < P) pend[last] = (uint32_t)M;
+        }
     }
 }
 
-// The queue position of every group's first entry (rank a multiple of B)
-// gets the group's size; the other positions stay zero.
-__global__ void k_pb_firsts(const uint32_t *__restrict__ key, const uint64_t *__restrict__ val, const int64_t *m_dev,
-                            int64_t P, const uint32_t *__restrict__ pstart, const uint32_t *__restrict__ pend,
-                            int32_t B, uint32_t *__restrict__ fsize, Ctl *ctl)
+// The queue position of every group's first entry (rank a multiple of B) gets
+// its bit and the group's size.  Ranks fit 32 bits (a queue position does), so
+// they are divided in 32.  Four entries a thread, the loads of each step of
+// their chains together.
+constexpr int kPbItems = 4;
+
+__global__ __launch_bounds__(kBlock) void k_pb_firsts(const uint32_t *__restrict__ key,
+                                                      const uint64_t *__restrict__ val, const int64_t *m_dev, int64_t P,
+                                                      const uint32_t *__restrict__ pstart,
+                                                      const uint32_t *__restrict__ pend, uint32_t B,
+                                                      uint32_t *__restrict__ fsize, uint64_t *__restrict__ fbits, Ctl *ctl)
 {
     if (read_err(ctl) != 0) return;
     const int64_t M = *m_dev;
-    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < M; s += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t p = key[s];
-        if ((int64_t)p >= P) continue;
-        const int64_t r = s - (int64_t)pstart[p];
-        if (r % B != 0) continue;
-        const int64_t left = (int64_t)pend[p] - s;
-        fsize[(uint32_t)val[s]] = (uint32_t)(left < B ? left : B);
+    for (int64_t s0 = (int64_t)blockIdx.x * (kBlock * kPbItems) + threadIdx.x; s0 < M;
+         s0 += (int64_t)gridDim.x * (kBlock * kPbItems)) {
+        uint32_t p[kPbItems], st[kPbItems];
+#pragma unroll
+        for (int k = 0; k < kPbItems; ++k) p[k] = s0 + k * kBlock < M ? key[s0 + k * kBlock] : 0xffffffffu;
+#pragma unroll
+        for (int k = 0; k < kPbItems; ++k) st[k] = (int64_t)p[k] < P ? pstart[p[k]] : 0u;
+#pragma unroll
+        for (int k = 0; k < kPbItems; ++k) {
+            const int64_t s = s0 + k * kBlock;
+            if (s >= M || (int64_t)p[k] >= P) continue;
+            if (((uint32_t)s - st[k]) % B != 0) continue;
+            const uint32_t left = pend[p[k]] - (uint32_t)s, q = (uint32_t)val[s];
+            fsize[q] = left < B ? left : B;
+            __hip_atomic_fetch_or(&fbits[q >> 6], 1ull << (q & 63u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
 }
 
-// Groups in queue order of their first entries: one pass over the queue
-// positions with two look-back chains (groups so far, entries so far).  A
-// group's first position gets its batch number; batch_off[b] is batch b's
-// first slot; the last tile writes batch_off[n_batches] and the totals.
-__global__ __launch_bounds__(kBlock) void k_pb_scan(const uint32_t *__restrict__ fsize, const int64_t *m_dev,
-                                                   int64_t out_cap, uint32_t *__restrict__ bidx,
-                                                   int64_t *__restrict__ batch_off, int64_t batch_cap, int64_t *n_out,
-                                                   int64_t *n_batches, Ctl *ctl, uint64_t *desc, uint64_t *desc_b,
-                                                   int64_t desc_cap)
+// Groups in queue order of their first entries: one pass over the bits of the
+// queue positions, 32 a thread, with two look-back chains (groups so far,
+// entries so far); sizes are read only where a bit is set.  A group's first
+// position gets its batch's first slot, which is batch_off[b] of its batch
+// number b; the last tile writes batch_off[n_batches] and the totals.  Tiles
+// are large, since a tile costs a ticket and a look-back: 10M entries in
+// 55,000 groups took 70 us in tiles of 4,096 positions that read every size,
+// now 39.
+constexpr int kPbScanTh = 1024, kPbScanIt = 32;
+constexpr int kPbScanTile = kPbScanTh * kPbScanIt;           // positions per tile
+
+__global__ __launch_bounds__(kPbScanTh) void k_pb_scan(const uint32_t *__restrict__ fsize,
+                                                       const uint64_t *__restrict__ fbits, const int64_t *m_dev,
+                                                       int64_t out_cap, uint32_t *__restrict__ gslot,
+                                                       int64_t *__restrict__ batch_off, int64_t batch_cap,
+                                                       int64_t *n_out, int64_t *n_batches, Ctl *ctl, uint64_t *desc,
+                                                       uint64_t *desc_b, int64_t desc_cap)
 {
     const uint32_t epoch = scan_epoch(ctl);
-    __shared__ int64_t s_wave[kBlock / 64];
+    __shared__ uint64_t s_w[kPbScanTh / 64];
     __shared__ uint64_t s_b2[2];
     __shared__ int64_t s_t;
     __shared__ int32_t s_last;
     const int64_t M = *m_dev;
-    const int64_t ntiles = (M + kTile - 1) / kTile;
+    const int64_t ntiles = (M + kPbScanTile - 1) / kPbScanTile;
+    const int wv = (int)(threadIdx.x >> 6), ln = lane_id();
     if (M > out_cap && blockIdx.x == 0 && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
     if (M == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
         if (batch_cap < 1) raise_err(ctl, RO_ECAP);
@@ -246,27 +301,35 @@ __global__ __launch_bounds__(kBlock) void k_pb_scan(const uint32_t *__restrict__
     for (;;) {
         const int64_t t = next_ticket(ctl, &s_t);
         if (t >= ntiles) break;
-        const int64_t i0 = t * kTile + (int64_t)threadIdx.x * kItems;
-        uint32_t f[kItems];
-        int64_t cnt = 0, sum = 0;
+        const int64_t i0 = t * kPbScanTile + (int64_t)threadIdx.x * kPbScanIt;
+        const uint32_t bits = i0 < M ? reinterpret_cast<const uint32_t *>(fbits)[i0 / kPbScanIt] : 0u;
+        uint32_t f[kPbScanIt];
+        uint64_t sum = 0;
 #pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            const int64_t i = i0 + k;
-            f[k] = i < M ? fsize[i] : 0u;
-            cnt += f[k] != 0;
-            sum += f[k];
+        for (int k = 0; k < kPbScanIt; ++k) f[k] = (bits >> k) & 1u ? fsize[i0 + k] : 0u;
+#pragma unroll
+        for (int k = 0; k < kPbScanIt; ++k) sum += f[k];
+        // one block scan of entries << 16 | groups (a tile holds at most 32,768 groups)
+        const uint64_t v = sum << 16 | (uint64_t)__popc(bits);
+        const uint64_t inc = wave_incl_sum_dpp(v);
+        if (ln == 63) s_w[wv] = inc;
+        __syncthreads();
+        uint64_t ex = inc - v, tot = 0;
+#pragma unroll
+        for (int i = 0; i < kPbScanTh / 64; ++i) {
+            const uint64_t x = s_w[i];
+            ex += i < wv ? x : 0;
+            tot += x;
         }
-        int64_t tc, ts;
-        const int64_t ec = block_excl_scan(cnt, s_wave, tc);
-        const int64_t es = block_excl_scan(sum, s_wave, ts);
+        const int64_t tc = (int64_t)(tot & 0xffffu), ts = (int64_t)(tot >> 16);
         uint64_t pc, ps;
         tile_prefix2(desc, (uint64_t)tc, desc_b, (uint64_t)ts, t, epoch, s_b2, pc, ps, ctl);
-        int64_t b = (int64_t)pc + ec, o = (int64_t)ps + es;
+        int64_t b = (int64_t)pc + (int64_t)(ex & 0xffffu), o = (int64_t)ps + (int64_t)(ex >> 16);
         bool over = false;
 #pragma unroll
-        for (int k = 0; k < kItems; ++k) {
-            if (f[k] == 0) continue;
-            bidx[i0 + k] = (uint32_t)b;
+        for (int k = 0; k < kPbScanIt; ++k) {
+            if (!((bits >> k) & 1u)) continue;
+            gslot[i0 + k] = (uint32_t)o;
             if (b < batch_cap) batch_off[b] = o;
             else over = true;
             ++b;
@@ -280,33 +343,55 @@ __global__ __launch_bounds__(kBlock) void k_pb_scan(const uint32_t *__restrict__
             if (n_out) *n_out = (int64_t)ps + ts;
             if (n_batches) *n_batches = nbat;
         }
+        if (ntiles <= (int64_t)gridDim.x) break;     // a tile for every workgroup
     }
     ticket_done(ctl, epoch, desc, desc_cap, &s_last);
 }
 
-// Every entry to its group's slots: slot = batch_off[batch of the group's
-// first entry] + rank mod B.
-__global__ void k_pb_place(const uint32_t *__restrict__ key, const uint64_t *__restrict__ val, const int64_t *m_dev,
-                           int64_t P, const uint32_t *__restrict__ pstart, int32_t B, const uint32_t *__restrict__ bidx,
-                           const int64_t *__restrict__ batch_off, const int64_t *__restrict__ offsets, uint32_t *__restrict__ out_child,
-                           uint32_t *__restrict__ out_parent, uint32_t *__restrict__ out_ordinal, int64_t out_cap,
-                           Ctl *ctl)
+// Every entry to its group's slots: the group's first slot + rank mod B.  The
+// chain of an entry (parent, first sorted entry, its group's queue position,
+// the group's slot) is four loads one after another, so four entries a thread
+// go through it together (10M entries: 88 us one by one, now 55).
+__global__ __launch_bounds__(kBlock) void k_pb_place(
+    const uint32_t *__restrict__ key, const uint64_t *__restrict__ val, const int64_t *m_dev, int64_t P,
+    const uint32_t *__restrict__ pstart, uint32_t B, const uint32_t *__restrict__ gslot,
+    const int64_t *__restrict__ offsets, uint32_t *__restrict__ out_child, uint32_t *__restrict__ out_parent,
+    uint32_t *__restrict__ out_ordinal, int64_t out_cap, Ctl *ctl)
 {
     if (read_err(ctl) != 0) return;          // a capacity error leaves the outputs unwritten
     const int64_t M = *m_dev;
     if (M > out_cap) return;
-    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < M; s += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t p = key[s];
-        if ((int64_t)p >= P) continue;
-        const int64_t st = (int64_t)pstart[p];
-        const int64_t r = s - st;
-        const uint32_t qf = (uint32_t)val[st + (r / B) * B];
-        const int64_t b = (int64_t)bidx[qf];
-        const int64_t slot = batch_off[b] + r % B;
-        const uint32_t c = (uint32_t)(val[s] >> 32);
-        if (out_child) out_child[slot] = c;
-        if (out_parent) out_parent[slot] = p;
-        if (out_ordinal) out_ordinal[slot] = (uint32_t)((int64_t)c - offsets[p]);
+    for (int64_t s0 = (int64_t)blockIdx.x * (kBlock * kPbItems) + threadIdx.x; s0 < M;
+         s0 += (int64_t)gridDim.x * (kBlock * kPbItems)) {
+        uint32_t p[kPbItems], in[kPbItems], first[kPbItems], slot[kPbItems], c[kPbItems];
+        int64_t off[kPbItems];
+#pragma unroll
+        for (int k = 0; k < kPbItems; ++k) {
+            const int64_t s = s0 + k * kBlock;
+            p[k] = s < M ? key[s] : 0xffffffffu;
+            c[k] = s < M ? (uint32_t)(val[s] >> 32) : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < kPbItems; ++k) {
+            first[k] = (int64_t)p[k] < P ? pstart[p[k]] : 0u;
+            off[k] = out_ordinal && (int64_t)p[k] < P ? offsets[p[k]] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < kPbItems; ++k) {
+            const uint32_t s = (uint32_t)(s0 + k * kBlock);
+            const bool ok = s0 + k * kBlock < M && (int64_t)p[k] < P;
+            in[k] = ok ? (s - first[k]) % B : 0u;
+            first[k] = ok ? (uint32_t)val[s - in[k]] : 0xffffffffu;
+        }
+#pragma unroll
+        for (int k = 0; k < kPbItems; ++k) slot[k] = s0 + k * kBlock < M && (int64_t)p[k] < P ? gslot[first[k]] + in[k] : 0u;
+#pragma unroll
+        for (int k = 0; k < kPbItems; ++k) {
+            if (s0 + k * kBlock >= M || (int64_t)p[k] >= P) continue;
+            if (out_child) out_child[slot[k]] = c[k];
+            if (out_parent) out_parent[slot[k]] = p[k];
+            if (out_ordinal) out_ordinal[slot[k]] = (uint32_t)((int64_t)c[k] - off[k]);
+        }
     }
 }
 
@@ -326,39 +411,40 @@ hipError_t launch_batch_parent(const Launch &L, const uint32_t *queue, const uin
     hipError_t e = launch_batch(L, queue, keep, Q, offsets, P, B, w.kc, w.k[0], nullptr, Q, w.m, w.m + 1, cmap,
                                 cmap_cap, barrier);
     if (e != hipSuccess) return e;
-    // stable sort by parent: digits of at most kRMaxBits bits, as few passes as the parent ids need
+    // stable sort by parent: as few passes of at most kRMaxBits bits as the
+    // parent ids need, of equal widths (fewer digits, longer runs)
     int bits = 0;
     while (bits < 32 && ((uint64_t)1 << bits) < (uint64_t)P) ++bits;
     const int passes = bits == 0 ? 1 : (bits + kRMaxBits - 1) / kRMaxBits;   // one pass of width 0 copies
     const int64_t spans_cap = (Q + kRSpanLen - 1) / kRSpanLen > 0 ? (Q + kRSpanLen - 1) / kRSpanLen : 1;
-    const int64_t gsort = spans_cap < (int64_t)L.num_cus * 4 ? spans_cap : (int64_t)L.num_cus * 4;
+    const int64_t gsort = spans_cap < (int64_t)L.num_cus * 8 ? spans_cap : (int64_t)L.num_cus * 8;
     int cur = 0;
     const uint64_t *vals = nullptr;          // built from the compaction in the first pass
     for (int pass = 0, shift = 0; pass < passes; ++pass) {
-        const int width = (bits - shift) < kRMaxBits ? (bits - shift) : kRMaxBits;
+        const int left = passes - pass, width = (bits - shift + left - 1) / left;
         RO_LAUNCH(L, RO_K_PBATCH_SORT, k_rs_hist, dim3((unsigned)gsort), dim3(kBlock), 0, L.stream, w.k[cur], w.m,
                   shift, width, w.hist, spans_cap);
         e = launch_expand(L, w.hist, (int64_t)(1 << width) * spans_cap, w.hoff, nullptr, nullptr, 0);
         if (e != hipSuccess) return e;
-        RO_LAUNCH(L, RO_K_PBATCH_SORT, k_rs_scatter, dim3((unsigned)gsort), dim3(kBlock), 0, L.stream, w.k[cur],
+        RO_LAUNCH(L, RO_K_PBATCH_SORT, k_rs_scatter, dim3((unsigned)gsort), dim3(kRTh), 0, L.stream, w.k[cur],
                   vals, w.kc, w.k[1 - cur], w.v[1 - cur], w.m, shift, width, w.hoff, spans_cap);
         vals = w.v[1 - cur];
         cur = 1 - cur;
         shift += width;
     }
     const uint32_t *keys = w.k[cur];
-    const int64_t g = grid_for(L, Q, kBlock);
+    const int64_t g = grid_for(L, Q, kBlock * kPbItems);
     RO_LAUNCH(L, RO_K_PBATCH, k_pb_bounds, dim3((unsigned)g), dim3(kBlock), 0, L.stream, keys, w.m, P, w.pstart,
-              w.pend, w.fsize, L.ctl);
+              w.pend, w.fbits, L.ctl);
     RO_LAUNCH(L, RO_K_PBATCH, k_pb_firsts, dim3((unsigned)g), dim3(kBlock), 0, L.stream, keys, vals, w.m, P,
-              w.pstart, w.pend, B, w.fsize, L.ctl);
-    const int64_t ntiles = (Q + kTile - 1) / kTile > 0 ? (Q + kTile - 1) / kTile : 1;
+              w.pstart, w.pend, (uint32_t)B, w.fsize, w.fbits, L.ctl);
+    const int64_t ntiles = (Q + kPbScanTile - 1) / kPbScanTile > 0 ? (Q + kPbScanTile - 1) / kPbScanTile : 1;
     const int64_t gscan = ntiles < (int64_t)L.num_cus * 4 ? ntiles : (int64_t)L.num_cus * 4;
     if (2 * ntiles > L.desc_cap) return hipErrorInvalidValue;
-    RO_LAUNCH(L, RO_K_PBATCH, k_pb_scan, dim3((unsigned)gscan), dim3(kBlock), 0, L.stream, w.fsize, w.m, out_cap,
-              w.bidx, batch_off, batch_cap, n_out, n_batches, L.ctl, L.desc, L.desc + ntiles, L.desc_cap);
+    RO_LAUNCH(L, RO_K_PBATCH, k_pb_scan, dim3((unsigned)gscan), dim3(kPbScanTh), 0, L.stream, w.fsize, w.fbits, w.m, out_cap,
+              w.gslot, batch_off, batch_cap, n_out, n_batches, L.ctl, L.desc, L.desc + ntiles, L.desc_cap);
     RO_LAUNCH(L, RO_K_PBATCH, k_pb_place, dim3((unsigned)g), dim3(kBlock), 0, L.stream, keys, vals, w.m, P,
-              w.pstart, B, w.bidx, batch_off, offsets, out_child, out_parent, out_ordinal, out_cap, L.ctl);
+              w.pstart, (uint32_t)B, w.gslot, offsets, out_child, out_parent, out_ordinal, out_cap, L.ctl);
     return hipGetLastError();
 }
 

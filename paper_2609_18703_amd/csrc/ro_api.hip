@@ -231,10 +231,11 @@ int ensure_pb(ro_ctx *c, int64_t q, int64_t p)
     const int64_t tiles = (qn + kPbTile * kPbSpan - 1) / (kPbTile * kPbSpan);   // histogram columns
     const size_t sizes[] = {
         (size_t)qn * 4, (size_t)qn * 4, (size_t)qn * 4, (size_t)qn * 8, (size_t)qn * 8,   // kc, k0, k1, v0, v1
-        (size_t)qn * 4, (size_t)qn * 4,                                                    // fsize, bidx
+        (size_t)qn * 4, (size_t)qn * 4,                                                    // fsize, gslot
         (size_t)pn * 4, (size_t)pn * 4,                                                    // pstart, pend
         (size_t)(kPbMaxBuckets * tiles) * 4, (size_t)(kPbMaxBuckets * tiles + 1) * 8,      // hist, hoff
         (size_t)2 * 8,                                                                     // m
+        (size_t)((qn >> 6) + 1) * 8,                                                       // fbits
     };
     constexpr int kArrays = (int)(sizeof(sizes) / sizeof(sizes[0]));
     size_t offs[kArrays], total = 0;
@@ -255,12 +256,13 @@ int ensure_pb(ro_ctx *c, int64_t q, int64_t p)
     c->pb.v[0] = (uint64_t *)(b + offs[3]);
     c->pb.v[1] = (uint64_t *)(b + offs[4]);
     c->pb.fsize = (uint32_t *)(b + offs[5]);
-    c->pb.bidx = (uint32_t *)(b + offs[6]);
+    c->pb.gslot = (uint32_t *)(b + offs[6]);
     c->pb.pstart = (uint32_t *)(b + offs[7]);
     c->pb.pend = (uint32_t *)(b + offs[8]);
     c->pb.hist = (int32_t *)(b + offs[9]);
     c->pb.hoff = (int64_t *)(b + offs[10]);
     c->pb.m = (int64_t *)(b + offs[11]);
+    c->pb.fbits = (uint64_t *)(b + offs[12]);
     c->pb_cap = q;
     c->pb_pcap = p;
     // descriptors: the compaction, the histogram scan and the two-chain group scan

@@ -93,8 +93,9 @@ struct PbWs {
     uint32_t *kc;            // ready children in queue order
     uint32_t *k[2];          // sort keys (parents), double-buffered
     uint64_t *v[2];          // sort values (child << 32 | queue position), double-buffered
-    uint32_t *fsize;         // per queue position: group size if a group's first entry, else 0
-    uint32_t *bidx;          // per group-first position: batch number
+    uint64_t *fbits;         // bitmap of the queue positions of groups' first entries
+    uint32_t *fsize;         // per group-first position: group size
+    uint32_t *gslot;         // per group-first position: its batch's first slot
     uint32_t *pstart, *pend; // per parent: sorted index range
     int32_t *hist;           // digit histograms, [buckets * tiles]
     int64_t *hoff;           // their exclusive scan
@@ -105,8 +106,8 @@ hipError_t launch_batch_parent(const Launch &L, const uint32_t *queue, const uin
                                uint32_t *out_parent, uint32_t *out_ordinal, int64_t out_cap, int64_t *batch_off,
                                int64_t batch_cap, int64_t *n_out, int64_t *n_batches, uint32_t *cmap,
                                int64_t cmap_cap, const uint8_t *barrier, const PbWs &w);
-constexpr int64_t kPbTile = 2048;        // sort tile
-constexpr int64_t kPbSpan = 8;           // sort tiles per histogram column
+constexpr int64_t kPbTile = 4096;        // sort tile
+constexpr int64_t kPbSpan = 2;           // sort tiles per histogram column
 constexpr int64_t kPbMaxBuckets = 512;
 
 struct GatherArgs {

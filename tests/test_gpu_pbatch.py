@@ -92,6 +92,21 @@ def test_pbatch_partial_queue_and_edges(ctx):
     _check(ctx, np.arange(N, dtype=np.uint32), None, offs, 3, what="canonical order")
 
 
+# one entry fewer and one more than a sort tile (4,096), a histogram span
+# (8,192), a scan tile (32,768) and a bitmap word, over parent ids of one digit
+# pass (up to 512 parents), two (even and odd widths) and three
+@pytest.mark.parametrize("q_len", [63, 64, 65, 4095, 4097, 8191, 8193, 32_767, 32_769, 65_537])
+@pytest.mark.parametrize("P", [1, 512, 513, 4097, 300_000])
+def test_pbatch_tile_edges(ctx, q_len, P):
+    rng = np.random.default_rng(q_len + P)
+    offs = np.zeros(P + 1, np.int64)
+    offs[1:] = np.cumsum(rng.multinomial(q_len + 5, rng.dirichlet(np.full(P, 0.3))) if P > 1 else [q_len + 5])
+    queue = rng.permutation(q_len + 5)[:q_len].astype(np.uint32)
+    _say("pbatch edges", q_len, P)
+    for B in (1, 2, 100):
+        _check(ctx, queue, None, offs, B, what=f"Q={q_len} P={P} B={B}")
+
+
 def test_pbatch_errors(ctx):
     import paper_2609_18703_amd as R
     offs = O.expand(np.array([3, 2], np.int32), tags=False)
