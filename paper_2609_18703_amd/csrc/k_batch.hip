@@ -526,23 +526,22 @@ __global__ __launch_bounds__(kBlock) void k_batch(
 
 // The ready queue with a dispatch mask and no barrier: an entry is ready iff
 // its mask byte is set, so a tile's count of ready entries is known from the
-// mask alone, before any lineage lookup.  A workgroup takes kSup consecutive
-// tiles per ticket, counts them, publishes their aggregate and finishes the
-// look-back first; only then does it look up the tags of each tile's ready
-// entries and write them, staged in LDS, to the tile's contiguous slot range.
-template <int kMap, int kIt, int kSup>
+// mask alone, before any lineage lookup.  A workgroup counts its tile, posts
+// the count and finishes the look-back first; only then does it look up the
+// tags of the ready entries and write them, staged in LDS, to the tile's
+// contiguous slot range.
+template <int kMap, int kIt>
 __global__ __launch_bounds__(kBlock) void k_batch_keep(
     const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
     const int64_t *__restrict__ offsets, int64_t P, MapArgs map, int32_t B,
     uint32_t *__restrict__ out_child, uint32_t *__restrict__ out_parent, uint32_t *__restrict__ out_ordinal,
     int64_t out_cap, int64_t *n_out, int64_t *n_batches, Ctl *ctl, uint64_t *desc, int64_t desc_cap,
-    int64_t nsuper, int vec_ok)
+    int64_t ntiles, int vec_ok)
 {
     constexpr int kT = kBlock * kIt;
     const uint32_t epoch = scan_epoch(ctl);
     __shared__ uint32_t s_out[kT];
     __shared__ int64_t s_wave[kBlock / 64];
-    __shared__ int64_t s_sub[kSup];
     __shared__ uint64_t s_b;
     __shared__ int64_t s_t;
     __shared__ int32_t s_last;
@@ -550,60 +549,140 @@ __global__ __launch_bounds__(kBlock) void k_batch_keep(
     const int sh = map_shift(N, P);
     const int64_t nmap = map_entries<kMap>(map, N, sh);
     const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
-    const bool nt = Q > kTagNtEntries;
-    const bool single = nsuper == 1;
+    const bool single = ntiles == 1;
     for (;;) {
         const int64_t t = single ? 0 : next_ticket(ctl, &s_t);
-        if (t >= nsuper) break;
-        // ready flags of the super-tile's entries: bit k of km[s] is entry
-        // (tile s, this thread, item k)
-        uint32_t km[kSup];
-#pragma unroll
-        for (int s = 0; s < kSup; ++s)
-            km[s] = load_mask<kIt>(keep, (t * kSup + s) * kT + (int64_t)threadIdx.x * kIt, Q, vec_ok);
-        int64_t ex[kSup];
-        int64_t agg = 0;
-#pragma unroll
-        for (int s = 0; s < kSup; ++s) {
-            int64_t tot;
-            ex[s] = block_excl_scan(__popc(km[s]), s_wave, tot);
-            if (threadIdx.x == 0) s_sub[s] = agg;
-            agg += tot;
-        }
-        const int64_t pre = single ? 0 : (int64_t)tile_prefix(desc, t, epoch, (uint64_t)agg, &s_b, ctl);
-        if (single) __syncthreads();           // s_sub
-        if (pre + agg > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
+        if (t >= ntiles) break;
+        const int64_t i0 = t * kT + (int64_t)threadIdx.x * kIt;
+        const uint32_t km = load_mask<kIt>(keep, i0, Q, vec_ok);
+        int64_t tot;
+        const int64_t ex = block_excl_scan(__popc(km), s_wave, tot);
+        const int64_t base = single ? 0 : (int64_t)tile_prefix(desc, t, epoch, (uint64_t)tot, &s_b, ctl);
+        if (base + tot > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
+        uint32_t q[kIt], par[kIt], ord[kIt];
+        load_queue<kIt>(queue, i0, Q, vec_ok, q);
         bool bad_range = false;
-#pragma unroll 1
-        for (int s = 0; s < kSup; ++s) {
-            uint32_t q[kIt], par[kIt], ord[kIt];
-            load_queue<kIt>(queue, (t * kSup + s) * kT + (int64_t)threadIdx.x * kIt, Q, vec_ok, q);
-            uint32_t live = 0;
+        uint32_t live = 0;
 #pragma unroll
-            for (int k = 0; k < kIt; ++k) {
-                par[k] = 0xffffffffu;
-                ord[k] = 0xffffffffu;
-                if (km[s] & (1u << k)) {
-                    if ((int64_t)q[k] >= N) bad_range = true;
-                    else live |= 1u << k;
-                }
+        for (int k = 0; k < kIt; ++k) {
+            par[k] = 0xffffffffu;
+            ord[k] = 0xffffffffu;
+            if (km & (1u << k)) {
+                if ((int64_t)q[k] >= N) bad_range = true;
+                else live |= 1u << k;
             }
-            if (want_tags) thread_tags<kMap, kIt>(map, nmap, sh, offsets, P, q, live, par, ord);
-            const int64_t base = pre + s_sub[s];
-            const int64_t cnt_s = (s + 1 < kSup ? s_sub[s + 1] : agg) - s_sub[s];
-            write_slots<kIt>(out_child, out_parent, out_ordinal, q, par, ord, km[s], (int)ex[s], base,
-                             slot_room(out_cap, base, cnt_s), s_out, nt);
         }
+        if (want_tags) thread_tags<kMap, kIt>(map, nmap, sh, offsets, P, q, live, par, ord);
+        write_slots<kIt>(out_child, out_parent, out_ordinal, q, par, ord, km, (int)ex, base,
+                         slot_room(out_cap, base, tot), s_out, false);
         if (bad_range) raise_err(ctl, RO_ERANGE);
-        if (t == nsuper - 1 && threadIdx.x == 0) {
-            const int64_t m = pre + agg;
+        if (t == ntiles - 1 && threadIdx.x == 0) {
+            const int64_t m = base + tot;
             if (n_out) *n_out = m;
             if (n_batches) *n_batches = (m + B - 1) / B;
         }
         if (single) return;
-        if (nsuper <= (int64_t)gridDim.x) break;       // a tile for every workgroup
+        if (ntiles <= (int64_t)gridDim.x) break;       // a tile for every workgroup
     }
     ticket_done(ctl, epoch, desc, desc_cap, &s_last);
+}
+
+// A long queue with a dispatch mask: counted first, then filled with no order
+// between the workgroups.  Tickets and look-back hand on about one tile per
+// 100 ns however many wait, so a queue of 10M entries took 81 us in 610 tiles
+// (two or three workgroups per CU) and 154 in 2,441; reading the mask twice
+// costs less.  k_batch_count: a wave counts the ready entries of a tile of
+// 4,096, a workgroup 16 tiles, and writes each tile's place in its group and
+// the group's total; k_batch_fill: a tile per workgroup adds up the totals of
+// the groups before its own.
+// The counts use the look-back descriptors' room (epoch field 0, which no
+// look-back takes for its own).
+constexpr int kFillIt = 16, kFillTile = kBlock * kFillIt, kCountGrp = 16;
+
+__device__ __forceinline__ uint32_t nonzero_bytes(uint32_t x)
+{
+    return (uint32_t)__popc((x | ((x & 0x7f7f7f7fu) + 0x7f7f7f7fu)) & 0x80808080u);
+}
+
+__global__ __launch_bounds__(64 * kCountGrp) void k_batch_count(const uint8_t *__restrict__ keep, int64_t Q,
+                                                                uint64_t *__restrict__ tile_at,
+                                                                uint64_t *__restrict__ group_n, int vec_ok)
+{
+    __shared__ uint32_t s_c[kCountGrp];
+    const int wv = uni32((int)(threadIdx.x >> 6)), ln = lane_id();
+    const int64_t t = (int64_t)blockIdx.x * kCountGrp + wv, i0 = t * kFillTile;
+    uint32_t c = 0;
+    if (vec_ok && i0 + kFillTile <= Q) {
+        const uint4 *k4 = reinterpret_cast<const uint4 *>(keep + i0);
+        uint4 x[kFillTile / 1024];
+#pragma unroll
+        for (int k = 0; k < kFillTile / 1024; ++k) x[k] = k4[k * 64 + ln];
+#pragma unroll
+        for (int k = 0; k < kFillTile / 1024; ++k)
+            c += nonzero_bytes(x[k].x) + nonzero_bytes(x[k].y) + nonzero_bytes(x[k].z) + nonzero_bytes(x[k].w);
+    } else {
+        for (int k = ln; k < kFillTile; k += 64) c += i0 + k < Q && keep[i0 + k] != 0;
+    }
+    c = wave_sum(c);
+    if (ln == 0) s_c[wv] = c;
+    __syncthreads();
+    if (threadIdx.x < kCountGrp) {
+        uint32_t at = 0, all = 0;
+#pragma unroll
+        for (int k = 0; k < kCountGrp; ++k) {
+            at += k < (int)threadIdx.x ? s_c[k] : 0u;
+            all += s_c[k];
+        }
+        if (((int64_t)blockIdx.x * kCountGrp + threadIdx.x) * kFillTile < Q)
+            tile_at[(int64_t)blockIdx.x * kCountGrp + threadIdx.x] = at;
+        if (threadIdx.x == 0) group_n[blockIdx.x] = all;
+    }
+}
+
+template <int kMap>
+__global__ __launch_bounds__(kBlock) void k_batch_fill(
+    const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
+    const int64_t *__restrict__ offsets, int64_t P, MapArgs map, int32_t B, uint32_t *__restrict__ out_child,
+    uint32_t *__restrict__ out_parent, uint32_t *__restrict__ out_ordinal, int64_t out_cap, int64_t *n_out,
+    int64_t *n_batches, const uint64_t *__restrict__ tile_at, const uint64_t *__restrict__ group_n, Ctl *ctl,
+    int vec_ok)
+{
+    __shared__ uint32_t s_out[kFillTile];
+    __shared__ int64_t s_wave[kBlock / 64];
+    const int64_t N = offsets[P];
+    const int sh = map_shift(N, P);
+    const int64_t nmap = map_entries<kMap>(map, N, sh);
+    const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
+    const bool nt = Q > kTagNtEntries;
+    const int64_t t = blockIdx.x, i0 = t * kFillTile + (int64_t)threadIdx.x * kFillIt;
+    const uint32_t km = load_mask<kFillIt>(keep, i0, Q, vec_ok);
+    uint32_t q[kFillIt], par[kFillIt], ord[kFillIt];
+    load_queue<kFillIt>(queue, i0, Q, vec_ok, q);
+    int64_t before = threadIdx.x == 0 ? (int64_t)tile_at[t] : 0;
+    for (int64_t g = threadIdx.x; g < t / kCountGrp; g += kBlock) before += (int64_t)group_n[g];
+    bool bad_range = false;
+    uint32_t live = 0;
+#pragma unroll
+    for (int k = 0; k < kFillIt; ++k) {
+        par[k] = 0xffffffffu;
+        ord[k] = 0xffffffffu;
+        if (km & (1u << k)) {
+            if ((int64_t)q[k] >= N) bad_range = true;
+            else live |= 1u << k;
+        }
+    }
+    if (want_tags) thread_tags<kMap, kFillIt>(map, nmap, sh, offsets, P, q, live, par, ord);
+    if (bad_range) raise_err(ctl, RO_ERANGE);
+    const int64_t base = block_sum(before, s_wave);
+    int64_t tot;
+    const int64_t ex = block_excl_scan(__popc(km), s_wave, tot);
+    if (base + tot > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
+    write_slots<kFillIt>(out_child, out_parent, out_ordinal, q, par, ord, km, (int)ex, base,
+                         slot_room(out_cap, base, tot), s_out, nt);
+    if (t == gridDim.x - 1 && threadIdx.x == 0) {
+        if (n_out) *n_out = base + tot;
+        if (n_batches) *n_batches = (base + tot + B - 1) / B;
+    }
 }
 
 // Every queue entry is ready (no mask): the FIFO compaction is the identity,
@@ -668,8 +747,11 @@ __global__ __launch_bounds__(kBlock) void k_batch_all(
 //   57 as 6 of those);
 //   up to kMidQueue into tiles of 4,096 (1M entries: 29 us; 57 in 980 tiles of
 //   1,024, whose tickets and look-backs queue up; 66 in 61 of 16,384, too few
-//   for 256 CUs);
-//   beyond, four tiles of 4,096 per ticket (8M entries: 91 us, 107 one by one).
+//   for 256 CUs); with a barrier this is the largest tile, since the tags come
+//   before the count;
+//   beyond, a masked queue is counted first and needs no order between its
+//   tiles (4M entries: 28 us in all, 40 with four tiles of 4,096 per ticket; 10M:
+//   73 and 81; 41M: 380 and 431).
 constexpr int64_t kDirectQueue = 65536, kSmallQueue = 262144, kMidQueue = 1 << 20;
 
 template <int kMap>
@@ -690,13 +772,22 @@ hipError_t launch_batch_with(const Launch &L, const uint32_t *queue, const uint8
     auto tiles = [&](int64_t per) { return Q > 0 ? (Q + per - 1) / per : 1; };
     if (barrier == nullptr && kMap != kMapChild) {
         if constexpr (kMap != kMapChild) {
-            const int64_t per = Q <= kSmallQueue ? kBlock * 4 : (Q <= kMidQueue ? kBlock * 16 : kBlock * 64);
-            auto kern = Q <= kSmallQueue ? k_batch_keep<kMap, 4, 1>
-                                        : (Q <= kMidQueue ? k_batch_keep<kMap, 16, 1> : k_batch_keep<kMap, 16, 4>);
-            const int64_t nsuper = tiles(per), grid = nsuper < cap_grid ? nsuper : cap_grid;
+            if (Q > kMidQueue) {
+                const int64_t nt = tiles(kFillTile), ng = (nt + kCountGrp - 1) / kCountGrp;
+                if (nt + ng > L.desc_cap || nt > 0x7fffffff) return hipErrorInvalidValue;
+                RO_LAUNCH(L, RO_K_BATCH, k_batch_count, dim3((unsigned)ng), dim3(64 * kCountGrp), 0, L.stream, keep, Q,
+                          L.desc, L.desc + nt, aligned ? 1 : 0);
+                RO_LAUNCH(L, RO_K_BATCH, k_batch_fill<kMap>, dim3((unsigned)nt), dim3(kBlock), 0, L.stream, queue, keep, Q,
+                          offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.desc,
+                          L.desc + nt, L.ctl, aligned ? 1 : 0);
+                return hipGetLastError();
+            }
+            const bool small = Q <= kSmallQueue;
+            auto kern = small ? k_batch_keep<kMap, 4> : k_batch_keep<kMap, 16>;
+            const int64_t ntiles = tiles(small ? kBlock * 4 : kBlock * 16), grid = ntiles < cap_grid ? ntiles : cap_grid;
             RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P,
                       map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.ctl, L.desc, L.desc_cap,
-                      nsuper, aligned ? 1 : 0);
+                      ntiles, aligned ? 1 : 0);
         }
         return hipGetLastError();
     }

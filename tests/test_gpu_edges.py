@@ -134,7 +134,7 @@ def _batch_case(ctx, counts, queue, keep, barrier, B):
 
 
 # queue sizes on both sides of every path (offsets searched, tiles of 1,024,
-# tiles of 4,096, four tiles per ticket); the reservation decides between the
+# tiles of 4,096, counted first); the reservation decides between the
 # map of 64-child masks and the coarse one, or leaves children past the map
 @pytest.mark.parametrize("q_len", [1023, 65_536, 65_537, 262_144, 262_145, 1_048_576, 1_048_577])
 @pytest.mark.parametrize("reserve", [1000, 1 << 21, 13 << 20])
@@ -156,6 +156,33 @@ def test_batch_paths(q_len, reserve):
         _say("batch paths", q_len, reserve, k is not None, bar is not None)
         _batch_case(c, counts, queue, k, bar, 256)
     c.close()
+
+
+# counted queues: one tile past a group of 16 tiles, a ragged tail, arrays off
+# their 16-byte alignment, mask bytes other than 1, room for a part only
+@pytest.mark.parametrize("q_len", [(1 << 20) + 1, (1 << 20) + 65_536, (1 << 20) + 3 * 65_536 + 4095])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_batch_counted(ctx, q_len, shift):
+    import paper_2609_18703_amd as R
+    rng = np.random.default_rng(q_len)
+    offs = O.expand(np.array([3, 0, q_len - 1000, 997], np.int32), tags=False)
+    queue = rng.permutation(q_len).astype(np.uint32)
+    keep = rng.choice(np.array([0, 1, 0x7f, 0x80, 0xff], np.uint8), q_len)
+    keep[4096:8192] = 0
+    _say("batch counted", q_len, shift)
+    want = O.batch(queue, keep, offs, 48)
+    m = len(want[0])
+    q = _i32(np.concatenate([np.zeros(shift, np.uint32), queue]))[shift:]
+    k = D.to_dev(np.concatenate([np.zeros(shift, np.uint8), keep]))[shift:]
+    for cap in (m, m - 1):
+        outs = [torch.full((m + 8 + shift,), -1, dtype=torch.int32, device="cuda")[shift:] for _ in range(3)]
+        sc = _zeros(2, torch.int64)
+        ctx.batch(q, k, D.to_dev(offs), 48, *outs, sc[0:1], sc[1:2], q_len=q_len, out_cap=cap)
+        assert ctx.status() == (R.OK if cap == m else R.ECAP)
+        assert sc.tolist() == [m, len(want[3])]
+        for t, w in zip(outs, want[:3]):
+            h = t.cpu().numpy().view(np.uint32)
+            assert np.array_equal(h[:cap], w[:cap]) and (h[cap:] == 0xffffffff).all()
 
 
 def test_stream_word_and_tile_edges(ctx):
