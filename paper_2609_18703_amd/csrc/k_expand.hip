@@ -143,12 +143,105 @@ __global__ __launch_bounds__(kBlock) void k_expand_tags(const int64_t *__restric
     }
 }
 
+// Offsets and lineage keys of up to 4,096 parents (one scan tile) in one
+// launch: every workgroup scans the counts for itself and keeps the offsets in
+// LDS for its searches; the first one writes them.  What bounds a small
+// expansion is the launches and the chain of searches through memory (1,000
+// parents, 7,389 children: 5.7 and 8.9 us as two launches, now 5.9; 2,431
+// parents, 1M children: 7.6 and 10.1, now 11.6), so a thread takes four children
+// only (16, staged in LDS: 9.6 and 10.7).  LDS holds 32 bits per offset: more
+// children than that are an error and get no keys.
+__global__ __launch_bounds__(kBlock) void k_expand_small(const int32_t *__restrict__ counts, int64_t P,
+                                                         int64_t *__restrict__ offsets,
+                                                         uint32_t *__restrict__ child_parent,
+                                                         uint32_t *__restrict__ child_ordinal, int64_t child_cap,
+                                                         int vec_ok, Ctl *ctl)
+{
+    typedef uint32_t t4 __attribute__((ext_vector_type(4)));
+    __shared__ uint32_t s_off[kTile + 1];
+    __shared__ int64_t s_wave[kBlock / 64];
+    const int64_t i0 = (int64_t)threadIdx.x * kItems;
+    int32_t v[kItems];
+    int64_t sum = 0;
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) v[k] = i0 + k < P ? counts[i0 + k] : 0;
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        if (v[k] < 0) { bad = true; v[k] = 0; }
+        sum += v[k];
+    }
+    int64_t N;
+    int64_t run = block_excl_scan(sum, s_wave, N);
+#pragma unroll
+    for (int k = 0; k < kItems; ++k) {
+        if (i0 + k < P) {
+            s_off[i0 + k] = (uint32_t)run;
+            if (blockIdx.x == 0) offsets[i0 + k] = run;
+        }
+        run += v[k];
+    }
+    if (threadIdx.x == 0) s_off[P] = (uint32_t)N;
+    if (blockIdx.x == 0) {
+        if (bad) raise_err(ctl, RO_EINVAL);
+        if (threadIdx.x == 0) {
+            offsets[P] = N;
+            if (N >= ((int64_t)1 << 32)) raise_err(ctl, RO_EOVERFLOW);
+            else if (N > child_cap) raise_err(ctl, RO_ECAP);
+        }
+    }
+    __syncthreads();
+    if (N > child_cap || N >= ((int64_t)1 << 32)) return;
+    const bool nt = N > kTagsNtChildren;
+    for (int64_t c0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4; c0 < N; c0 += (int64_t)gridDim.x * kBlock * 4) {
+        // the last parent starting at or before the thread's first child
+        int64_t lo = 0, hi = P;
+        while (hi - lo > 1) {
+            const int64_t m = (lo + hi) >> 1;
+            if (s_off[m] <= (uint32_t)c0) lo = m; else hi = m;
+        }
+        t4 par, ord;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int64_t c = c0 + k;
+            if (c < N && c >= (int64_t)s_off[lo + 1]) lo = advance_parent(s_off, P, lo, c);
+            par[k] = (uint32_t)lo;
+            ord[k] = (uint32_t)c - s_off[lo];
+        }
+        if (vec_ok && c0 + 4 <= N) {
+            if (nt) {
+                if (child_parent) __builtin_nontemporal_store(par, reinterpret_cast<t4 *>(child_parent + c0));
+                if (child_ordinal) __builtin_nontemporal_store(ord, reinterpret_cast<t4 *>(child_ordinal + c0));
+            } else {
+                if (child_parent) *reinterpret_cast<t4 *>(child_parent + c0) = par;
+                if (child_ordinal) *reinterpret_cast<t4 *>(child_ordinal + c0) = ord;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (c0 + k >= N) continue;
+                if (child_parent) child_parent[c0 + k] = par[k];
+                if (child_ordinal) child_ordinal[c0 + k] = ord[k];
+            }
+        }
+    }
+}
+
 hipError_t launch_expand(const Launch &L, const int32_t *counts, int64_t P,
                          int64_t *offsets, uint32_t *child_parent, uint32_t *child_ordinal,
                          int64_t child_cap)
 {
     const int64_t ntiles = P > 0 ? (P + kTile - 1) / kTile : 1;
     const int want = (child_parent != nullptr || child_ordinal != nullptr);
+    if (want && P <= kTile) {
+        // the capacity bounds the children, which only the device knows
+        const bool aligned = ((reinterpret_cast<uintptr_t>(child_parent) |
+                               reinterpret_cast<uintptr_t>(child_ordinal)) & 15u) == 0;
+        const int64_t need = child_cap / (kBlock * 4) + 1, most = (int64_t)L.num_cus * 8;
+        RO_LAUNCH(L, RO_K_EXPAND_TAGS, k_expand_small, dim3((unsigned)(need < most ? need : most)), dim3(kBlock), 0, L.stream,
+                  counts, P, offsets, child_parent, child_ordinal, child_cap, aligned ? 1 : 0, L.ctl);
+        return hipGetLastError();
+    }
     const int64_t grid = ntiles < (int64_t)L.num_cus * 4 ? ntiles : (int64_t)L.num_cus * 4;
     RO_LAUNCH(L, RO_K_EXPAND_SCAN, k_expand_scan, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, counts, P,
                        offsets, child_cap, want, L.ctl, L.desc, L.desc_cap, ntiles);

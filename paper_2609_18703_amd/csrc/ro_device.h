@@ -289,7 +289,8 @@ __device__ __forceinline__ v2i64 ld_pair(const int64_t *p) { return *reinterpret
 
 // ---- searches ---------------------------------------------------------------
 // First index i in [lo, hi) with a[i] > x (hi if none).
-__device__ __forceinline__ int64_t upper_bound_g(const int64_t *a, int64_t lo, int64_t hi, int64_t x)
+template <typename T>
+__device__ __forceinline__ int64_t upper_bound_g(const T *a, int64_t lo, int64_t hi, int64_t x)
 {
     while (lo < hi) {
         int64_t mid = (lo + hi) >> 1;
@@ -311,7 +312,8 @@ __device__ __forceinline__ int64_t lower_bound_g(const int64_t *a, int64_t lo, i
 // Parent of child c (largest p with offsets[p] <= c) when p is known to be
 // >= p; walks a few steps, then falls back to a binary search so that long
 // runs of empty parents cost a logarithm.
-__device__ __forceinline__ int64_t advance_parent(const int64_t *offsets, int64_t P, int64_t p, int64_t c)
+template <typename T>
+__device__ __forceinline__ int64_t advance_parent(const T *offsets, int64_t P, int64_t p, int64_t c)
 {
 #pragma unroll 1
     for (int s = 0; s < 4; ++s) {
