@@ -238,7 +238,7 @@ hipError_t launch_expand(const Launch &L, const int32_t *counts, int64_t P,
         const bool aligned = ((reinterpret_cast<uintptr_t>(child_parent) |
                                reinterpret_cast<uintptr_t>(child_ordinal)) & 15u) == 0;
         const int64_t need = child_cap / (kBlock * 4) + 1, most = (int64_t)L.num_cus * 8;
-        RO_LAUNCH(L, RO_K_EXPAND_TAGS, k_expand_small, dim3((unsigned)(need < most ? need : most)), dim3(kBlock), 0, L.stream,
+        RO_LAUNCH(L, RO_K_EXPAND_SCAN, k_expand_small, dim3((unsigned)(need < most ? need : most)), dim3(kBlock), 0, L.stream,
                   counts, P, offsets, child_parent, child_ordinal, child_cap, aligned ? 1 : 0, L.ctl);
         return hipGetLastError();
     }
