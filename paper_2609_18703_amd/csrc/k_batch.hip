@@ -84,11 +84,31 @@ static bool use_mask_map(int64_t Q, int64_t P, int64_t reserved)
 }
 
 // which structure a batch kernel finds an entry's parent in
-enum BatchMap { kMapSearch = 0, kMapCoarse = 1, kMapMask = 2, kMapChild = 3 };
+enum BatchMap { kMapSearch = 0, kMapCoarse = 1, kMapMask = 2, kMapChild = 3, kMapLds = 4 };
 struct MapArgs {
     const void *map;         // coarse or mask map, or the child -> parent map
     int64_t cap;             // its entries
 };
+
+// Offsets of few parents, searched in LDS: every workgroup loads them for
+// itself (P entries of 8 bytes), and a step of a search costs an LDS read
+// instead of a trip to the cache.  Held in 32 bits: a child id is smaller than
+// any offset that does not fit.
+constexpr int kLdsParents = 4096;
+
+template <int kMap>
+__device__ __forceinline__ void load_lds_offsets(const int64_t *__restrict__ offsets, int64_t P, uint32_t *s_off,
+                                                 MapArgs &map)
+{
+    if constexpr (kMap == kMapLds) {
+        for (int p = (int)threadIdx.x; p < (int)P; p += kBlock) {
+            const int64_t o = offsets[p];
+            s_off[p] = o > 0xffffffffll ? 0xffffffffu : (uint32_t)(o < 0 ? 0 : o);
+        }
+        map.map = s_off;
+        __syncthreads();
+    }
+}
 
 // entries of a thread whose lookups are in flight together
 #ifndef RO_BATCH_LOOKUPS
@@ -330,6 +350,27 @@ __device__ __forceinline__ void entry_tags(const MapArgs &m, int64_t nmap, int s
             par[k] = p[k];
             ord[k] = (uint32_t)((int64_t)c[k] - st[k]);
         }
+    } else if constexpr (kMap == kMapLds) {
+        const uint32_t *so = static_cast<const uint32_t *>(m.map);
+        uint32_t lo[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) lo[k] = 0;
+        // the last parent starting at or before the child, K searches in step
+        for (uint32_t len = (uint32_t)P; len > 1;) {
+            const uint32_t half = len >> 1;
+            uint32_t v[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) v[k] = so[lo[k] + half];
+#pragma unroll
+            for (int k = 0; k < K; ++k) lo[k] += v[k] <= c[k] ? half : 0u;
+            len -= half;
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (!((live >> k) & 1u)) continue;
+            par[k] = lo[k];
+            ord[k] = c[k] - so[lo[k]];
+        }
     } else if constexpr (kMap == kMapCoarse) {
         tags_of<K>(static_cast<const uint2 *>(m.map), nmap, sh, offsets, P, c, live, par, ord);
     } else {
@@ -351,7 +392,7 @@ __device__ __forceinline__ void entry_tags(const MapArgs &m, int64_t nmap, int s
 template <int kMap>
 __device__ __forceinline__ int64_t map_entries(const MapArgs &m, int64_t N, int sh)
 {
-    if constexpr (kMap == kMapSearch || kMap == kMapChild) return 0;
+    if constexpr (kMap == kMapSearch || kMap == kMapChild || kMap == kMapLds) return 0;
     const int s = kMap == kMapMask ? kMaskShift : sh;
     const int64_t n = (N + ((int64_t)1 << s) - 1) >> s;
     return n < m.cap ? n : m.cap;
@@ -461,6 +502,8 @@ __global__ __launch_bounds__(kBlock) void k_batch(
     uint64_t *desc, int64_t desc_cap, int64_t ntiles, int vec_ok)
 {
     constexpr int kT = kBlock * kIt;
+    __shared__ uint32_t s_off[kMap == kMapLds ? kLdsParents : 1];
+    load_lds_offsets<kMap>(offsets, P, s_off, map);
     const uint32_t epoch = scan_epoch(ctl);
     __shared__ uint32_t s_out[kT];             // one output array of a tile, in slot order
     __shared__ int64_t s_wave[kBlock / 64];
@@ -539,6 +582,8 @@ __global__ __launch_bounds__(kBlock) void k_batch_keep(
     int64_t ntiles, int vec_ok)
 {
     constexpr int kT = kBlock * kIt;
+    __shared__ uint32_t s_off[kMap == kMapLds ? kLdsParents : 1];
+    load_lds_offsets<kMap>(offsets, P, s_off, map);
     const uint32_t epoch = scan_epoch(ctl);
     __shared__ uint32_t s_out[kT];
     __shared__ int64_t s_wave[kBlock / 64];
@@ -594,7 +639,9 @@ __global__ __launch_bounds__(kBlock) void k_batch_keep(
 // costs less.  k_batch_count: a wave counts the ready entries of a tile of
 // 4,096, a workgroup 16 tiles, and writes each tile's place in its group and
 // the group's total; k_batch_fill: a tile per workgroup adds up the totals of
-// the groups before its own.
+// the groups before its own.  In a short queue (up to kDirectQueue entries) it
+// counts the mask before its tile itself, at most 64 KB: no ticket, no look-back
+// and no count at the end (7,389 entries: 10.4 us, now 7.6).
 // The counts use the look-back descriptors' room (epoch field 0, which no
 // look-back takes for its own).
 constexpr int kFillIt = 16, kFillTile = kBlock * kFillIt, kCountGrp = 16;
@@ -639,7 +686,7 @@ __global__ __launch_bounds__(64 * kCountGrp) void k_batch_count(const uint8_t *_
     }
 }
 
-template <int kMap>
+template <int kMap, int kIt, bool kCounted>
 __global__ __launch_bounds__(kBlock) void k_batch_fill(
     const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
     const int64_t *__restrict__ offsets, int64_t P, MapArgs map, int32_t B, uint32_t *__restrict__ out_child,
@@ -647,23 +694,38 @@ __global__ __launch_bounds__(kBlock) void k_batch_fill(
     int64_t *n_batches, const uint64_t *__restrict__ tile_at, const uint64_t *__restrict__ group_n, Ctl *ctl,
     int vec_ok)
 {
-    __shared__ uint32_t s_out[kFillTile];
+    constexpr int kT = kBlock * kIt;
+    __shared__ uint32_t s_off[kMap == kMapLds ? kLdsParents : 1];
+    load_lds_offsets<kMap>(offsets, P, s_off, map);
+    __shared__ uint32_t s_out[kT];
     __shared__ int64_t s_wave[kBlock / 64];
     const int64_t N = offsets[P];
     const int sh = map_shift(N, P);
     const int64_t nmap = map_entries<kMap>(map, N, sh);
     const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
     const bool nt = Q > kTagNtEntries;
-    const int64_t t = blockIdx.x, i0 = t * kFillTile + (int64_t)threadIdx.x * kFillIt;
-    const uint32_t km = load_mask<kFillIt>(keep, i0, Q, vec_ok);
-    uint32_t q[kFillIt], par[kFillIt], ord[kFillIt];
-    load_queue<kFillIt>(queue, i0, Q, vec_ok, q);
-    int64_t before = threadIdx.x == 0 ? (int64_t)tile_at[t] : 0;
-    for (int64_t g = threadIdx.x; g < t / kCountGrp; g += kBlock) before += (int64_t)group_n[g];
+    const int64_t t = blockIdx.x, i0 = t * kT + (int64_t)threadIdx.x * kIt;
+    const uint32_t km = load_mask<kIt>(keep, i0, Q, vec_ok);
+    uint32_t q[kIt], par[kIt], ord[kIt];
+    load_queue<kIt>(queue, i0, Q, vec_ok, q);
+    int64_t before = 0;
+    if constexpr (kCounted) {
+        if (threadIdx.x == 0) before = (int64_t)tile_at[t];
+        for (int64_t g = threadIdx.x; g < t / kCountGrp; g += kBlock) before += (int64_t)group_n[g];
+    } else if (vec_ok) {
+        const uint4 *k4 = reinterpret_cast<const uint4 *>(keep);
+#pragma unroll 4
+        for (int64_t j = threadIdx.x; j < t * kT / 16; j += kBlock) {
+            const uint4 x = k4[j];
+            before += nonzero_bytes(x.x) + nonzero_bytes(x.y) + nonzero_bytes(x.z) + nonzero_bytes(x.w);
+        }
+    } else {
+        for (int64_t j = threadIdx.x; j < t * kT; j += kBlock) before += keep[j] != 0;
+    }
     bool bad_range = false;
     uint32_t live = 0;
 #pragma unroll
-    for (int k = 0; k < kFillIt; ++k) {
+    for (int k = 0; k < kIt; ++k) {
         par[k] = 0xffffffffu;
         ord[k] = 0xffffffffu;
         if (km & (1u << k)) {
@@ -671,13 +733,13 @@ __global__ __launch_bounds__(kBlock) void k_batch_fill(
             else live |= 1u << k;
         }
     }
-    if (want_tags) thread_tags<kMap, kFillIt>(map, nmap, sh, offsets, P, q, live, par, ord);
+    if (want_tags) thread_tags<kMap, kIt>(map, nmap, sh, offsets, P, q, live, par, ord);
     if (bad_range) raise_err(ctl, RO_ERANGE);
     const int64_t base = block_sum(before, s_wave);
     int64_t tot;
     const int64_t ex = block_excl_scan(__popc(km), s_wave, tot);
     if (base + tot > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
-    write_slots<kFillIt>(out_child, out_parent, out_ordinal, q, par, ord, km, (int)ex, base,
+    write_slots<kIt>(out_child, out_parent, out_ordinal, q, par, ord, km, (int)ex, base,
                          slot_room(out_cap, base, tot), s_out, nt);
     if (t == gridDim.x - 1 && threadIdx.x == 0) {
         if (n_out) *n_out = base + tot;
@@ -697,6 +759,8 @@ __global__ __launch_bounds__(kBlock) void k_batch_all(
     int64_t max_id, int32_t B, uint32_t *__restrict__ out_child, uint32_t *__restrict__ out_parent,
     uint32_t *__restrict__ out_ordinal, int64_t out_cap, int64_t *n_out, int64_t *n_batches, Ctl *ctl)
 {
+    __shared__ uint32_t s_off[kMap == kMapLds ? kLdsParents : 1];
+    load_lds_offsets<kMap>(offsets, P, s_off, map);
     const int64_t NP = offsets[P];
     const int64_t N = min64(NP, max_id);       // ids past a child map are out of range
     const int sh = map_shift(NP, P);
@@ -741,10 +805,11 @@ __global__ __launch_bounds__(kBlock) void k_batch_all(
 // Sizes at which a queue changes path (entries):
 //   up to kDirectQueue the offsets are searched and no map is built: the map
 //   is a launch of about 5 us (100,000 entries under 243 parents: 88.7 us for
-//   the whole chain searched, 92 with the map);
-//   up to kSmallQueue a masked queue is cut into tiles of 1,024 entries
-//   (7,389 entries: 10 us, 39 us as one tile of 16,384; 98,000 entries: 18 us,
-//   57 as 6 of those);
+//   the whole chain searched, 92 with the map); a masked queue's tiles of 1,024
+//   count the mask before them themselves (7,389 entries: 7.6 us, 10.4 with
+//   tickets and look-back, 39 as one tile of 16,384);
+//   up to kSmallQueue a masked queue is cut into tiles of 1,024 entries (98,000
+//   entries: 18 us, 57 as 6 tiles of 16,384);
 //   up to kMidQueue into tiles of 4,096 (1M entries: 29 us; 57 in 980 tiles of
 //   1,024, whose tickets and look-backs queue up; 66 in 61 of 16,384, too few
 //   for 256 CUs); with a barrier this is the largest tile, since the tags come
@@ -772,14 +837,22 @@ hipError_t launch_batch_with(const Launch &L, const uint32_t *queue, const uint8
     auto tiles = [&](int64_t per) { return Q > 0 ? (Q + per - 1) / per : 1; };
     if (barrier == nullptr && kMap != kMapChild) {
         if constexpr (kMap != kMapChild) {
-            if (Q > kMidQueue) {
-                const int64_t nt = tiles(kFillTile), ng = (nt + kCountGrp - 1) / kCountGrp;
-                if (nt + ng > L.desc_cap || nt > 0x7fffffff) return hipErrorInvalidValue;
-                RO_LAUNCH(L, RO_K_BATCH, k_batch_count, dim3((unsigned)ng), dim3(64 * kCountGrp), 0, L.stream, keep, Q,
-                          L.desc, L.desc + nt, aligned ? 1 : 0);
-                RO_LAUNCH(L, RO_K_BATCH, k_batch_fill<kMap>, dim3((unsigned)nt), dim3(kBlock), 0, L.stream, queue, keep, Q,
-                          offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.desc,
-                          L.desc + nt, L.ctl, aligned ? 1 : 0);
+            if constexpr (kMap != kMapLds) {
+                if (Q > kMidQueue) {
+                    const int64_t nt = tiles(kFillTile), ng = (nt + kCountGrp - 1) / kCountGrp;
+                    if (nt + ng > L.desc_cap || nt > 0x7fffffff) return hipErrorInvalidValue;
+                    RO_LAUNCH(L, RO_K_BATCH, k_batch_count, dim3((unsigned)ng), dim3(64 * kCountGrp), 0, L.stream, keep, Q,
+                              L.desc, L.desc + nt, aligned ? 1 : 0);
+                    RO_LAUNCH(L, RO_K_BATCH, (k_batch_fill<kMap, kFillIt, true>), dim3((unsigned)nt), dim3(kBlock), 0,
+                              L.stream, queue, keep, Q, offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.desc,
+                              L.desc + nt, L.ctl, aligned ? 1 : 0);
+                    return hipGetLastError();
+                }
+            }
+            if (Q <= kDirectQueue) {
+                RO_LAUNCH(L, RO_K_BATCH, (k_batch_fill<kMap, 4, false>), dim3((unsigned)tiles(kBlock * 4)), dim3(kBlock), 0,
+                          L.stream, queue, keep, Q, offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out,
+                          n_batches, nullptr, nullptr, L.ctl, aligned ? 1 : 0);
                 return hipGetLastError();
             }
             const bool small = Q <= kSmallQueue;
@@ -810,10 +883,17 @@ hipError_t launch_batch(const Launch &L, const uint32_t *queue, const uint8_t *k
     if (cpar)
         return launch_batch_with<kMapChild>(L, queue, keep, Q, offsets, P, MapArgs{cpar, cpar_n}, cpar_n, B, out_child,
                                             out_parent, out_ordinal, out_cap, n_out, n_batches, barrier);
+    const bool tags = out_parent != nullptr || out_ordinal != nullptr;
+    // Few parents and a short queue: the offsets in LDS.  7,389 entries under
+    // 1,000 parents take 7.6 us (10.4 with a search through memory); at 1M
+    // entries under 2,431 parents the batch takes 24 us, as long as with the mask
+    // map and its launch, so the line lies at kSmallQueue.
+    if ((tags || barrier != nullptr) && P <= kLdsParents && Q <= kSmallQueue)
+        return launch_batch_with<kMapLds>(L, queue, keep, Q, offsets, P, MapArgs{nullptr, 0}, kAnyId, B, out_child,
+                                          out_parent, out_ordinal, out_cap, n_out, n_batches, barrier);
     // A map costs a launch and a search per block; a short unmasked queue
     // (fewer entries than parents, such as one wave of a stream) searches
     // the offsets directly instead.  The maps' parent fields keep a flag bit.
-    const bool tags = out_parent != nullptr || out_ordinal != nullptr;
     const bool use_map = (tags || barrier != nullptr) && cmap_words_cap >= 4 && P < ((int64_t)1 << 31) &&
                          !(keep == nullptr && barrier == nullptr && Q < P) && Q > kDirectQueue;
     if (!use_map)

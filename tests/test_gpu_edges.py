@@ -226,3 +226,46 @@ def test_stream_emission_beyond_capacity_is_emitted_later(ctx):
     assert ep.tolist()[:6] == list(range(4, 10))
     assert ed.tolist()[:sc[1].item()] == list(range(4 * int(offs[4]), 4 * n))
     st.close()
+
+
+# one fewer, as many and one more parents than the paths for few parents take
+# (4,096, offsets in LDS), with empty parents at both ends and in between
+@pytest.mark.parametrize("n_parents", [1, 2, 4095, 4096, 4097])
+@pytest.mark.parametrize("fan", [2, 300])
+def test_few_parents(ctx, n_parents, fan):
+    rng = np.random.default_rng(n_parents + fan)
+    counts = np.where(rng.random(n_parents) < 0.3, 0, rng.integers(1, 2 * fan, n_parents)).astype(np.int32)
+    counts[n_parents // 2] = 5000                          # several 1,024-child spans
+    if n_parents > 2:
+        counts[[0, 1, -1]] = 0
+    offs, par, ordi = O.expand(counts)
+    n = len(par)
+    _say("few parents", n_parents, fan, n)
+    for shift in (0, 1):                                   # key arrays on and off their 16-byte alignment
+        o = _zeros(n_parents + 1, torch.int64)
+        tags = [torch.full((n + 8,), -1, dtype=torch.int32, device="cuda")[shift:shift + n] for _ in range(2)]
+        ctx.expand(D.to_dev(counts), o, *tags)
+        ctx.check("expand")
+        assert np.array_equal(o.cpu().numpy(), offs)
+        for t, w in zip(tags, (par, ordi)):
+            assert np.array_equal(t.cpu().numpy().view(np.uint32), w)
+    queue = rng.permutation(n).astype(np.uint32)
+    keep = (rng.random(n) < 0.8).astype(np.uint8)
+    barrier = (rng.random(n_parents) < 0.1).astype(np.uint8)
+    for k, bar in ((None, None), (keep, None), (None, barrier), (keep, barrier)):
+        _batch_case(ctx, counts, queue, k, bar, 48)
+
+
+def test_expand_errors_with_few_parents(ctx):
+    import paper_2609_18703_amd as R
+    tags = [_zeros(8, torch.int32) for _ in range(2)]
+    off = _zeros(4, torch.int64)
+    ctx.expand(D.to_dev(np.array([3, -1, 2], np.int32)), off, *tags)
+    assert ctx.status() == R.EINVAL
+    for t in tags:                                         # that call's are unspecified
+        t.zero_()
+    ctx.expand(D.to_dev(np.array([3, 4, 2], np.int32)), off, *tags)
+    assert ctx.status() == R.ECAP and off.tolist() == [0, 3, 7, 9]
+    ctx.expand(D.to_dev(np.array([2 ** 31 - 1, 2 ** 31 - 1, 2], np.int32)), off, *tags)
+    assert ctx.status() == R.EOVERFLOW and off.tolist() == [0, 2 ** 31 - 1, 2 ** 32 - 2, 2 ** 32]
+    assert not any(t.any() for t in tags)
