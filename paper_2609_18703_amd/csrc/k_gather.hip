@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kTh) void k_gather_scan(
     __shared__ uint64_t s_b;
     __shared__ int64_t s_t;
     __shared__ int64_t s_p[2][2];
-    __shared__ int32_t s_flag;
+    __shared__ int32_t s_valid, s_last;         // two words: waves still read the first when the second is set
     const int64_t N0 = offsets[P];
     const int64_t N = N0 <= canon_cap ? N0 : 0;
     const int64_t ntiles = (N + kT - 1) / kT;
@@ -242,11 +242,11 @@ __global__ __launch_bounds__(kTh) void k_gather_scan(
     const int wv = uni32((int)(threadIdx.x >> 6)), ln = lane_id();
     // an invalid Expansion found by the scatter: no tiles (one thread looks,
     // since an error may also be raised while the scan runs)
-    if (threadIdx.x == 0) s_flag = read_err(ctl) == 0 ? 1 : 0;
+    if (threadIdx.x == 0) s_valid = read_err(ctl) == 0 ? 1 : 0;
     __syncthreads();
     const bool single = ntiles == 1;
     const bool one = ntiles <= (int64_t)gridDim.x;      // one tile and one ticket per workgroup
-    int64_t t = s_flag == 0 ? ntiles : (single || ntiles == 0 ? 0 : next_ticket(ctl, &s_t));
+    int64_t t = s_valid == 0 ? ntiles : (single || ntiles == 0 ? 0 : next_ticket(ctl, &s_t));
     int64_t filled = 0;
 
     // Tile tt's parents, by waves 1 and 2: q0 is the first parent starting in
@@ -462,10 +462,10 @@ __global__ __launch_bounds__(kTh) void k_gather_scan(
             ctl->n_rejected = 0;
             __hip_atomic_store(&ctl->gdone, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        s_flag = last;
+        s_last = last;
     }
     __syncthreads();
-    if (parts > 1 && s_flag) ticket_reset(ctl, sepoch, desc, desc_cap);
+    if (parts > 1 && s_last) ticket_reset(ctl, sepoch, desc, desc_cap);
 }
 
 // ---------------------------------------------------------------- finalize

@@ -117,6 +117,31 @@ def test_gather_scan_tiles(ctx, n, missing):
     _gather_case(ctx, counts, lengths, states, order)
 
 
+# A scan that follows an error runs no tiles, and its last workgroup still
+# settles the call: every wave has to leave by the same way (one workgroup, a
+# few, and more than one per CU, at both tile sizes).
+@pytest.mark.parametrize("n", [500, 5000, 131_072, 131_073, 400_000])
+def test_gather_after_an_error_runs_no_tiles(ctx, n):
+    import paper_2609_18703_amd as R
+    counts = np.full(n // 100 + 1, 100)
+    counts[-1] = n - 100 * (n // 100)
+    order = np.random.default_rng(n).permutation(n)
+    lengths, states = np.full(n, 3), np.zeros(n, np.uint8)
+    rp, ro, rs, off, data = _reports(counts, lengths, states, order)
+    offs = D.to_dev(O.expand(counts.astype(np.int32), tags=False))
+    cols = (_i32(rp), _i32(ro), D.to_dev(rs), D.to_dev(off), D.to_dev(data), offs)
+    bad = rp.copy()
+    bad[n // 2] = len(counts)                              # no such parent
+    for k in range(20):
+        _say("gather after an error", n, k)
+        out = torch.full((3 * n,), 0xA5, dtype=torch.uint8, device="cuda")
+        ctx.gather(_i32(bad), *cols[1:], _zeros(len(counts) + 1, torch.int64), out)
+        ctx.gather(*cols, _zeros(len(counts) + 1, torch.int64), out)      # the error is still recorded
+        assert ctx.status() == R.ERANGE
+        assert bool((out == 0xA5).all())
+    _gather_case(ctx, counts, lengths, states, order)
+
+
 def _batch_case(ctx, counts, queue, keep, barrier, B):
     offs = O.expand(np.asarray(counts, np.int32), tags=False)
     P, Q = len(counts), len(queue)
