@@ -181,7 +181,7 @@ __global__ void k_batch_cmap(const int64_t *__restrict__ offsets, int64_t P, uin
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < nmap;
          j += (int64_t)gridDim.x * blockDim.x) {
         const int64_t c0 = j << sh;
-        const int64_t p0 = upper_bound_g(offsets, 0, P + 1, c0) - 1;
+        const int64_t p0 = max64(upper_bound_g(offsets, 0, P + 1, c0) - 1, 0);
         const int64_t last = c0 + (1 << sh) - 1 < N ? c0 + (1 << sh) - 1 : N - 1;
         const bool one = offsets[p0 + 1] > last;
         map[j] = make_uint2((uint32_t)p0 | (one ? kMapOne : 0u), (uint32_t)(c0 - offsets[p0]));
@@ -290,7 +290,10 @@ __device__ __forceinline__ void tags_of_mask(const uint4 *__restrict__ map, int6
         const int j = (int)(c[k] & ((1u << kMaskShift) - 1));
         const uint64_t m = ((uint64_t)e[k].w << 32 | e[k].z) & ((2ull << j) - 1);
         const uint32_t n = (uint32_t)__popcll(m);
-        par[k] = (e[k].x & ~kMapOne) + n;
+        // offsets that are no expansion may hold more starts than parents follow
+        // p0; the barrier is read at the result, so it stays below P
+        const uint32_t p = (e[k].x & ~kMapOne) + n;
+        par[k] = p < (uint32_t)P ? p : (uint32_t)P - 1u;
         ord[k] = n ? (uint32_t)(j - (63 - __clzll((long long)m))) : e[k].y + (uint32_t)j;
         if (((live >> k) & 1u) && ((n && (e[k].x & kMapOne)) || (int64_t)(c[k] >> kMaskShift) >= nmap)) slow |= 1u << k;
     }
@@ -298,7 +301,7 @@ __device__ __forceinline__ void tags_of_mask(const uint4 *__restrict__ map, int6
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             if (!((slow >> k) & 1u)) continue;
-            const int64_t p = search_parent(offsets, 0, P + 1, (int64_t)c[k]);
+            const int64_t p = max64(search_parent(offsets, 0, P + 1, (int64_t)c[k]), 0);
             par[k] = (uint32_t)p;
             ord[k] = (uint32_t)((int64_t)c[k] - offsets[p]);
         }
@@ -382,8 +385,9 @@ __device__ __forceinline__ void entry_tags(const MapArgs &m, int64_t nmap, int s
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             if (!((live >> k) & 1u)) continue;
-            par[k] = (uint32_t)(pp[k] - 1);
-            ord[k] = (uint32_t)((int64_t)c[k] - offsets[pp[k] - 1]);
+            const int64_t p = max64(pp[k] - 1, 0);          // -1 only where the offsets do not start at 0
+            par[k] = (uint32_t)p;
+            ord[k] = (uint32_t)((int64_t)c[k] - offsets[p]);
         }
     }
 }

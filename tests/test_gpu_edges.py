@@ -210,6 +210,36 @@ def test_batch_counted(ctx, q_len, shift):
             assert np.array_equal(h[:cap], w[:cap]) and (h[cap:] == 0xffffffff).all()
 
 
+def test_batch_parents_of_malformed_offsets_stay_below_the_count():
+    """ro_batch does not check the offsets.  The last parent is moved to the
+    first block of the last 1,024 children, so later blocks of the mask map
+    count on from it: the parents looked up, at which the barrier is read, must
+    still be parents.  (The barrier is followed by bytes of the same
+    allocation that would suppress the entries.)"""
+    import paper_2609_18703_amd as R
+    P, span = 5000, 78 * 1024
+    starts = np.arange(P, dtype=np.int64) * 16
+    starts[4992:4998] = [span + 64 + 8, span + 64 + 24, span + 64 + 40, span + 128 + 8, span + 128 + 24, span + 128 + 40]
+    starts[4998:] = [span + 192 + 5, span + 1]
+    offs = np.concatenate([starts, [span + 300]])
+    n, q_len = int(offs[-1]), 70_000
+    queue = np.concatenate([np.arange(n - 300, n), np.arange(q_len - 300)]).astype(np.uint32)
+    bar = torch.ones(P + 4096, dtype=torch.uint8, device="cuda")
+    bar[:P] = 0
+    c = R.Context()
+    c.reserve(n, P, q_len)
+    for keep in (None, torch.ones(q_len, dtype=torch.uint8, device="cuda")):
+        outs = [torch.full((q_len,), -1, dtype=torch.int32, device="cuda") for _ in range(3)]
+        sc = _zeros(2, torch.int64)
+        _say("batch malformed offsets", keep is not None)
+        c.batch(_i32(queue), keep, D.to_dev(offs), 64, *outs, sc[0:1], sc[1:2], barrier=bar[:P])
+        c.check("batch")
+        assert sc.tolist() == [q_len, -(-q_len // 64)]
+        assert np.array_equal(outs[0].cpu().numpy().view(np.uint32), queue)
+        assert int(outs[1].cpu().numpy().view(np.uint32).max()) < P
+    c.close()
+
+
 def test_stream_word_and_tile_edges(ctx):
     """Completion found by seen words: parents of one to many 32-child words
     at every alignment, empty parents among them, children in random order
