@@ -75,11 +75,18 @@ constexpr int kMaskShift = 6;
 // children under 300,000 parents 23 us with this map, 48 with the coarse one;
 // 5M under 30,000 46 and 78; 8M under 20,000 91 and 107; 20M under 2.7M 238
 // and 955; but 41M under 100,000 540 (a 10 MB map) against 448.  A short queue
-// over a large reservation keeps the coarse map, whose build writes less.
+// over a large reservation keeps the coarse map, whose build writes less.  So
+// does an expansion that is mostly empty parents, which would make most
+// entries search after all: more parents than children reserved, or many
+// beside both the queue (a queue rarely names a child twice) and the
+// reservation (100,000 children of 1M parents, 90,000 entries with a barrier:
+// 28 us, 62 with this map; 1M of 4M parents 36 and 59; but 4M under 1M parents,
+// 200,000 entries, 28 and 25).
 constexpr int64_t kMaskChildren = (int64_t)12 << 20;
 static bool use_mask_map(int64_t Q, int64_t P, int64_t reserved)
 {
     if (reserved > kMaskChildren && reserved > 4 * Q) return false;
+    if (P > reserved || (P > 2 * Q && 4 * P > reserved)) return false;
     return Q <= kMaskChildren || Q < 64 * P;
 }
 
@@ -115,10 +122,41 @@ __device__ __forceinline__ void load_lds_offsets(const int64_t *__restrict__ off
 #define RO_BATCH_LOOKUPS 4
 #endif
 
+// First index i in [0, n) with a[i] > x (n if none), for K keys at once
+// (n >= 1, a nondecreasing).  The halving is branch-free and its trip count
+// depends on n only, so the K searches step together and each step's K loads
+// are in flight at the same time.
+template <int K>
+__device__ __forceinline__ void upper_bound_k(const int64_t *a, int64_t n, const int64_t (&x)[K], int64_t (&r)[K])
+{
+    int64_t base[K];
+#pragma unroll
+    for (int k = 0; k < K; ++k) base[k] = 0;
+    int64_t len = n;
+    while (len > 1) {
+        const int64_t half = len >> 1;
+        int64_t v[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = a[base[k] + half];
+#pragma unroll
+        for (int k = 0; k < K; ++k) base[k] = v[k] <= x[k] ? base[k] + half : base[k];
+        len -= half;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) r[k] = base[k] + (a[base[k]] <= x[k] ? 1 : 0);
+}
+
 // A wave builds 16 entries (1,024 children): the first parent starting among
 // them by a wave search, then 64 parents' starts per step, each of which sets
 // its bit in LDS; the parent of a block's first child is the one starting
-// there, or the last one starting before.
+// there, or the last one starting before.  1,024 children of parents that are
+// not empty take 17 steps at most.  A run of empty parents is stepped over by a
+// search (ten million of them were 156,000 dependent steps of one wave, 53 ms),
+// and where empty parents still make it more than kMaskSteps every child's
+// parent is searched, four blocks of children at a time: the logarithm of the
+// parents left, however they lie.
+constexpr int kMaskSteps = 20, kMaskSearch = 4;
+
 __global__ __launch_bounds__(kBlock) void k_batch_mask_map(const int64_t *__restrict__ offsets, int64_t P,
                                                            uint4 *__restrict__ map, int64_t map_cap)
 {
@@ -140,12 +178,15 @@ __global__ __launch_bounds__(kBlock) void k_batch_mask_map(const int64_t *__rest
         }
         __builtin_amdgcn_wave_barrier();
         const int64_t q0 = cb == 0 ? 0 : wave_last_le(offsets, 0, P + 1, cb - 1) + 1;
-        for (int64_t qb = q0;; qb += 64) {
+        int steps = 0;
+        bool was_idle = false;
+        for (int64_t qb = q0; steps < kMaskSteps; qb += 64, ++steps) {
             const int64_t q = qb + lane;
             const int64_t st = q < P ? offsets[q] : N, en = q < P ? offsets[q + 1] : N;
-            if (st >= cb && st < ce) {
+            const bool here = st >= cb && st < ce, starts = here && en > st;
+            if (here) {
                 const int b = (int)((st - cb) >> kMaskShift), j = (int)(st & ((1 << kMaskShift) - 1));
-                if (en > st) {
+                if (starts) {
                     if (j > 0) atomicOr((unsigned long long *)&s_mask[w][b], 1ull << j);
                     else s_at0[w][b] = (uint32_t)q + 1;
                     atomicMax(&s_last[w][b], (uint32_t)q + 1);
@@ -154,18 +195,48 @@ __global__ __launch_bounds__(kBlock) void k_batch_mask_map(const int64_t *__rest
                 }
             }
             if (__ballot(st >= ce) != 0) break;
+            // 64 empty parents lie at one child; after 64 more, on to the last
+            // parent there (a search as long as about six steps)
+            const bool idle = __ballot(starts) == 0;
+            if (idle && was_idle) {
+                qb = wave_last_le(offsets, qb, P + 1, __shfl(st, 0)) - 64;
+                steps += 6;
+            }
+            was_idle = idle;
         }
         __builtin_amdgcn_wave_barrier();
-        const int64_t b = wt * kB + lane;
-        if (lane < kB) {
-            uint32_t before = (uint32_t)q0;               // the last parent starting before the block, plus 1
-            for (int k = 0; k < lane; ++k) before = s_last[w][k] > before ? s_last[w][k] : before;
-            before = s_at0[w][lane] ? s_at0[w][lane] : before;
-            const uint32_t p0 = before ? before - 1 : 0u;
-            const uint64_t m = s_mask[w][lane];
-            if (b < nmap)
-                map[b] = make_uint4(p0 | (s_empty[w][lane] ? kMapOne : 0u),
-                                    (uint32_t)((b << kMaskShift) - offsets[p0]), (uint32_t)m, (uint32_t)(m >> 32));
+        if (steps < kMaskSteps) {
+            const int64_t b = wt * kB + lane;
+            if (lane < kB) {
+                uint32_t before = (uint32_t)q0;           // the last parent starting before the block, plus 1
+                for (int k = 0; k < lane; ++k) before = s_last[w][k] > before ? s_last[w][k] : before;
+                before = s_at0[w][lane] ? s_at0[w][lane] : before;
+                const uint32_t p0 = before ? before - 1 : 0u;
+                const uint64_t m = s_mask[w][lane];
+                if (b < nmap)
+                    map[b] = make_uint4(p0 | (s_empty[w][lane] ? kMapOne : 0u),
+                                        (uint32_t)((b << kMaskShift) - offsets[p0]), (uint32_t)m, (uint32_t)(m >> 32));
+            }
+        } else {
+            // parents [lo, lo + len) hold the span's children
+            const int64_t lo = q0 > 0 ? q0 - 1 : 0;
+            const int64_t len = min64(wave_last_le(offsets, lo, P + 1, ce - 1) + 1, P) - lo;
+#pragma unroll 1
+            for (int k0 = 0; k0 < kB; k0 += kMaskSearch) {
+                int64_t c[kMaskSearch], r[kMaskSearch];
+#pragma unroll
+                for (int k = 0; k < kMaskSearch; ++k) c[k] = min64(cb + (k0 + k) * 64 + lane, ce - 1);
+                upper_bound_k<kMaskSearch>(offsets + lo, len > 0 ? len : 1, c, r);
+#pragma unroll
+                for (int k = 0; k < kMaskSearch; ++k) {
+                    const int64_t b = wt * kB + k0 + k, p = lo + max64(r[k] - 1, 0);
+                    const int64_t before = __shfl_up(p, 1);
+                    const uint64_t m = __ballot(lane > 0 && p != before), e = __ballot(lane > 0 && p > before + 1);
+                    if (lane == 0 && b < nmap)
+                        map[b] = make_uint4((uint32_t)p | (e ? kMapOne : 0u), (uint32_t)(c[k] - offsets[p]), (uint32_t)m,
+                                            (uint32_t)(m >> 32));
+                }
+            }
         }
         __builtin_amdgcn_wave_barrier();
     }
@@ -266,7 +337,9 @@ __device__ __forceinline__ void tags_of(const uint2 *__restrict__ map, int64_t n
     }
 }
 
-// The parent of child c by the offsets alone, among [lo, hi).
+// The last parent among [lo, hi) that starts at or before child c (lo - 1 if
+// none does), out of line: its registers would cost the common path a wave per
+// SIMD.
 __device__ __noinline__ int64_t search_parent(const int64_t *offsets, int64_t lo, int64_t hi, int64_t c)
 {
     return upper_bound_g(offsets, lo, hi, c) - 1;
@@ -298,38 +371,19 @@ __device__ __forceinline__ void tags_of_mask(const uint4 *__restrict__ map, int6
         if (((live >> k) & 1u) && ((n && (e[k].x & kMapOne)) || (int64_t)(c[k] >> kMaskShift) >= nmap)) slow |= 1u << k;
     }
     if (slow) {
+        // the parent lies between the count and the next block's first parent;
+        // a child past the map may have any
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             if (!((slow >> k) & 1u)) continue;
-            const int64_t p = max64(search_parent(offsets, 0, P + 1, (int64_t)c[k]), 0);
+            const int64_t j = (int64_t)(c[k] >> kMaskShift);
+            const int64_t lo = j < nmap ? (int64_t)par[k] : 0;
+            const int64_t hi = j + 1 < nmap ? min64((int64_t)(map[j + 1].x & ~kMapOne) + 1, P) : P;
+            const int64_t p = max64(search_parent(offsets, lo, hi, (int64_t)c[k]), 0);
             par[k] = (uint32_t)p;
             ord[k] = (uint32_t)((int64_t)c[k] - offsets[p]);
         }
     }
-}
-
-// First index i in [0, n) with a[i] > x (n if none), for K keys at once
-// (n >= 1, a nondecreasing).  The halving is branch-free and its trip count
-// depends on n only, so the K searches step together and each step's K loads
-// are in flight at the same time.
-template <int K>
-__device__ __forceinline__ void upper_bound_k(const int64_t *a, int64_t n, const int64_t (&x)[K], int64_t (&r)[K])
-{
-    int64_t base[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) base[k] = 0;
-    int64_t len = n;
-    while (len > 1) {
-        const int64_t half = len >> 1;
-        int64_t v[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) v[k] = a[base[k] + half];
-#pragma unroll
-        for (int k = 0; k < K; ++k) base[k] = v[k] <= x[k] ? base[k] + half : base[k];
-        len -= half;
-    }
-#pragma unroll
-    for (int k = 0; k < K; ++k) r[k] = base[k] + (a[base[k]] <= x[k] ? 1 : 0);
 }
 
 // Tags of K entries by whichever structure the launch chose.

@@ -210,6 +210,47 @@ def test_batch_counted(ctx, q_len, shift):
             assert np.array_equal(h[:cap], w[:cap]) and (h[cap:] == 0xffffffff).all()
 
 
+# Empty parents in long runs (in front, in the middle of a block, at a span's
+# edge, behind), between all children, and in clumps of every length up to
+# several steps: the walk over the parents, its jump over a run and the search
+# that replaces it, and entries whose parent is searched after all.  The
+# reservation decides between the mask map and the coarse one.
+@pytest.mark.parametrize("shape", ["front", "middle", "spread", "clumps"])
+@pytest.mark.parametrize("reserve", [100_000, 12 << 20])
+def test_batch_among_empty_parents(shape, reserve):
+    import paper_2609_18703_amd as R
+    rng = np.random.default_rng(len(shape))
+    if shape == "front":
+        counts = np.concatenate([np.zeros(1_100_000, np.int64), rng.integers(1, 200, 800), np.zeros(1000, np.int64)])
+    elif shape == "middle":
+        empty = [np.zeros(k, np.int64) for k in (1_000_003, 63, 64, 65, 127, 128, 129, 192, 300, 5000)]
+        full = [[33], [31], [64], [960], [64, 1, 1], [62], [2, 100], [924, 1024], rng.integers(1, 3, 3000), rng.integers(1, 200, 700)]
+        counts = np.concatenate([np.concatenate([f, e]) for f, e in zip(full, empty)])
+    elif shape == "spread":
+        counts = np.zeros(900_000, np.int64)
+        counts[rng.choice(len(counts), 80_000, replace=False)] = 1
+    else:
+        counts = np.concatenate([np.concatenate([rng.integers(1, 40, rng.integers(1, 8)), np.zeros(rng.integers(0, 400), np.int64)])
+                                 for _ in range(1200)])
+    n = int(counts.sum())
+    q_len = min(n, 90_000)
+    assert q_len > 65_536
+    queue = rng.permutation(n)[:q_len].astype(np.uint32)
+    keep = (rng.random(q_len) < 0.8).astype(np.uint8)
+    barrier = (rng.random(len(counts)) < 0.1).astype(np.uint8)
+    c = R.Context()
+    c.reserve(max(reserve, n), len(counts), q_len)
+    for k, bar in ((keep, None), (None, barrier), (keep, barrier)):
+        _say("batch among empty parents", shape, n, len(counts), reserve, k is not None, bar is not None)
+        c.trace(True)
+        _batch_case(c, counts, queue, k, bar, 256)
+        # a million empty parents one step of 64 after another are 17,000
+        # dependent loads, 5 ms; the map takes some 15 us
+        launches, ms = c.trace_read()["batch_samples"]
+        assert launches == 1 and ms < 1.0
+    c.close()
+
+
 def test_batch_parents_of_malformed_offsets_stay_below_the_count():
     """ro_batch does not check the offsets.  The last parent is moved to the
     first block of the last 1,024 children, so later blocks of the mask map
