@@ -142,7 +142,9 @@ int ro_ctx_trace_read(ro_ctx *ctx, int64_t *launches, double *total_ms, int32_t 
  * [offsets[p], offsets[p+1]).  If child_parent / child_ordinal are not NULL,
  * child c also gets its key (p, c - offsets[p]); both need room for N
  * entries, N <= child_cap (RO_ECAP otherwise).  A negative count is
- * RO_EINVAL; N >= 2^32 is RO_EOVERFLOW. */
+ * RO_EINVAL; N >= 2^32 is RO_EOVERFLOW.  A key array may share memory with
+ * the counts, which are all read before a key is written; the offsets and
+ * the two key arrays may not share memory with one another. */
 int ro_expand(ro_ctx *ctx, const int32_t *counts, int64_t n_parents, int64_t *offsets,
               uint32_t *child_parent, uint32_t *child_ordinal, int64_t child_cap);
 

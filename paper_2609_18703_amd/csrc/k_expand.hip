@@ -233,7 +233,13 @@ hipError_t launch_expand(const Launch &L, const int32_t *counts, int64_t P,
 {
     const int64_t ntiles = P > 0 ? (P + kTile - 1) / kTile : 1;
     const int want = (child_parent != nullptr || child_ordinal != nullptr);
-    if (want && P <= kTile) {
+    // every workgroup of the one-launch form reads the counts while others
+    // write already: an output in the counts' memory takes the two launches,
+    // of which the first reads all counts
+    const int64_t key_bytes = (child_cap < (int64_t)1 << 32 ? child_cap : (int64_t)1 << 32) * 4;
+    const bool apart = !overlap(counts, P * 4, child_parent, key_bytes) && !overlap(counts, P * 4, child_ordinal, key_bytes) &&
+                       !overlap(counts, P * 4, offsets, (P + 1) * 8);
+    if (want && P <= kTile && apart) {
         // the capacity bounds the children, which only the device knows
         const bool aligned = ((reinterpret_cast<uintptr_t>(child_parent) |
                                reinterpret_cast<uintptr_t>(child_ordinal)) & 15u) == 0;

@@ -95,14 +95,6 @@ namespace {
 
 int hip_fail(hipError_t e) { return e == hipSuccess ? RO_OK : RO_EHIP; }
 
-// Byte ranges [a, a + na) and [b, b + nb) share a byte (NULL or empty: never).
-bool overlap(const void *a, int64_t na, const void *b, int64_t nb)
-{
-    if (!a || !b || na <= 0 || nb <= 0) return false;
-    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-    return x < y + (uintptr_t)nb && y < x + (uintptr_t)na;
-}
-
 // The batch kernels read the queue, mask, offsets and barrier and write the
 // tag arrays through restrict-qualified pointers: a tag array that shares
 // memory with any of those, or with another tag array, is rejected.

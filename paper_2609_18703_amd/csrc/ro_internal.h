@@ -63,6 +63,14 @@ void trace_end(const Launch &L, int kernel);
         ::ro::trace_end((L), (kid));         \
     } while (0)
 
+// Byte ranges [a, a + na) and [b, b + nb) share a byte (NULL or empty: never).
+inline bool overlap(const void *a, int64_t na, const void *b, int64_t nb)
+{
+    if (!a || !b || na <= 0 || nb <= 0) return false;
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + (uintptr_t)nb && y < x + (uintptr_t)na;
+}
+
 constexpr uint32_t kMaxScanEpoch = 65535;
 constexpr uint32_t kMaxCanonEpoch = (1u << 30) - 1;
 

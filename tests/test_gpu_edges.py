@@ -353,6 +353,34 @@ def test_few_parents(ctx, n_parents, fan):
         _batch_case(ctx, counts, queue, k, bar, 48)
 
 
+# The counts lie in the memory of an output: at the front, in the middle and at
+# the end of a key array, or in the offsets' own memory (one tile of parents).
+@pytest.mark.parametrize("n_parents", [40, 4096])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_expand_counts_in_an_outputs_memory(ctx, n_parents, noalloc):
+    import paper_2609_18703_amd as R
+    counts = np.random.default_rng(n_parents).integers(0, 200, n_parents).astype(np.int32)
+    offs, par, ordi = O.expand(counts)
+    n = len(par)
+    for where in ("parent", "ordinal", "offsets"):
+        for at in (0, (n - n_parents) // 2, n - n_parents) if where != "offsets" else (0, n_parents):
+            _say("expand counts in", where, n_parents, n, at)
+            o = torch.full((n_parents + 1,), -1, dtype=torch.int64, device="cuda")
+            tags = {k: torch.full((n,), -1, dtype=torch.int32, device="cuda") for k in ("parent", "ordinal")}
+            home = o.view(torch.int32) if where == "offsets" else tags[where]
+            k = home[at:at + n_parents]
+            k.copy_(torch.from_numpy(counts))
+            if noalloc:
+                R.expand_noalloc(k, o, tags["parent"], tags["ordinal"])
+                torch.cuda.synchronize()
+            else:
+                ctx.expand(k, o, tags["parent"], tags["ordinal"])
+                ctx.check("expand")
+            assert np.array_equal(o.cpu().numpy(), offs)
+            assert np.array_equal(tags["parent"].cpu().numpy().view(np.uint32), par)
+            assert np.array_equal(tags["ordinal"].cpu().numpy().view(np.uint32), ordi)
+
+
 def test_expand_errors_with_few_parents(ctx):
     import paper_2609_18703_amd as R
     tags = [_zeros(8, torch.int32) for _ in range(2)]
