@@ -69,12 +69,13 @@ constexpr int64_t kTagsNtChildren = (int64_t)8 << 20;
 __global__ __launch_bounds__(kBlock) void k_expand_tags(const int64_t *__restrict__ offsets, int64_t P,
                                                         uint32_t *__restrict__ child_parent,
                                                         uint32_t *__restrict__ child_ordinal,
-                                                        int64_t child_cap, int vec_ok)
+                                                        int64_t child_cap, int64_t done_up_to, int vec_ok)
 {
     constexpr int kWaveSpan = 64 * kItems;            // children per wave and step
     __shared__ alignas(16) uint32_t s_stage[kBlock / 64][kWaveSpan];
     const int64_t N = offsets[P];
     if (N > child_cap || N >= ((int64_t)1 << 32)) return;     // reported by the scan
+    if (N <= done_up_to) return;                              // the launch before has written them
     const int lane = lane_id();
     const bool nt = N > kTagsNtChildren;
     uint32_t *stage = s_stage[threadIdx.x >> 6];
@@ -151,11 +152,27 @@ __global__ __launch_bounds__(kBlock) void k_expand_tags(const int64_t *__restric
 // parents, 1M children: 7.6 and 10.1, now 11.6), so a thread takes four children
 // only (16, staged in LDS: 9.6 and 10.7).  LDS holds 32 bits per offset: more
 // children than that are an error and get no keys.
+//
+// The scan in every workgroup and the short spans cost more than they save
+// where there are many children: from 1M (4,096 parents, 4M children: 23.5 us,
+// 18.0 as two launches) to 8M (100 parents, 6M: 13.8 and 17.6; 41M: 70 and 65.5),
+// kSmallKeys / P in between.  The host knows the capacity and not the children:
+// where that allows for more, one workgroup per CU scans, writes the offsets and
+// the keys of a few children, and k_expand_tags follows, which writes the keys
+// of more (4,096 parents, 4M children 16.2 us; 7,000 children of 1,000 parents
+// with room for 41M 8.0, as two launches 14.2).
+constexpr int64_t kSmallKeys = (int64_t)2 << 30;
+static int64_t small_children(int64_t P)
+{
+    const int64_t n = kSmallKeys / (P > 0 ? P : 1);
+    return n < (int64_t)1 << 20 ? (int64_t)1 << 20 : (n > (int64_t)8 << 20 ? (int64_t)8 << 20 : n);
+}
+
 __global__ __launch_bounds__(kBlock) void k_expand_small(const int32_t *__restrict__ counts, int64_t P,
                                                          int64_t *__restrict__ offsets,
                                                          uint32_t *__restrict__ child_parent,
                                                          uint32_t *__restrict__ child_ordinal, int64_t child_cap,
-                                                         int vec_ok, Ctl *ctl)
+                                                         int64_t max_children, int vec_ok, Ctl *ctl)
 {
     typedef uint32_t t4 __attribute__((ext_vector_type(4)));
     __shared__ uint32_t s_off[kTile + 1];
@@ -191,8 +208,7 @@ __global__ __launch_bounds__(kBlock) void k_expand_small(const int32_t *__restri
         }
     }
     __syncthreads();
-    if (N > child_cap || N >= ((int64_t)1 << 32)) return;
-    const bool nt = N > kTagsNtChildren;
+    if (N > child_cap || N > max_children) return;
     for (int64_t c0 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4; c0 < N; c0 += (int64_t)gridDim.x * kBlock * 4) {
         // the last parent starting at or before the thread's first child
         int64_t lo = 0, hi = P;
@@ -209,13 +225,8 @@ __global__ __launch_bounds__(kBlock) void k_expand_small(const int32_t *__restri
             ord[k] = (uint32_t)c - s_off[lo];
         }
         if (vec_ok && c0 + 4 <= N) {
-            if (nt) {
-                if (child_parent) __builtin_nontemporal_store(par, reinterpret_cast<t4 *>(child_parent + c0));
-                if (child_ordinal) __builtin_nontemporal_store(ord, reinterpret_cast<t4 *>(child_ordinal + c0));
-            } else {
-                if (child_parent) *reinterpret_cast<t4 *>(child_parent + c0) = par;
-                if (child_ordinal) *reinterpret_cast<t4 *>(child_ordinal + c0) = ord;
-            }
+            if (child_parent) *reinterpret_cast<t4 *>(child_parent + c0) = par;
+            if (child_ordinal) *reinterpret_cast<t4 *>(child_ordinal + c0) = ord;
         } else {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
@@ -225,6 +236,18 @@ __global__ __launch_bounds__(kBlock) void k_expand_small(const int32_t *__restri
             }
         }
     }
+}
+
+// done_up_to: expansions of that many children have their keys already.
+static hipError_t launch_keys(const Launch &L, const int64_t *offsets, int64_t P, uint32_t *child_parent,
+                              uint32_t *child_ordinal, int64_t child_cap, int64_t done_up_to)
+{
+    const bool aligned = ((reinterpret_cast<uintptr_t>(child_parent) |
+                           reinterpret_cast<uintptr_t>(child_ordinal)) & 15u) == 0;
+    const int64_t grid = (int64_t)L.num_cus * 8;
+    RO_LAUNCH(L, RO_K_EXPAND_TAGS, k_expand_tags, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, offsets, P,
+              child_parent, child_ordinal, child_cap, done_up_to, aligned ? 1 : 0);
+    return hipGetLastError();
 }
 
 hipError_t launch_expand(const Launch &L, const int32_t *counts, int64_t P,
@@ -240,36 +263,29 @@ hipError_t launch_expand(const Launch &L, const int32_t *counts, int64_t P,
     const bool apart = !overlap(counts, P * 4, child_parent, key_bytes) && !overlap(counts, P * 4, child_ordinal, key_bytes) &&
                        !overlap(counts, P * 4, offsets, (P + 1) * 8);
     if (want && P <= kTile && apart) {
-        // the capacity bounds the children, which only the device knows
         const bool aligned = ((reinterpret_cast<uintptr_t>(child_parent) |
                                reinterpret_cast<uintptr_t>(child_ordinal)) & 15u) == 0;
-        const int64_t need = child_cap / (kBlock * 4) + 1, most = (int64_t)L.num_cus * 8;
+        // a capacity for many: only as many workgroups as there are CUs scan
+        const int64_t few = small_children(P), per = kBlock * 4;
+        const bool keys = child_cap > few;
+        const int64_t most = keys ? (int64_t)L.num_cus : (int64_t)L.num_cus * 8, need = child_cap / per + 1;
+        const int64_t here = keys ? most * per : few;
         RO_LAUNCH(L, RO_K_EXPAND_SCAN, k_expand_small, dim3((unsigned)(need < most ? need : most)), dim3(kBlock), 0, L.stream,
-                  counts, P, offsets, child_parent, child_ordinal, child_cap, aligned ? 1 : 0, L.ctl);
+                  counts, P, offsets, child_parent, child_ordinal, child_cap, here, aligned ? 1 : 0, L.ctl);
+        if (keys) return launch_keys(L, offsets, P, child_parent, child_ordinal, child_cap, here);
         return hipGetLastError();
     }
     const int64_t grid = ntiles < (int64_t)L.num_cus * 4 ? ntiles : (int64_t)L.num_cus * 4;
     RO_LAUNCH(L, RO_K_EXPAND_SCAN, k_expand_scan, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, counts, P,
                        offsets, child_cap, want, L.ctl, L.desc, L.desc_cap, ntiles);
-    if (want) {
-        const bool aligned = ((reinterpret_cast<uintptr_t>(child_parent) |
-                               reinterpret_cast<uintptr_t>(child_ordinal)) & 15u) == 0;
-        const int64_t grid2 = (int64_t)L.num_cus * 8;
-        RO_LAUNCH(L, RO_K_EXPAND_TAGS, k_expand_tags, dim3((unsigned)grid2), dim3(kBlock), 0, L.stream, offsets,
-                           P, child_parent, child_ordinal, child_cap, aligned ? 1 : 0);
-    }
+    if (want) return launch_keys(L, offsets, P, child_parent, child_ordinal, child_cap, -1);
     return hipGetLastError();
 }
 
 hipError_t launch_expand_tags(const Launch &L, const int64_t *offsets, int64_t P, uint32_t *child_parent,
                               uint32_t *child_ordinal, int64_t child_cap)
 {
-    const bool aligned = ((reinterpret_cast<uintptr_t>(child_parent) |
-                           reinterpret_cast<uintptr_t>(child_ordinal)) & 15u) == 0;
-    const int64_t grid2 = (int64_t)L.num_cus * 8;
-    RO_LAUNCH(L, RO_K_EXPAND_TAGS, k_expand_tags, dim3((unsigned)grid2), dim3(kBlock), 0, L.stream, offsets, P,
-              child_parent, child_ordinal, child_cap, aligned ? 1 : 0);
-    return hipGetLastError();
+    return launch_keys(L, offsets, P, child_parent, child_ordinal, child_cap, -1);
 }
 
 }  // namespace ro

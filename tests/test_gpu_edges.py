@@ -353,6 +353,43 @@ def test_few_parents(ctx, n_parents, fan):
         _batch_case(ctx, counts, queue, k, bar, 48)
 
 
+# Key arrays with room for more children than one launch takes, for as many as
+# its workgroups take at once (1,024 each, one per CU), one more, more than one
+# launch takes, and none at all.
+@pytest.mark.parametrize("n_parents", [1, 300, 4096])
+def test_expand_with_room_for_many(ctx, n_parents):
+    import paper_2609_18703_amd as R
+    room = 9 << 20
+    here = 1024 * torch.cuda.get_device_properties(0).multi_processor_count
+    tags = [torch.empty(room, dtype=torch.int32, device="cuda") for _ in range(2)]
+    for n in (0, 5, here - 1, here, here + 1, (1 << 20) + 3, (8 << 20) + 5):
+        counts = np.random.default_rng(n).multinomial(n, np.ones(n_parents) / n_parents).astype(np.int32)
+        offs, par, ordi = O.expand(counts)
+        for lo in (0, 1):                                  # on and off their 16-byte alignment
+            _say("expand with room for many", n_parents, n, lo)
+            o = _zeros(n_parents + 1, torch.int64)
+            for t in tags:
+                t.fill_(-1)
+            ctx.expand(D.to_dev(counts), o, *[t[lo:] for t in tags])
+            ctx.check("expand")
+            assert np.array_equal(o.cpu().numpy(), offs)
+            for t, w in zip(tags, (par, ordi)):
+                h = t[lo:].cpu().numpy().view(np.uint32)
+                assert np.array_equal(h[:n], w) and (h[n:] == 0xffffffff).all()
+    for t in tags:
+        t.fill_(-1)
+    big = np.array([room, 1], np.int32)
+    o = _zeros(3, torch.int64)
+    ctx.expand(D.to_dev(big), o, *tags)
+    assert ctx.status() == R.ECAP and o.tolist() == [0, room, room + 1]
+    ctx.expand(D.to_dev(np.array([2 ** 31 - 1, 2 ** 31 - 1], np.int32)), o, *tags)
+    assert ctx.status() == R.ECAP
+    o = _zeros(4, torch.int64)
+    ctx.expand(D.to_dev(np.array([2 ** 31 - 1, 2 ** 31 - 1, 2], np.int32)), o, *tags)
+    assert ctx.status() == R.EOVERFLOW
+    assert all(bool((t == -1).all()) for t in tags)
+
+
 # The counts lie in the memory of an output: at the front, in the middle and at
 # the end of a key array, or in the offsets' own memory (one tile of parents).
 @pytest.mark.parametrize("n_parents", [40, 4096])
