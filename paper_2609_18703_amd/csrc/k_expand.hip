@@ -69,10 +69,12 @@ constexpr int64_t kTagsNtChildren = (int64_t)8 << 20;
 __global__ __launch_bounds__(kBlock) void k_expand_tags(const int64_t *__restrict__ offsets, int64_t P,
                                                         uint32_t *__restrict__ child_parent,
                                                         uint32_t *__restrict__ child_ordinal,
-                                                        int64_t child_cap, int64_t done_up_to, int vec_ok)
+                                                        int64_t child_cap, int64_t done_up_to,
+                                                        const uint32_t *__restrict__ only_if, int vec_ok)
 {
     constexpr int kWaveSpan = 64 * kItems;            // children per wave and step
     __shared__ alignas(16) uint32_t s_stage[kBlock / 64][kWaveSpan];
+    if (only_if && *only_if == 0) return;
     const int64_t N = offsets[P];
     if (N > child_cap || N >= ((int64_t)1 << 32)) return;     // reported by the scan
     if (N <= done_up_to) return;                              // the launch before has written them
@@ -238,15 +240,17 @@ __global__ __launch_bounds__(kBlock) void k_expand_small(const int32_t *__restri
     }
 }
 
-// done_up_to: expansions of that many children have their keys already.
+// done_up_to: expansions of that many children have their keys already; only_if
+// (or null): a device word, 0 for nothing to do.
 static hipError_t launch_keys(const Launch &L, const int64_t *offsets, int64_t P, uint32_t *child_parent,
-                              uint32_t *child_ordinal, int64_t child_cap, int64_t done_up_to)
+                              uint32_t *child_ordinal, int64_t child_cap, int64_t done_up_to,
+                              const uint32_t *only_if = nullptr)
 {
     const bool aligned = ((reinterpret_cast<uintptr_t>(child_parent) |
                            reinterpret_cast<uintptr_t>(child_ordinal)) & 15u) == 0;
     const int64_t grid = (int64_t)L.num_cus * 8;
     RO_LAUNCH(L, RO_K_EXPAND_TAGS, k_expand_tags, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, offsets, P,
-              child_parent, child_ordinal, child_cap, done_up_to, aligned ? 1 : 0);
+              child_parent, child_ordinal, child_cap, done_up_to, only_if, aligned ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -283,9 +287,9 @@ hipError_t launch_expand(const Launch &L, const int32_t *counts, int64_t P,
 }
 
 hipError_t launch_expand_tags(const Launch &L, const int64_t *offsets, int64_t P, uint32_t *child_parent,
-                              uint32_t *child_ordinal, int64_t child_cap)
+                              uint32_t *child_ordinal, int64_t child_cap, const uint32_t *only_if)
 {
-    return launch_keys(L, offsets, P, child_parent, child_ordinal, child_cap, -1);
+    return launch_keys(L, offsets, P, child_parent, child_ordinal, child_cap, -1, only_if);
 }
 
 }  // namespace ro

@@ -47,16 +47,24 @@ __device__ __forceinline__ uint32_t word_share(int64_t w, int64_t st, int64_t en
 
 // Validates the expansion once: offsets[0] = 0, nondecreasing, offsets[P] = N.
 // Marks the parents without children complete: the first emission takes them.
+// Notes the offsets, and whether any differs from the last ones: a reset
+// stream's may, and then its child -> parent map is built again (10M children:
+// 30 us a reset; the comparison and a launch that finds nothing to do take 8).
 __global__ void k_stream_check(const int64_t *__restrict__ offsets, int64_t P, int64_t N, uint64_t *__restrict__ ready,
-                               Ctl *ctl)
+                               int64_t *__restrict__ mapped, uint32_t *__restrict__ remap, Ctl *ctl)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool bad = (g == 0) && (offsets[0] != 0 || offsets[P] != N);
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     for (int64_t w = g >> 6; w * 64 < P; w += nwaves) {
         const int64_t p = w * 64 + lane_id();
-        const int64_t k = p < P ? offsets[p + 1] - offsets[p] : 1;
+        const int64_t st = p < P ? offsets[p] : 0;
+        const int64_t k = p < P ? offsets[p + 1] - st : 1;
         if (k < 0) bad = true;
+        if (p < P && mapped[p] != st) {
+            mapped[p] = st;
+            *remap = 1;
+        }
         const uint64_t m = __ballot(k == 0);
         if (lane_id() == 0) ready[w] = m;
     }
@@ -506,9 +514,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 // for children of emitted parents, and those were all reported.
 __global__ void k_stream_clear(uint32_t *__restrict__ seen, int64_t n_seen, uint32_t *__restrict__ words,
                                int64_t n_words, uint8_t *__restrict__ emitted, uint8_t *__restrict__ barrier,
-                               int64_t n_emitted)
+                               int64_t n_emitted, uint32_t *__restrict__ remap)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g == 0) *remap = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = g; i < n_seen; i += stride) seen[i] = 0;
     for (int64_t i = g; i < n_words; i += stride) words[i] = 0;
@@ -521,14 +530,15 @@ __global__ void k_stream_clear(uint32_t *__restrict__ seen, int64_t n_seen, uint
 hipError_t launch_stream_reset(const Launch &L, StreamState &s)
 {
     RO_LAUNCH(L, RO_K_MISC, k_stream_clear, dim3((unsigned)L.num_cus * 4), dim3(256), 0, L.stream, s.seen,
-              (s.N + 31) / 32 + 1, s.words, stream_word_count(s.N), s.emitted, s.barrier, s.P);
-    return launch_stream_init(L, s);
+              (s.N + 31) / 32 + 1, s.words, stream_word_count(s.N), s.emitted, s.barrier, s.P, s.remap);
+    const hipError_t e = launch_stream_init(L, s);
+    return e != hipSuccess ? e : launch_expand_tags(L, s.offsets, s.P, s.cpar, nullptr, s.N, s.remap);
 }
 
 hipError_t launch_stream_init(const Launch &L, StreamState &s)
 {
     RO_LAUNCH(L, RO_K_MISC, k_stream_check, dim3((unsigned)L.num_cus), dim3(256), 0, L.stream, s.offsets, s.P,
-              s.N, s.ready, L.ctl);
+              s.N, s.ready, s.mapped, s.remap, L.ctl);
     return hipGetLastError();
 }
 

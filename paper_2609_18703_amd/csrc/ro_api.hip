@@ -627,6 +627,8 @@ int ro_stream_create(ro_ctx *c, const int64_t *offsets, int64_t n_parents, int64
         (size_t)(P + 1) * sizeof(uint64_t),                 // gkey
         (size_t)(P + 1),                                    // ebar
         (size_t)(N > 0 ? N : 1) * sizeof(uint32_t),         // cpar
+        (size_t)(P + 1) * sizeof(int64_t),                  // mapped
+        sizeof(uint32_t),                                   // remap
     };
     constexpr int kArrays = (int)(sizeof(sizes) / sizeof(sizes[0]));
     size_t offs[kArrays], total = 0;
@@ -665,6 +667,8 @@ int ro_stream_create(ro_ctx *c, const int64_t *offsets, int64_t n_parents, int64
     st.gkey = (uint64_t *)(block + offs[10]);
     st.ebar = (uint8_t *)(block + offs[11]);
     st.cpar = (uint32_t *)(block + offs[12]);
+    st.mapped = (int64_t *)(block + offs[13]);
+    st.remap = (uint32_t *)(block + offs[14]);
     st.barrier = barrier;
     st.run_epoch = 1;
     st.gf_epoch = 0;

@@ -199,6 +199,44 @@ def test_stream_reset_replays(ctx, run_left):
         assert empties <= set(got[r * len(waves)]["parent"].tolist()), r
 
 
+def test_stream_reset_with_other_offsets(ctx):
+    """The offsets of a reset stream may be others of the same P and N: the
+    batches, reports and emissions of the next run follow them."""
+    rng = np.random.default_rng(22)
+    first = rng.integers(0, 9, 3000).astype(np.int32)
+    offsets = torch.zeros(len(first) + 1, dtype=torch.int64, device="cuda")
+    n = int(first.sum())
+    st = None
+    for run, counts in enumerate((first, rng.permutation(first), first[::-1].copy())):
+        offs, par, ordi = O.expand(counts)
+        ctx.expand(D.to_dev(counts), offsets)
+        if st is None:
+            st = ctx.stream(offsets, n)
+        else:
+            st.reset()
+        queue = rng.permutation(n).astype(np.uint32)
+        tags = [torch.full((n,), -1, dtype=torch.int32, device="cuda") for _ in range(2)]
+        _say("stream reset with other offsets", run)
+        st.batch(_i32(queue), None, 64, None, *tags)
+        ctx.check("batch")
+        assert np.array_equal(_u32(tags[0], n), par[queue]) and np.array_equal(_u32(tags[1], n), ordi[queue])
+        off = 7 * np.arange(n + 1, dtype=np.int64)
+        data = rng.integers(0, 256, 7 * n, dtype=np.uint8)
+        held = D.to_dev(data)                       # read when the parents are emitted
+        st.report(*tags, torch.zeros(n, dtype=torch.uint8, device="cuda"), D.to_dev(off), held)
+        ep = torch.full((len(counts),), -1, dtype=torch.int32, device="cuda")
+        eo = torch.zeros(len(counts) + 1, dtype=torch.int64, device="cuda")
+        ed = torch.zeros(7 * n, dtype=torch.uint8, device="cuda")
+        st.emit(ep, eo, ed)
+        ctx.check("emission")
+        assert np.array_equal(_u32(ep, len(counts)), np.arange(len(counts)))
+        assert np.array_equal(eo.cpu().numpy(), 7 * offs)
+        at = np.empty(n, np.int64)
+        at[queue] = np.arange(n)
+        assert np.array_equal(ed.cpu().numpy(), data.reshape(n, 7)[at].ravel())
+    st.close()
+
+
 @pytest.mark.parametrize("seed", [0, 1, 2])
 def test_stream_mixed_states_and_empty_parents(ctx, seed):
     rng = np.random.default_rng(seed)
