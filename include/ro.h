@@ -278,7 +278,8 @@ int ro_broadcast(ro_ctx *ctx, const uint32_t *const *maps, const int64_t *map_le
  * generation-fence).  One Grain per child of an expansion: READY at
  * generation 0 when created or reset; reservation moves it to IN-FLIGHT, a
  * retry back to READY at the next generation, an accepted report seals it.
- * The state lives in device memory allocated here (about 9 bytes per child). */
+ * The state lives in device memory allocated here (about 13 bytes per child;
+ * ro_grains_commit adds 16 per report of its largest call). */
 enum { RO_WAITING = 0, RO_READY = 1, RO_IN_FLIGHT = 2, RO_SEALED = 3 };
 typedef struct ro_grains ro_grains;
 int ro_grains_create(ro_ctx *ctx, int64_t n_children, ro_grains **out);

@@ -14,32 +14,42 @@
 // load and every atomic).  Reserving sets the child's in-flight bit, which also
 // catches a child named twice and a sealed one (sealing leaves the bit set).
 //
-// A commit call first validates and tests the fence, then finds the children
-// with several passing reports, the first of each (in report order), and lists
-// their reports; every other report is settled by then, accepted or stale.  Its
-// last pass takes the list, 16 lanes to a report: the first is accepted,
-// another one's state and bytes are compared with it, 16 bytes a lane and load.
+// A commit call first validates and tests the fence, and finds the children
+// with several passing reports and the first of each (in report order).  Every
+// other report is accepted or stale; of those the first is accepted, another
+// one's state and bytes are compared with it by 16 lanes, 16 bytes a lane and
+// load.
 //
 // Random returning atomics reach about 26 x 10^9 a second on this chip however
 // small the bitmap is (10M reservations: 387 us on 1.25 MB, 441 on records of
 // 160 MB; now 108).  So a large call sorts its children into at most 512 bins of
 // neighbours first, in LDS tile by tile and with coalesced stores, and one
-// workgroup per bin then sets the bits in LDS (use_bins); a smaller one sets
-// them by atomics in one pass less.  A commit of 10.2M reports with 1.2% repeats
-// in random order takes 350 us (two passes over records: 1,330, of them 820 in
-// the second, where a wave compared its lanes' repeats one by one, byte by byte).
+// workgroup per bin then sets the bits in LDS (use_bins).  A commit of 10.2M
+// reports with 1.2% repeats in random order takes 350 us (two passes over
+// records: 1,330, of them 820 in the second, where a wave compared its lanes'
+// repeats one by one, byte by byte).
+//
+// A smaller call goes by atomics, in two passes whose cost follows its reports
+// and not the table.  A commit seals every child that passes, so a child's entry
+// of `first` and its contested bit serve one commit between two resets, and only
+// the reset clears them.  (Bitmaps cleared by each call took a third pass, which
+// swept the table: 1,000 reports a commit 15.8 us on 100,000 children and 40 on
+// 400M, now 12.9 and 20; 300,000 on 400M 90 and 57.)
 #include "ro_copy.h"
 
 namespace ro {
 
 constexpr int kGItems = 4;
 
-// Sets the bits of the wave's children (lanes with valid set) in a bitmap whose
-// words lie kStride apart, and returns whether each was set before.  Children
-// that follow one another, as in a queue in canonical order, share their words:
-// one atomic per word instead of one per child.  Called by all lanes of the wave.
-template <int kStride>
-__device__ __forceinline__ bool claim_bit(uint32_t *bits, uint32_t c, bool valid)
+// cidx of a report that did not pass the fence, and of one that is not counted;
+// kNone also in `first`, for no report
+constexpr uint32_t kStale = 0xfffffffeu, kNone = 0xffffffffu;
+
+// Sets the in-flight bits of the wave's children (lanes with valid set) and
+// returns whether each was set before.  Children that follow one another, as in
+// a queue in canonical order, share their words: one atomic per word instead of
+// one per child.  Called by all lanes of the wave.
+__device__ __forceinline__ bool claim_bit(GrainBits *bits, uint32_t c, bool valid)
 {
     const int lane = lane_id();
     const uint32_t c0 = (uint32_t)uni32((int32_t)c);
@@ -49,25 +59,38 @@ __device__ __forceinline__ bool claim_bit(uint32_t *bits, uint32_t c, bool valid
         uint32_t old = 0;
         if (lead == lane) {
             const int len = 32 - j < 64 - lane ? 32 - j : 64 - lane;
-            old = __hip_atomic_fetch_or(&bits[(int64_t)(c >> 5) * kStride], (0xffffffffu >> (32 - len)) << j,
-                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            old = __hip_atomic_fetch_or(&bits[c >> 5].inflight, (0xffffffffu >> (32 - len)) << j, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
         }
         old = (uint32_t)__shfl((int)old, lead, 64);
         return (old >> j) & 1u;
     }
     if (!valid) return false;
     const uint32_t bit = 1u << (c & 31u);
-    const uint32_t old = __hip_atomic_fetch_or(&bits[(int64_t)(c >> 5) * kStride], bit, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-    return (old & bit) != 0;
+    return (__hip_atomic_fetch_or(&bits[c >> 5].inflight, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) != 0;
 }
 
-// Every child READY at generation 0: the bitmaps (and the call's, which are
-// clear between calls) to zero.
-__global__ void k_grains_fill(uint4 *__restrict__ bits, int64_t n)
+// The same for the sealed bits, which nobody asks for.
+__device__ __forceinline__ void seal_bit(GrainBits *bits, uint32_t c, bool valid)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        bits[i] = make_uint4(0, 0, 0, 0);
+    const int lane = lane_id();
+    const uint32_t c0 = (uint32_t)uni32((int32_t)c);
+    const int j = (int)(c & 31u);
+    uint32_t m = valid ? 1u << j : 0u;
+    if (__ballot(valid && c == c0 + (uint32_t)lane) == ~0ull) {
+        const int len = 32 - j < 64 - lane ? 32 - j : 64 - lane;
+        m = lane == 0 || j == 0 ? (0xffffffffu >> (32 - len)) << j : 0u;
+    }
+    if (m) __hip_atomic_fetch_or(&bits[c >> 5].sealed, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Every child READY at generation 0, with no report: the bitmaps and the bins'
+// counts to zero, `first` to no report.
+__global__ void k_grains_fill(uint4 *__restrict__ zero, int64_t n_zero, uint4 *__restrict__ first, int64_t n_first)
+{
+    const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = tid; i < n_zero; i += stride) zero[i] = make_uint4(0, 0, 0, 0);
+    for (int64_t i = tid; i < n_first; i += stride) first[i] = make_uint4(kNone, kNone, kNone, kNone);
 }
 
 // Phase and generation of every Grain, for inspection.
@@ -100,7 +123,7 @@ __global__ __launch_bounds__(kBlock) void k_grains_dispatch(const uint32_t *__re
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) retried[k] = ok[k] && out_gen ? g.bits[c[k] >> 5].retried : 0u;
 #pragma unroll
-        for (int k = 0; k < kGItems; ++k) set[k] = claim_bit<4>(&g.bits->inflight, c[k], ok[k]);
+        for (int k = 0; k < kGItems; ++k) set[k] = claim_bit(g.bits, c[k], ok[k]);
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) {
             if (!ok[k]) continue;
@@ -162,6 +185,7 @@ __global__ __launch_bounds__(kBlock) void k_grains_retry(const uint32_t *__restr
 struct Bins {
     int shift, n;
 };
+constexpr int kMaxBinShift = 17;
 
 // Adds one to the counter of every valid lane's bin; returns what it held
 // before (a value of its own per lane).  Lanes of one bin, as in a queue in
@@ -181,14 +205,12 @@ __device__ __forceinline__ uint32_t bin_rank(uint32_t *s_cnt, uint32_t b, bool v
     return valid ? atomicAdd(&s_cnt[b], 1u) : 0u;
 }
 
-// cidx of a report that did not pass the fence, and of one that is not counted
-constexpr uint32_t kStale = 0xfffffffeu, kNone = 0xffffffffu;
 
 // Pass 1: validation and the fence.  Per report its provisional outcome in
 // state_out (its state if it passed, RO_PENDING if not) and, if it passed, its
-// child in cidx.  Two reports of one child meet at its bit of the call's
-// bitmap; the later one marks the child contested and clears its entry of
-// `first` for the next pass.  With bins only the reports per bin are counted.
+// child in cidx.  Two reports of one child meet at its entry of `first`, which
+// ends as the smaller index; the later to arrive marks the child contested.
+// With bins only the reports per bin are counted.
 template <bool kBins>
 __global__ __launch_bounds__(kBlock) void k_grains_first(
     const uint32_t *__restrict__ rp, const uint32_t *__restrict__ ro_, const uint8_t *__restrict__ rs,
@@ -202,7 +224,7 @@ __global__ __launch_bounds__(kBlock) void k_grains_first(
         __syncthreads();
     }
     if (blockIdx.x == 0 && threadIdx.x < 4 && counts) counts[threadIdx.x] = 0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *g.n_list = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 2) g.n_list[threadIdx.x] = 0;
     int err = 0;
     const int64_t span = (int64_t)kBlock * kGItems;
     for (int64_t base = (int64_t)blockIdx.x * span; base < n; base += (int64_t)gridDim.x * span) {
@@ -251,8 +273,13 @@ __global__ __launch_bounds__(kBlock) void k_grains_first(
         }
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) {
-            if constexpr (kBins) (void)bin_rank(s_hist, c[k] >> bins.shift, ok[k]);
-            met[k] = kBins ? false : claim_bit<1>(g.met, c[k], ok[k]);
+            met[k] = false;
+            if constexpr (kBins) {
+                (void)bin_rank(s_hist, c[k] >> bins.shift, ok[k]);
+            } else if (ok[k]) {
+                const uint32_t i = (uint32_t)(base + k * kBlock + threadIdx.x);
+                met[k] = __hip_atomic_fetch_min(&g.first[c[k]], i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kNone;
+            }
         }
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) {
@@ -260,11 +287,9 @@ __global__ __launch_bounds__(kBlock) void k_grains_first(
             if (i >= n) continue;
             state_out[i] = ok[k] ? (uint8_t)s[k] : (uint8_t)RO_PENDING;
             if (kBins || ok[k]) cidx[i] = ok[k] ? c[k] : (s[k] == RO_PENDING ? kNone : kStale);
-            if (met[k]) {
+            if (met[k])
                 __hip_atomic_fetch_or(&g.contested[c[k] >> 5], 1u << (c[k] & 31u), __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
-                g.first[c[k]] = 0xffffffffu;
-            }
         }
     }
     if constexpr (kBins) {
@@ -276,38 +301,102 @@ __global__ __launch_bounds__(kBlock) void k_grains_first(
     if (err) raise_err(ctl, err);
 }
 
-// Pass 2: a report that did not pass is stale, one of a child with no other
-// report is accepted; those of contested children are listed, and the first of
-// them recorded.  The list is gathered in LDS: one atomic on its length per
-// wave took 980 us for 10M reports.
-constexpr int kListBuf = 2 * kBlock * kGItems;
+// Settles contested reports, one per lane with `have` set: report i, whose child's
+// first one is first[c].  Another than that is a duplicate if state, length and (for
+// SUCCESS) bytes are the same, a conflict otherwise.  Returns 0 for the first
+// itself, 1 for a duplicate, 2 for a conflict, -1 without a report.  A wave looks
+// at 64 reports at once, which is a chain of four loads, queues the comparisons
+// in LDS, and takes four of them at a time with 16 lanes each (taking a report's
+// chain by 16 lanes: 118 us for 240,000 listed reports, now 90).  The bytes go
+// 16 to a lane and load, four loads of each copy in flight; the last load of a
+// record overlaps the one before, so that none reads past its end.
+constexpr int kCmpLanes = 16, kCmpSteps = 4;
 
-__device__ __forceinline__ void flush_list(uint32_t *list, uint32_t *n_list, const uint32_t *s_buf, uint32_t n,
-                                           uint32_t *s_at)
+struct CmpJobs {
+    int64_t a[64], b[64], len[64];
+    int32_t diff[64];
+};
+
+__device__ __forceinline__ int settle_wave(bool have, int64_t i, uint32_t c, const uint8_t *__restrict__ rs,
+                                           const int64_t *__restrict__ roff, const uint8_t *__restrict__ data,
+                                           const uint32_t *__restrict__ first, uint8_t *__restrict__ state_out,
+                                           CmpJobs &jobs)
 {
-    if (threadIdx.x == 0) *s_at = __hip_atomic_fetch_add(n_list, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < n; j += blockDim.x) list[*s_at + j] = s_buf[j];
-    __syncthreads();
+    const int lane = lane_id(), sub = lane & (kCmpLanes - 1);
+    int kind = -1;
+    int64_t a = 0, b = 0, len = 0;
+    bool job = false;
+    if (have) {
+        const uint32_t s = rs[i];
+        b = roff[i];
+        len = roff[i + 1] - b;
+        const int64_t v = first[c];
+        kind = 0;
+        if (v != i) {
+            a = roff[v];
+            const bool same = rs[v] == s && (s != RO_SUCCESS || roff[v + 1] - a == len);
+            job = same && s == RO_SUCCESS && data != nullptr && len > 0;
+            kind = same ? 1 : 2;
+            state_out[i] = RO_PENDING;
+        }
+    }
+    const uint64_t jm = __ballot(job);
+    const int slot = (int)__popcll(jm & ((1ull << lane) - 1ull)), nj = (int)__popcll(jm);
+    if (job) {
+        jobs.a[slot] = a;
+        jobs.b[slot] = b;
+        jobs.len[slot] = len;
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int q = lane / kCmpLanes; q < nj; q += 64 / kCmpLanes) {
+        const uint8_t *pa = data + jobs.a[q], *pb = data + jobs.b[q];
+        const int64_t l = jobs.len[q];
+        uint32_t diff = 0;
+        if (l < 16) {
+            if (sub < l) diff = (uint32_t)(pa[sub] ^ pb[sub]);
+        } else {
+            constexpr int64_t kStep = 16 * kCmpLanes * kCmpSteps;
+            for (int64_t x = (int64_t)sub * 16; x < l && diff == 0; x += kStep) {
+                v4u32 A[kCmpSteps], B[kCmpSteps];
+#pragma unroll
+                for (int u = 0; u < kCmpSteps; ++u) {
+                    const int64_t y = min64(x + u * (16 * kCmpLanes), l - 16);
+                    A[u] = ld16v(reinterpret_cast<uint64_t>(pa + y));
+                    B[u] = ld16v(reinterpret_cast<uint64_t>(pb + y));
+                }
+#pragma unroll
+                for (int u = 0; u < kCmpSteps; ++u) {
+                    const v4u32 d = A[u] ^ B[u];
+                    diff |= d.x | d.y | d.z | d.w;
+                }
+            }
+        }
+        // lanes of this comparison that found a difference
+        const uint64_t dm = __ballot(diff != 0) >> (lane & ~(kCmpLanes - 1));
+        if (sub == 0) jobs.diff[q] = (dm & ((1u << kCmpLanes) - 1u)) != 0;
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (job && jobs.diff[slot]) kind = 2;
+    __builtin_amdgcn_wave_barrier();
+    return kind;
 }
 
-__global__ __launch_bounds__(kBlock) void k_grains_decide(const uint8_t *__restrict__ rs, int64_t n, GrainTab g,
+// Pass 2 of a call without bins: the children of passing reports become sealed
+// (also after a bad report); a report that did not pass is stale, one of a child
+// with no other report is accepted, those of contested children are settled.
+__global__ __launch_bounds__(kBlock) void k_grains_decide(const uint8_t *__restrict__ rs,
+                                                          const int64_t *__restrict__ roff,
+                                                          const uint8_t *__restrict__ data, int64_t n, GrainTab g,
                                                           const uint32_t *__restrict__ cidx,
-                                                          uint32_t *__restrict__ list,
-                                                          const uint8_t *__restrict__ state_out, int64_t *counts,
-                                                          Ctl *ctl)
+                                                          uint8_t *__restrict__ state_out, int64_t *counts, Ctl *ctl)
 {
     __shared__ int64_t s_wave[kBlock / 64];
-    __shared__ uint32_t s_buf[kListBuf];
-    __shared__ uint32_t s_n, s_at;
+    __shared__ CmpJobs s_jobs[kBlock / 64];
     __shared__ int32_t s_err;
-    if (threadIdx.x == 0) {
-        s_err = read_err(ctl);                       // the first pass found a bad report
-        s_n = 0;
-    }
+    if (threadIdx.x == 0) s_err = read_err(ctl);     // the first pass found a bad report
     __syncthreads();
-    if (s_err) return;
-    int64_t accepted = 0, stale = 0;
+    const bool bad = s_err != 0;
+    int64_t cnt[4] = {0, 0, 0, 0};                   // accepted, stale, duplicate, conflict
     const int64_t span = (int64_t)kBlock * kGItems;
     for (int64_t base = (int64_t)blockIdx.x * span; base < n; base += (int64_t)gridDim.x * span) {
         uint32_t so[kGItems], s[kGItems], c[kGItems], w[kGItems];
@@ -319,32 +408,30 @@ __global__ __launch_bounds__(kBlock) void k_grains_decide(const uint8_t *__restr
             c[k] = so[k] != RO_PENDING ? cidx[i] : 0u;
         }
 #pragma unroll
-        for (int k = 0; k < kGItems; ++k) w[k] = so[k] != RO_PENDING ? g.contested[c[k] >> 5] : 0u;
+        for (int k = 0; k < kGItems; ++k) w[k] = so[k] != RO_PENDING ? g.contested[c[k] >> 5] >> (c[k] & 31u) & 1u : 0u;
+#pragma unroll
+        for (int k = 0; k < kGItems; ++k) seal_bit(g.bits, c[k], so[k] != RO_PENDING);
+        if (bad) continue;
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) {
-            const int64_t i = base + k * kBlock + threadIdx.x;
-            if (so[k] == RO_PENDING) {
-                stale += s[k] != RO_PENDING;
-            } else if ((w[k] >> (c[k] & 31u)) & 1u) {
-                s_buf[atomicAdd(&s_n, 1u)] = (uint32_t)i;
-                __hip_atomic_fetch_min(&g.first[c[k]], (uint32_t)i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                ++accepted;
-            }
+            const bool two = w[k] != 0;
+            cnt[0] += so[k] != RO_PENDING && !two;
+            cnt[1] += so[k] == RO_PENDING && s[k] != RO_PENDING;
+            if (__ballot(two) == 0) continue;
+            const int kind = settle_wave(two, base + k * kBlock + threadIdx.x, c[k], rs, roff, data, g.first, state_out,
+                                         s_jobs[threadIdx.x >> 6]);
+            cnt[0] += kind == 0;
+            cnt[2] += kind == 1;
+            cnt[3] += kind == 2;
         }
-        __syncthreads();
-        const uint32_t m = s_n;
-        if (m > kListBuf / 2) {                      // the next round might not fit
-            flush_list(list, g.n_list, s_buf, m, &s_at);
-            if (threadIdx.x == 0) s_n = 0;
-        }
-        __syncthreads();
     }
-    if (s_n) flush_list(list, g.n_list, s_buf, s_n, &s_at);
-    if (counts) {
-        const int64_t a = block_sum(accepted, s_wave), b = block_sum(stale, s_wave);
-        if (threadIdx.x == 0 && a) __hip_atomic_fetch_add(&counts[0], a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (threadIdx.x == 0 && b) __hip_atomic_fetch_add(&counts[1], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (counts && !bad) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t t = block_sum(cnt[q], s_wave);
+            if (threadIdx.x == 0 && t)
+                __hip_atomic_fetch_add(&counts[q], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
 }
 
@@ -404,9 +491,8 @@ __device__ __forceinline__ uint32_t split_tile(const uint32_t (&c)[kIt], const b
 }
 
 // A large reservation: generations out and the children into the bins.  A bin
-// has room for each of its children once (its stretch of `first`, which only a
-// commit call uses otherwise); a child beyond that, in a bin where some child
-// is named twice, sets its bit here.
+// has room for each of its children once (its stretch of `room`); a child beyond
+// that, in a bin where some child is named twice, sets its bit here.
 constexpr int kDispIt = 16;
 
 __global__ __launch_bounds__(kSplitTh) void k_grains_dispatch_split(const uint32_t *__restrict__ child, int64_t n,
@@ -445,7 +531,7 @@ __global__ __launch_bounds__(kSplitTh) void k_grains_dispatch_split(const uint32
             const uint32_t x = s_k[j], b = x >> bins.shift, at = s_base[b] + j;
             const int64_t slot = ((int64_t)b << bins.shift) + at;
             if (at < (1u << bins.shift) && slot < N) {
-                g.first[slot] = x;
+                g.room[slot] = x;
             } else {
                 const uint32_t bit = 1u << (x & 31u);
                 if (__hip_atomic_fetch_or(&g.bits[x >> 5].inflight, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)
@@ -472,7 +558,7 @@ __global__ __launch_bounds__(kSplitTh) void k_grains_dispatch_bins(int64_t N, Gr
     bool twice = false;
 #pragma unroll 4
     for (int64_t j = threadIdx.x; j < cnt; j += kSplitTh) {
-        const uint32_t x = g.first[c0 + j] & mask, bit = 1u << (x & 31u);
+        const uint32_t x = g.room[c0 + j] & mask, bit = 1u << (x & 31u);
         if (atomicOr(&s_bits[x >> 5], bit) & bit) twice = true;
     }
     __syncthreads();
@@ -531,14 +617,19 @@ __global__ __launch_bounds__(kSplitTh) void k_grains_split(int64_t n, GrainTab g
 }
 
 // Third pass, one workgroup per bin: the children become sealed; those met
-// twice are contested, and where there are any the bin is read again to list
-// their reports and find the first of each.
+// twice are contested and get neighbouring entries of `room`, and the bin is
+// read again to list their reports, each with its child's entry, and to find
+// the first of each there.  The list is gathered in LDS: one atomic on its
+// length per wave took 980 us for 10M reports.  (120,000 contested of 10M children fill half a
+// megabyte; found at the children's own places, 53 and 88 us here and in the
+// last pass, now 46 and 84).
 __global__ __launch_bounds__(kSplitTh) void k_grains_bins(GrainTab g, Bins bins, const uint2 *__restrict__ pair,
-                                                          uint32_t *__restrict__ list, int64_t *counts)
+                                                          uint32_t *__restrict__ list, uint32_t *__restrict__ entry,
+                                                          int64_t *counts)
 {
     extern __shared__ uint32_t s_bits[];
-    __shared__ uint32_t s_w[kGrainBins / 64], s_buf[2 * kSplitTh];
-    __shared__ uint32_t s_start, s_any, s_n, s_at;
+    __shared__ uint32_t s_w[kSplitTh / 64], s_buf[2 * kSplitTh], s_ent[2 * kSplitTh];
+    __shared__ uint32_t s_start, s_any, s_n, s_at, s_slot;
     const int tid = (int)threadIdx.x;
     const uint32_t mask = (1u << bins.shift) - 1u;
     const int words = 1 << (bins.shift - 5);
@@ -564,30 +655,63 @@ __global__ __launch_bounds__(kSplitTh) void k_grains_bins(GrainTab g, Bins bins,
     }
     if (any) s_any = 1;
     __syncthreads();
-    const int64_t c0 = (int64_t)blockIdx.x << bins.shift;
-    GrainBits *dst = g.bits + (c0 >> 5);
-    for (int w = tid; w < words; w += kSplitTh) {
+    GrainBits *dst = g.bits + ((int64_t)blockIdx.x << (bins.shift - 5));
+    for (int w = tid; w < words; w += kSplitTh)
         if (s_bits[w]) dst[w].sealed |= s_bits[w];
-        for (uint32_t m = s_two[w]; m; m &= m - 1)
-            __hip_atomic_store(&g.first[c0 + w * 32 + (__ffs(m) - 1)], 0xffffffffu, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    }
     uint32_t listed = 0;
     if (s_any) {
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // `first` is set before anyone lowers it
+        __syncthreads();
+        // s_bits[w]: contested children before word w, of the kWords words of a thread
+        constexpr int kWords = (1 << (kMaxBinShift - 5)) / kSplitTh;
+        uint32_t two[kWords], own = 0;
+#pragma unroll
+        for (int q = 0; q < kWords; ++q) {
+            two[q] = tid * kWords + q < words ? (uint32_t)__popc(s_two[tid * kWords + q]) : 0u;
+            own += two[q];
+        }
+        const uint32_t inc = (uint32_t)wave_incl_sum_dpp(own);
+        if (lane_id() == 63) s_w[tid >> 6] = inc;
+        __syncthreads();
+        uint32_t before = inc - own, all = 0;
+#pragma unroll
+        for (int v = 0; v < kSplitTh / 64; ++v) {
+            before += v < (tid >> 6) ? s_w[v] : 0u;
+            all += s_w[v];
+        }
+        if (tid == 0) s_slot = __hip_atomic_fetch_add(g.n_list + 1, all, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int q = 0; q < kWords; ++q) {
+            if (tid * kWords + q < words) s_bits[tid * kWords + q] = before;
+            before += two[q];
+        }
+        __syncthreads();
+        uint32_t *room = g.room + s_slot;
+        for (uint32_t j = tid; j < all; j += kSplitTh)
+            __hip_atomic_store(&room[j], kNone, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // they are set before anyone lowers them
         __syncthreads();
         for (uint32_t j0 = 0; j0 < cnt; j0 += kSplitTh) {
             const uint32_t j = j0 + tid;
             const uint2 e = j < cnt ? pp[j] : make_uint2(0, 0);
-            const uint32_t x = e.x & mask;
-            if (j < cnt && ((s_two[x >> 5] >> (x & 31u)) & 1u)) {
-                s_buf[atomicAdd(&s_n, 1u)] = e.y;
-                __hip_atomic_fetch_min(&g.first[e.x], e.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t x = e.x & mask, m2 = s_two[x >> 5], bit = 1u << (x & 31u);
+            if (j < cnt && (m2 & bit)) {
+                const uint32_t r = s_bits[x >> 5] + (uint32_t)__popc(m2 & (bit - 1u)), at = atomicAdd(&s_n, 1u);
+                s_buf[at] = e.y;
+                s_ent[at] = s_slot + r;
+                __hip_atomic_fetch_min(&room[r], e.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             __syncthreads();
             const uint32_t m = s_n;
             if (m > kSplitTh || j0 + kSplitTh >= cnt) {
-                if (m) flush_list(list, g.n_list, s_buf, m, &s_at);
+                if (m) {
+                    if (tid == 0) s_at = __hip_atomic_fetch_add(g.n_list, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __syncthreads();
+                    for (uint32_t k = tid; k < m; k += kSplitTh) {
+                        list[s_at + k] = s_buf[k];
+                        entry[s_at + k] = s_ent[k];
+                    }
+                    __syncthreads();
+                }
                 listed += m;
                 if (tid == 0) s_n = 0;
             }
@@ -598,99 +722,27 @@ __global__ __launch_bounds__(kSplitTh) void k_grains_bins(GrainTab g, Bins bins,
         __hip_atomic_fetch_add(&counts[0], (int64_t)(cnt - listed), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Last pass: in a call without bins its children become sealed and its bitmaps
-// are cleared; then the listed reports are settled.  Another one than the
-// child's first is a duplicate if state, length and (for SUCCESS) bytes are the
-// same, a conflict otherwise.  A wave looks at 64 reports at once, which is a
-// chain of four loads, queues the comparisons in LDS, and takes four of them
-// at a time with 16 lanes each (taking a report's chain by 16 lanes: 118 us for
-// 240,000 listed reports, now 90).  The bytes go 16 to a lane and load, four
-// loads of each copy in flight; the last load of a record overlaps the one
-// before, so that none reads past its end.
-constexpr int kCmpLanes = 16, kCmpSteps = 4;
-
+// Last pass of a large call: the listed reports are settled.
 __global__ __launch_bounds__(kBlock) void k_grains_settle(const uint8_t *__restrict__ rs,
                                                           const int64_t *__restrict__ roff,
-                                                          const uint8_t *__restrict__ data, GrainTab g, int64_t words,
-                                                          const uint32_t *__restrict__ cidx,
+                                                          const uint8_t *__restrict__ data, GrainTab g,
                                                           const uint32_t *__restrict__ list,
+                                                          const uint32_t *__restrict__ entry,
                                                           uint8_t *__restrict__ state_out, int64_t *counts, Ctl *ctl)
 {
-    constexpr int kWaves = kBlock / 64;
-    __shared__ int64_t s_wave[kWaves];
-    __shared__ int64_t s_a[kWaves][64], s_b[kWaves][64], s_len[kWaves][64];
-    __shared__ int32_t s_diff[kWaves][64];
-    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t w = tid; w < words; w += stride) {
-        const uint32_t m = g.met[w];
-        if (m == 0) continue;
-        g.bits[w].sealed |= m;
-        g.met[w] = 0;
-        if (g.contested[w]) g.contested[w] = 0;
-    }
+    __shared__ int64_t s_wave[kBlock / 64];
+    __shared__ CmpJobs s_jobs[kBlock / 64];
     if (blockIdx.x == 0)
         for (int b = threadIdx.x; b < kGrainBins; b += kBlock) g.hist[b] = 0;
     if (read_err(ctl) != 0) return;                  // a bad report: no bytes are compared
     const int64_t nl = *g.n_list;
-    const int wv = (int)(threadIdx.x >> 6), lane = lane_id(), sub = lane & (kCmpLanes - 1);
+    const int64_t tid = (int64_t)blockIdx.x * kBlock + threadIdx.x, stride = (int64_t)gridDim.x * kBlock;
     int64_t cnt[3] = {0, 0, 0};                      // accepted, duplicate, conflict
-    for (int64_t j0 = tid - lane; j0 < nl; j0 += stride) {
-        int kind = -1;
-        int64_t i = 0, a = 0, b = 0, len = 0;
-        bool job = false;
-        if (j0 + lane < nl) {
-            i = list[j0 + lane];
-            const uint32_t s = rs[i];
-            b = roff[i];
-            len = roff[i + 1] - b;
-            const int64_t v = g.first[cidx[i]];
-            kind = 0;
-            if (v != i) {
-                a = roff[v];
-                const bool same = rs[v] == s && (s != RO_SUCCESS || roff[v + 1] - a == len);
-                job = same && s == RO_SUCCESS && data != nullptr && len > 0;
-                kind = same ? 1 : 2;
-                state_out[i] = RO_PENDING;
-            }
-        }
-        const uint64_t jobs = __ballot(job);
-        const int slot = (int)__popcll(jobs & ((1ull << lane) - 1ull)), nj = (int)__popcll(jobs);
-        if (job) {
-            s_a[wv][slot] = a;
-            s_b[wv][slot] = b;
-            s_len[wv][slot] = len;
-        }
-        __builtin_amdgcn_wave_barrier();
-        for (int q = lane / kCmpLanes; q < nj; q += 64 / kCmpLanes) {
-            const uint8_t *pa = data + s_a[wv][q], *pb = data + s_b[wv][q];
-            const int64_t l = s_len[wv][q];
-            uint32_t diff = 0;
-            if (l < 16) {
-                if (sub < l) diff = (uint32_t)(pa[sub] ^ pb[sub]);
-            } else {
-                constexpr int64_t kStep = 16 * kCmpLanes * kCmpSteps;
-                for (int64_t x = (int64_t)sub * 16; x < l && diff == 0; x += kStep) {
-                    v4u32 A[kCmpSteps], B[kCmpSteps];
-#pragma unroll
-                    for (int u = 0; u < kCmpSteps; ++u) {
-                        const int64_t y = min64(x + u * (16 * kCmpLanes), l - 16);
-                        A[u] = ld16v(reinterpret_cast<uint64_t>(pa + y));
-                        B[u] = ld16v(reinterpret_cast<uint64_t>(pb + y));
-                    }
-#pragma unroll
-                    for (int u = 0; u < kCmpSteps; ++u) {
-                        const v4u32 d = A[u] ^ B[u];
-                        diff |= d.x | d.y | d.z | d.w;
-                    }
-                }
-            }
-            // lanes of this comparison that found a difference
-            const uint64_t dm = __ballot(diff != 0) >> (lane & ~(kCmpLanes - 1));
-            if (sub == 0) s_diff[wv][q] = (dm & ((1u << kCmpLanes) - 1u)) != 0;
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (job && s_diff[wv][slot]) kind = 2;
-        __builtin_amdgcn_wave_barrier();
+    for (int64_t j0 = tid - lane_id(); j0 < nl; j0 += stride) {
+        const bool have = j0 + lane_id() < nl;
+        const int64_t i = have ? list[j0 + lane_id()] : 0;
+        const int kind = settle_wave(have, i, have ? entry[j0 + lane_id()] : 0u, rs, roff, data, g.room, state_out,
+                                     s_jobs[threadIdx.x >> 6]);
         cnt[0] += kind == 0;
         cnt[1] += kind == 1;
         cnt[2] += kind == 2;
@@ -714,27 +766,31 @@ static int64_t grid_for(const Launch &L, int64_t n, int64_t per_block)
 // Words of each bitmap of n children, a whole number of 256-byte lines.
 int64_t grain_words(int64_t n) { return ((n >> 5) + 64) & ~(int64_t)63; }
 
-// Bins for calls that name a good part of many children: at least an eighth of
-// the table (a bin's bitmap is swept whole), and enough to pay for the launches
-// (reset, reservation and commit of 289,000 children take 125 us by atomics and
-// about 120 with bins, 825,000 206 and 129).  The two bitmaps
-// of a bin of 2^17 children take 32 KB of LDS; 512 of those hold 67M children.
-constexpr int64_t kBinCall = (int64_t)3 << 17;
-constexpr int kMaxBinShift = 17;
-static bool use_bins(int64_t n, int64_t N, Bins &bins)
+// Bins for large calls, since a bin's bitmap is swept whole and the launches have
+// to be paid for.  The two bitmaps of a bin of 2^17 children take 32 KB of LDS; 512
+// of those hold 67M children.
+// A reservation takes them from 393,216 children and an eighth of the table on
+// (1M of 1M 92 us by atomics, 30 with bins; 390,000 of 1M 25 and 29; 700,000 of
+// 10M 37 and 41).  A commit by atomics makes two of them per report, so its line
+// lies lower: some 12 us and 90 per million reports against 30, 20 per million
+// and a half per million children (390,000 reports on 1M children 45 us and 36,
+// 300,000 on 10M 39 and 37, 1M on 40M 113 and 69).
+static int64_t reserve_line(int64_t N) { return N / 8 > (int64_t)3 << 17 ? N / 8 : (int64_t)3 << 17; }
+static int64_t commit_line(int64_t N) { return ((int64_t)1 << 18) + N / 128; }
+static bool use_bins(int64_t n, int64_t N, int64_t line, Bins &bins)
 {
     bins.shift = 10;
     while (bins.shift < kMaxBinShift && (N >> bins.shift) >= kGrainBins) ++bins.shift;
     bins.n = (int)((N >> bins.shift) + 1 < kGrainBins ? (N >> bins.shift) + 1 : kGrainBins);
-    return n >= kBinCall && n >= N / 8 && (N >> bins.shift) < kGrainBins;
+    return n >= line && (N >> bins.shift) < kGrainBins;
 }
 
 hipError_t launch_grains_fill(const Launch &L, const GrainTab &g, int64_t n)
 {
-    // four words of a record, met, contested; the bins' counts
-    const int64_t quads = (grain_words(n) * 6 + 2 * kGrainBins) / 4;
-    RO_LAUNCH(L, RO_K_GRAINS, k_grains_fill, dim3((unsigned)grid_for(L, quads, kBlock)), dim3(kBlock), 0, L.stream,
-              reinterpret_cast<uint4 *>(g.bits), quads);
+    // four words of a record, contested; the bins' counts
+    const int64_t zero = (grain_words(n) * 5 + 2 * kGrainBins) / 4, first = (n + 3) / 4;
+    RO_LAUNCH(L, RO_K_GRAINS, k_grains_fill, dim3((unsigned)grid_for(L, zero > first ? zero : first, kBlock)), dim3(kBlock),
+              0, L.stream, reinterpret_cast<uint4 *>(g.bits), zero, reinterpret_cast<uint4 *>(g.first), first);
     return hipGetLastError();
 }
 
@@ -749,7 +805,7 @@ hipError_t launch_grains_dispatch(const Launch &L, const uint32_t *child, int64_
                                   uint32_t *out_gen)
 {
     Bins bins;
-    if (use_bins(n, N, bins)) {
+    if (use_bins(n, N, reserve_line(N), bins)) {
         const int64_t tiles = (n + kSplitTh * kDispIt - 1) / (kSplitTh * kDispIt), most = (int64_t)L.num_cus * 2;
         RO_LAUNCH(L, RO_K_GRAINS, k_grains_dispatch_split, dim3((unsigned)(tiles < most ? tiles : most)), dim3(kSplitTh), 0,
                   L.stream, child, n, N, g, bins, out_gen, L.ctl);
@@ -774,28 +830,27 @@ hipError_t launch_grains_commit(const Launch &L, const uint32_t *rp, const uint3
                                 const int64_t *offsets, int64_t P, int64_t N, const GrainTab &g, uint32_t *cidx,
                                 uint32_t *list, uint2 *pair, uint8_t *state_out, int64_t *counts)
 {
-    const int64_t grid = grid_for(L, n, kBlock * kGItems), words = grain_words(N);
+    const int64_t grid = grid_for(L, n, kBlock * kGItems);
     Bins bins;
-    if (use_bins(n, N, bins)) {
-        // fewer workgroups: each adds its counts of all bins
-        const int64_t most = (int64_t)L.num_cus * 4, grid_f = grid < most ? grid : most;
-        RO_LAUNCH(L, RO_K_FENCE_FIRST, k_grains_first<true>, dim3((unsigned)grid_f), dim3(kBlock), 0, L.stream, rp, ro, rs,
-                  roff, rgen, n, offsets, P, N, g, bins, cidx, state_out, counts, L.ctl);
-        const int64_t tiles = (n + kSplitTh * kPairIt - 1) / (kSplitTh * kPairIt), most_s = (int64_t)L.num_cus * 2;
-        RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_split, dim3((unsigned)(tiles < most_s ? tiles : most_s)), dim3(kSplitTh),
-                  0, L.stream, n, g, bins, cidx, pair, counts);
-        RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_bins, dim3((unsigned)bins.n), dim3(kSplitTh),
-                  (size_t)8 << (bins.shift - 5), L.stream, g, bins, pair, list, counts);
-    } else {
+    if (!use_bins(n, N, commit_line(N), bins)) {
         RO_LAUNCH(L, RO_K_FENCE_FIRST, k_grains_first<false>, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, rp, ro, rs,
                   roff, rgen, n, offsets, P, N, g, bins, cidx, state_out, counts, L.ctl);
-        RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_decide, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, rs, n, g, cidx,
-                  list, state_out, counts, L.ctl);
+        RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_decide, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, rs, roff, data, n,
+                  g, cidx, state_out, counts, L.ctl);
+        return hipGetLastError();
     }
+    // fewer workgroups: each adds its counts of all bins
+    const int64_t most = (int64_t)L.num_cus * 4, grid_f = grid < most ? grid : most;
+    RO_LAUNCH(L, RO_K_FENCE_FIRST, k_grains_first<true>, dim3((unsigned)grid_f), dim3(kBlock), 0, L.stream, rp, ro, rs,
+              roff, rgen, n, offsets, P, N, g, bins, cidx, state_out, counts, L.ctl);
+    const int64_t tiles = (n + kSplitTh * kPairIt - 1) / (kSplitTh * kPairIt), most_s = (int64_t)L.num_cus * 2;
+    RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_split, dim3((unsigned)(tiles < most_s ? tiles : most_s)), dim3(kSplitTh), 0,
+              L.stream, n, g, bins, cidx, pair, counts);
+    RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_bins, dim3((unsigned)bins.n), dim3(kSplitTh), (size_t)8 << (bins.shift - 5),
+              L.stream, g, bins, pair, list, cidx, counts);
     // the list may hold every report; mostly it holds a few
-    const int64_t items = n > words ? n : words;
-    RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_settle, dim3((unsigned)grid_for(L, items, kBlock)), dim3(kBlock), 0,
-              L.stream, rs, roff, data, g, words, cidx, list, state_out, counts, L.ctl);
+    RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_settle, dim3((unsigned)grid_for(L, n, kBlock)), dim3(kBlock), 0, L.stream, rs,
+              roff, data, g, list, cidx, state_out, counts, L.ctl);
     return hipGetLastError();
 }
 

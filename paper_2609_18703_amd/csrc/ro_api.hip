@@ -513,11 +513,11 @@ int ro_grains_create(ro_ctx *c, int64_t n_children, ro_grains **out)
 {
     if (out) *out = nullptr;
     if (!c || !out || n_children < 0 || n_children >= ((int64_t)1 << 32)) return RO_EINVAL;
-    const int64_t n = n_children > 0 ? n_children : 1, w = grain_words(n);
+    const int64_t n = n_children > 0 ? n_children : 1, w = grain_words(n), n4 = (n + 3) & ~(int64_t)3;
     ro_grains *g = (ro_grains *)calloc(1, sizeof(ro_grains));
     if (!g) return RO_EINVAL;
     uint32_t *b = nullptr;
-    if (dev_alloc(&b, 6 * w + 2 * kGrainBins + 64 + 2 * n) != hipSuccess) {
+    if (dev_alloc(&b, 5 * w + 2 * kGrainBins + 64 + 3 * n4) != hipSuccess) {
         free(g);
         return RO_EHIP;
     }
@@ -525,13 +525,13 @@ int ro_grains_create(ro_ctx *c, int64_t n_children, ro_grains **out)
     g->n = n_children;
     g->block = b;
     g->tab.bits = reinterpret_cast<GrainBits *>(b);
-    g->tab.met = b + 4 * w;
-    g->tab.contested = b + 5 * w;
-    g->tab.hist = b + 6 * w;
+    g->tab.contested = b + 4 * w;
+    g->tab.hist = b + 5 * w;
     g->tab.cursor = g->tab.hist + kGrainBins;
     g->tab.n_list = g->tab.cursor + kGrainBins;
-    g->tab.gen = g->tab.n_list + 64;
-    g->tab.first = g->tab.gen + n;
+    g->tab.first = g->tab.n_list + 64;
+    g->tab.gen = g->tab.first + n4;
+    g->tab.room = g->tab.gen + n4;
     if (launch_grains_fill(launch_of(c), g->tab, n) != hipSuccess) {
         (void)hipFree(b);
         free(g);

@@ -170,13 +170,14 @@ struct alignas(16) GrainBits {
     uint32_t pad;
 };
 struct GrainTab {
-    GrainBits *bits;         // [grain_words(n)]; met, contested, hist and cursor follow in the same block
-    uint32_t *met;           // children with a passing report in the current commit call
-    uint32_t *contested;     // ... with more than one
+    GrainBits *bits;         // [grain_words(n)]; the others follow in the same block
+    uint32_t *contested;     // children that had several passing reports in a call without bins
     uint32_t *hist, *cursor; // [kGrainBins] entries per bin of the current call, zero between calls
-    uint32_t *n_list;        // reports of contested children in the current call
+    uint32_t *n_list;        // [2] in the current call with bins: reports of contested children, and those children
+    uint32_t *first;         // [n] a child's first passing report, 0xffffffff before: a commit seals
+                             // every child it sets, so only a reset clears it
     uint32_t *gen;           // [n] generation of the children that were retried
-    uint32_t *first;         // [n] contested children: index of the first passing report
+    uint32_t *room;          // [n] a large reservation's children by bin, a large commit's first reports of contested ones
 };
 constexpr int kGrainBins = 512;
 int64_t grain_words(int64_t n);

@@ -321,3 +321,52 @@ def test_fence_around_the_size_of_a_binned_call(ctx, n_children, order):
     ph, gg = _phases(g, N)
     assert np.array_equal(ph, np.full(N, O.IN_FLIGHT, np.uint32)) and not gg.any()
     g.close(); og.close()
+
+
+# Commits in waves: by atomics (one report, a thousand, one less than the line)
+# and with bins (2^18 and a 128th of the table, and more), each with identical and
+# conflicting repeats among them, and each sent a second time whole, when every
+# report is stale although it stands at the same place; then all of it again
+# after a reset.
+@pytest.mark.parametrize("n_children", [300_000, 1 << 23, (1 << 23) + 127, (1 << 23) + 128])
+def test_fence_commits_in_waves(ctx, n_children):
+    rng = np.random.default_rng(n_children)
+    N = n_children
+    counts = np.full(N // 8 + 1, 8, np.int32)
+    counts[-1] = N - 8 * (N // 8)
+    offs = O.expand(counts, tags=False)
+    og, g = O.Grains(N), ctx.grains(N)
+    line = (1 << 18) + N // 128
+    sizes = [1, 1000, 1, 5000, line] if N < 1 << 20 else [1000, line - 1, line, line + 9000, 77]
+    for run in range(2):
+        queue = rng.permutation(N)[:sum(sizes)].astype(np.uint32)
+        g.dispatch(_i32(queue))
+        og.dispatch(queue)
+        for child in np.split(queue, np.cumsum(sizes)[:-1]):
+            m = len(child) // 50
+            if len(child) > 1:                             # repeats in place of the last reports
+                child = child.copy()
+                child[len(child) - m:] = child[rng.integers(0, len(child) - m, m)]
+                child = rng.permutation(child)
+            n = len(child)
+            st = (child % 3).astype(np.uint8)
+            lens = np.where(st == 0, child % 70, 0)
+            off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+            data = np.repeat((child % 251).astype(np.uint8), lens)
+            if len(data):
+                data[rng.integers(0, len(data), n // 100)] ^= 1
+            cols = ((child // 8).astype(np.uint32), (child % 8).astype(np.uint32), st, off, data, np.zeros(n, np.uint32), offs)
+            for again in range(2):
+                _say("fence waves", N, run, n, again)
+                want = og.commit(*cols)
+                got = _commit(ctx, g, *cols)
+                assert got[1] == tuple(want[1]) and np.array_equal(got[0], want[0])
+                assert not again or got[1] == (0, n, 0, 0)
+        ph, gg = _phases(g, N)
+        assert np.array_equal(ph, og.phase()) and np.array_equal(gg, og.gen())
+        g.reset()
+        og.close()
+        og = O.Grains(N)
+    ph, gg = _phases(g, N)
+    assert (ph == O.READY).all() and not gg.any()
+    g.close(); og.close()
