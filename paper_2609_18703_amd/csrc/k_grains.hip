@@ -579,7 +579,7 @@ constexpr int kPairIt = 8;
 
 __global__ __launch_bounds__(kSplitTh) void k_grains_split(int64_t n, GrainTab g, Bins bins,
                                                            const uint32_t *__restrict__ cidx, uint2 *__restrict__ pair,
-                                                           int64_t *counts)
+                                                           int64_t *counts, Ctl *ctl)
 {
     __shared__ uint32_t s_k[kSplitTh * kPairIt], s_i[kSplitTh * kPairIt];
     __shared__ uint32_t s_cnt[kGrainBins + 1], s_base[kGrainBins], s_w[kGrainBins / 64];
@@ -612,7 +612,7 @@ __global__ __launch_bounds__(kSplitTh) void k_grains_split(int64_t n, GrainTab g
     }
     if (stale) atomicAdd(&s_stale, stale);
     __syncthreads();
-    if (counts && tid == 0 && s_stale)
+    if (counts && tid == 0 && s_stale && read_err(ctl) == 0)         // after a bad report nothing is counted
         __hip_atomic_fetch_add(&counts[1], (int64_t)s_stale, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -625,7 +625,7 @@ __global__ __launch_bounds__(kSplitTh) void k_grains_split(int64_t n, GrainTab g
 // last pass, now 46 and 84).
 __global__ __launch_bounds__(kSplitTh) void k_grains_bins(GrainTab g, Bins bins, const uint2 *__restrict__ pair,
                                                           uint32_t *__restrict__ list, uint32_t *__restrict__ entry,
-                                                          int64_t *counts)
+                                                          int64_t *counts, Ctl *ctl)
 {
     extern __shared__ uint32_t s_bits[];
     __shared__ uint32_t s_w[kSplitTh / 64], s_buf[2 * kSplitTh], s_ent[2 * kSplitTh];
@@ -718,7 +718,7 @@ __global__ __launch_bounds__(kSplitTh) void k_grains_bins(GrainTab g, Bins bins,
             __syncthreads();
         }
     }
-    if (counts && tid == 0 && cnt > listed)
+    if (counts && tid == 0 && cnt > listed && read_err(ctl) == 0)
         __hip_atomic_fetch_add(&counts[0], (int64_t)(cnt - listed), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -845,9 +845,9 @@ hipError_t launch_grains_commit(const Launch &L, const uint32_t *rp, const uint3
               roff, rgen, n, offsets, P, N, g, bins, cidx, state_out, counts, L.ctl);
     const int64_t tiles = (n + kSplitTh * kPairIt - 1) / (kSplitTh * kPairIt), most_s = (int64_t)L.num_cus * 2;
     RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_split, dim3((unsigned)(tiles < most_s ? tiles : most_s)), dim3(kSplitTh), 0,
-              L.stream, n, g, bins, cidx, pair, counts);
+              L.stream, n, g, bins, cidx, pair, counts, L.ctl);
     RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_bins, dim3((unsigned)bins.n), dim3(kSplitTh), (size_t)8 << (bins.shift - 5),
-              L.stream, g, bins, pair, list, cidx, counts);
+              L.stream, g, bins, pair, list, cidx, counts, L.ctl);
     // the list may hold every report; mostly it holds a few
     RO_LAUNCH(L, RO_K_FENCE_DECIDE, k_grains_settle, dim3((unsigned)grid_for(L, n, kBlock)), dim3(kBlock), 0, L.stream, rs,
               roff, data, g, list, cidx, state_out, counts, L.ctl);

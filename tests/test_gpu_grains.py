@@ -370,3 +370,40 @@ def test_fence_commits_in_waves(ctx, n_children):
     ph, gg = _phases(g, N)
     assert (ph == O.READY).all() and not gg.any()
     g.close(); og.close()
+
+
+@pytest.mark.parametrize("below", [True, False])
+def test_fence_counts_nothing_after_a_bad_report(ctx, below):
+    """A call with an invalid report (no such parent) counts no report,
+    whichever path its size takes; the next Call on the set is right."""
+    import paper_2609_18703_amd as R
+    N = 300_000
+    n = (1 << 18) + N // 128 - (1 if below else 0)
+    offs = O.expand(np.full(N // 4, 4, np.int32), tags=False)
+    g = ctx.grains(N)
+    child = np.random.default_rng(n).permutation(N)[:n].astype(np.uint32)
+    child[1000:2000] = child[:1000]                        # repeats
+    par, ordi = child // 4, child % 4
+    bad = par.copy()
+    bad[n // 2] = N
+    gen = np.zeros(n, np.uint32)
+    gen[::10] = 3                                          # stale
+    st, off, data = np.zeros(n, np.uint8), 2 * np.arange(n + 1, dtype=np.int64), np.zeros(2 * n, np.uint8)
+    cols = [D.to_dev(x) for x in (st, off, data)]
+    cnt = torch.full((4,), -1, dtype=torch.int64, device="cuda")
+    for p, want in ((bad, None), (par, O.Grains(N))):
+        _say("fence bad report", below, want is not None)
+        g.reset()
+        g.dispatch(_i32(np.arange(N)))
+        out = torch.zeros(n, dtype=torch.uint8, device="cuda")
+        g.commit(_i32(p), _i32(ordi), *cols, _i32(gen), D.to_dev(offs), out, cnt)
+        if want is None:
+            assert ctx.status() == R.ERANGE
+            assert cnt.tolist() == [0, 0, 0, 0]
+        else:
+            ctx.check("commit")
+            want.dispatch(np.arange(N))
+            w = want.commit(par, ordi, st, off, data, gen, offs)
+            assert np.array_equal(out.cpu().numpy(), w[0]) and tuple(cnt.tolist()) == tuple(w[1])
+            want.close()
+    g.close()
