@@ -198,46 +198,55 @@ __global__ __launch_bounds__(kBlock) void k_gather_scatter(
 // whose slots are the level below's output): nothing is copied, and the scan
 // checks that every surviving record already sits at its output position;
 // any other would overwrite bytes still to be read (RO_EINVAL).
-// Two tile sizes.  Up to kScanSmall reports a tile is 1,024 children by 256
-// threads (100,000 children: 98 workgroups, 13 us); beyond, 8,192 children by
-// one workgroup of 1,024 threads per CU, since a look-back reads as many
-// descriptors as there are tiles in flight and every tile draws a ticket
-// (41M children: 255 us; tiles of 4,096 with two workgroups of 512 threads
-// 285 us, of 4,096 by 256 threads 444 us, of 16,384, whose registers spill,
-// 263 us; before, tiles of 4,096 walked child by child, 305 us.  1M children:
-// 18 us, 36 us with the small tile, 39 us before; 300,000: 26, 30 and 44 us).
-// The report count stands for the child count, which only the device knows.
-constexpr int64_t kScanSmall = 131072;
+// Two tile sizes, chosen on the device, which alone knows the children (a gather
+// may have few reports of many, and any reservation): 1,024 children up to
+// kScanSmall, a tile for each of 256 CUs, and 8,192 beyond, since a look-back
+// reads as many descriptors as there are tiles in flight and every tile draws a
+// ticket.  1,000 children 8 us (11 as one large tile), 40,000 11.7 (15.6),
+// 262,144 16.0 (15.5), 400,000 20 with small tiles and 16.3, 1M 35 and 17, 41M
+// 724 and 220 (tiles of 4,096 with two workgroups of 512 threads 285, of 16,384,
+// whose registers spill, 263; walked child by child in tiles of 4,096 305, and
+// 1M 39).
+constexpr int64_t kScanSmall = 262144;
 constexpr int kScanTh = 1024, kScanIt = 8;
-constexpr int kScanSmallTh = 256, kScanSmallIt = 4;
 
-template <int kTh, int kIt, bool kInPlace>
-__global__ __launch_bounds__(kTh) void k_gather_scan(
+// LDS of a tile (sized for the larger)
+struct ScanLds {
+    static constexpr int kT = kScanTh * kScanIt, kG = kT / kGrp;
+    uint64_t pre[kT];                           // exclusive byte sum inside the child's group
+    uint64_t gt[kG];                            // byte total of each group
+    uint64_t gbase[kG];                         // exclusive byte sum of the groups
+    uint64_t m[3][kG + 1];                      // per state: mask of the group's children
+    uint64_t cp[kG + 1];                        // exclusive packed counts of the groups
+    uint64_t b;
+    int64_t t;
+    int64_t p[2][2];
+    int32_t valid, last;                        // two words: waves still read the first when the second is set
+};
+
+template <int kIt, bool kInPlace>
+__device__ __forceinline__ void scan_tiles(
     const int64_t *__restrict__ offsets, int64_t P, const Canon *__restrict__ canon, int64_t canon_cap,
     int64_t *__restrict__ out_off, int64_t out_cap, int has_data, int32_t *__restrict__ ns, int32_t *__restrict__ nf,
     int32_t *__restrict__ nk, int64_t *__restrict__ cdst, int64_t *__restrict__ sub_base, const uint8_t *out,
-    int64_t *n_rejected, uint32_t epoch, Ctl *ctl, uint64_t *desc, int64_t desc_cap)
+    int64_t *n_rejected, uint32_t epoch, Ctl *ctl, uint64_t *desc, int64_t desc_cap, int64_t N0, int64_t N, ScanLds &lds)
 {
+    constexpr int kTh = kScanTh;
     constexpr int kT = kTh * kIt;               // children per tile
     constexpr int kG = kT / kGrp;               // groups per tile
     constexpr int kCF = 21, kCK = 42;           // a packed count: SUCCESS, FAILED << 21, SKIPPED << 42
     constexpr uint64_t kCM = (1u << kCF) - 1;
     constexpr int kGL = kG <= 64 ? 1 : kG / 64; // groups per lane of the wave that scans them
-    static_assert(kGrp == 64 && (kG <= 64 || kG % 64 == 0), "one wave load per group");
-    __shared__ uint64_t s_pre[kT];              // exclusive byte sum inside the child's group
-    __shared__ uint64_t s_gt[kG];               // byte total of each group
-    __shared__ uint64_t s_gbase[kG];            // exclusive byte sum of the groups
-    __shared__ uint64_t s_m[3][kG + 1];         // per state: mask of the group's children
-    __shared__ uint64_t s_cp[kG + 1];           // exclusive packed counts of the groups
-    __shared__ uint64_t s_b;
-    __shared__ int64_t s_t;
-    __shared__ int64_t s_p[2][2];
-    __shared__ int32_t s_valid, s_last;         // two words: waves still read the first when the second is set
-    const int64_t N0 = offsets[P];
-    const int64_t N = N0 <= canon_cap ? N0 : 0;
+    static_assert(kGrp == 64 && (kG <= 64 || kG % 64 == 0) && kIt <= kScanIt, "one wave load per group");
     const int64_t ntiles = (N + kT - 1) / kT;
     const uint32_t parts = ntiles > 1 ? (uint32_t)min64((int64_t)gridDim.x, ntiles) : 1u;
     if (blockIdx.x >= parts) return;
+    uint64_t *s_pre = lds.pre, *s_gt = lds.gt, *s_gbase = lds.gbase, *s_cp = lds.cp;
+    auto &s_m = lds.m;
+    auto &s_p = lds.p;
+    uint64_t &s_b = lds.b;
+    int64_t &s_t = lds.t;
+    int32_t &s_valid = lds.valid, &s_last = lds.last;
     const uint32_t sepoch = scan_epoch(ctl);
     const int wv = uni32((int)(threadIdx.x >> 6)), ln = lane_id();
     // an invalid Expansion found by the scatter: no tiles (one thread looks,
@@ -468,6 +477,24 @@ __global__ __launch_bounds__(kTh) void k_gather_scan(
     if (parts > 1 && s_last) ticket_reset(ctl, sepoch, desc, desc_cap);
 }
 
+template <bool kInPlace>
+__global__ __launch_bounds__(kScanTh) void k_gather_scan(
+    const int64_t *__restrict__ offsets, int64_t P, const Canon *__restrict__ canon, int64_t canon_cap,
+    int64_t *__restrict__ out_off, int64_t out_cap, int has_data, int32_t *__restrict__ ns, int32_t *__restrict__ nf,
+    int32_t *__restrict__ nk, int64_t *__restrict__ cdst, int64_t *__restrict__ sub_base, const uint8_t *out,
+    int64_t *n_rejected, uint32_t epoch, Ctl *ctl, uint64_t *desc, int64_t desc_cap)
+{
+    __shared__ ScanLds lds;
+    const int64_t N0 = offsets[P];
+    const int64_t N = N0 <= canon_cap ? N0 : 0;
+    if (N <= kScanSmall)
+        scan_tiles<1, kInPlace>(offsets, P, canon, canon_cap, out_off, out_cap, has_data, ns, nf, nk, cdst, sub_base, out,
+                                n_rejected, epoch, ctl, desc, desc_cap, N0, N, lds);
+    else
+        scan_tiles<kScanIt, kInPlace>(offsets, P, canon, canon_cap, out_off, out_cap, has_data, ns, nf, nk, cdst, sub_base,
+                                      out, n_rejected, epoch, ctl, desc, desc_cap, N0, N, lds);
+}
+
 // ---------------------------------------------------------------- finalize
 // Complete / state of every parent from its counts, once the scan is done, and
 // the slot offsets of parents with no child at or after their start.  Part of
@@ -602,11 +629,8 @@ hipError_t launch_gather(const Launch &L, const GatherArgs &a, const GatherWs &w
     // output aliasing the report bytes: the scan checks that nothing moves,
     // and there is nothing to copy
     const bool in_place = a.out_data != nullptr && a.out_data == a.data;
-    const bool small = a.n <= kScanSmall;
-    auto scan = in_place ? (small ? k_gather_scan<kScanSmallTh, kScanSmallIt, true> : k_gather_scan<kScanTh, kScanIt, true>)
-                         : (small ? k_gather_scan<kScanSmallTh, kScanSmallIt, false> : k_gather_scan<kScanTh, kScanIt, false>);
-    const int64_t grid_s = (int64_t)L.num_cus * (small ? 4 : 1);
-    RO_LAUNCH(L, RO_K_GATHER_SCAN, scan, dim3((unsigned)grid_s), dim3(small ? kScanSmallTh : kScanTh), 0, L.stream, a.offsets,
+    auto scan = in_place ? k_gather_scan<true> : k_gather_scan<false>;
+    RO_LAUNCH(L, RO_K_GATHER_SCAN, scan, dim3((unsigned)L.num_cus), dim3(kScanTh), 0, L.stream, a.offsets,
               a.P, w.canon, w.canon_cap, a.out_off, a.out_cap, a.out_data != nullptr ? 1 : 0, a.ns, a.nf, a.nk, a.cdst,
               w.sub_base, a.out_data, a.n_rejected, epoch, L.ctl, L.desc, L.desc_cap);
     GatherFin fin;

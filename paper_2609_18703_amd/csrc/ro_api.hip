@@ -135,7 +135,7 @@ hipError_t dev_alloc(T **p, int64_t n)
 }
 
 int64_t tiles_for(int64_t n) { return (n + kTile - 1) / kTile + 1; }
-// look-back tiles of a gather's scan (at its smaller tile)
+// look-back tiles at the smallest tile, 1,024 entries
 int64_t scan_tiles_for(int64_t n) { return (n + 4 * kBlock - 1) / (4 * kBlock) + 1; }
 
 // Make sure the look-back descriptors cover `tiles` tiles.

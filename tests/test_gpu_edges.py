@@ -92,11 +92,12 @@ def test_gather_groups_and_units(ctx, n, record):
         _gather_case(ctx, counts, lengths, states, order, mis=mis, lead=mis % 7)
 
 
-# both scan tile sizes (up to 131,072 reports tiles of 1,024 children, beyond
-# tiles of 8,192), whole and ragged last tiles, parents over several tiles,
-# empty parents at tile boundaries, reports missing
+# both scan tile sizes (up to 262,144 children tiles of 1,024, beyond tiles of
+# 8,192), whole and ragged last tiles, parents over several tiles, empty parents
+# at tile boundaries, reports missing, few reports of many children
 @pytest.mark.parametrize("n, missing", [(8192, 0), (8193, 9), (131_072, 0), (131_073, 0), (139_264, 0), (139_265, 50),
-                                        (150_000, 149_000), (300_001, 0)])
+                                        (150_000, 149_000), (262_144, 0), (262_145, 0), (262_145, 262_000),
+                                        (300_001, 0), (1_000_003, 999_000)])
 def test_gather_scan_tiles(ctx, n, missing):
     rng = np.random.default_rng(n + missing)
     counts = [0, 0, min(n // 3, 100_000), 0]
