@@ -744,13 +744,39 @@ __global__ __launch_bounds__(64 * kCountGrp) void k_batch_count(const uint8_t *_
     }
 }
 
+// In a long queue every tile would add up many groups (3 x 10^9 entries: 12.7 ms,
+// of them more than half for that, and 6.9 with look-back): past kGroupScan of
+// them one workgroup replaces the groups' totals by what lies before each.
+constexpr int64_t kGroupScan = 2048;
+
+__global__ __launch_bounds__(64 * kCountGrp) void k_batch_groups(uint64_t *__restrict__ group_n, int64_t n)
+{
+    __shared__ uint64_t s_w[kCountGrp];
+    const int wv = (int)(threadIdx.x >> 6);
+    uint64_t sum = 0;
+    for (int64_t g0 = 0; g0 < n; g0 += 64 * kCountGrp) {
+        const int64_t g = g0 + threadIdx.x;
+        const uint64_t v = g < n ? group_n[g] : 0, inc = wave_incl_sum_dpp(v);
+        if (lane_id() == 63) s_w[wv] = inc;
+        __syncthreads();
+        uint64_t at = sum + inc - v;
+#pragma unroll
+        for (int k = 0; k < kCountGrp; ++k) {
+            at += k < wv ? s_w[k] : 0;
+            sum += s_w[k];
+        }
+        if (g < n) group_n[g] = at;
+        __syncthreads();
+    }
+}
+
 template <int kMap, int kIt, bool kCounted>
 __global__ __launch_bounds__(kBlock) void k_batch_fill(
     const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
     const int64_t *__restrict__ offsets, int64_t P, MapArgs map, int32_t B, uint32_t *__restrict__ out_child,
     uint32_t *__restrict__ out_parent, uint32_t *__restrict__ out_ordinal, int64_t out_cap, int64_t *n_out,
-    int64_t *n_batches, const uint64_t *__restrict__ tile_at, const uint64_t *__restrict__ group_n, Ctl *ctl,
-    int vec_ok)
+    int64_t *n_batches, const uint64_t *__restrict__ tile_at, const uint64_t *__restrict__ group_n, int64_t n_groups,
+    Ctl *ctl, int vec_ok)
 {
     constexpr int kT = kBlock * kIt;
     __shared__ uint32_t s_off[kMap == kMapLds ? kLdsParents : 1];
@@ -769,7 +795,11 @@ __global__ __launch_bounds__(kBlock) void k_batch_fill(
     int64_t before = 0;
     if constexpr (kCounted) {
         if (threadIdx.x == 0) before = (int64_t)tile_at[t];
-        for (int64_t g = threadIdx.x; g < t / kCountGrp; g += kBlock) before += (int64_t)group_n[g];
+        if (n_groups > kGroupScan) {
+            if (threadIdx.x == 0) before += (int64_t)group_n[t / kCountGrp];
+        } else {
+            for (int64_t g = threadIdx.x; g < t / kCountGrp; g += kBlock) before += (int64_t)group_n[g];
+        }
     } else if (vec_ok) {
         const uint4 *k4 = reinterpret_cast<const uint4 *>(keep);
 #pragma unroll 4
@@ -901,16 +931,18 @@ hipError_t launch_batch_with(const Launch &L, const uint32_t *queue, const uint8
                     if (nt + ng > L.desc_cap || nt > 0x7fffffff) return hipErrorInvalidValue;
                     RO_LAUNCH(L, RO_K_BATCH, k_batch_count, dim3((unsigned)ng), dim3(64 * kCountGrp), 0, L.stream, keep, Q,
                               L.desc, L.desc + nt, aligned ? 1 : 0);
+                    if (ng > kGroupScan)
+                        RO_LAUNCH(L, RO_K_BATCH, k_batch_groups, dim3(1), dim3(64 * kCountGrp), 0, L.stream, L.desc + nt, ng);
                     RO_LAUNCH(L, RO_K_BATCH, (k_batch_fill<kMap, kFillIt, true>), dim3((unsigned)nt), dim3(kBlock), 0,
                               L.stream, queue, keep, Q, offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.desc,
-                              L.desc + nt, L.ctl, aligned ? 1 : 0);
+                              L.desc + nt, ng, L.ctl, aligned ? 1 : 0);
                     return hipGetLastError();
                 }
             }
             if (Q <= kDirectQueue) {
                 RO_LAUNCH(L, RO_K_BATCH, (k_batch_fill<kMap, 4, false>), dim3((unsigned)tiles(kBlock * 4)), dim3(kBlock), 0,
                           L.stream, queue, keep, Q, offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out,
-                          n_batches, nullptr, nullptr, L.ctl, aligned ? 1 : 0);
+                          n_batches, nullptr, nullptr, 0, L.ctl, aligned ? 1 : 0);
                 return hipGetLastError();
             }
             const bool small = Q <= kSmallQueue;

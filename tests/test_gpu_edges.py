@@ -211,6 +211,34 @@ def test_batch_counted(ctx, q_len, shift):
             assert np.array_equal(h[:cap], w[:cap]) and (h[cap:] == 0xffffffff).all()
 
 
+# More groups of counted tiles than every tile adds up for itself (2,048 of 65,536
+# entries), by one group and with a ragged end; compared on the GPU.
+@pytest.mark.parametrize("extra", [0, 1, 70_001])
+def test_batch_counted_in_many_groups(extra):
+    import paper_2609_18703_amd as R
+    q_len = 2048 * 65_536 + extra
+    offs = torch.arange(0, 1001, dtype=torch.int64, device="cuda") * 200_000
+    queue = torch.arange(q_len, dtype=torch.int32, device="cuda")
+    queue = torch.where(queue % 3 == 0, queue ^ 1, queue).contiguous()
+    keep = (torch.arange(q_len, dtype=torch.int32, device="cuda") * 7919 % 10 < 7).to(torch.uint8)
+    want = queue[keep.bool()]
+    m = want.numel()
+    outs = [torch.full((m + 4,), -1, dtype=torch.int32, device="cuda") for _ in range(3)]
+    sc = _zeros(2, torch.int64)
+    c = R.Context()
+    c.reserve(1 << 20, 1000, q_len)
+    _say("batch counted in many groups", q_len, m)
+    torch.cuda.synchronize()
+    c.batch(queue, keep, offs, 100, *outs, sc[0:1], sc[1:2], q_len=q_len, out_cap=m)
+    c.check("batch")
+    assert sc.tolist() == [m, -(-m // 100)]
+    assert torch.equal(outs[0][:m], want)
+    assert torch.equal(outs[1][:m], want // 200_000)
+    assert torch.equal(outs[2][:m], want % 200_000)
+    assert all(bool((t[m:] == -1).all()) for t in outs)
+    c.close()
+
+
 # Empty parents in long runs (in front, in the middle of a block, at a span's
 # edge, behind), between all children, and in clumps of every length up to
 # several steps: the walk over the parents, its jump over a run and the search
