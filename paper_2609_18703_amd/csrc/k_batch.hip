@@ -770,12 +770,13 @@ __global__ __launch_bounds__(64 * kCountGrp) void k_batch_groups(uint64_t *__res
     }
 }
 
-template <int kMap, int kIt, bool kCounted>
+// kWalk: the grid is smaller than the tiles, and a workgroup strides over them.
+template <int kMap, int kIt, bool kCounted, bool kWalk = false>
 __global__ __launch_bounds__(kBlock) void k_batch_fill(
     const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
     const int64_t *__restrict__ offsets, int64_t P, MapArgs map, int32_t B, uint32_t *__restrict__ out_child,
     uint32_t *__restrict__ out_parent, uint32_t *__restrict__ out_ordinal, int64_t out_cap, int64_t *n_out,
-    int64_t *n_batches, const uint64_t *__restrict__ tile_at, const uint64_t *__restrict__ group_n, int64_t n_groups,
+    int64_t *n_batches, const uint64_t *__restrict__ tile_at, const uint64_t *__restrict__ group_n, int scanned,
     Ctl *ctl, int vec_ok)
 {
     constexpr int kT = kBlock * kIt;
@@ -788,51 +789,54 @@ __global__ __launch_bounds__(kBlock) void k_batch_fill(
     const int64_t nmap = map_entries<kMap>(map, N, sh);
     const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
     const bool nt = Q > kTagNtEntries;
-    const int64_t t = blockIdx.x, i0 = t * kT + (int64_t)threadIdx.x * kIt;
-    const uint32_t km = load_mask<kIt>(keep, i0, Q, vec_ok);
-    uint32_t q[kIt], par[kIt], ord[kIt];
-    load_queue<kIt>(queue, i0, Q, vec_ok, q);
-    int64_t before = 0;
-    if constexpr (kCounted) {
-        if (threadIdx.x == 0) before = (int64_t)tile_at[t];
-        if (n_groups > kGroupScan) {
-            if (threadIdx.x == 0) before += (int64_t)group_n[t / kCountGrp];
-        } else {
-            for (int64_t g = threadIdx.x; g < t / kCountGrp; g += kBlock) before += (int64_t)group_n[g];
-        }
-    } else if (vec_ok) {
-        const uint4 *k4 = reinterpret_cast<const uint4 *>(keep);
+    const int64_t ntiles = kWalk ? (Q + kT - 1) / kT : (int64_t)gridDim.x;
+    int64_t t = blockIdx.x;
+    do {
+        const int64_t i0 = t * kT + (int64_t)threadIdx.x * kIt;
+        const uint32_t km = load_mask<kIt>(keep, i0, Q, vec_ok);
+        uint32_t q[kIt], par[kIt], ord[kIt];
+        load_queue<kIt>(queue, i0, Q, vec_ok, q);
+        int64_t before = 0;
+        if constexpr (kCounted) {
+            if (threadIdx.x == 0) before = (int64_t)tile_at[t];
+            // the totals of the groups before, or what lies before this one
+            const int64_t at = t / kCountGrp;
+            for (int64_t g = scanned * at + threadIdx.x; g < at + scanned; g += kBlock) before += (int64_t)group_n[g];
+        } else if (vec_ok) {
+            const uint4 *k4 = reinterpret_cast<const uint4 *>(keep);
 #pragma unroll 4
-        for (int64_t j = threadIdx.x; j < t * kT / 16; j += kBlock) {
-            const uint4 x = k4[j];
-            before += nonzero_bytes(x.x) + nonzero_bytes(x.y) + nonzero_bytes(x.z) + nonzero_bytes(x.w);
+            for (int64_t j = threadIdx.x; j < t * kT / 16; j += kBlock) {
+                const uint4 x = k4[j];
+                before += nonzero_bytes(x.x) + nonzero_bytes(x.y) + nonzero_bytes(x.z) + nonzero_bytes(x.w);
+            }
+        } else {
+            for (int64_t j = threadIdx.x; j < t * kT; j += kBlock) before += keep[j] != 0;
         }
-    } else {
-        for (int64_t j = threadIdx.x; j < t * kT; j += kBlock) before += keep[j] != 0;
-    }
-    bool bad_range = false;
-    uint32_t live = 0;
+        bool bad_range = false;
+        uint32_t live = 0;
 #pragma unroll
-    for (int k = 0; k < kIt; ++k) {
-        par[k] = 0xffffffffu;
-        ord[k] = 0xffffffffu;
-        if (km & (1u << k)) {
-            if ((int64_t)q[k] >= N) bad_range = true;
-            else live |= 1u << k;
+        for (int k = 0; k < kIt; ++k) {
+            par[k] = 0xffffffffu;
+            ord[k] = 0xffffffffu;
+            if (km & (1u << k)) {
+                if ((int64_t)q[k] >= N) bad_range = true;
+                else live |= 1u << k;
+            }
         }
-    }
-    if (want_tags) thread_tags<kMap, kIt>(map, nmap, sh, offsets, P, q, live, par, ord);
-    if (bad_range) raise_err(ctl, RO_ERANGE);
-    const int64_t base = block_sum(before, s_wave);
-    int64_t tot;
-    const int64_t ex = block_excl_scan(__popc(km), s_wave, tot);
-    if (base + tot > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
-    write_slots<kIt>(out_child, out_parent, out_ordinal, q, par, ord, km, (int)ex, base,
-                         slot_room(out_cap, base, tot), s_out, nt);
-    if (t == gridDim.x - 1 && threadIdx.x == 0) {
-        if (n_out) *n_out = base + tot;
-        if (n_batches) *n_batches = (base + tot + B - 1) / B;
-    }
+        if (want_tags) thread_tags<kMap, kIt>(map, nmap, sh, offsets, P, q, live, par, ord);
+        if (bad_range) raise_err(ctl, RO_ERANGE);
+        const int64_t base = block_sum(before, s_wave);
+        int64_t tot;
+        const int64_t ex = block_excl_scan(__popc(km), s_wave, tot);
+        if (base + tot > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
+        write_slots<kIt>(out_child, out_parent, out_ordinal, q, par, ord, km, (int)ex, base,
+                             slot_room(out_cap, base, tot), s_out, nt);
+        if (t == ntiles - 1 && threadIdx.x == 0) {
+            if (n_out) *n_out = base + tot;
+            if (n_batches) *n_batches = (base + tot + B - 1) / B;
+        }
+        t += gridDim.x;
+    } while (kWalk && t < ntiles);
 }
 
 // Every queue entry is ready (no mask): the FIFO compaction is the identity,
@@ -907,6 +911,17 @@ __global__ __launch_bounds__(kBlock) void k_batch_all(
 //   73 and 81; 41M: 380 and 431).
 constexpr int64_t kDirectQueue = 65536, kSmallQueue = 262144, kMidQueue = 1 << 20;
 
+// Workgroups of a counted queue's fill with the coarse map.  A lookup reads two
+// of its entries and searches the offsets between, at random; where those
+// outgrow the L2s, fewer lookups in flight are faster (10M entries under 10M
+// parents: 663 us with all tiles at once, 626 with three workgroups per CU, 598
+// with two, 506 with one; 4M under 3M parents 220, 220, 210, 207; 4M under 1M
+// 152, 150, 148, 156; under 530,000 107, and 109 with two).
+static int64_t fill_grid(const Launch &L, int64_t P)
+{
+    return P >= (int64_t)2 << 20 ? L.num_cus : (P >= (int64_t)3 << 18 ? 2 * (int64_t)L.num_cus : (int64_t)1 << 31);
+}
+
 template <int kMap>
 hipError_t launch_batch_with(const Launch &L, const uint32_t *queue, const uint8_t *keep, int64_t Q,
                              const int64_t *offsets, int64_t P, MapArgs map, int64_t max_id, int32_t B,
@@ -933,9 +948,18 @@ hipError_t launch_batch_with(const Launch &L, const uint32_t *queue, const uint8
                               L.desc, L.desc + nt, aligned ? 1 : 0);
                     if (ng > kGroupScan)
                         RO_LAUNCH(L, RO_K_BATCH, k_batch_groups, dim3(1), dim3(64 * kCountGrp), 0, L.stream, L.desc + nt, ng);
-                    RO_LAUNCH(L, RO_K_BATCH, (k_batch_fill<kMap, kFillIt, true>), dim3((unsigned)nt), dim3(kBlock), 0,
-                              L.stream, queue, keep, Q, offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.desc,
-                              L.desc + nt, ng, L.ctl, aligned ? 1 : 0);
+                    // tiles at a time (fill_grid): all, but for a coarse map beside offsets beyond the caches
+                    auto kern = k_batch_fill<kMap, kFillIt, true>;
+                    int64_t grid = nt;
+                    if constexpr (kMap == kMapCoarse) {
+                        const int64_t at_once = fill_grid(L, P);
+                        if (at_once < nt) {
+                            kern = k_batch_fill<kMap, kFillIt, true, true>;
+                            grid = at_once;
+                        }
+                    }
+                    RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.desc,
+                              L.desc + nt, ng > kGroupScan ? 1 : 0, L.ctl, aligned ? 1 : 0);
                     return hipGetLastError();
                 }
             }

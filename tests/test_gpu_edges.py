@@ -211,6 +211,27 @@ def test_batch_counted(ctx, q_len, shift):
             assert np.array_equal(h[:cap], w[:cap]) and (h[cap:] == 0xffffffff).all()
 
 
+# Counted queues over a coarse map whose tiles outnumber the workgroups: two per
+# CU from 3 x 2^18 parents on and one from 2^21 on, one parent before and at each line.
+@pytest.mark.parametrize("n_parents, per_cu", [((3 << 18) - 1, 0), (3 << 18, 2), ((1 << 21) - 1, 2), (1 << 21, 1)])
+def test_batch_counted_in_turns(n_parents, per_cu):
+    import paper_2609_18703_amd as R
+    rng = np.random.default_rng(n_parents)
+    counts = rng.integers(0, 3, n_parents)
+    counts[n_parents // 2] = 2_500_000 - min(int(counts.sum()), 2_400_000)
+    n = int(counts.sum())
+    tiles = max(per_cu, 1) * torch.cuda.get_device_properties(0).multi_processor_count + 7
+    q_len = max(tiles * 4096 - 1000, (1 << 20) + 1)
+    assert q_len <= n
+    queue = rng.permutation(n)[:q_len].astype(np.uint32)
+    keep = (rng.random(q_len) < 0.8).astype(np.uint8)
+    c = R.Context()
+    c.reserve(13 << 20, n_parents, q_len)                  # more than 12M children and four queues: the coarse map
+    _say("batch counted in turns", n_parents, n, q_len)
+    _batch_case(c, counts, queue, keep, None, 256)
+    c.close()
+
+
 # More groups of counted tiles than every tile adds up for itself (2,048 of 65,536
 # entries), by one group and with a ragged end; compared on the GPU.
 @pytest.mark.parametrize("extra", [0, 1, 70_001])
