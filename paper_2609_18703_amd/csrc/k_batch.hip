@@ -4,11 +4,19 @@
 // sit in one FIFO queue in enqueue order; each elastic reservation removes at
 // most B entries from the head and may mix parents.  Taking the reservations
 // one after another until the queue is empty is a stable compaction of the
-// ready entries cut into consecutive chunks of B, which is what this kernel
-// computes in one pass: a workgroup scan of the ready flags and a decoupled
-// look-back across tiles give every ready entry its FIFO slot.  A barred
-// parent's entries (Sec. 4 "Commit, Failure, and Recovery": queued siblings
-// of a group failure are suppressed before dispatch) are simply not ready.
+// ready entries cut into consecutive chunks of B, which is what these kernels
+// compute.  A barred parent's entries (Sec. 4 "Commit, Failure, and Recovery":
+// queued siblings of a group failure are suppressed before dispatch) are simply
+// not ready.  Where an entry's slot comes from:
+//   no mask, no barrier   the entry's own place (k_batch_all);
+//   a mask                the count of set mask bytes before it, which short
+//                         queues count in every tile, long ones in a launch of
+//                         their own (k_batch_count, k_batch_fill) and those in
+//                         between by ticket and look-back (k_batch_keep);
+//   a barrier             look-back over the tiles' ready entries, after their
+//                         parents are looked up (k_batch).
+// Where its parent comes from: an offsets search, in LDS or memory, or one of
+// two maps built for the call, or a stream's own map.
 #include "ro_device.h"
 
 namespace ro {
@@ -625,12 +633,12 @@ __global__ __launch_bounds__(kBlock) void k_batch(
     ticket_done(ctl, epoch, desc, desc_cap, &s_last);
 }
 
-// The ready queue with a dispatch mask and no barrier: an entry is ready iff
-// its mask byte is set, so a tile's count of ready entries is known from the
-// mask alone, before any lineage lookup.  A workgroup counts its tile, posts
-// the count and finishes the look-back first; only then does it look up the
-// tags of the ready entries and write them, staged in LDS, to the tile's
-// contiguous slot range.
+// The ready queue of kDirectQueue to kMidQueue entries with a dispatch mask and
+// no barrier: an entry is ready iff its mask byte is set, so a tile's count of
+// ready entries is known from the mask alone, before any lineage lookup.  A
+// workgroup counts its tile, posts the count and finishes the look-back first;
+// only then does it look up the tags of the ready entries and write them, staged
+// in LDS, to the tile's contiguous slot range.
 template <int kMap, int kIt>
 __global__ __launch_bounds__(kBlock) void k_batch_keep(
     const uint32_t *__restrict__ queue, const uint8_t *__restrict__ keep, int64_t Q,
@@ -652,15 +660,14 @@ __global__ __launch_bounds__(kBlock) void k_batch_keep(
     const int sh = map_shift(N, P);
     const int64_t nmap = map_entries<kMap>(map, N, sh);
     const bool want_tags = out_parent != nullptr || out_ordinal != nullptr;
-    const bool single = ntiles == 1;
     for (;;) {
-        const int64_t t = single ? 0 : next_ticket(ctl, &s_t);
+        const int64_t t = next_ticket(ctl, &s_t);
         if (t >= ntiles) break;
         const int64_t i0 = t * kT + (int64_t)threadIdx.x * kIt;
         const uint32_t km = load_mask<kIt>(keep, i0, Q, vec_ok);
         int64_t tot;
         const int64_t ex = block_excl_scan(__popc(km), s_wave, tot);
-        const int64_t base = single ? 0 : (int64_t)tile_prefix(desc, t, epoch, (uint64_t)tot, &s_b, ctl);
+        const int64_t base = (int64_t)tile_prefix(desc, t, epoch, (uint64_t)tot, &s_b, ctl);
         if (base + tot > out_cap && threadIdx.x == 0) raise_err(ctl, RO_ECAP);
         uint32_t q[kIt], par[kIt], ord[kIt];
         load_queue<kIt>(queue, i0, Q, vec_ok, q);
@@ -684,7 +691,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_keep(
             if (n_out) *n_out = m;
             if (n_batches) *n_batches = (m + B - 1) / B;
         }
-        if (single) return;
         if (ntiles <= (int64_t)gridDim.x) break;       // a tile for every workgroup
     }
     ticket_done(ctl, epoch, desc, desc_cap, &s_last);
@@ -895,11 +901,12 @@ __global__ __launch_bounds__(kBlock) void k_batch_all(
 }
 
 // Sizes at which a queue changes path (entries):
-//   up to kDirectQueue the offsets are searched and no map is built: the map
-//   is a launch of about 5 us (100,000 entries under 243 parents: 88.7 us for
-//   the whole chain searched, 92 with the map); a masked queue's tiles of 1,024
-//   count the mask before them themselves (7,389 entries: 7.6 us, 10.4 with
-//   tickets and look-back, 39 as one tile of 16,384);
+//   up to kDirectQueue the offsets are searched, more than kLdsParents of them
+//   through memory: a map is a launch and a search per block of the whole
+//   expansion (65,536 masked entries under 5,000 parents 10.2 us and one more,
+//   with the map, 13.8; under 1M 16.8 and 30.8; under 10M 24.7 and 97); a masked
+//   queue's tiles of 1,024 count the mask before them themselves (7,389 entries:
+//   7.6 us, 10.4 with tickets and look-back, 39 as one tile of 16,384);
 //   up to kSmallQueue a masked queue is cut into tiles of 1,024 entries (98,000
 //   entries: 18 us, 57 as 6 tiles of 16,384);
 //   up to kMidQueue into tiles of 4,096 (1M entries: 29 us; 57 in 980 tiles of
@@ -938,9 +945,13 @@ hipError_t launch_batch_with(const Launch &L, const uint32_t *queue, const uint8
     }
     const bool aligned = ((reinterpret_cast<uintptr_t>(queue) | reinterpret_cast<uintptr_t>(keep)) & 15u) == 0;
     auto tiles = [&](int64_t per) { return Q > 0 ? (Q + per - 1) / per : 1; };
-    if (barrier == nullptr && kMap != kMapChild) {
-        if constexpr (kMap != kMapChild) {
-            if constexpr (kMap != kMapLds) {
+    // offsets in LDS come with short queues only, a map with longer ones
+    constexpr bool kShort = kMap == kMapLds || kMap == kMapSearch, kLong = kMap != kMapLds;
+    const bool small = !kLong || Q <= kSmallQueue;
+    const int64_t ntiles = tiles(small ? kBlock * 4 : kBlock * 16), grid_t = ntiles < cap_grid ? ntiles : cap_grid;
+    if constexpr (kMap != kMapChild) {
+        if (barrier == nullptr) {
+            if constexpr (kLong) {
                 if (Q > kMidQueue) {
                     const int64_t nt = tiles(kFillTile), ng = (nt + kCountGrp - 1) / kCountGrp;
                     if (nt + ng > L.desc_cap || nt > 0x7fffffff) return hipErrorInvalidValue;
@@ -948,40 +959,43 @@ hipError_t launch_batch_with(const Launch &L, const uint32_t *queue, const uint8
                               L.desc, L.desc + nt, aligned ? 1 : 0);
                     if (ng > kGroupScan)
                         RO_LAUNCH(L, RO_K_BATCH, k_batch_groups, dim3(1), dim3(64 * kCountGrp), 0, L.stream, L.desc + nt, ng);
-                    // tiles at a time (fill_grid): all, but for a coarse map beside offsets beyond the caches
                     auto kern = k_batch_fill<kMap, kFillIt, true>;
                     int64_t grid = nt;
                     if constexpr (kMap == kMapCoarse) {
-                        const int64_t at_once = fill_grid(L, P);
-                        if (at_once < nt) {
+                        if (fill_grid(L, P) < nt) {
                             kern = k_batch_fill<kMap, kFillIt, true, true>;
-                            grid = at_once;
+                            grid = fill_grid(L, P);
                         }
                     }
-                    RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.desc,
-                              L.desc + nt, ng > kGroupScan ? 1 : 0, L.ctl, aligned ? 1 : 0);
+                    RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P,
+                              map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.desc, L.desc + nt,
+                              ng > kGroupScan ? 1 : 0, L.ctl, aligned ? 1 : 0);
                     return hipGetLastError();
                 }
             }
-            if (Q <= kDirectQueue) {
-                RO_LAUNCH(L, RO_K_BATCH, (k_batch_fill<kMap, 4, false>), dim3((unsigned)tiles(kBlock * 4)), dim3(kBlock), 0,
-                          L.stream, queue, keep, Q, offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap, n_out,
-                          n_batches, nullptr, nullptr, 0, L.ctl, aligned ? 1 : 0);
-                return hipGetLastError();
+            if constexpr (kShort) {
+                if (Q <= kDirectQueue) {
+                    RO_LAUNCH(L, RO_K_BATCH, (k_batch_fill<kMap, 4, false>), dim3((unsigned)tiles(kBlock * 4)), dim3(kBlock),
+                              0, L.stream, queue, keep, Q, offsets, P, map, B, out_child, out_parent, out_ordinal, out_cap,
+                              n_out, n_batches, nullptr, nullptr, 0, L.ctl, aligned ? 1 : 0);
+                    return hipGetLastError();
+                }
             }
-            const bool small = Q <= kSmallQueue;
-            auto kern = small ? k_batch_keep<kMap, 4> : k_batch_keep<kMap, 16>;
-            const int64_t ntiles = tiles(small ? kBlock * 4 : kBlock * 16), grid = ntiles < cap_grid ? ntiles : cap_grid;
-            RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P,
+            auto kern = k_batch_keep<kMap, 4>;
+            if constexpr (kLong) {
+                if (!small) kern = k_batch_keep<kMap, 16>;
+            }
+            RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid_t), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P,
                       map, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, L.ctl, L.desc, L.desc_cap,
                       ntiles, aligned ? 1 : 0);
+            return hipGetLastError();
         }
-        return hipGetLastError();
     }
-    const bool small = Q <= kSmallQueue;
-    auto kern = small ? k_batch<kMap, 4> : k_batch<kMap, 16>;
-    const int64_t ntiles = tiles(small ? kBlock * 4 : kBlock * 16), grid = ntiles < cap_grid ? ntiles : cap_grid;
-    RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P, map,
+    auto kern = k_batch<kMap, 4>;
+    if constexpr (kLong) {
+        if (!small) kern = k_batch<kMap, 16>;
+    }
+    RO_LAUNCH(L, RO_K_BATCH, kern, dim3((unsigned)grid_t), dim3(kBlock), 0, L.stream, queue, keep, Q, offsets, P, map,
               max_id, B, out_child, out_parent, out_ordinal, out_cap, n_out, n_batches, barrier, L.ctl, L.desc,
               L.desc_cap, ntiles, aligned ? 1 : 0);
     return hipGetLastError();

@@ -7,13 +7,13 @@
 // facts are published once and conflicting repeats are rejected (Sec. 4,
 // publication rules).
 //
-// Per wave:   report  -> canonical slots + seen bits (+ a count for parents
-//                        with many children).
-// Per emit:   select  -> ascending list of newly complete parents and the
-//                        exclusive scan of their child counts (two look-back
-//                        chains in one pass over all parents): a "virtual"
-//                        expansion whose children are the emitted parents'
-//                        children, in order;
+// Per wave:   report  -> canonical slots + seen bits; the report that completes
+//                        a parent sets its ready bit.
+// Per emit:   select  -> ascending list of the parents whose ready bit is set
+//                        and the exclusive scan of their child counts (two
+//                        look-back chains in one pass over the bits): a
+//                        "virtual" expansion whose children are the emitted
+//                        parents' children, in order;
 //             scan    -> over the virtual children: each one's canonical slot,
 //                        output position and source, the emitted slot
 //                        offsets and per-state counts;

@@ -299,16 +299,6 @@ __device__ __forceinline__ int64_t upper_bound_g(const T *a, int64_t lo, int64_t
     return lo;
 }
 
-// First index i in [lo, hi) with a[i] >= x (hi if none).
-__device__ __forceinline__ int64_t lower_bound_g(const int64_t *a, int64_t lo, int64_t hi, int64_t x)
-{
-    while (lo < hi) {
-        int64_t mid = (lo + hi) >> 1;
-        if (a[mid] < x) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-}
-
 // Parent of child c (largest p with offsets[p] <= c) when p is known to be
 // >= p; walks a few steps, then falls back to a binary search so that long
 // runs of empty parents cost a logarithm.
@@ -352,16 +342,6 @@ __device__ __forceinline__ int lds_last_le(const int16_t *a, int lo, int hi, int
     while (hi - lo > 1) {
         const int m = (lo + hi) >> 1;
         if (a[m] <= x) lo = m; else hi = m;
-    }
-    return lo;
-}
-
-// First i in [lo, hi) with a[i] >= x (hi if none).
-__device__ __forceinline__ int lds_first_ge(const int16_t *a, int lo, int hi, int x)
-{
-    while (lo < hi) {
-        const int m = (lo + hi) >> 1;
-        if (a[m] < x) lo = m + 1; else hi = m;
     }
     return lo;
 }
