@@ -16,10 +16,11 @@ extern "C" {
  * few calls instead of about 2^30 or 2^32.  The context's next gathers use
  * canonical epochs up to the last one and then wrap after canon_left - 1 of
  * them; the stream s (may be NULL) wraps its slot epoch after run_left
- * resets and its group-failure epoch after gf_left reports; the Grain set g
- * (may be NULL) has no epoch, so fence_left moves nothing.  A value below 1,
- * or one that would move an epoch backwards, leaves that epoch as it is.  Results are unchanged by design: every wrap clears what an old
- * epoch could be confused with. */
+ * resets and its group-failure epoch after gf_left reports.  A Grain set has
+ * no epoch: g (may be NULL) and fence_left are taken and move nothing.  A value
+ * below 1, or one that would move an epoch backwards, leaves that epoch as it
+ * is.  Results are unchanged by design: every wrap clears what an old epoch
+ * could be confused with. */
 int ro_debug_epochs(ro_ctx *ctx, ro_stream *s, ro_grains *g, int64_t canon_left, int64_t run_left,
                     int64_t gf_left, int64_t fence_left);
 
