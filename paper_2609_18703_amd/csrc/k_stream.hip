@@ -537,7 +537,7 @@ hipError_t launch_stream_reset(const Launch &L, StreamState &s)
 
 hipError_t launch_stream_init(const Launch &L, StreamState &s)
 {
-    RO_LAUNCH(L, RO_K_MISC, k_stream_check, dim3((unsigned)L.num_cus), dim3(256), 0, L.stream, s.offsets, s.P,
+    RO_LAUNCH(L, RO_K_MISC, k_stream_check, dim3((unsigned)L.num_cus * 4), dim3(256), 0, L.stream, s.offsets, s.P,
               s.N, s.ready, s.mapped, s.remap, L.ctl);
     return hipGetLastError();
 }
