@@ -151,15 +151,16 @@ def cdiv(a, b):
 
 def _gather_bytes(P, N, S):
     """One ro_gather of N reports into P parents moving S payload bytes."""
-    nsub = cdiv(N, 256)
+    nsub = cdiv(N, 256)                 # byte starts of groups of children (kept per 64, counted per 256)
     return {
         # report parent/ordinal/state/offset in, canonical 16-B slot out, counters zeroed
         "gather_scatter": 33 * N + 12 * P,
-        # canonical slots in, parent slot offsets and sub-tile bases out
+        # canonical slots in, parent slot offsets and group starts out
         "gather_scan": 16 * N + 8 * P + 8 * nsub,
-        # counters and offsets in, complete and state out
+        # counters and offsets in, complete and state out (a launch of its own
+        # only where no bytes are copied)
         "gather_finalize": 22 * P,
-        # canonical slots and sub-tile bases in, payload read and written
+        # canonical slots and group starts in, payload read and written
         "gather_copy": 16 * N + 8 * nsub + 2 * S,
     }
 
@@ -188,23 +189,20 @@ def alg_nested(P1, N1, N2, S2, S1, upper_in_place):
     return _add(a, _gather_bytes(P1, N1, 0 if upper_in_place else S1))
 
 
-def alg_stream(P, N, S, n_waves, emit_wave):
-    """emit_wave[p]: the wave in which parent p completes."""
-    nsub = cdiv(N, 256)
-    alive = int((emit_wave.astype(np.int64) + 1).sum())   # parent-waves a parent is still open
+def alg_stream(P, N, S, n_waves):
     return {
         "expand_scan": 12 * P + 8,
-        "batch_samples": n_waves * 4 * cdiv(N, 64),
         "batch": 12 * N,                                   # wave ids in, tags out
         "stream_report": 33 * N,                           # report in, canonical slot out
-        # per wave: emitted flags of every parent, counters of the open ones;
-        # once per parent: its emission record; virtual expansion: offsets in,
-        # per-child slot map out
-        "stream_select": n_waves * P + 20 * alive + 30 * P + 24 * P + 4 * N,
-        "stream_scan": 20 * N + 8 * P + 8 * nsub,
-        "stream_copy": 20 * N + 8 * nsub + 2 * S,
-        "stream_finish": 16 * P,
-        "misc": cdiv(N, 8) + 13 * P,                       # reset of seen bits, counters, flags
+        # per wave: one bit per parent; once per parent: its offsets in, its
+        # emission record out
+        "stream_select": n_waves * cdiv(P, 8) + 54 * P,
+        # canonical slots in, position and source of every emitted child out
+        "stream_scan": 32 * N + 8 * P,
+        "stream_copy": 16 * N + 2 * S,
+        # reset: seen bits, word counts, emitted flags, ready bits; the offsets
+        # compared with those of the child -> parent map
+        "misc": cdiv(N, 4) + P + cdiv(P, 8) + 16 * P,
     }
 
 
@@ -334,7 +332,7 @@ def stage_stream(ctx, parents):
                        f"clipped to [1,100000], records uniform [64,512] B, all succeed, "
                        f"{len(s.waves)} waves of {N // len(s.waves)} in random order, B={s.batch_size}, seed 4",
            "parents": P, "children": N, "waves": len(s.waves), "bytes": total, "batch_size": s.batch_size}
-    return Job("stream-waves", step, N, alg_stream(P, N, total, len(s.waves), ew), cfg, check)
+    return Job("stream-waves", step, N, alg_stream(P, N, total, len(s.waves)), cfg, check)
 
 
 def stage_ops(ctx, parents):
@@ -378,17 +376,15 @@ def stage_ops(ctx, parents):
 
 
 def alg_fence(P, N, M, L, n0, n1, rep_bytes):
-    """Algorithmic bytes of one fence step: the grain fill (phase, generation
-    and fence key, 16 B a child); dispatch and retry, 20 B an entry (id in,
-    phase read and written, generation in or out); the first fence pass, 45 B
-    a report (key, ordinal, state, generation, the next offset, the grain's
-    phase and generation, the key's read and write) plus the offsets; the
-    deciding pass, 30 B a report (key, ordinal, state, generation, fence key,
-    grain generation, state out, phase out) plus the bytes of compared
-    repeats."""
-    return {"grains": 16 * N + 20 * (M + 2 * L),
-            "fence_first": 45 * (n0 + n1) + 2 * 8 * (P + 1),
-            "fence_decide": 30 * (n0 + n1) + 2 * 8 * (P + 1) + rep_bytes}
+    """Algorithmic bytes of one fence step: the reset (bits and first-report
+    entries, about 5 B a child); dispatch and retry, 8 B an entry (id in,
+    generation in or out); the first fence pass, 27 B a report (parent, ordinal,
+    state, offset and generation in; provisional state, child out) plus the
+    offsets; the later passes, 5 B a report (child, state) plus the bytes of
+    compared repeats.  Phase bits are looked up in cache."""
+    return {"grains": 5 * N + 8 * (M + 2 * L),
+            "fence_first": 27 * (n0 + n1) + 2 * 8 * (P + 1),
+            "fence_decide": 5 * (n0 + n1) + rep_bytes}
 
 
 def stage_fence(ctx, parents):
@@ -497,8 +493,12 @@ def stage_pbatch(ctx, parents):
            "parents": P, "queue": Q, "ready": M, "batches": n_b, "batch_size": c.batch_size}
     bits = max(int(P - 1).bit_length(), 0)
     passes = max(-(-bits // 9), 1)
-    tiles = -(-Q // 16384)                 # histogram columns: spans of 8 sort tiles
-    hist = 512 * tiles if passes * 9 == bits or bits > 9 else (1 << bits) * tiles
+    spans = -(-Q // 8192)                  # histogram columns: spans of two sort tiles
+    left, hist = bits, 0                   # digits of equal widths
+    for p in range(passes):
+        width = -(-left // (passes - p))
+        hist += (1 << width) * spans
+        left -= width
     alg = {
         # compaction: queue id and ready flag in, child and parent out
         "batch": 5 * Q + 8 * M, "batch_samples": 4 * (N // 64),
@@ -506,11 +506,11 @@ def stage_pbatch(ctx, parents):
         # keys and compacted children and writes keys and (child, position)
         # values, later ones read and write keys and values
         "pbatch_sort": passes * 4 * M + 20 * M + (passes - 1) * 24 * M,
-        "expand_scan": passes * 12 * hist,
-        # bounds (keys in, group sizes cleared), group firsts (keys), group
-        # scan (sizes in, batch numbers and offsets out), placement (keys,
-        # values in; child, parent, ordinal out)
-        "pbatch": 8 * M + 4 * M + 4 * M + 12 * n_b + 24 * M,
+        "expand_scan": 12 * hist,
+        # bounds (keys in), group firsts (keys in; sizes, bits out), group scan
+        # (bits and sizes in, slots and offsets out), placement (keys, values
+        # in; child, parent, ordinal out)
+        "pbatch": 4 * M + 4 * M + 4 * n_b + M // 4 + 16 * n_b + 24 * M,
     }
     return Job("zipf-pbatch", step, M, alg, cfg, check,
                metric="children/sec through parent-bound reservation; achieved HBM GB/s vs peak")
