@@ -104,7 +104,7 @@ __device__ __forceinline__ v4u32 shift16v(v4u32 lo, v4u32 hi, uint32_t sh)
     return r;
 }
 
-// One unit's window of a sub-tile.  A step of the wave covers 64
+// A unit's part of up to kSub records.  A step of the wave covers 64
 // consecutive output chunks, one per lane, each written with one aligned
 // 16-byte store.  A chunk inside one record takes one 16-byte load from its
 // exact (byte-aligned) source address: a misaligned 16-byte global load
