@@ -507,10 +507,10 @@ def stage_pbatch(ctx, parents):
         # values, later ones read and write keys and values
         "pbatch_sort": passes * 4 * M + 20 * M + (passes - 1) * 24 * M,
         "expand_scan": 12 * hist,
-        # bounds (keys in), group firsts (keys in; sizes, bits out), group scan
-        # (bits and sizes in, slots and offsets out), placement (keys, values
+        # bounds (keys in, marks cleared), group firsts (keys in; marks out),
+        # group scan (marks in, slots and offsets out), placement (keys, values
         # in; child, parent, ordinal out)
-        "pbatch": 4 * M + 4 * M + 4 * n_b + M // 4 + 16 * n_b + 24 * M,
+        "pbatch": 4 * M + 4 * M + n_b + 2 * M + 12 * n_b + 24 * M,
     }
     return Job("zipf-pbatch", step, M, alg, cfg, check,
                metric="children/sec through parent-bound reservation; achieved HBM GB/s vs peak")

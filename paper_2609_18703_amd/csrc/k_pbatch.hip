@@ -200,12 +200,12 @@ __global__ __launch_bounds__(kRTh) void k_rs_scatter(const uint32_t *__restrict_
 // an error (an id out of range leaves its entry's parent unset) the parents
 // are not trusted: every kernel from here on returns at once.
 __global__ void k_pb_bounds(const uint32_t *__restrict__ key, const int64_t *m_dev, int64_t P,
-                            uint32_t *__restrict__ pstart, uint32_t *__restrict__ pend, uint64_t *__restrict__ fbits,
+                            uint32_t *__restrict__ pstart, uint32_t *__restrict__ pend, uint4 *__restrict__ fmark,
                             Ctl *ctl)
 {
     const int64_t M = *m_dev;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t w = tid; w <= M >> 6; w += stride) fbits[w] = 0;     // set next, at groups' firsts (none after an error)
+    for (int64_t w = tid; w <= M >> 4; w += stride) fmark[w] = make_uint4(0, 0, 0, 0);   // set next, at groups' firsts (none after an error)
     if (read_err(ctl) != 0) return;
     // four keys a thread, and the one before them
     for (int64_t s0 = 4 * tid; s0 < M; s0 += 4 * stride) {
@@ -233,16 +233,20 @@ __global__ void k_pb_bounds(const uint32_t *__restrict__ key, const int64_t *m_d
 }
 
 // The queue position of every group's first entry (rank a multiple of B) gets
-// its bit and the group's size.  Ranks fit 32 bits (a queue position does), so
-// they are divided in 32.  Four entries a thread, the loads of each step of
-// their chains together.
+// a byte with the group's size: a full group's and a size that a byte cannot
+// hold have marks of their own.  A byte needs no atomic: bits, set 64 to a word
+// by neighbouring lanes, took 584 us for one parent's 10M batches of one, the
+// bytes 22.  Ranks fit 32 bits (a queue position does), so they are
+// divided in 32.  Four entries a thread, the loads of each step of their
+// chains together.
+constexpr uint32_t kMarkFull = 255, kMarkLook = 254;
 constexpr int kPbItems = 4;
 
 __global__ __launch_bounds__(kBlock) void k_pb_firsts(const uint32_t *__restrict__ key,
                                                       const uint64_t *__restrict__ val, const int64_t *m_dev, int64_t P,
                                                       const uint32_t *__restrict__ pstart,
                                                       const uint32_t *__restrict__ pend, uint32_t B,
-                                                      uint32_t *__restrict__ fsize, uint64_t *__restrict__ fbits, Ctl *ctl)
+                                                      uint32_t *__restrict__ fsize, uint8_t *__restrict__ fmark, Ctl *ctl)
 {
     if (read_err(ctl) != 0) return;
     const int64_t M = *m_dev;
@@ -259,26 +263,27 @@ __global__ __launch_bounds__(kBlock) void k_pb_firsts(const uint32_t *__restrict
             if (s >= M || (int64_t)p[k] >= P) continue;
             if (((uint32_t)s - st[k]) % B != 0) continue;
             const uint32_t left = pend[p[k]] - (uint32_t)s, q = (uint32_t)val[s];
-            fsize[q] = left < B ? left : B;
-            __hip_atomic_fetch_or(&fbits[q >> 6], 1ull << (q & 63u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const bool look = left < B && left >= kMarkLook;
+            if (look) fsize[q] = left;
+            fmark[q] = (uint8_t)(look ? kMarkLook : left < B ? left : B < kMarkLook ? B : kMarkFull);
         }
     }
 }
 
-// Groups in queue order of their first entries: one pass over the bits of the
+// Groups in queue order of their first entries: one pass over the bytes of the
 // queue positions, 32 a thread, with two look-back chains (groups so far,
-// entries so far); sizes are read only where a bit is set.  A group's first
+// entries so far); sizes are read only where a byte says so.  A group's first
 // position gets its batch's first slot, which is batch_off[b] of its batch
 // number b; the last tile writes batch_off[n_batches] and the totals.  Tiles
 // are large, since a tile costs a ticket and a look-back: 10M entries in
 // 55,000 groups took 70 us in tiles of 4,096 positions that read every size,
-// now 39.
+// now 35.
 constexpr int kPbScanTh = 1024, kPbScanIt = 32;
 constexpr int kPbScanTile = kPbScanTh * kPbScanIt;           // positions per tile
 
 __global__ __launch_bounds__(kPbScanTh) void k_pb_scan(const uint32_t *__restrict__ fsize,
-                                                       const uint64_t *__restrict__ fbits, const int64_t *m_dev,
-                                                       int64_t out_cap, uint32_t *__restrict__ gslot,
+                                                       const uint4 *__restrict__ fmark, const int64_t *m_dev,
+                                                       int64_t out_cap, uint32_t B, uint32_t *__restrict__ gslot,
                                                        int64_t *__restrict__ batch_off, int64_t batch_cap,
                                                        int64_t *n_out, int64_t *n_batches, Ctl *ctl, uint64_t *desc,
                                                        uint64_t *desc_b, int64_t desc_cap)
@@ -302,11 +307,18 @@ __global__ __launch_bounds__(kPbScanTh) void k_pb_scan(const uint32_t *__restric
         const int64_t t = next_ticket(ctl, &s_t);
         if (t >= ntiles) break;
         const int64_t i0 = t * kPbScanTile + (int64_t)threadIdx.x * kPbScanIt;
-        const uint32_t bits = i0 < M ? reinterpret_cast<const uint32_t *>(fbits)[i0 / kPbScanIt] : 0u;
-        uint32_t f[kPbScanIt];
+        // bytes at M and above are cleared up to a multiple of 16
+        const uint4 none = make_uint4(0, 0, 0, 0);
+        const uint4 x0 = i0 < M ? fmark[i0 >> 4] : none, x1 = i0 + 16 < M ? fmark[(i0 >> 4) + 1] : none;
+        const uint32_t x[kPbScanIt / 4] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+        uint32_t f[kPbScanIt], bits = 0;
         uint64_t sum = 0;
 #pragma unroll
-        for (int k = 0; k < kPbScanIt; ++k) f[k] = (bits >> k) & 1u ? fsize[i0 + k] : 0u;
+        for (int k = 0; k < kPbScanIt; ++k) {
+            const uint32_t m = x[k >> 2] >> (8 * (k & 3)) & 255u;
+            f[k] = m == kMarkFull ? B : m == kMarkLook ? fsize[i0 + k] : m;
+            bits |= m ? 1u << k : 0u;
+        }
 #pragma unroll
         for (int k = 0; k < kPbScanIt; ++k) sum += f[k];
         // one block scan of entries << 16 | groups (a tile holds at most 32,768 groups)
@@ -435,14 +447,14 @@ hipError_t launch_batch_parent(const Launch &L, const uint32_t *queue, const uin
     const uint32_t *keys = w.k[cur];
     const int64_t g = grid_for(L, Q, kBlock * kPbItems);
     RO_LAUNCH(L, RO_K_PBATCH, k_pb_bounds, dim3((unsigned)g), dim3(kBlock), 0, L.stream, keys, w.m, P, w.pstart,
-              w.pend, w.fbits, L.ctl);
+              w.pend, reinterpret_cast<uint4 *>(w.fmark), L.ctl);
     RO_LAUNCH(L, RO_K_PBATCH, k_pb_firsts, dim3((unsigned)g), dim3(kBlock), 0, L.stream, keys, vals, w.m, P,
-              w.pstart, w.pend, (uint32_t)B, w.fsize, w.fbits, L.ctl);
+              w.pstart, w.pend, (uint32_t)B, w.fsize, w.fmark, L.ctl);
     const int64_t ntiles = (Q + kPbScanTile - 1) / kPbScanTile > 0 ? (Q + kPbScanTile - 1) / kPbScanTile : 1;
     const int64_t gscan = ntiles < (int64_t)L.num_cus * 4 ? ntiles : (int64_t)L.num_cus * 4;
     if (2 * ntiles > L.desc_cap) return hipErrorInvalidValue;
-    RO_LAUNCH(L, RO_K_PBATCH, k_pb_scan, dim3((unsigned)gscan), dim3(kPbScanTh), 0, L.stream, w.fsize, w.fbits, w.m, out_cap,
-              w.gslot, batch_off, batch_cap, n_out, n_batches, L.ctl, L.desc, L.desc + ntiles, L.desc_cap);
+    RO_LAUNCH(L, RO_K_PBATCH, k_pb_scan, dim3((unsigned)gscan), dim3(kPbScanTh), 0, L.stream, w.fsize,
+              reinterpret_cast<const uint4 *>(w.fmark), w.m, out_cap, (uint32_t)B, w.gslot, batch_off, batch_cap, n_out, n_batches, L.ctl, L.desc, L.desc + ntiles, L.desc_cap);
     RO_LAUNCH(L, RO_K_PBATCH, k_pb_place, dim3((unsigned)g), dim3(kBlock), 0, L.stream, keys, vals, w.m, P,
               w.pstart, (uint32_t)B, w.gslot, offsets, out_child, out_parent, out_ordinal, out_cap, L.ctl);
     return hipGetLastError();

@@ -227,7 +227,7 @@ int ensure_pb(ro_ctx *c, int64_t q, int64_t p)
         (size_t)pn * 4, (size_t)pn * 4,                                                    // pstart, pend
         (size_t)(kPbMaxBuckets * tiles) * 4, (size_t)(kPbMaxBuckets * tiles + 1) * 8,      // hist, hoff
         (size_t)2 * 8,                                                                     // m
-        (size_t)((qn >> 6) + 1) * 8,                                                       // fbits
+        (size_t)((qn >> 4) + 1) * 16,                                                      // fmark, read 16 bytes at a time
     };
     constexpr int kArrays = (int)(sizeof(sizes) / sizeof(sizes[0]));
     size_t offs[kArrays], total = 0;
@@ -254,7 +254,7 @@ int ensure_pb(ro_ctx *c, int64_t q, int64_t p)
     c->pb.hist = (int32_t *)(b + offs[9]);
     c->pb.hoff = (int64_t *)(b + offs[10]);
     c->pb.m = (int64_t *)(b + offs[11]);
-    c->pb.fbits = (uint64_t *)(b + offs[12]);
+    c->pb.fmark = (uint8_t *)(b + offs[12]);
     c->pb_cap = q;
     c->pb_pcap = p;
     // descriptors: the compaction, the histogram scan and the two-chain group scan

@@ -102,8 +102,8 @@ struct PbWs {
     uint32_t *kc;            // ready children in queue order
     uint32_t *k[2];          // sort keys (parents), double-buffered
     uint64_t *v[2];          // sort values (child << 32 | queue position), double-buffered
-    uint64_t *fbits;         // bitmap of the queue positions of groups' first entries
-    uint32_t *fsize;         // per group-first position: group size
+    uint8_t *fmark;          // per queue position: mark of a group's first entry (its size, or a code), else 0
+    uint32_t *fsize;         // per group-first position whose mark says so: group size
     uint32_t *gslot;         // per group-first position: its batch's first slot
     uint32_t *pstart, *pend; // per parent: sorted index range
     int32_t *hist;           // digit histograms, [buckets * tiles]

@@ -107,6 +107,44 @@ def test_pbatch_tile_edges(ctx, q_len, P):
         _check(ctx, queue, None, offs, B, what=f"Q={q_len} P={P} B={B}")
 
 
+# sizes that a byte holds, its two codes and more: a full group, remainders on
+# both sides of each, and a batch that takes a whole parent
+@pytest.mark.parametrize("B", [1, 252, 253, 254, 255, 256, 257, 512, 1 << 30])
+def test_pbatch_group_sizes(ctx, B):
+    rng = np.random.default_rng(B % 1000)
+    counts = rng.permutation(np.concatenate([np.arange(248, 262), np.arange(504, 516), [0, 1, 2, 767, 1024]]))
+    offs = O.expand(counts.astype(np.int32), tags=False)
+    N = int(offs[-1])
+    _say("pbatch group sizes", B, N)
+    _check(ctx, rng.permutation(N).astype(np.uint32), None, offs, B, what=f"B={B} random")
+    _check(ctx, np.arange(N, dtype=np.uint32), None, offs, B, what=f"B={B} canonical")
+
+
+def test_pbatch_batches_of_one_cost_no_contention(ctx):
+    """10M batches of one from one parent, whose first entries are neighbours
+    in the queue.  The kernels that form the batches have 120 MB more
+    of them to write than for batches of 256 and took 2.8 times as long;
+    when neighbours set bits of one word, it was 7 times."""
+    n = 10_000_000
+    q = torch.arange(n, dtype=torch.int32, device="cuda")
+    offs = torch.tensor([0, n], dtype=torch.int64, device="cuda")
+    outs = [torch.zeros(n, dtype=torch.int32, device="cuda") for _ in range(3)]
+    boff = torch.zeros(n + 1, dtype=torch.int64, device="cuda")
+    sc = torch.zeros(2, dtype=torch.int64, device="cuda")
+    ms = {}
+    for B in (256, 1):
+        call = lambda: ctx.batch_parent(q, None, offs, B, boff, *outs, sc[0:1], sc[1:2])
+        call()
+        ctx.trace(True)
+        for _ in range(5):
+            call()
+        ms[B] = ctx.trace_read()["pbatch"][1]
+        ctx.check()
+        ctx.trace(False)
+    _say("batches of 256 and of one:", ms)
+    assert ms[1] < 4.5 * ms[256]
+
+
 def test_pbatch_errors(ctx):
     import paper_2609_18703_amd as R
     offs = O.expand(np.array([3, 2], np.int32), tags=False)
