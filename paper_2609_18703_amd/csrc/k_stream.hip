@@ -88,29 +88,35 @@ __global__ __launch_bounds__(kBlock) void k_stream_report(
     int err = 0;
     int64_t rej = 0;
     if (gtid == 0 && n > 0 && roff[0] < 0) err = RO_EINVAL;
-    for (int64_t i = gtid; i < n; i += gstride) {
+    const int ln = lane_id();
+    for (int64_t i0 = gtid - ln; i0 < n; i0 += gstride) {
         // all columns at once, then the parent's two offsets: every check that
         // stood between two loads was a trip to memory
-        uint32_t s = rs[i];
-        const int64_t o0 = roff[i], o1 = roff[i + 1];
-        const uint32_t p = rp[i], o = ro_[i];
+        const int64_t i = i0 + ln;
+        const bool here = i < n;
+        uint32_t s = here ? rs[i] : (uint32_t)RO_PENDING;
+        const int64_t o0 = here ? roff[i] : 0, o1 = here ? roff[i + 1] : 0;
+        const uint32_t p = here ? rp[i] : 0u, o = here ? ro_[i] : 0u;
         const bool known = (int64_t)p < P;
         const int64_t st = known ? offsets[p] : 0, en = known ? offsets[p + 1] : 0;
-        if (o1 < o0) { err = RO_EINVAL; continue; }
-        if (s > RO_PENDING && !(s == RO_GROUP_FAILED && barrier)) { err = RO_ESTATE; continue; }
-        if (s == RO_PENDING) continue;
-        if (!known) { err = RO_ERANGE; continue; }
-        const int64_t k = en - st;
-        if ((int64_t)o >= k) { err = RO_ERANGE; continue; }
-        const int64_t c = st + (int64_t)o;
-        if (st < 0 || c >= N) { err = RO_EINVAL; continue; }
+        const int64_t k = en - st, c = st + (int64_t)o;
         const int64_t len = s == RO_SUCCESS ? o1 - o0 : 0;
-        if (len >= ((int64_t)1 << 32)) { err = RO_EOVERFLOW; continue; }
-        if (gf_rejected(barrier, gkey, gf_epoch, p, i)) { ++rej; continue; }
+        int bad = 0;
+        bool counts = false;
+        if (o1 < o0) bad = RO_EINVAL;
+        else if (s > RO_PENDING && !(s == RO_GROUP_FAILED && barrier)) bad = RO_ESTATE;
+        else if (s == RO_PENDING) bad = 0;
+        else if (!known || (int64_t)o >= k) bad = RO_ERANGE;
+        else if (st < 0 || c >= N) bad = RO_EINVAL;
+        else if (len >= ((int64_t)1 << 32)) bad = RO_EOVERFLOW;
+        else if (gf_rejected(barrier, gkey, gf_epoch, p, i)) ++rej;
+        else counts = true;
+        if (bad) err = bad;
         if (s == RO_GROUP_FAILED) s = RO_FAILED;
         // first report of this child, in this wave or any earlier one
         const uint32_t bit = 1u << (c & 31);
-        const uint32_t old = atomicOr(&seen[c >> 5], bit);
+        const uint32_t old = change_bits<true>(seen + (c >> 5), bit, counts);
+        if (!counts) continue;
         if (old & bit) { err = RO_EDUP; continue; }
         Canon e;
         e.src = reinterpret_cast<uint64_t>(data) + (uint64_t)o0;

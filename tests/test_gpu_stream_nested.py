@@ -237,6 +237,82 @@ def test_stream_reset_with_other_offsets(ctx):
     st.close()
 
 
+@pytest.mark.parametrize("order", ["canonical", "reversed", "every other", "pairs swapped", "runs of 5", "mixed"])
+def test_stream_reports_of_neighbours(ctx, order):
+    """Reports whose children are neighbours: lanes of one wavefront in one
+    word of seen bits, over parents around a word's size, with pending ones
+    between them."""
+    rng = np.random.default_rng(len(order))
+    counts = rng.permutation(np.concatenate([np.arange(0, 70), [95, 96, 97, 500], np.full(40, 1), np.full(40, 32),
+                                             rng.integers(0, 40, 150)])).astype(np.int32)
+    N = int(counts.sum())
+    ids = np.arange(N)
+    if order == "reversed":
+        ids = ids[::-1]
+    elif order == "every other":
+        ids = np.concatenate([ids[0::2], ids[1::2]])
+    elif order == "pairs swapped":
+        ids = (ids ^ 1)[(ids ^ 1) < N]
+    elif order == "runs of 5":
+        ids = np.concatenate([ids[k * 5:k * 5 + 5] for k in rng.permutation(N // 5 + 1)])
+    elif order == "mixed":
+        far = rng.random(N) < 0.3
+        ids[far] = rng.permutation(ids[far])
+    parts = np.split(ids.astype(np.uint32), [N // 3 + 1, N // 2 + 7])
+    waves, late = [], np.zeros(0, np.uint32)
+    for w, part in enumerate(parts):
+        st = rng.choice(np.array([0, 0, 0, 1, 2], np.uint8), len(part))
+        if w < 2:
+            st[rng.random(len(part)) < 0.2] = W.PENDING
+            late = np.concatenate([late, part[st == W.PENDING]])
+        waves.append((part, st, rng.integers(0, 40, len(part))))
+    waves.append((late, np.zeros(len(late), np.uint8), rng.integers(0, 40, len(late))))
+    _say("stream neighbours", order, N)
+    _stream_case(ctx, counts, waves)
+
+
+@pytest.mark.parametrize("apart", [1, 2, 31, 63, 64, 300])
+def test_stream_duplicate_in_one_wave(ctx, apart):
+    """A child reported twice by one call is found, however close."""
+    n = 1000
+    offs = torch.tensor([0, 400, n], dtype=torch.int64, device="cuda")
+    st = ctx.stream(offs, n)
+    child = np.arange(600)
+    child[500] = child[500 - apart]
+    par = (child >= 400).astype(np.uint32)
+    args = [torch.zeros(600, dtype=torch.uint8, device="cuda"), D.to_dev(np.arange(601, dtype=np.int64)),
+            torch.zeros(600, dtype=torch.uint8, device="cuda")]
+    _say("stream duplicate", apart)
+    st.report(_i32(par), _i32((child - 400 * par).astype(np.uint32)), *args)
+    assert ctx.status() == O.EDUP
+    st.close()
+
+
+def test_stream_canonical_reports_cost_no_more_than_random_ones(ctx):
+    """2M reports in one call: in canonical order they took a third of the time
+    of random order; when each made its own atomic on its word, 1.8 times."""
+    n, k = 2_000_000, 20
+    offs = torch.arange(0, n + 1, k, dtype=torch.int64, device="cuda")
+    s, data = torch.zeros(n, dtype=torch.uint8, device="cuda"), torch.zeros(n, dtype=torch.uint8, device="cuda")
+    off = torch.arange(n + 1, dtype=torch.int64, device="cuda")
+    st = ctx.stream(offs, n)
+    ms = {}
+    for name, c in (("random", torch.randperm(n, device="cuda")), ("canonical", torch.arange(n, device="cuda"))):
+        par, ordi = (c // k).int(), (c % k).int()
+        for timed in (False, True):
+            ctx.trace(timed)
+            for _ in range(5):
+                st.reset()
+                st.report(par, ordi, s, off, data)
+            if timed:
+                ms[name] = ctx.trace_read()["stream_report"][1]
+        ctx.check()
+        ctx.trace(False)
+    _say("random and canonical:", ms)
+    st.close()
+    assert ms["canonical"] < ms["random"]
+
+
 @pytest.mark.parametrize("seed", [0, 1, 2])
 def test_stream_mixed_states_and_empty_parents(ctx, seed):
     rng = np.random.default_rng(seed)
