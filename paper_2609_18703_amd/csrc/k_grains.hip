@@ -45,45 +45,6 @@ constexpr int kGItems = 4;
 // kNone also in `first`, for no report
 constexpr uint32_t kStale = 0xfffffffeu, kNone = 0xffffffffu;
 
-// Sets the in-flight bits of the wave's children (lanes with valid set) and
-// returns whether each was set before.  Children that follow one another, as in
-// a queue in canonical order, share their words: one atomic per word instead of
-// one per child.  Called by all lanes of the wave.
-__device__ __forceinline__ bool claim_bit(GrainBits *bits, uint32_t c, bool valid)
-{
-    const int lane = lane_id();
-    const uint32_t c0 = (uint32_t)uni32((int32_t)c);
-    if (__ballot(valid && c == c0 + (uint32_t)lane) == ~0ull) {
-        const int j = (int)(c & 31u);
-        const int lead = lane - (j < lane ? j : lane);
-        uint32_t old = 0;
-        if (lead == lane) {
-            const int len = 32 - j < 64 - lane ? 32 - j : 64 - lane;
-            old = __hip_atomic_fetch_or(&bits[c >> 5].inflight, (0xffffffffu >> (32 - len)) << j, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
-        }
-        old = (uint32_t)__shfl((int)old, lead, 64);
-        return (old >> j) & 1u;
-    }
-    if (!valid) return false;
-    const uint32_t bit = 1u << (c & 31u);
-    return (__hip_atomic_fetch_or(&bits[c >> 5].inflight, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit) != 0;
-}
-
-// The same for the sealed bits, which nobody asks for.
-__device__ __forceinline__ void seal_bit(GrainBits *bits, uint32_t c, bool valid)
-{
-    const int lane = lane_id();
-    const uint32_t c0 = (uint32_t)uni32((int32_t)c);
-    const int j = (int)(c & 31u);
-    uint32_t m = valid ? 1u << j : 0u;
-    if (__ballot(valid && c == c0 + (uint32_t)lane) == ~0ull) {
-        const int len = 32 - j < 64 - lane ? 32 - j : 64 - lane;
-        m = lane == 0 || j == 0 ? (0xffffffffu >> (32 - len)) << j : 0u;
-    }
-    if (m) __hip_atomic_fetch_or(&bits[c >> 5].sealed, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Every child READY at generation 0, with no report: the bitmaps and the bins'
 // counts to zero, `first` to no report.
 __global__ void k_grains_fill(uint4 *__restrict__ zero, int64_t n_zero, uint4 *__restrict__ first, int64_t n_first)
@@ -123,7 +84,10 @@ __global__ __launch_bounds__(kBlock) void k_grains_dispatch(const uint32_t *__re
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) retried[k] = ok[k] && out_gen ? g.bits[c[k] >> 5].retried : 0u;
 #pragma unroll
-        for (int k = 0; k < kGItems; ++k) set[k] = claim_bit(g.bits, c[k], ok[k]);
+        for (int k = 0; k < kGItems; ++k) {
+            const uint32_t bit = 1u << (c[k] & 31u);
+            set[k] = (change_bits<true>(&g.bits[c[k] >> 5].inflight, bit, ok[k]) & bit) != 0;
+        }
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) {
             if (!ok[k]) continue;
@@ -157,19 +121,13 @@ __global__ __launch_bounds__(kBlock) void k_grains_retry(const uint32_t *__restr
         for (int k = 0; k < kGItems; ++k) f[k] = ok[k] ? g.bits[c[k] >> 5] : GrainBits{0, 0, 0, 0};
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) {
-            if (!ok[k]) continue;
             const uint32_t bit = 1u << (c[k] & 31u);
-            if ((f[k].sealed & bit) ||
-                !(__hip_atomic_fetch_and(&g.bits[c[k] >> 5].inflight, ~bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & bit)) {
-                err = RO_ESTATE;
-                continue;
-            }
-            if (f[k].retried & bit) {
-                g.gen[c[k]] += 1u;
-            } else {
-                g.gen[c[k]] = 1u;
-                __hip_atomic_fetch_or(&g.bits[c[k] >> 5].retried, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+            const bool open = ok[k] && !(f[k].sealed & bit);
+            const bool mine = (change_bits<false>(&g.bits[c[k] >> 5].inflight, bit, open) & bit) != 0 && open;
+            if (ok[k] && !mine) err = RO_ESTATE;
+            const bool again = (f[k].retried & bit) != 0;
+            if (mine) g.gen[c[k]] = again ? g.gen[c[k]] + 1u : 1u;
+            (void)change_bits<true>(&g.bits[c[k] >> 5].retried, bit, mine && !again);
         }
     }
     if (err) raise_err(ctl, err);
@@ -410,7 +368,8 @@ __global__ __launch_bounds__(kBlock) void k_grains_decide(const uint8_t *__restr
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) w[k] = so[k] != RO_PENDING ? g.contested[c[k] >> 5] >> (c[k] & 31u) & 1u : 0u;
 #pragma unroll
-        for (int k = 0; k < kGItems; ++k) seal_bit(g.bits, c[k], so[k] != RO_PENDING);
+        for (int k = 0; k < kGItems; ++k)
+            (void)change_bits<true>(&g.bits[c[k] >> 5].sealed, 1u << (c[k] & 31u), so[k] != RO_PENDING);
         if (bad) continue;
 #pragma unroll
         for (int k = 0; k < kGItems; ++k) {
