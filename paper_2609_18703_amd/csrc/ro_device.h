@@ -39,6 +39,14 @@ __device__ __forceinline__ uint64_t dpp_add64(uint64_t v)
     const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(v >> 32), kCtrl, kRows, 0xf, false);
     return v + ((uint64_t)hi << 32 | lo);
 }
+// A value of another lane of the same four: 0x00 the first one's, 0xb1 the
+// neighbour's, 0x4e the other pair's.
+template <int kCtrl>
+__device__ __forceinline__ uint32_t quad_dpp(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xf, 0xf, false);
+}
+
 __device__ __forceinline__ uint64_t wave_incl_sum_dpp(uint64_t v)
 {
     v = dpp_add64<0x111, 0xf>(v);           // row_shr:1
