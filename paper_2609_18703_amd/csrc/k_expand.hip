@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kBlock) void k_expand_tags(const int64_t *__restric
     __shared__ alignas(16) uint32_t s_stage[kBlock / 64][kWaveSpan];
     if (only_if && *only_if == 0) return;
     const int64_t N = offsets[P];
-    if (N > child_cap || N >= ((int64_t)1 << 32)) return;     // reported by the scan
+    if (N > child_cap || N >= ((int64_t)1 << 32) || P == 0) return;     // reported by the scan
     if (N <= done_up_to) return;                              // the launch before has written them
     const int lane = lane_id();
     const bool nt = N > kTagsNtChildren;
@@ -90,7 +90,8 @@ __global__ __launch_bounds__(kBlock) void k_expand_tags(const int64_t *__restric
         const int64_t pf = wave_last_le(offsets, 0, P + 1, cb);
         const int64_t pl = wave_last_le(offsets, 0, P + 1, ce - 1);
         const int64_t c0 = cb + (int64_t)lane * kItems;
-        int64_t p = c0 < N ? upper_bound_g(offsets, pf, pl + 1, c0) - 1 : pl;
+        // (a stream's offsets are not checked yet: below the first one there is no parent)
+        int64_t p = c0 < N ? max64(upper_bound_g(offsets, pf, pl + 1, c0) - 1, 0) : pl;
         int64_t start = offsets[p];
         int64_t next = offsets[p + 1];
         uint32_t par[kItems], ord[kItems];

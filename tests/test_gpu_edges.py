@@ -332,6 +332,31 @@ def test_batch_parents_of_malformed_offsets_stay_below_the_count():
     c.close()
 
 
+def test_stream_batch_parents_of_malformed_offsets_stay_below_the_count():
+    """A stream reports offsets that do not start at 0, or fall, as an error, but
+    builds its child -> parent map from them all the same: what a batch finds
+    there before the error is read must still be parents, whose offsets are
+    read."""
+    import paper_2609_18703_amd as R
+    n = 5000
+    for what, offs in (("late start", [700, 700, 1500, 4000, n]), ("all late", [n - 1, n, n, n, n]),
+                       ("falling", [0, 4000, 100, 4500, n]), ("late and falling", [3000, 200, 4000, 50, n])):
+        c = R.Context()
+        offsets = D.to_dev(np.array(offs, np.int64))
+        _say("stream of malformed offsets", what)
+        st = c.stream(offsets, n)
+        for again in range(2):
+            outs = [torch.full((n,), -1, dtype=torch.int32, device="cuda") for _ in range(3)]
+            st.batch(_i32(np.arange(n, dtype=np.uint32)), None, 64, *outs)
+            par = outs[1].cpu().numpy()
+            assert par.min() >= 0 and par.max() < 4, what
+            assert c.status() == R.EINVAL, what
+            st.reset()
+        assert c.status() == R.EINVAL, what
+        st.close()
+        c.close()
+
+
 def test_stream_word_and_tile_edges(ctx):
     """Completion found by seen words: parents of one to many 32-child words
     at every alignment, empty parents among them, children in random order
