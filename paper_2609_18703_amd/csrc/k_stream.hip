@@ -92,11 +92,11 @@ __global__ __launch_bounds__(kBlock) void k_stream_report(
     for (int64_t i0 = gtid - ln; i0 < n; i0 += gstride) {
         // all columns at once, then the parent's two offsets: every check that
         // stood between two loads was a trip to memory
-        const int64_t i = i0 + ln;
-        const bool here = i < n;
-        uint32_t s = here ? rs[i] : (uint32_t)RO_PENDING;
-        const int64_t o0 = here ? roff[i] : 0, o1 = here ? roff[i + 1] : 0;
-        const uint32_t p = here ? rp[i] : 0u, o = here ? ro_[i] : 0u;
+        const int64_t i = min64(i0 + ln, n - 1);
+        uint32_t s = rs[i];
+        const int64_t o0 = roff[i], o1 = roff[i + 1];
+        const uint32_t p = rp[i], o = ro_[i];
+        if (i0 + ln >= n) s = RO_PENDING;
         const bool known = (int64_t)p < P;
         const int64_t st = known ? offsets[p] : 0, en = known ? offsets[p + 1] : 0;
         const int64_t k = en - st, c = st + (int64_t)o;

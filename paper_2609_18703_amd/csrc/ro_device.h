@@ -78,45 +78,53 @@ __device__ __forceinline__ T wave_sum(T v)
     return v;
 }
 
-// Sets each valid lane's bit of its word at[w], or clears it, and returns what
-// the word held before, earlier lanes' changes counted in.  Lanes that follow one
-// another in one word make one atomic between them: as single ones, 64 of a wave
-// meet at two or three addresses, where each waits for the one before it, and
-// children in canonical order (or reversed, or in short runs) come that way (2M
-// reports of a stream in canonical order: 215 us, now 40; in random order 120 and
-// 117).  Called by all lanes of the wave.
 template <bool kSet>
-__device__ __forceinline__ uint32_t change_bits(uint32_t *at, uint32_t bit, bool valid)
+__device__ __forceinline__ uint32_t change_word(uint32_t *at, uint32_t m)
+{
+    return kSet ? __hip_atomic_fetch_or(at, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                : __hip_atomic_fetch_and(at, ~m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The part of change_bits where lanes of one word follow one another: joins has
+// the lanes that share the word of the one before.  Out of line, so that calls
+// without such lanes do not fetch its code.
+template <bool kSet>
+__device__ __attribute__((noinline)) uint32_t change_runs(uint32_t *at, uint32_t bit, bool valid, uint64_t joins)
 {
     const int ln = lane_id();
-    const uint64_t a = valid ? reinterpret_cast<uint64_t>(at) : 0ull;
-    const uint32_t key = (uint32_t)(a >> 2);                // words of one bitmap: far less than 16 GB
-    const uint32_t prev = (uint32_t)__shfl_up((int)key, 1, 64);
-    const uint64_t joins = __ballot(valid && ln > 0 && prev == key);
-    const auto apply = [at](uint32_t m) {
-        return kSet ? __hip_atomic_fetch_or(at, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                    : __hip_atomic_fetch_and(at, ~m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    };
-    uint32_t old = 0;
-    if (joins == 0) {
-        if (valid) old = apply(bit);
-        return old;
-    }
     const uint64_t heads = ~joins;                           // lane 0 among them
     const uint64_t after = ln < 63 ? heads & (~0ull << (ln + 1)) : 0ull;
     const int head = 63 - __clzll((long long)(heads & (~0ull >> (63 - ln))));
     const int tail = after ? __ffsll((unsigned long long)after) - 2 : 63;
-    uint32_t run = valid ? bit : 0u;
+    uint32_t run = valid ? bit : 0u, old = 0;
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) {
         const uint32_t x = (uint32_t)__shfl_up((int)run, d, 64);
         if (ln - d >= head) run |= x;
     }
-    if (valid && ln == tail) old = apply(run);
+    if (valid && ln == tail) old = change_word<kSet>(at, run);
     const uint32_t before = (uint32_t)__shfl_up((int)run, 1, 64);
     old = (uint32_t)__shfl((int)old, tail, 64);
     if (ln > head) old = kSet ? old | before : old & ~before;
     return old;
+}
+
+// Sets each valid lane's bit of its word at[w], or clears it, and returns what
+// the word held before, earlier lanes' changes counted in.  Lanes that follow one
+// another in one word make one atomic between them: as single ones, 64 of a wave
+// meet at two or three addresses, where each waits for the one before it, and
+// children in canonical order (or reversed, or in short runs) come that way (2M
+// reports of a stream in canonical order: 215 us, now 42; in random order 120
+// both).  Called by all lanes of the wave.
+template <bool kSet>
+__device__ __forceinline__ uint32_t change_bits(uint32_t *at, uint32_t bit, bool valid)
+{
+    const uint64_t a = valid ? reinterpret_cast<uint64_t>(at) : 0ull;
+    const uint32_t key = (uint32_t)(a >> 2);                // words of one bitmap: far less than 16 GB
+    const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)key, 0x138, 0xf, 0xf, false);   // wave_shr:1
+    const uint64_t joins = __ballot(valid && lane_id() > 0 && prev == key);
+    if (joins != 0) return change_runs<kSet>(at, bit, valid, joins);
+    return valid ? change_word<kSet>(at, bit) : 0u;
 }
 
 // Exclusive scan over the kBlock threads of a workgroup.  `s_wave` holds
