@@ -20,6 +20,7 @@
 //             out     -> counts, states, trailing offsets, capacity, and the
 //                        emitted bytes from the per-child positions.
 #include "ro_copy.h"
+#include "ro_keys.h"
 
 namespace ro {
 
@@ -47,14 +48,18 @@ __device__ __forceinline__ uint32_t word_share(int64_t w, int64_t st, int64_t en
 
 // Validates the expansion once: offsets[0] = 0, nondecreasing, offsets[P] = N.
 // Marks the parents without children complete: the first emission takes them.
-// Notes the offsets, and whether any differs from the last ones: a reset
-// stream's may, and then its child -> parent map is built again (10M children:
-// 30 us a reset; the comparison and a launch that finds nothing to do take 8).
+// Notes the offsets and, for a reset, whether any differs from the last ones: a
+// reset stream's may, and then k_stream_clear builds its child -> parent map
+// again.  It finds that out without a word to be cleared in between: remap[0]
+// becomes this reset's number, one more than remap[2], and remap[1] the same
+// where an offset differs.
 __global__ void k_stream_check(const int64_t *__restrict__ offsets, int64_t P, int64_t N, uint64_t *__restrict__ ready,
                                int64_t *__restrict__ mapped, uint32_t *__restrict__ remap, Ctl *ctl)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     bool bad = (g == 0) && (offsets[0] != 0 || offsets[P] != N);
+    const uint32_t run = remap ? remap[2] + 1u : 0u;
+    if (remap && g == 0) remap[0] = run;
     const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
     for (int64_t w = g >> 6; w * 64 < P; w += nwaves) {
         const int64_t p = w * 64 + lane_id();
@@ -63,7 +68,7 @@ __global__ void k_stream_check(const int64_t *__restrict__ offsets, int64_t P, i
         if (k < 0) bad = true;
         if (p < P && mapped[p] != st) {
             mapped[p] = st;
-            *remap = 1;
+            if (remap) remap[1] = run;
         }
         const uint64_t m = __ballot(k == 0);
         if (lane_id() == 0) ready[w] = m;
@@ -517,34 +522,56 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 
 // Forgets every report and emission: seen bits, counters and emitted flags
 // back to zero.  Canonical slots need no clearing, since a slot is read only
-// for children of emitted parents, and those were all reported.
-__global__ void k_stream_clear(uint32_t *__restrict__ seen, int64_t n_seen, uint32_t *__restrict__ words,
+// for children of emitted parents, and those were all reported.  Builds the
+// child -> parent map again if the check before found other offsets (10M
+// children of 500,000 parents: 27 us a reset, 11 without; a launch of its own
+// that mostly finds nothing to do took 5.5 more).
+__global__ __launch_bounds__(kBlock) void k_stream_clear(uint32_t *__restrict__ seen, int64_t n_seen, uint32_t *__restrict__ words,
                                int64_t n_words, uint8_t *__restrict__ emitted, uint8_t *__restrict__ barrier,
-                               int64_t n_emitted, uint32_t *__restrict__ remap)
+                               int64_t n_emitted, const int64_t *__restrict__ offsets, int64_t N,
+                               uint32_t *__restrict__ cpar, uint32_t *__restrict__ remap)
 {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (g == 0) *remap = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const uint32_t run = remap[0], other = remap[1];
+    if (g == 0) remap[2] = run;
     for (int64_t i = g; i < n_seen; i += stride) seen[i] = 0;
     for (int64_t i = g; i < n_words; i += stride) words[i] = 0;
     for (int64_t i = g; i < n_emitted; i += stride) {
         emitted[i] = 0;
         if (barrier) barrier[i] = 0;
     }
+    if (run == other) write_keys(offsets, n_emitted, cpar, nullptr, N, -1, 1);
+}
+
+// A thread per item, up to four workgroups per CU.
+static unsigned reset_grid(const Launch &L, int64_t items)
+{
+    const int64_t g = (items + kBlock - 1) / kBlock, most = (int64_t)L.num_cus * 4;
+    return (unsigned)(g < 1 ? 1 : g < most ? g : most);
+}
+
+static hipError_t launch_stream_check(const Launch &L, StreamState &s, uint32_t *remap)
+{
+    RO_LAUNCH(L, RO_K_MISC, k_stream_check, dim3(reset_grid(L, s.P)), dim3(kBlock), 0, L.stream, s.offsets, s.P, s.N,
+              s.ready, s.mapped, remap, L.ctl);
+    return hipGetLastError();
+}
+
+// A new stream, whose state is all zero.
+hipError_t launch_stream_init(const Launch &L, StreamState &s)
+{
+    const hipError_t e = launch_stream_check(L, s, nullptr);
+    return e != hipSuccess ? e : launch_expand_tags(L, s.offsets, s.P, s.cpar, nullptr, s.N);
 }
 
 hipError_t launch_stream_reset(const Launch &L, StreamState &s)
 {
-    RO_LAUNCH(L, RO_K_MISC, k_stream_clear, dim3((unsigned)L.num_cus * 4), dim3(256), 0, L.stream, s.seen,
-              (s.N + 31) / 32 + 1, s.words, stream_word_count(s.N), s.emitted, s.barrier, s.P, s.remap);
-    const hipError_t e = launch_stream_init(L, s);
-    return e != hipSuccess ? e : launch_expand_tags(L, s.offsets, s.P, s.cpar, nullptr, s.N, s.remap);
-}
-
-hipError_t launch_stream_init(const Launch &L, StreamState &s)
-{
-    RO_LAUNCH(L, RO_K_MISC, k_stream_check, dim3((unsigned)L.num_cus * 4), dim3(256), 0, L.stream, s.offsets, s.P,
-              s.N, s.ready, s.mapped, s.remap, L.ctl);
+    const hipError_t e = launch_stream_check(L, s, s.remap);
+    if (e != hipSuccess) return e;
+    RO_LAUNCH(L, RO_K_MISC, k_stream_clear, dim3(reset_grid(L, s.P + s.N / kItems)), dim3(kBlock), 0, L.stream, s.seen,
+              (s.N + 31) / 32 + 1, s.words, stream_word_count(s.N), s.emitted, s.barrier, s.P, s.offsets, s.N, s.cpar,
+              s.remap);
     return hipGetLastError();
 }
 

@@ -628,7 +628,7 @@ int ro_stream_create(ro_ctx *c, const int64_t *offsets, int64_t n_parents, int64
         (size_t)(P + 1),                                    // ebar
         (size_t)(N > 0 ? N : 1) * sizeof(uint32_t),         // cpar
         (size_t)(P + 1) * sizeof(int64_t),                  // mapped
-        sizeof(uint32_t),                                   // remap
+        3 * sizeof(uint32_t),                               // remap
     };
     constexpr int kArrays = (int)(sizeof(sizes) / sizeof(sizes[0]));
     size_t offs[kArrays], total = 0;
@@ -672,8 +672,7 @@ int ro_stream_create(ro_ctx *c, const int64_t *offsets, int64_t n_parents, int64
     st.barrier = barrier;
     st.run_epoch = 1;
     st.gf_epoch = 0;
-    if (launch_stream_init(launch_of(c), st) != hipSuccess ||
-        launch_expand_tags(launch_of(c), offsets, P, st.cpar, nullptr, N) != hipSuccess) {
+    if (launch_stream_init(launch_of(c), st) != hipSuccess) {
         (void)hipStreamSynchronize(c->stream);     // a launch that did start still uses the block
         (void)hipFree(block);
         free(s);

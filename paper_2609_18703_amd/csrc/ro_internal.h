@@ -93,9 +93,8 @@ hipError_t launch_batch(const Launch &L, const uint32_t *queue, const uint8_t *k
                         int64_t out_cap, int64_t *n_out, int64_t *n_batches, uint32_t *cmap,
                         int64_t cmap_cap, const uint8_t *barrier, const uint32_t *cpar = nullptr,
                         int64_t cpar_n = 0);
-// only_if (or null): a device word, 0 for nothing to do
 hipError_t launch_expand_tags(const Launch &L, const int64_t *offsets, int64_t P, uint32_t *child_parent,
-                              uint32_t *child_ordinal, int64_t child_cap, const uint32_t *only_if = nullptr);
+                              uint32_t *child_ordinal, int64_t child_cap);
 
 // parent-bound reservation workspace ([cap] queue entries, [pcap] parents)
 struct PbWs {
@@ -220,7 +219,7 @@ struct StreamState {
     uint8_t *ebar;           // [P] per emitted parent: barred
     uint32_t *cpar;          // [N] parent of every child (for the stream's batches)
     int64_t *mapped;         // [P+1] the offsets cpar was built from
-    uint32_t *remap;         // [1] this reset found others
+    uint32_t *remap;         // [3] number of this reset, of the last one that found others, resets done
     uint32_t run_epoch;      // slot tag epoch of this run (advanced by each reset)
     uint32_t gf_epoch;       // epoch of the current report call in gkey
 };
