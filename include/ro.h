@@ -194,7 +194,7 @@ int ro_batch(ro_ctx *ctx, const uint32_t *queue, const uint8_t *keep, int64_t q_
  * slots [batch_off[j], batch_off[j+1]) (int64, device; batch_off[n_batches]
  * = M), so it needs n_batches + 1 <= batch_cap (RO_ECAP; n_batches <= M).
  * M and n_batches go to *n_out_dev and *n_batches_dev (either may be
- * NULL).  Workspace: about 36 bytes per queue entry and 8 per parent, held
+ * NULL).  Workspace: about 37 bytes per queue entry and 8 per parent, held
  * by the context and grown on demand. */
 int ro_batch_parent(ro_ctx *ctx, const uint32_t *queue, const uint8_t *keep, int64_t q_len,
                     const int64_t *offsets, int64_t n_parents, int32_t batch_size, uint32_t *out_child,
